@@ -152,9 +152,10 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     k.take(&c->qtotals, 4);
     k.take(&c->delta, 2);
     k.take(&c->nodes, (size_t)c->max_nodes);
-    k.take(&c->sorted_idx, (size_t)c->max_nodes);
+    k.take(&c->plan_list, (size_t)c->max_nodes);
     k.take(&c->step, 1);
     k.take(&c->batch, (size_t)c->batch_max);
+    k.take(&c->batch_seg, (size_t)c->batch_max);
     k.take(&c->cand, (size_t)2 * c->batch_max * F);
     k.take(&c->hist_entries, (size_t)c->batch_max);
     k.take(&c->hist_counts, 2);
@@ -253,15 +254,9 @@ static int check_shape(const qgbdt_shape* shape) {
         shape->n_bins > (shape->bin_bytes == 2 ? 1024 : 256) || shape->max_leaves < 1)
         return set_error(nullptr, QGBDT_E_INVALID_ARG, "shape out of range (rows %lld, features %d, bins %d, leaves %d)",
                          (long long)shape->n_rows, shape->n_features, shape->n_bins, shape->max_leaves);
-    if (shape->max_leaves > TABLE_MAX)
-        return set_error(nullptr, QGBDT_E_UNSUPPORTED, "max_leaves=%d: at most %d (the kernels keep a round's table in LDS)",
-                         shape->max_leaves, TABLE_MAX);
-    // the plan kernel keeps its sort and replay state of all nodes in LDS
-    const size_t L = (size_t)shape->max_leaves, max_nodes = 6 * L + 1, p_max = max_nodes + (max_nodes & 1);
-    const size_t plan_lds = p_max * 24 + L * 16 + max_nodes * 12 + (4 * L + 8) * 4;
-    if (plan_lds + 512 > 160 * 1024)  // (the kernel's few static words come on top)
-        return set_error(nullptr, QGBDT_E_UNSUPPORTED, "max_leaves=%d: the growth bookkeeping would need %zu bytes of LDS (limit 160 KB: at most 658 leaves)",
-                         shape->max_leaves, plan_lds);
+    if (shape->max_leaves > MAX_TREE_LEAVES)
+        return set_error(nullptr, QGBDT_E_UNSUPPORTED, "max_leaves=%d: at most %d (the growth bookkeeping of all nodes lives in one workgroup's LDS)",
+                         shape->max_leaves, MAX_TREE_LEAVES);
     return QGBDT_OK;
 }
 

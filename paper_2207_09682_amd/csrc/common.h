@@ -36,20 +36,33 @@ struct StepState {
     int32_t rounds;
     int32_t n_part_items;  // row segments of the current round's partitions
     int32_t n_scan_items;  // histograms to scan in the current round
-    int32_t n_sorted;      // nodes in the kept gain order (see tree_plan_kernel)
-    int32_t pad[1];
+    int32_t n_known;       // nodes that have passed through tree_plan_kernel (all but the last round's children)
+    int32_t n_list;        // entries of the kept gain order (see tree_plan_kernel)
     int64_t hist_units;    // rows*features of the histogram builds the sequential algorithm performs
     int64_t prof_rows_contig, prof_rows_idx;  // rows seen by histogram launches
     int64_t prof_launches;                    // histogram launches that had rows
     int64_t prof_builds;                      // histogram builds served by those launches
 };
 
-// One node expanded in the current round.
+// One node expanded in the current round, with everything the partition kernels need of it (one 64-byte record
+// instead of a look-up in the node table that depends on it).
 struct BatchEntry {
+    int64_t begin;      // the node's rows: slice of buffer `buf`
+    int32_t count;
     int32_t node;
     int32_t seg_start;  // first partition segment of this node
     int32_t n_seg;
     int32_t new_slot;   // histogram slot of the child that is built from its rows
+    int32_t buf;
+    int32_t feature, bin;  // its split
+    int32_t pad[4];
+};
+
+// One known node whose split is not committed yet and has a gain, in the gain order kept from round to round.
+struct PlanEntry {
+    unsigned long long key;  // bits of the gain (> 0): ordered like the gain
+    uint32_t ids;            // node id, left child's id in the upper half (0xffff: not expanded)
+    uint32_t leaf;           // leaf id, 0xffff: not an open leaf (its parent's split is not committed)
 };
 
 // Candidate of one (leaf, feature) pair produced by the scan kernel.
@@ -187,9 +200,10 @@ struct qgbdt_ctx {
     int64_t* qtotals;      // [3] sum g~, sum h~, sum |g~|
     float* delta;          // [2]
     qgbdt::Node* nodes;          // [max_nodes]
-    int32_t* sorted_idx;         // [max_nodes] node ids by descending gain, kept from round to round
+    qgbdt::PlanEntry* plan_list; // [max_nodes] uncommitted nodes by descending gain, kept from round to round
     qgbdt::StepState* step;      // [1]
     qgbdt::BatchEntry* batch;    // [batch_max]
+    int32_t* batch_seg;          // [batch_max] their first segments, for the search segment -> node
     qgbdt::FeatCand* cand;       // [2*batch_max][F]
     qgbdt::HistEntry* hist_entries;  // [batch_max]
     int32_t* hist_counts;        // [2] entries, items
@@ -219,6 +233,9 @@ constexpr int PART_SEG = 1024;  // rows per partition segment of the batched par
 // limits it to 658).  Kernels keep the first work item of every build / node in LDS and search there: a binary
 // search through global memory costs a chain of dependent loads per work item.
 constexpr int TABLE_MAX = 768;
+// Largest leaf budget: 6 * 658 + 1 nodes may become known, and the growth bookkeeping (tree_plan_kernel) holds them in
+// one workgroup's LDS, as 64 masks of 64 gain ranks and with 16-bit node ids.
+constexpr int MAX_TREE_LEAVES = 658;
 
 int set_error(qgbdt_ctx* ctx, int code, const char* fmt, ...);
 

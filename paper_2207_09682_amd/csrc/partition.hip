@@ -169,19 +169,19 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
 // Work items are row segments of PART_SEG rows; segment -> (batch entry, segment of that
 // node) by binary search over the entries' first-segment numbers.
 
-// (The round's table is copied into LDS once per workgroup and searched there: through global memory the search is
-// a chain of dependent loads per segment.)
-__device__ __forceinline__ void load_batch(const BatchEntry* __restrict__ batch, int n_batch, BatchEntry* s_batch) {
-    for (int t = threadIdx.x; t < n_batch; t += blockDim.x) s_batch[t] = batch[t];
+// (The entries' first segments are copied into LDS once per workgroup and searched there: through global memory the
+// search is a chain of dependent loads per segment.)
+__device__ __forceinline__ void load_batch(const int32_t* __restrict__ batch_seg, int n_batch, int* s_start) {
+    for (int t = threadIdx.x; t < n_batch; t += blockDim.x) s_start[t] = batch_seg[t];
     __syncthreads();
 }
-__device__ __forceinline__ int find_batch(const BatchEntry* s_batch, int n_batch, int item) {
+__device__ __forceinline__ int find_batch(const int* s_start, int n_batch, int item) {
     int lo = 0, hi = n_batch - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (s_batch[mid].seg_start <= item) lo = mid; else hi = mid - 1;
+        if (s_start[mid] <= item) lo = mid; else hi = mid - 1;
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // Left-going rows per segment (flags kept as bytes); on the way the histogram slots
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
                                                                int bb, int F, IdxSet idxs,
                                                                const StepState* __restrict__ step,
                                                                const BatchEntry* __restrict__ batch,
-                                                               const Node* __restrict__ nodes,
+                                                               const int32_t* __restrict__ batch_seg,
                                                                uint8_t* __restrict__ flags,
                                                                int32_t* __restrict__ seg_counts, int64_t* hist_base,
                                                                int64_t hist_words) {
@@ -206,19 +206,18 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
             z[i] = 0;
     }
     __shared__ int sc[4];
-    __shared__ BatchEntry s_batch[TABLE_MAX];
-    load_batch(batch, n_batch, s_batch);
+    __shared__ int s_start[TABLE_MAX];
+    load_batch(batch_seg, n_batch, s_start);
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const BatchEntry be = s_batch[find_batch(s_batch, n_batch, item)];
-        const Node nd = nodes[be.node];
+        const BatchEntry nd = batch[find_batch(s_start, n_batch, item)];
         const int32_t* src = idxs.p[nd.buf] + nd.begin;
         const uint8_t* brow = rows.bins[ordered ? nd.buf : BUF_ORIGINAL] + (ordered ? nd.begin * (int64_t)F : 0);
         // with a feature-major copy of the matrix the split feature's column is read instead: the ascending row
         // ids of a node then fall into few sectors, where the row-major matrix costs one sector per row
-        const uint8_t* col = (bins_t && !ordered) ? bins_t + (int64_t)nd.best.feature * n_rows * bb : nullptr;
-        const int64_t sbegin = (int64_t)(item - be.seg_start) * PART_SEG;
-        const int64_t send = min(nd.count, sbegin + PART_SEG);
-        const int feature = nd.best.feature, bin = nd.best.bin;
+        const uint8_t* col = (bins_t && !ordered) ? bins_t + (int64_t)nd.feature * n_rows * bb : nullptr;
+        const int64_t sbegin = (int64_t)(item - nd.seg_start) * PART_SEG;
+        const int64_t send = min((int64_t)nd.count, sbegin + PART_SEG);
+        const int feature = nd.feature, bin = nd.bin;
         int cnt = 0;
         for (int64_t p = sbegin + threadIdx.x; p < send; p += blockDim.x) {
             const int64_t row = (ordered || nd.buf == BUF_ORIGINAL) ? p : (int64_t)src[p];  // the root's list is the identity
@@ -244,6 +243,7 @@ template <int MODE>  // 0: row ids, 1: row ids and packed gradients, 2: those an
 __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows, RowDest out, int F, IdxSet idxs,
                                                                  const StepState* __restrict__ step,
                                                                  const BatchEntry* __restrict__ batch,
+                                                                 const int32_t* __restrict__ batch_seg,
                                                                  const Node* __restrict__ nodes,
                                                                  const uint8_t* __restrict__ flags,
                                                                  const int32_t* __restrict__ seg_prefix) {
@@ -254,13 +254,12 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
     __shared__ int s_dpos[PART_SEG];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int dpr = F / 4;
-    __shared__ BatchEntry s_batch[TABLE_MAX];
-    load_batch(batch, n_batch, s_batch);
+    __shared__ int s_start[TABLE_MAX];
+    load_batch(batch_seg, n_batch, s_start);
     // Segments are taken from the last to the first: the count kernel has just streamed the same
     // rows front to back, so the tail of that stream is what the memory-side cache still holds.
     for (int item = n_items - 1 - (int)blockIdx.x; item >= 0; item -= (int)gridDim.x) {
-        const BatchEntry be = s_batch[find_batch(s_batch, n_batch, item)];
-        const Node nd = nodes[be.node];
+        const BatchEntry nd = batch[find_batch(s_start, n_batch, item)];
         const int cbuf = child_buffer(nd.buf);
         const bool identity = nd.buf == BUF_ORIGINAL;  // the root's list: row id = position, never stored
         const int32_t* src = idxs.p[nd.buf] + nd.begin;
@@ -269,12 +268,12 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
         int16_t* gdst = MODE >= 1 ? out.gh[cbuf] + nd.begin : nullptr;
         const uint8_t* bsrc = MODE == 2 ? rows.bins[nd.buf] + nd.begin * (int64_t)F : nullptr;
         uint8_t* bdst = MODE == 2 ? out.bins[cbuf] + nd.begin * (int64_t)F : nullptr;
-        const int64_t sbegin = (int64_t)(item - be.seg_start) * PART_SEG;
-        const int64_t send = min(nd.count, sbegin + PART_SEG);
+        const int64_t sbegin = (int64_t)(item - nd.seg_start) * PART_SEG;
+        const int64_t send = min((int64_t)nd.count, sbegin + PART_SEG);
         const int n = (int)(send - sbegin);
-        const int64_t before = seg_prefix[item] - seg_prefix[be.seg_start];  // left rows in earlier segments
+        const int64_t before = seg_prefix[item] - seg_prefix[nd.seg_start];  // left rows in earlier segments
         const int64_t lpos0 = before;                          // first left slot of this segment (slice-relative)
-        const int64_t rpos0 = nd.n_left + (sbegin - before);   // first right slot
+        const int64_t rpos0 = nodes[nd.node].n_left + (sbegin - before);   // first right slot
         int fl[4], rank[4], g16[4];
         int32_t v[4];
 #pragma unroll
@@ -350,7 +349,7 @@ int launch_batch_partition_count(qgbdt_ctx* ctx, const RowSource& rows, const ui
     const int64_t W = (int64_t)ctx->shape.n_features * ctx->shape.n_bins;
     hipLaunchKernelGGL(batch_part_count_kernel, dim3(batch_part_grid(ctx)), dim3(256), 0, ctx->stream, rows, bins_t,
                        ctx->shape.n_rows, ordered ? 1 : 0, ctx->shape.bin_bytes, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch,
-                       ctx->nodes, ctx->flags, ctx->seg_counts, ctx->hist_pool, W);
+                       ctx->batch_seg, ctx->flags, ctx->seg_counts, ctx->hist_pool, W);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
@@ -360,7 +359,7 @@ int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool o
     for (int b = 0; b < 3; ++b) { out.bins[b] = ctx->obins[b]; out.gh[b] = ctx->ogh[b]; }
 #define QG_SCATTER(MODE_)                                                                                              \
     hipLaunchKernelGGL(batch_part_scatter_kernel<MODE_>, dim3(batch_part_grid(ctx)), dim3(256), 0, ctx->stream, rows, \
-                       out, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch, ctx->nodes, ctx->flags,       \
+                       out, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch, ctx->batch_seg, ctx->nodes, ctx->flags, \
                        ctx->seg_prefix)
     if (ordered) QG_SCATTER(2);
     else if (rows.gh_pos) QG_SCATTER(1);

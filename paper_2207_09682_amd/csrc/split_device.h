@@ -68,7 +68,7 @@ __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const q
 // The same reduction by a group of `sub` consecutive lanes (a power of two, 64 at most; `sl` = lane inside
 // the group), so that one wavefront serves 64 / sub leaves at a time.  The winner's candidate travels with
 // the comparison: no load depends on another.  Every lane of the group returns the winner's gain and feature
-// (feature < 0: no split).
+// (feature < 0: no split).  (The count estimate is left out: growth counts rows, and a 64-bit division is a long chain.)
 __device__ inline void reduce_features_lanes(const FeatCand* cand, int F, const qgbdt_leafstat& st, qgbdt_split* out,
                                              int sl, int sub, double& gain, int& feature) {
     double bg = 0.0;
@@ -99,7 +99,6 @@ __device__ inline void reduce_features_lanes(const FeatCand* cand, int F, const 
             s.gain = bg; s.feature = bf; s.bin = bb;
             s.left_g = packed_g(bl); s.left_h = packed_h(bl);
             s.right_g = st.sum_g - s.left_g; s.right_h = st.sum_h - s.left_h;
-            s.left_count = count_estimate(s.left_h, st.sum_h, st.n_rows);
         }
         *out = s;
     }

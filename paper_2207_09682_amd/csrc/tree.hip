@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = t; i < hist_words; i += stride) hist0[i] = 0;  // (the root's row list is the identity: never stored)
     if (t == 0) {
-        step->done = 0; step->n_sorted = 0; step->n_nodes = 1; step->n_leaves = 1; step->n_commits = 0; step->n_expanded = 0;
+        step->done = 0; step->n_known = 0; step->n_list = 0; step->n_nodes = 1; step->n_leaves = 1; step->n_commits = 0; step->n_expanded = 0;
         step->n_slots = 1; step->n_batch = 0; step->rounds = 0; step->n_part_items = 0; step->n_scan_items = 1;
         step->hist_units = N * (int64_t)F;
         Node r;
@@ -88,368 +88,453 @@ __device__ __forceinline__ int block_scan_incl(int v, int* tmp /*[16]*/) {
     return v + add;
 }
 
-// Wavefront-wide maximum of one unsigned value per lane with DPP moves (no LDS traffic);
-// the result is uniform.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#define QG_DPP(x, ctrl, rmask) (uint32_t)__builtin_amdgcn_update_dpp((int)(x), (int)(x), ctrl, rmask, 0xf, false)
-    v = max(v, QG_DPP(v, 0xB1, 0xf));   // quad_perm [1,0,3,2]
-    v = max(v, QG_DPP(v, 0x4E, 0xf));   // quad_perm [2,3,0,1]
-    v = max(v, QG_DPP(v, 0x141, 0xf));  // row_half_mirror
-    v = max(v, QG_DPP(v, 0x140, 0xf));  // row_mirror: every lane of a row holds the row's maximum
-    v = max(v, QG_DPP(v, 0x142, 0xa));  // row_bcast:15 into rows 1 and 3
-    v = max(v, QG_DPP(v, 0x143, 0xc));  // row_bcast:31 into rows 2 and 3
-#undef QG_DPP
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+// Barrier for data exchanged through LDS only: unlike __syncthreads it does not wait for the acknowledgement of
+// global stores that nobody in the workgroup reads.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Exclusive prefix sum over P values in LDS (in place); every thread owns a contiguous run.
-// Returns the total.
-__device__ inline int block_scan_array(int* v, int P, int* tmp /*[16]*/) {
-    const int per = (P + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int a = min((int)threadIdx.x * per, P), b = min(a + per, P);
-    int local = 0;
-    for (int i = a; i < b; ++i) local += v[i];
-    const int incl = block_scan_incl(local, tmp);
-    int run = incl - local;
-    for (int i = a; i < b; ++i) { const int x = v[i]; v[i] = run; run += x; }
-    __shared__ int s_scan_total;
-    if (threadIdx.x == blockDim.x - 1) s_scan_total = incl;
-    __syncthreads();
-    return s_scan_total;
+__device__ __forceinline__ unsigned long long lane_bits(unsigned long long w, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(w >> 32), lane);
+    return ((unsigned long long)hi << 32) | lo;
 }
 
-// Priority of an open leaf in the replay as one unsigned word: better gain rank first, then
-// the lower leaf id.  Never 0.
-__device__ __forceinline__ uint32_t replay_key(int rank, int leaf) {
-    return ((uint32_t)(0xffff - rank) << 16) | (uint32_t)(0xffff - leaf);
+// The lowest `k` set bits of m (k < popcount of m), by halving: six steps.
+__device__ __forceinline__ unsigned long long lowest_bits(unsigned long long m, int k) {
+    int at = 0;  // length of the prefix that is taken
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+        const int c = __popcll(m & ((1ull << (at + s)) - 1ull));  // at + s <= 63
+        if (c <= k) at += s;
+    }
+    return m & ((1ull << at) - 1ull);
 }
 
-// Commit phase and choice of the round's batch.  One workgroup of 1024 threads.
-//  0. (at most 256 features) Half of the workgroup reduces the per-feature candidates of the histograms scanned
-//     last to their nodes' best splits, which saves the launch that would do it.
-//  1. All known nodes are kept sorted by the gain of their best split: a node's gain never changes, so
-//     the order of the previous call is read back and last round's children are merged in (each
-//     finds its place by a binary search and a count; old entries shift by the number of new ones
-//     in front of them).  A node's rank is the number of nodes with a strictly larger gain.
-//  2. One wavefront replays best-first selection: the open leaves are kept in an array indexed
-//     by leaf id whose entries combine (rank, leaf id) and carry the node, so the leaf with the largest gain
-//     (ties: lowest leaf id) is one wavefront-wide maximum; it is committed if it has been expanded
-//     (its children become open leaves: the left one in its place, the right one as the next
-//     leaf id), else the replay stops.  Only the order is recorded.
+constexpr uint32_t NO_NODE = 0xffffu;
+
+// LDS of the plan kernel, as byte offsets into its dynamic LDS (offsets, not pointers: the compiler then sees LDS accesses
+// everywhere; through a struct of generic pointers they became flat ones, three times as slow).
+// p_max: all nodes that can be known.  Arrays by gain rank unless noted.
+struct PlanLds {
+    int key;      // u64 [p_max] gain bits in the new order
+    int okey;     // u64 [p_max + 8] gain bits in the kept order; once merged: `info`, what the selection needs of a rank
+    int ids;      // u32 [p_max] node | left child << 16
+    int oids;     // u32 [p_max] the same in the kept order; once merged: `ckey`, u64 [p_max / 2], order of the splits committed now
+    int leaf;     // u16 [p_max] leaf id of an open leaf, else NO_NODE
+    int oleaf;    // u16 [p_max] the same in the kept order; once merged: `corder`, place among the splits committed now
+    int rank_of;  // u16 [p_max] by node: its rank, NO_NODE: committed before or without a gain
+    int par;      // u16 [p_max] rank of the parent, NO_NODE: an open leaf
+    int shift;    // i32 [p_max] larger new keys of an old entry, then places of the new ones
+    int nkey;     // u64 [2*batch_max + 4] gain bits of last round's children (0: no split)
+    int commit;   // u16 [num_leaves] ranks of the splits committed now, in order
+    int chosen;   // u16 [batch_max] ranks of the nodes to expand
+    int bytes;
+};
+__host__ __device__ __forceinline__ PlanLds plan_lds_layout(int max_nodes, int batch_max, int num_leaves) {
+    const int p = (max_nodes + 3) & ~3;
+    PlanLds l;
+    l.key = 0; l.okey = l.key + 8 * p; l.nkey = l.okey + 8 * (p + 8); l.ids = l.nkey + 16 * batch_max + 32; l.oids = l.ids + 4 * p;
+    l.shift = l.oids + 4 * p; l.leaf = l.shift + 4 * p; l.oleaf = l.leaf + 2 * p; l.rank_of = l.oleaf + 2 * p;
+    l.par = l.rank_of + 2 * p; l.commit = l.par + 2 * p; l.chosen = l.commit + ((2 * num_leaves + 7) & ~7);
+    l.bytes = l.chosen + ((2 * batch_max + 7) & ~7);
+    return l;
+}
+
+// Leaf id of the node at rank p once its parent is committed.  Left children take their parent's id, the right child
+// of the k-th committed split of this call is leaf leaves0 + k; the chain ends at the latest at the grandparent, which
+// was an open leaf before the call.
+__device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* par, const unsigned long long* info,
+                                          const uint16_t* corder, int leaves0, int p) {
+    for (;;) {
+        const int lf = leaf[p];
+        if (lf != (int)NO_NODE) return lf;
+        const int q = par[p];
+        if ((int)((uint32_t)info[q] & 0xffffu) != p) return leaves0 + corder[q];
+        p = q;
+    }
+}
+
+// Commit phase and choice of the round's batch.  One workgroup of 1024 threads, bound by the latency of its chain of
+// phases (about 0.1 us for a barrier, 0.06 us for a dependent LDS access), so everything that is a set of nodes is a
+// bit mask over gain ranks (64 ranks to a word, at most 64 words) or a pass with one thread per rank.
+//  0. (at most 256 features) The per-feature candidates of the histograms scanned last are reduced to their nodes'
+//     best splits, by groups of lanes just wide enough that one pass serves all of them, which saves the launch that
+//     would do it.
+//  1. The known nodes that are not committed and have a gain are kept sorted by it in global memory; last round's
+//     children (node ids n_known ..) are merged in.  A node's place is a count of larger keys; every wavefront counts
+//     over a sixteenth of the keys for all nodes and the counts are added up in LDS.
+//  2. Best-first selection (commit the open leaf with the largest gain, its children become open leaves; stop at the
+//     first that has not been expanded) without a replay: with distinct gains a node is selected when the *worst* rank
+//     on its path from an open leaf is reached, then the worst rank behind that one, and so on -- the order of
+//     selection is the lexicographic order of the running maxima of the ranks, read from the node upwards.  Paths are
+//     at most three nodes long (children are expanded one level ahead of the open leaves), so the order key is one
+//     64-bit word; the splits committed are the expanded nodes whose key is below that of every node that is not
+//     expanded.  Equal gains are resolved by leaf ids, which depend on the order itself: if two known nodes tie, one
+//     wavefront replays the selection split by split (a bit per open leaf at its rank, the first set bit is next;
+//     0.25 us per split).
 //  3. All threads write the outputs of the committed splits.
-//  4. The batch is chosen by walking the sorted order (prefix sums over sorted positions).
-__global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch,
-                                                         int32_t* __restrict__ sorted_idx, int32_t* hist_counts, int F,
-                                                         int num_leaves, int batch_max, int max_expand, int p_max,
-                                                         TreeOut out, const FeatCand* __restrict__ cand,
+//  4. The batch is chosen with popcounts over the masks: open leaves that are not expanded (class 0), then children of
+//     expanded open leaves (class 1; one level ahead only: a node's rows outlive the expansion of its children but
+//     not that of its grandchildren), by rank, if fewer than the remaining number of splits have a larger gain.
+// Measured per launch against the version that kept all nodes in the order and replayed every split: 20.6 -> 10.1 us
+// (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
+// (20 M x 200, 511 leaves).
+__global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch, int32_t* batch_seg,
+                                                         PlanEntry* list, int32_t* hist_counts, int F, int num_leaves,
+                                                         int batch_max, int max_expand, TreeOut out,
+                                                         const FeatCand* __restrict__ cand,
                                                          const ScanItem* __restrict__ scan_items) {
-    // the fields of the growth state this kernel needs, in three loads that are in flight together
+    // the fields of the growth state this kernel needs and (for the first 1024 ranks) the kept order, in loads that are
+    // in flight together
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int max_nodes = 2 * max_expand + 1;
     const int4* sp = reinterpret_cast<const int4*>(step);
     const int4 st0 = sp[0], st1 = sp[1], st2 = sp[2];
+    PlanEntry mine = list[min(tid, max_nodes - 1)];
     if (st0.x) return;  // done
     extern __shared__ unsigned char plan_lds[];
-    const int n_nodes0 = st0.y;
-    const int n_old = st2.z;             // nodes already in the sorted order (all but last round's children)
-    const int m_new = n_nodes0 - n_old;
-    const int cap = 2 * max_expand + 1;  // nodes
-    const int P = n_nodes0;              // sorted positions in use
-    unsigned long long* skey = reinterpret_cast<unsigned long long*>(plan_lds);  // [p_max] gain bits, sorted
-    int* sidx = reinterpret_cast<int*>(skey + p_max);                            // [p_max] node at a sorted position
-    unsigned long long* okeys = reinterpret_cast<unsigned long long*>(sidx + p_max);  // [p_max] the order so far
-    int* oidx = reinterpret_cast<int*>(okeys + p_max);                                // [p_max]
-    unsigned long long* nkey = reinterpret_cast<unsigned long long*>(oidx + p_max);   // [2*batch_max] keys of the new nodes
-    // open leaves by leaf id: replay key (upper word; 0: no gain) and node (lower word)
-    unsigned long long* open = nkey + 2 * batch_max;                             // [num_leaves+1]
-    int* open_node = reinterpret_cast<int*>(open);                               // (the lower word of entry l is open_node[2 * l])
-    int* rankof = reinterpret_cast<int*>(open + num_leaves + 1);                 // [cap] -1: cannot be split, -2: split
-    int* posof = rankof + cap;                                                   // [cap] sorted position
-    int* child = posof + cap;                                                    // [cap] left child, -1 if not expanded
-    int* commit = child + cap;                                                   // [num_leaves] nodes committed, in order
-    // per node, once the ranks are known (reuses the sorted keys): left child and the ranks of both children
-    unsigned long long* ninfo = skey;                                            // [cap]; ~0: not expanded
-    int* commit_lid = commit + num_leaves;                                       // [num_leaves] their leaf ids
-    int* flag = reinterpret_cast<int*>(okeys);  // [P] per sorted position, reuses the old order once it is merged
-    int* flag2 = flag + p_max;                  // [P]
-    __shared__ int s_tmp[16];
-    __shared__ int s_done, s_ncommit, s_nleaves;
-    __shared__ unsigned long long s_units;
-    const int tid = threadIdx.x;
-    const int commits0 = st0.w, leaves0 = st0.z;
-    if (tid == 0) { s_done = 0; s_ncommit = 0; s_units = 0ull; }
-    // A node's sort key never changes: the gain of its best split (0 bits when it has none).  The order of
-    // the nodes known at the previous call is kept in global memory; only last round's children are new.
-    //
-    // (matrices of at most 256 features) The new nodes' best splits are not in memory yet: the split scan has left
-    // one candidate per feature, which the lower half of the workgroup reduces here instead of in a launch of its
-    // own -- groups of lanes as wide as the feature count (a power of two, one wavefront at most) take a scanned
-    // histogram each, write its node's best split and this kernel's entries of the node -- while the upper half
-    // reads the known nodes back.  A node that has just been scanned is not expanded, and an open leaf only if it
-    // is the root.
-    const bool fused = cand != nullptr;
-    const int half = (int)blockDim.x / 2;
-    if (fused && tid < half) {
-        // as few lanes per histogram as lets all histograms be reduced at once (a lane then takes several
-        // features, four loads in flight): a second pass would wait for a second round of memory latencies
-        const int n_scan = st2.y;  // histograms scanned in the last round
-        int sub = 64;
-        while (sub > 1 && (sub / 2 >= F || (half / sub) < n_scan)) sub >>= 1;
-        const int per_pass = half / sub;
-        const int grp = tid / sub, sl = tid % sub;
-        for (int item = grp; item < n_scan; item += per_pass) {
-            const ScanItem it = scan_items[item];
+    const PlanLds lay = plan_lds_layout(max_nodes, batch_max, num_leaves);
+    unsigned long long* const key = reinterpret_cast<unsigned long long*>(plan_lds + lay.key);
+    unsigned long long* const okey = reinterpret_cast<unsigned long long*>(plan_lds + lay.okey);
+    unsigned long long* const nkey = reinterpret_cast<unsigned long long*>(plan_lds + lay.nkey);
+    uint32_t* const ids = reinterpret_cast<uint32_t*>(plan_lds + lay.ids);
+    uint32_t* const oids = reinterpret_cast<uint32_t*>(plan_lds + lay.oids);
+    int* const shift = reinterpret_cast<int*>(plan_lds + lay.shift);
+    uint16_t* const leaf = reinterpret_cast<uint16_t*>(plan_lds + lay.leaf);
+    uint16_t* const oleaf = reinterpret_cast<uint16_t*>(plan_lds + lay.oleaf);
+    uint16_t* const rank_of = reinterpret_cast<uint16_t*>(plan_lds + lay.rank_of);
+    uint16_t* const par = reinterpret_cast<uint16_t*>(plan_lds + lay.par);
+    uint16_t* const commit = reinterpret_cast<uint16_t*>(plan_lds + lay.commit);
+    uint16_t* const chosen = reinterpret_cast<uint16_t*>(plan_lds + lay.chosen);
+    __shared__ unsigned long long s_open[64], s_exp[64], s_comm[64], s_cls1[64];
+    __shared__ unsigned long long s_c0[64], s_c1[64], s_prefix[64];  // batch candidates; prefix counts: class 0 | class 1 << 16 | committed << 32
+    __shared__ int s_nc, s_nnew, s_tie, s_stop, s_n0, s_npass;
+    __shared__ int s_wsum[16];
+    __shared__ unsigned long long s_units[8], s_first[8];  // (eight partial results: an atomic on one address is expanded into a loop over the lanes)
+    const int n_nodes = st0.y, leaves0 = st0.z, commits0 = st0.w;
+    const int n_expanded0 = st1.x, n_slots = st1.y;
+    const int n_known = st2.z, n_list = st2.w, n_scan = st2.y;
+    const int m_new = n_nodes - n_known;
+
+    for (int i = tid; i < n_nodes; i += 1024) { rank_of[i] = (uint16_t)NO_NODE; par[i] = (uint16_t)NO_NODE; shift[i] = 0; }
+    for (int p = tid; p < n_list; p += 1024) {
+        if (p >= 1024) mine = list[p];
+        okey[p] = mine.key; oids[p] = mine.ids; oleaf[p] = (uint16_t)mine.leaf;
+    }
+    if (tid < 64) { s_open[tid] = 0ull; s_exp[tid] = 0ull; s_comm[tid] = 0ull; s_cls1[tid] = 0ull; }
+    if (tid == 0) { s_nc = 0; s_nnew = 0; s_tie = 0; s_stop = -1; }
+    if (tid < 8) { s_units[tid] = 0ull; s_first[tid] = ~0ull; okey[n_list + tid] = 0ull; }
+    if (tid < 4) nkey[m_new + tid] = 0ull;
+    // Scanned histogram j belongs to node n_known + j: the best splits of last round's children.
+    if (cand != nullptr) {
+        int lg = 6;  // log2 of the lanes that share a histogram
+        while (lg > 0 && ((1 << (lg - 1)) >= F || (1024 >> lg) < n_scan)) --lg;
+        const int sl = tid & ((1 << lg) - 1);
+        for (int item = tid >> lg; item < n_scan; item += 1024 >> lg) {
             double gain = 0.0;
             int feature = -1;
-            if (it.valid)  // uniform over the group of lanes (a histogram that was not scanned leaves its node without a split)
-                reduce_features_lanes(cand + (int64_t)item * F, F, it.stat, it.out, sl, sub, gain, feature);
-            if (sl == 0) {
-                const int i = (int)((reinterpret_cast<const char*>(it.out) - reinterpret_cast<const char*>(&nodes[0].best)) /
-                                    (ptrdiff_t)sizeof(Node));
-                const bool splittable = feature >= 0 && gain > 0.0;
-                child[i] = -1;
-                if (i == 0) open_node[0] = 0;
-                rankof[i] = splittable ? 0 : -1;
-                nkey[i - n_old] = splittable ? (unsigned long long)__double_as_longlong(gain) : 0ull;
-            }
+            reduce_features_lanes(cand + (int64_t)item * F, F, scan_items[item].stat, &nodes[n_known + item].best, sl, 1 << lg, gain, feature);
+            if (sl == 0)
+                nkey[item] = (feature >= 0 && gain > 0.0) ? (unsigned long long)__double_as_longlong(gain) : 0ull;
         }
     } else {
-        const int first = fused ? tid - half : tid, stride = fused ? half : (int)blockDim.x;
-        const int n_read = fused ? n_old : n_nodes0;
-        for (int i0 = first; i0 < n_read; i0 += 2 * stride) {  // two nodes per step: their loads are in flight together
-            int st[2], ex[2], ch[2], lid[2], ft[2];
-            double gn[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const Node* nd = &nodes[min(i0 + u * stride, n_read - 1)];
-                st[u] = nd->state; ex[u] = nd->expanded; ch[u] = nd->child; lid[u] = nd->leaf_id;
-                ft[u] = nd->best.feature; gn[u] = nd->best.gain;
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int i = i0 + u * stride;
-                if (i >= n_read) break;
-                const bool splittable = ft[u] >= 0 && gn[u] > 0.0;
-                const unsigned long long kb = splittable ? (unsigned long long)__double_as_longlong(gn[u]) : 0ull;
-                child[i] = ex[u] ? ch[u] : -1;
-                if (st[u] == 1) open_node[2 * lid[u]] = i;
-                rankof[i] = st[u] == 2 ? -2 : (splittable ? 0 : -1);  // ranks are filled in below
-                if (i >= n_old) nkey[i - n_old] = kb;
-                else skey[i] = kb;  // by node id for now; gathered into the kept order next
-            }
+        for (int t = tid; t < m_new; t += 1024) {
+            const qgbdt_split* b = &nodes[n_known + t].best;
+            const double gain = b->gain;
+            nkey[t] = (b->feature >= 0 && gain > 0.0) ? (unsigned long long)__double_as_longlong(gain) : 0ull;
         }
     }
-    __syncthreads();
-    for (int p = tid; p < n_old; p += blockDim.x) {
-        const int i = sorted_idx[p];
-        oidx[p] = i;
-        okeys[p] = skey[i];
-    }
-    __syncthreads();
+    lds_barrier();
     // merge: old entries keep their order and come first among equal keys; new ones follow by node id
-    for (int p = tid; p < n_old; p += blockDim.x) {
-        const unsigned long long kb = okeys[p];
+    // (a wavefront's share of the keys comes in runs of 4 new and 8 old ones, whose loads are in flight together; the
+    // entries behind the ends are 0 and larger than nothing)
+    for (int p0 = 0; p0 < n_list; p0 += 64) {
+        const int p = p0 + lane;
+        const unsigned long long kb = p < n_list ? okey[p] : ~0ull;
         int c = 0;
-        for (int u = 0; u < m_new; ++u) c += nkey[u] > kb ? 1 : 0;
-        posof[oidx[p]] = p + c;
+        for (int u0 = 4 * wave; u0 < m_new; u0 += 64) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c += nkey[u0 + u] > kb ? 1 : 0;
+        }
+        if (c) atomicAdd(&shift[p], c);
     }
-    for (int t = (int)blockDim.x - 1 - tid; t < m_new; t += blockDim.x) {  // (from the last thread down: other wavefronts than the loop above, mostly)
+    for (int t0 = 0; t0 < m_new; t0 += 64) {
+        const int t = t0 + lane;
+        const unsigned long long kb = t < m_new ? nkey[t] : 0ull;
+        if (kb == 0ull) continue;  // (per lane: a child without a split has no rank)
+        int c = 0;
+        for (int u0 = 4 * wave; u0 < m_new; u0 += 64) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c += (nkey[u0 + u] > kb || (nkey[u0 + u] == kb && u0 + u < t)) ? 1 : 0;
+        }
+        for (int p0 = 8 * wave; p0 < n_list; p0 += 128) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c += okey[p0 + u] >= kb ? 1 : 0;
+        }
+        if (c) atomicAdd(&shift[n_list + t], c);
+        if (wave == 0) atomicAdd(&s_nnew, 1);
+    }
+    lds_barrier();
+    for (int p = tid; p < n_list; p += 1024) {
+        const uint32_t id = oids[p];
+        const int q = p + shift[p];
+        key[q] = okey[p]; ids[q] = id; leaf[q] = oleaf[p];
+        rank_of[id & 0xffffu] = (uint16_t)q;
+    }
+    for (int t = 1023 - tid; t < m_new; t += 1024) {  // (from the last thread down: other wavefronts than the loop above, mostly)
         const unsigned long long kb = nkey[t];
-        int lo = 0, hi = n_old;  // first old position with a smaller key
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (okeys[mid] >= kb) lo = mid + 1; else hi = mid;
+        if (kb == 0ull) continue;
+        const int q = shift[n_list + t];
+        key[q] = kb; ids[q] = (uint32_t)(n_known + t) | (NO_NODE << 16);
+        leaf[q] = (uint16_t)(n_known + t == 0 ? 0u : NO_NODE);  // the root is an open leaf from the start
+        rank_of[n_known + t] = (uint16_t)q;
+    }
+    lds_barrier();
+    const int P = n_list + s_nnew;  // ranks in use
+    // of every rank: the ranks of both children (info), expanded, tie with the next rank; of the children: their parent
+    unsigned long long* const info = okey;
+    uint16_t* const corder = oleaf;
+    for (int p = tid; p < P; p += 1024) {
+        const uint32_t child = ids[p] >> 16;
+        uint32_t lo = 0xffffffffu;
+        if (child != NO_NODE) {
+            const uint32_t rl = rank_of[child], rr = rank_of[child + 1];
+            lo = rl | (rr << 16);
+            if (rl != NO_NODE) par[rl] = (uint16_t)p;
+            if (rr != NO_NODE) par[rr] = (uint16_t)p;
         }
-        int b = 0;
-        for (int u = 0; u < m_new; ++u) b += (nkey[u] > kb || (nkey[u] == kb && u < t)) ? 1 : 0;
-        posof[n_old + t] = lo + b;
+        const uint32_t tie = (p + 1 < P && key[p + 1] == key[p]) ? 2u : 0u;
+        info[p] = ((unsigned long long)(tie | (child != NO_NODE ? 1u : 0u)) << 32) | lo;
+        corder[p] = (uint16_t)NO_NODE;
+        if (tie) s_tie = 1;
     }
-    __syncthreads();
-    for (int p = tid; p < n_old; p += blockDim.x) {
-        const int q = posof[oidx[p]];
-        skey[q] = okeys[p]; sidx[q] = oidx[p];
-    }
-    __syncthreads();  // (the loop above read skey-by-id only through okeys; new entries may now overwrite it)
-    for (int t = tid; t < m_new; t += blockDim.x) {
-        const int q = posof[n_old + t];
-        skey[q] = nkey[t]; sidx[q] = n_old + t;
-    }
-    __syncthreads();
-    for (int p = tid; p < P; p += blockDim.x) {
-        const int i = sidx[p];
-        sorted_idx[p] = i;
-        if (rankof[i] == 0) {
-            const unsigned long long kb = skey[p];
-            int r = p;
-            while (r > 0 && skey[r - 1] == kb) --r;  // equal gains share a rank
-            rankof[i] = r;
-        }
-    }
-    if (tid == 0) step->n_sorted = n_nodes0;
-    __syncthreads();
-    for (int l = tid; l < leaves0; l += blockDim.x) {
-        const int i = open_node[2 * l];
-        const int r = rankof[i];
-        open[l] = ((unsigned long long)(r >= 0 ? replay_key(r, l) : 0u) << 32) | (uint32_t)i;
-    }
-    for (int i = tid; i < n_nodes0; i += blockDim.x) {  // (overwrites the sorted keys: the ranks made from them are final)
-        const int c0 = child[i];
-        ninfo[i] = c0 < 0 ? ~0ull
-                          : ((unsigned long long)(uint32_t)c0 << 32) | ((uint32_t)(rankof[c0] + 2) << 16) | (uint32_t)(rankof[c0 + 1] + 2);
-    }
-    __syncthreads();
-
-    if (tid < 64) {
-        int n_commits = commits0, n_leaves = leaves0;
-        for (;;) {
-            if (n_commits >= num_leaves - 1) { if (tid == 0) s_done = 1; break; }
-            // a lane's best open leaf (four loads in flight per step), then the wavefront's
-            uint32_t mk = 0u;
-            int mn = 0;
-            for (int l0 = tid; l0 < n_leaves; l0 += 256) {
-                unsigned long long e[4];
+    lds_barrier();
+    const int budget = num_leaves - 1 - commits0;
+    unsigned long long* ckey = reinterpret_cast<unsigned long long*>(oids);
+    if (!s_tie) {
+        // order key of rank p: running maxima of (rank + 1) on the path up to the open leaf, the largest first
+        auto order_key = [&](int p) {
+            unsigned long long k0 = (unsigned long long)(p + 1), k1 = 0, k2 = 0;  // up to three maxima, largest first
+            int q = par[p], top = p;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) e[u] = (l0 + 64 * u < n_leaves) ? open[l0 + 64 * u] : 0ull;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t k = (uint32_t)(e[u] >> 32);
-                    if (k > mk) { mk = k; mn = (int)(uint32_t)e[u]; }
+            for (int u = 0; u < 2; ++u) {
+                if (q != (int)NO_NODE) {
+                    if (q > top) { k2 = k1; k1 = k0; k0 = (unsigned long long)(q + 1); top = q; }
+                    q = par[q];
                 }
             }
-            const uint32_t m = wave_max_u32(mk);
-            if (m == 0u) { if (tid == 0) s_done = 1; break; }  // no open leaf has a gain > 0
-            // keys are distinct (they hold the leaf id): exactly one lane has the maximum, and its node
-            const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(mk == m)) - 1);
-            const int bi = __builtin_amdgcn_readlane(mn, src);
-            const int wl = 0xffff - (int)(m & 0xffffu);
-            const unsigned long long info = ninfo[bi];
-            if (info == ~0ull) break;  // the next split is not known yet
-            // commit: the left child takes the leaf's place, the right child the next leaf id
-            const int c0 = (int)(info >> 32);
-            const int r0 = (int)((info >> 16) & 0xffffu) - 2, r1 = (int)(info & 0xffffu) - 2;
-            if (tid == 0) {
-                commit[n_commits - commits0] = bi;
-                commit_lid[n_commits - commits0] = wl;
-                open[wl] = ((unsigned long long)(r0 >= 0 ? replay_key(r0, wl) : 0u) << 32) | (uint32_t)c0;
-                open[n_leaves] = ((unsigned long long)(r1 >= 0 ? replay_key(r1, n_leaves) : 0u) << 32) | (uint32_t)(c0 + 1);
-            }
-            n_commits += 1; n_leaves += 1;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            return (k0 << 26) | (k1 << 13) | k2;
+        };
+        for (int p0 = wave * 64; p0 < P; p0 += 1024) {
+            const int p = p0 + lane;
+            if (p < P && !((info[p] >> 32) & 1ull)) atomicMin(&s_first[lane & 7], order_key(p));
         }
-        if (tid == 0) {
-            s_ncommit = n_commits - commits0; s_nleaves = n_leaves;
-            step->n_commits = n_commits; step->n_leaves = n_leaves;
+        lds_barrier();
+        unsigned long long first = s_first[0];
+#pragma unroll
+        for (int u = 1; u < 8; ++u) first = min(first, s_first[u]);
+        for (int p = tid; p < P; p += 1024) {
+            if (!((info[p] >> 32) & 1ull)) continue;
+            const unsigned long long k = order_key(p);
+            if (k < first) ckey[atomicAdd(&s_nc, 1)] = (k << 12) | (unsigned long long)p;
+        }
+        lds_barrier();
+        const int nc = s_nc;
+        for (int c = tid; c < nc; c += 1024) {
+            const unsigned long long k = ckey[c];
+            int o = 0;
+            for (int u = 0; u < nc; ++u) o += ckey[u] < k ? 1 : 0;
+            const int p = (int)(k & 0xfffull);
+            if (o < budget) { commit[o] = (uint16_t)p; corder[p] = (uint16_t)o; }
+        }
+    } else {
+        for (int p0 = wave * 64; p0 < P; p0 += 1024) {
+            const int p = p0 + lane;
+            const unsigned long long mo = __ballot(p < P && leaf[p] != NO_NODE);
+            if (lane == 0) s_open[p0 >> 6] = mo;
+        }
+        lds_barrier();
+        if (wave == 0) {
+            unsigned long long ow = s_open[lane];  // this lane's word of open leaves
+            int nc = 0, stop = 0;
+            bool out_of_leaves = false;
+            for (;;) {
+                const unsigned long long any = __ballot(ow != 0ull);
+                if (any == 0ull || nc >= budget) { out_of_leaves = true; break; }
+                const int src = __ffsll((long long)any) - 1;
+                int r = src * 64 + __ffsll((long long)lane_bits(ow, src)) - 1;
+                if ((info[r] >> 33) & 1ull) {  // equal gains: the lowest leaf id of the run's open leaves
+                    int best = r, bl = leaf_id_at(leaf, par, info, corder, leaves0, r);
+                    for (int q = r; (info[q] >> 33) & 1ull;) {
+                        ++q;
+                        if (!((lane_bits(ow, q >> 6) >> (q & 63)) & 1ull)) continue;
+                        const int ql = leaf_id_at(leaf, par, info, corder, leaves0, q);
+                        if (ql < bl) { bl = ql; best = q; }
+                    }
+                    r = __builtin_amdgcn_readfirstlane(best);
+                }
+                const unsigned long long inf = info[r];
+                if (!((inf >> 32) & 1ull)) { stop = r; break; }  // the next split is not known yet
+                const int rl = (int)((uint32_t)inf & 0xffffu), rr = (int)((uint32_t)inf >> 16);
+                if (lane == (r >> 6)) ow &= ~(1ull << (r & 63));
+                if (lane == (rl >> 6)) ow |= 1ull << (rl & 63);  // (NO_NODE >> 6 is no lane)
+                if (lane == (rr >> 6)) ow |= 1ull << (rr & 63);
+                if (lane == 0) { commit[nc] = (uint16_t)r; corder[r] = (uint16_t)nc; }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                nc += 1;
+            }
+            if (lane == 0) { s_nc = nc; s_stop = stop; s_first[0] = out_of_leaves ? ~0ull : 0ull; }
         }
     }
-    __syncthreads();
+    __syncthreads();  // (also: the best splits stored above are read below)
+    const int n_commit = min(s_nc, budget);
+    unsigned long long first_open = s_first[0];
+#pragma unroll
+    for (int u = 1; u < 8; ++u) first_open = min(first_open, s_first[u]);
+    const bool done = n_commit >= budget || first_open == ~0ull;  // (no leaf with a gain is left)
+    // the leaf the selection stopped at (an order key ends with the node's own rank)
+    const int stop = s_tie ? s_stop
+                           : (int)((first_open & 0x1fffull) ? first_open & 0x1fffull : ((first_open >> 13) & 0x1fffull) ? (first_open >> 13) & 0x1fffull : first_open >> 26) - 1;
+    // the masks after the commits
+    for (int p0 = wave * 64; p0 < P; p0 += 1024) {
+        const int p = p0 + lane;
+        bool open = false, expanded = false, committed = false;
+        if (p < P) {
+            const unsigned long long inf = info[p];
+            expanded = (inf >> 32) & 1ull;
+            committed = corder[p] != NO_NODE;
+            const int q = par[p];
+            open = !committed && (q == (int)NO_NODE || corder[q] != NO_NODE);
+            if (open && expanded) {  // its children may be expanded one level ahead
+                const uint32_t rl = (uint32_t)inf & 0xffffu, rr = (uint32_t)inf >> 16;
+                if (rl != NO_NODE) atomicOr(&s_cls1[rl >> 6], 1ull << (rl & 63));
+                if (rr != NO_NODE) atomicOr(&s_cls1[rr >> 6], 1ull << (rr & 63));
+            }
+        }
+        const unsigned long long mo = __ballot(open), me = __ballot(expanded), mc = __ballot(committed);
+        if (lane == 0) { s_open[p0 >> 6] = mo; s_exp[p0 >> 6] = me; s_comm[p0 >> 6] = mc; }
+    }
     // outputs and node states of the splits committed above
-    const int n_commit = s_ncommit;
-    for (int c = tid; c < n_commit; c += blockDim.x) {
-        const int i = commit[c], k = commits0 + c;
+    for (int c = tid; c < n_commit; c += 1024) {
+        const int r = commit[c], lid = leaf_id_at(leaf, par, info, corder, leaves0, r), k = commits0 + c;
+        const int i = (int)(ids[r] & 0xffffu), ch = (int)(ids[r] >> 16);
         const Node nd = nodes[i];
-        out.t.split_leaf[k] = commit_lid[c]; out.t.split_feature[k] = nd.best.feature; out.t.split_bin[k] = nd.best.bin;
+        out.t.split_leaf[k] = lid; out.t.split_feature[k] = nd.best.feature; out.t.split_bin[k] = nd.best.bin;
         out.t.split_gain[k] = nd.best.gain;
         out.t.split_stats[4 * k + 0] = nd.best.left_g; out.t.split_stats[4 * k + 1] = nd.best.left_h;
         out.t.split_stats[4 * k + 2] = nd.best.right_g; out.t.split_stats[4 * k + 3] = nd.best.right_h;
         out.t.split_n_left[k] = nd.n_left;
         const int64_t nl = nd.n_left, nr = nd.count - nd.n_left;
-        atomicAdd(&s_units, (unsigned long long)((nl <= nr ? nl : nr) * (int64_t)F));
-        nodes[nd.child].state = 1; nodes[nd.child].leaf_id = commit_lid[c];
-        nodes[nd.child + 1].state = 1; nodes[nd.child + 1].leaf_id = leaves0 + c;
+        atomicAdd(&s_units[lane & 7], (unsigned long long)((nl <= nr ? nl : nr) * (int64_t)F));
+        // a child that has itself been committed in this call is internal; its own iteration says so
+        const int q0 = rank_of[ch], q1 = rank_of[ch + 1];
+        if (q0 == (int)NO_NODE || corder[q0] == NO_NODE) { nodes[ch].state = 1; nodes[ch].leaf_id = lid; }
+        if (q1 == (int)NO_NODE || corder[q1] == NO_NODE) { nodes[ch + 1].state = 1; nodes[ch + 1].leaf_id = leaves0 + c; }
+        nodes[i].state = 2;
     }
-    __syncthreads();  // a child may itself have been committed in this call: "internal" is written last
-    for (int c = tid; c < n_commit; c += blockDim.x) nodes[commit[c]].state = 2;
-    if (tid == 0) step->hist_units += (int64_t)s_units;
-    if (s_done) {
+    lds_barrier();
+    if (tid == 0) {
+        unsigned long long units = s_units[0];
+#pragma unroll
+        for (int u = 1; u < 8; ++u) units += s_units[u];
+        step->hist_units += (int64_t)units;
+        step->n_commits = commits0 + n_commit; step->n_leaves = leaves0 + n_commit; step->n_known = n_nodes;
+    }
+    if (done) {
         if (tid == 0) {
             step->done = 1; step->n_batch = 0; step->n_part_items = 0; step->n_scan_items = 0;
             hist_counts[0] = 0; hist_counts[1] = 0;
         }
         return;
     }
-    // Batch.  One expansion is certain (the leaf the replay stopped at); expansions beyond those
+    // One expansion is certain (the leaf the selection stopped at); expansions beyond those
     // that the remaining certain ones will need may be spent on speculation.
-    const int remaining = (num_leaves - 1) - (commits0 + n_commit);
-    const int n_expanded0 = st1.x;
+    const int remaining = budget - n_commit;
     const int spare = (max_expand - n_expanded0) - remaining;
     int want = 1 + (spare > 0 ? spare : 0);
     if (want > remaining) want = remaining;
     if (want > batch_max) want = batch_max;
-    // Candidates, marked at their sorted positions: open leaves that are not expanded yet (class 0:
-    // the leaf the replay stopped at is the best of them) and, one level ahead, the not yet
-    // expanded children of expanded open leaves (class 1).  A node's rows outlive the expansion of
-    // its children, so expanding the children of a leaf whose split is not committed yet is safe.
-    // flag: 1 = committed (in this call or before), 1<<16 = class 0 candidate;  flag2: class (1 or 2), 0 none.
-    for (int p = tid; p < P; p += blockDim.x) { flag[p] = 0; flag2[p] = 0; }
-    __syncthreads();
-    for (int c = tid; c < n_commit; c += blockDim.x) flag[posof[commit[c]]] = 1;
-    for (int i = tid; i < n_nodes0; i += blockDim.x)
-        if (rankof[i] == -2) flag[posof[i]] = 1;  // split in an earlier call
-    const int n_leaves_now = s_nleaves;
-    for (int l = tid; l < n_leaves_now; l += blockDim.x) {
-        const unsigned long long e = open[l];
-        if ((e >> 32) == 0ull) continue;
-        const int i = (int)(uint32_t)e;
-        const int c0 = child[i];
-        if (c0 < 0) {
-            const int p = posof[i];
-            flag[p] = 1 << 16; flag2[p] = 1;
-        } else {
-            if (rankof[c0] >= 0 && child[c0] < 0) flag2[posof[c0]] = 2;
-            if (rankof[c0 + 1] >= 0 && child[c0 + 1] < 0) flag2[posof[c0 + 1]] = 2;
+    if (wave == 0) {
+        const int left = P - 64 * lane;
+        const unsigned long long used = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull;
+        const unsigned long long cw = s_comm[lane], ew = s_exp[lane], un = used & ~cw;
+        // A candidate is worth expanding if fewer than `remaining` nodes that can still be committed have a larger
+        // gain; the leaf the selection stopped at always is.
+        const int words = (P + 63) >> 6;
+        int nu = __popcll(un);
+        for (int o = 1; o < words; o <<= 1) { const int u = __shfl_up(nu, o); if (lane >= o) nu += u; }
+        const int before = nu - __popcll(un);
+        const unsigned long long pass = before >= remaining ? 0ull : nu <= remaining ? un : lowest_bits(un, remaining - before);
+        const unsigned long long c0 = s_open[lane] & ~ew & (pass | (lane == (stop >> 6) ? 1ull << (stop & 63) : 0ull));
+        const unsigned long long c1 = s_cls1[lane] & ~ew & pass;
+        const unsigned long long own = (unsigned long long)__popcll(c0) | ((unsigned long long)__popcll(c1) << 16) |
+                                       ((unsigned long long)__popcll(cw) << 32);
+        unsigned long long cnt = own;
+        for (int o = 1; o < words; o <<= 1) { const unsigned long long u = __shfl_up(cnt, o); if (lane >= o) cnt += u; }
+        s_c0[lane] = c0; s_c1[lane] = c1; s_prefix[lane] = cnt - own;
+        if (lane == words - 1) { s_n0 = (int)(cnt & 0xffffu); s_npass = (int)(cnt & 0xffffu) + (int)((cnt >> 16) & 0xffffu); }
+    }
+    lds_barrier();
+    const int n0 = s_n0, n_batch = min(s_npass, want);
+    for (int p = tid; p < P; p += 1024) {
+        const int w = p >> 6;
+        const unsigned long long bit = 1ull << (p & 63), below = bit - 1ull, pre = s_prefix[w];
+        const unsigned long long cw = s_comm[w], c0 = s_c0[w], c1 = s_c1[w];
+        uint32_t id = ids[p];
+        if ((c0 | c1) & bit) {  // order of the batch: class 0 by gain, then class 1 by gain
+            const int o = (c0 & bit) ? (int)(pre & 0xffffu) + __popcll(c0 & below)
+                                     : n0 + (int)((pre >> 16) & 0xffffu) + __popcll(c1 & below);
+            if (o < n_batch) {
+                chosen[o] = (uint16_t)p;
+                id = (id & 0xffffu) | ((uint32_t)(n_nodes + 2 * o) << 16);
+            }
+        }
+        if (!(cw & bit)) {
+            PlanEntry e;
+            e.key = key[p]; e.ids = id; e.leaf = (s_open[w] & bit) ? (uint32_t)leaf_id_at(leaf, par, info, corder, leaves0, p) : NO_NODE;
+            list[p - (int)((pre >> 32) & 0xffffu) - __popcll(cw & below)] = e;
         }
     }
-    __syncthreads();
-    // prefix over sorted positions: nodes committed in this call and class-0 candidates in front
-    block_scan_array(flag, P, s_tmp);
-    // A candidate is worth expanding if fewer than `remaining` nodes that can still be committed
-    // have a larger gain; the best class-0 candidate always is.
-    for (int p = tid; p < P; p += blockDim.x) {
-        const int cls = flag2[p];
-        int v = 0;
-        if (cls) {
-            const int before = flag[p];
-            const int rank_now = p - (before & 0xffff);
-            const bool pass = rank_now < remaining || (cls == 1 && (before >> 16) == 0);
-            if (pass) v = (cls == 1) ? 1 : (1 << 16);
-        }
-        flag2[p] = v;
-    }
-    __syncthreads();
-    for (int p = tid; p < P; p += blockDim.x) flag[p] = flag2[p];
-    __syncthreads();
-    const int totals = block_scan_array(flag, P, s_tmp);
-    const int n0 = totals & 0xffff, n_pass = n0 + (totals >> 16);
-    const int n_batch = n_pass < want ? n_pass : want;
-    // order of the batch: class 0 by gain, then class 1 by gain
-    for (int p = tid; p < P; p += blockDim.x) {
-        const int v = flag2[p];
-        if (!v) continue;
-        const int o = (v & 0xffff) ? (flag[p] & 0xffff) : n0 + (flag[p] >> 16);
-        if (o < n_batch) batch[o].node = sidx[p];
-    }
-    __syncthreads();
-    __threadfence_block();
-    // segments of the batched partition, new histogram slots, child ids
-    int nseg = 0;
-    if (tid < n_batch) nseg = (int)((nodes[batch[tid].node].count + PART_SEG - 1) / PART_SEG);
-    const int incl = block_scan_incl(nseg, s_tmp);
-    const int n_nodes = n_nodes0, n_slots = st1.y;
+    lds_barrier();
+    // the batch's records: segments of the batched partition, new histogram slots, child ids
+    BatchEntry be;
+    be.n_seg = 0;
     if (tid < n_batch) {
-        const int i = batch[tid].node;
-        batch[tid].seg_start = incl - nseg;
-        batch[tid].n_seg = nseg;
-        batch[tid].new_slot = n_slots + tid;
+        const int i = (int)(ids[chosen[tid]] & 0xffffu);
+        const Node* nd = &nodes[i];
+        be.begin = nd->begin; be.count = (int32_t)nd->count; be.node = i; be.buf = nd->buf;
+        be.feature = nd->best.feature; be.bin = nd->best.bin;
+        be.n_seg = (be.count + PART_SEG - 1) / PART_SEG;
+        be.new_slot = n_slots + tid;
+        be.pad[0] = be.pad[1] = be.pad[2] = be.pad[3] = 0;
         nodes[i].expanded = 1;
         nodes[i].child = n_nodes + 2 * tid;
     }
-    if (tid == n_batch - 1) step->n_part_items = incl;
-    __syncthreads();
-    if (tid == 0) {
+    int incl = be.n_seg;
+    for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(incl, o); if (lane >= o) incl += u; }
+    if (n_batch > 64) {  // uniform over the workgroup
+        if (lane == 63) s_wsum[wave] = incl;
+        lds_barrier();
+        for (int k = 0; k < wave; ++k) incl += s_wsum[k];
+    }
+    if (tid < n_batch) {
+        be.seg_start = incl - be.n_seg;
+        batch[tid] = be;
+        batch_seg[tid] = be.seg_start;
+    }
+    if (tid == n_batch - 1) {
+        step->n_part_items = incl;
         step->n_batch = n_batch;
         step->n_nodes = n_nodes + 2 * n_batch;
         step->n_slots = n_slots + n_batch;
         step->n_expanded = n_expanded0 + n_batch;
         step->rounds = st1.w + 1;
         step->n_scan_items = 2 * n_batch;
+        step->n_list = P - n_commit;
     }
 }
 
@@ -583,17 +668,14 @@ __global__ __launch_bounds__(256) void tree_gather_rows_kernel(const StepState* 
         out[S.begin + j] = identity ? (int32_t)(S.begin + j) : src[S.begin + j];
 }
 
-// LDS of the plan kernel: sort keys and order of all nodes, the new nodes' keys, per-node replay state, and the
-// per-leaf arrays of the replay.
+// LDS of the plan kernel for this context's node capacity.
 static size_t plan_kernel_lds(const qgbdt_ctx* ctx, int num_leaves) {
-    const int p_max = ctx->max_nodes + (ctx->max_nodes & 1);
-    return (size_t)p_max * 24 + (size_t)ctx->batch_max * 16 + (size_t)ctx->max_nodes * 12 +
-           (size_t)(4 * num_leaves + 8) * sizeof(int);
+    return (size_t)plan_lds_layout(ctx->max_nodes, ctx->batch_max, num_leaves).bytes;
 }
 
 int prepare_tree_kernels(qgbdt_ctx* ctx) {
     const size_t plan_lds = plan_kernel_lds(ctx, ctx->shape.max_leaves);
-    if (plan_lds + 512 > 160 * 1024)  // (the kernel's few static words come on top)
+    if (ctx->max_nodes > 4096 || plan_lds + 8192 > 160 * 1024)  // (masks and static words come on top)
         return set_error(ctx, QGBDT_E_UNSUPPORTED, "max_leaves=%d needs %zu bytes of LDS for the growth bookkeeping (limit 160 KB)",
                          ctx->shape.max_leaves, plan_lds);
     if (plan_lds > 48 * 1024)
@@ -681,7 +763,6 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
                            p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, fused_cand == nullptr);
     if (rc != QGBDT_OK) return rc;
 
-    const int p_max = ctx->max_nodes + (ctx->max_nodes & 1);  // even: 8-byte arrays follow 4-byte ones
     const size_t plan_lds = plan_kernel_lds(ctx, p->num_leaves);  // at most what prepare_tree_kernels allowed
     const int round_cap = 4 * ctx->shape.max_leaves + 8;  // every round commits or expands at least one node
     int launched = 0;
@@ -689,8 +770,8 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     for (;;) {
         for (int r = 0; r < to_launch; ++r) {
             hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes,
-                               ctx->batch, ctx->sorted_idx, ctx->hist_counts, F, p->num_leaves, ctx->batch_max,
-                               ctx->max_expand, p_max, out, fused_cand, ctx->scan_items);
+                               ctx->batch, ctx->batch_seg, ctx->plan_list, ctx->hist_counts, F, p->num_leaves, ctx->batch_max,
+                               ctx->max_expand, out, fused_cand, ctx->scan_items);
             rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
             if (rc != QGBDT_OK) return rc;
             hipLaunchKernelGGL(tree_mid_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
@@ -708,8 +789,8 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         launched += to_launch;
         // one more plan: commits what the last round made known and tells whether the tree is finished
         hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes,
-                           ctx->batch, ctx->sorted_idx, ctx->hist_counts, F, p->num_leaves, ctx->batch_max,
-                           ctx->max_expand, p_max, out, fused_cand, ctx->scan_items);
+                           ctx->batch, ctx->batch_seg, ctx->plan_list, ctx->hist_counts, F, p->num_leaves, ctx->batch_max,
+                           ctx->max_expand, out, fused_cand, ctx->scan_items);
         QG_HIP(ctx, hipGetLastError());
         QG_HIP(ctx, hipMemcpyAsync(ctx->host_state, ctx->step, sizeof(StepState), hipMemcpyDeviceToHost, ctx->stream));
         QG_HIP(ctx, hipStreamSynchronize(ctx->stream));
