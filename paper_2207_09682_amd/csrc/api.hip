@@ -90,7 +90,10 @@ static void derive_sizes(qgbdt_ctx* c) {
     c->batch_max = L;
     c->max_expand = 3 * L;
     c->max_nodes = 2 * c->max_expand + 1;
-    c->max_seg = (int)(c->shape.n_rows / PART_SEG) + c->batch_max + 2;
+    c->seg_rows = 256 * part_rows(c->shape.n_rows);
+    c->seg_supers = part_supers(c->shape.n_rows) ? 1 : 0;
+    c->max_seg = (int)(c->shape.n_rows / c->seg_rows) + c->batch_max + 2;
+    c->max_super = c->max_seg / PART_SUPER + c->batch_max + 2;
 }
 
 // Bytes of the row groups' slots (local bins handed over to the reduce kernel): the largest any plan of this
@@ -146,7 +149,8 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     k.take(&c->flags, N);
     k.take(&c->part_counts, (size_t)PART_GROUPS);
     k.take(&c->seg_counts, (size_t)c->max_seg);
-    k.take(&c->seg_prefix, (size_t)c->max_seg + 1);
+    k.take(&c->super_counts, (size_t)c->max_super);
+    k.take(&c->part_masks, (size_t)c->max_seg * (size_t)(c->seg_rows / 64));
     k.take(&c->absmax_part, (size_t)2 * QUANT_PARTS);
     k.take(&c->qtotals_part, (size_t)3 * QUANT_PARTS);
     k.take(&c->qtotals, 4);

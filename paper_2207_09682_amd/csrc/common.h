@@ -55,7 +55,8 @@ struct BatchEntry {
     int32_t new_slot;   // histogram slot of the child that is built from its rows
     int32_t buf;
     int32_t feature, bin;  // its split
-    int32_t pad[4];
+    int32_t super_start;   // first of its groups of PART_SUPER segments (without such counters: of its segments)
+    int32_t pad[3];
 };
 
 // One known node whose split is not committed yet and has a gain, in the gain order kept from round to round.
@@ -173,7 +174,10 @@ struct qgbdt_ctx {
     int batch_max;   // most nodes expanded per round
     int max_expand;  // most expansions per tree (sequential ones plus speculative ones)
     int max_nodes;
+    int seg_rows;   // rows per segment of the batched partition
+    int seg_supers; // 1: with counters per PART_SUPER segments
     int max_seg;
+    int max_super;
     int rounds_hint;
     // workspace
     int ordered;           // the workspace holds leaf-ordered copies of the rows (narrow rows, QGBDT_WS_ROW_COPIES)
@@ -191,10 +195,11 @@ struct qgbdt_ctx {
     int64_t* hist_pool;    // [max_expand + 1][nb*F]
     void* hist_partials;   // [max_items][n_tiles] local bins of the row groups, summed by the reduce kernel
     size_t hist_partials_bytes;
-    uint8_t* flags;        // [N] partition flags
+    uint8_t* flags;        // [N] partition flags (stand-alone partition)
+    unsigned long long* part_masks;  // [max_seg][rows per segment / 64] a bit per row of the round's partitions: goes left
     int64_t* part_counts;  // [PART_GROUPS] (stand-alone partition)
     int32_t* seg_counts;   // [max_seg] left rows per partition segment
-    int32_t* seg_prefix;   // [max_seg + 1]
+    int32_t* super_counts; // [max_super] left rows per group of PART_SUPER segments of a node
     float* absmax_part;    // [QUANT_PARTS][2] per-workgroup max|g|, max h
     int64_t* qtotals_part; // [QUANT_PARTS][3] per-workgroup quantized totals
     int64_t* qtotals;      // [3] sum g~, sum h~, sum |g~|
@@ -228,7 +233,16 @@ namespace qgbdt {
 constexpr int PART_GROUPS = 512;
 constexpr int REFIT_PARTS = 32;
 constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
-constexpr int PART_SEG = 1024;  // rows per partition segment of the batched partition
+// Rows per thread of a segment of the batched partition (256 threads; the loads of a thread's rows are in flight
+// together), and whether the left rows of PART_SUPER segments are summed up in one counter on the way.
+//  - Up to 2^18 rows 2 rows per thread: segments of 2048 rows would leave most compute units without one (count + scatter
+//    kernel per round on 10 k x 28 in ordered mode: 17.0 us with 8, 10.0 us with 2); above that 8, which spreads a
+//    wavefront's fixed work per segment (1 M x 28: 10.8 us with 8, 14.6 us with 2).
+//  - The counters save the scatter kernel a walk over all of a node's segments (2 KB per wavefront and million rows), but
+//    their device-wide atomics lengthen the count kernel by about 2 us: 1 M x 28 7.9 us with, 6.1 us without.
+inline int part_rows(int64_t n_rows) { return n_rows > ((int64_t)1 << 18) ? 8 : 2; }
+inline bool part_supers(int64_t n_rows) { return n_rows > ((int64_t)3 << 20); }
+constexpr int PART_SUPER = 32;  // segments whose left rows are summed up in one counter
 // Most nodes expanded in one round = most builds of a histogram launch (the leaf budget; the growth bookkeeping
 // limits it to 658).  Kernels keep the first work item of every build / node in LDS and search there: a binary
 // search through global memory costs a chain of dependent loads per work item.
@@ -279,7 +293,8 @@ int launch_fix_frequent_bins(qgbdt_ctx* ctx, int64_t* hist, const int64_t* total
 int require_workspace(qgbdt_ctx* ctx);   // QGBDT_E_WORKSPACE unless a workspace block is set
 int prepare_hist_kernels(qgbdt_ctx* ctx);  // once per context: dynamic-LDS limits of the kernels that exceed the default
 int prepare_tree_kernels(qgbdt_ctx* ctx);
-int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered);  // !ordered: row ids and, with rows.gh_pos, packed gradients
+// !ordered: row ids and, with rows.gh_pos, packed gradients; `plan`: of the histogram launch that follows
+int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered, const HistPlan& plan);
 int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const float2* pairs, const int32_t* row_idx,
                  const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves,
                  const int32_t* n_leaves_dev, double* value_out);

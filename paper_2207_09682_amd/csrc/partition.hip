@@ -7,7 +7,7 @@
 // qgbdt_partition_rows (row ids only), then the batched form of grow_tree, which serves
 // all nodes of a round at once and, for narrow rows, also moves the bin rows and packed
 // gradients into leaf order.
-#include "common.h"
+#include "split_device.h"
 
 namespace qgbdt {
 
@@ -166,8 +166,10 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
 
 // ---- batched partition of the nodes expanded in one round of grow_tree ---------------
 //
-// Work items are row segments of PART_SEG rows; segment -> (batch entry, segment of that
-// node) by binary search over the entries' first-segment numbers.
+// Work items are row segments of 256 * R rows (R: part_rows); segment -> (batch entry, segment of that
+// node) by binary search over the entries' first-segment numbers.  A wavefront takes 64 * R consecutive rows of
+// its segment; which of them go left is one 64-bit mask per 64 rows (128 bytes of masks for 1024 rows instead of a byte
+// per row), from which the scatter derives every destination without exchanging anything between wavefronts.
 
 // (The entries' first segments are copied into LDS once per workgroup and searched there: through global memory the
 // search is a chain of dependent loads per segment.)
@@ -184,132 +186,267 @@ __device__ __forceinline__ int find_batch(const int* s_start, int n_batch, int i
     return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// Left-going rows per segment (flags kept as bytes); on the way the histogram slots
+// Left-going rows per segment, as masks and counts; on the way the histogram slots
 // that this round's builds accumulate into are cleared.  In ordered mode the rows of a
 // node are physically contiguous in its buffer and the bin is read at the row's position;
 // otherwise it is gathered from the original matrix through the row id.
+// Bound by the gather (a line of the split feature's column, or of the matrix, for one to a few rows at the deep
+// levels): all R row ids of a thread, then all its bins are in flight together.
+// Measured per round with one row in flight at a time and a flag byte per row, then so: 43.1 -> 41.2 us on 10.5 M x 28
+// (bound; 6 TB/s of lines), 7.2 -> 6.1 us on 1 M x 28, 12.1 -> 10.7 us on 2 M x 40 of 16-bit bins.
+template <int R>
 __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, const uint8_t* __restrict__ bins_t, int64_t n_rows, int ordered,
                                                                int bb, int F, IdxSet idxs,
                                                                const StepState* __restrict__ step,
                                                                const BatchEntry* __restrict__ batch,
                                                                const int32_t* __restrict__ batch_seg,
-                                                               uint8_t* __restrict__ flags,
-                                                               int32_t* __restrict__ seg_counts, int64_t* hist_base,
+                                                               unsigned long long* __restrict__ masks,
+                                                               int32_t* __restrict__ seg_counts,
+                                                               int32_t* __restrict__ super_counts, int64_t* hist_base,
                                                                int64_t hist_words) {
+    constexpr int PART_SEG = 256 * R;
     if (step->done) return;
     const int n_items = step->n_part_items, n_batch = step->n_batch;
     if (n_batch <= 0) return;
     {
-        int64_t* z = hist_base + (int64_t)batch[0].new_slot * hist_words;  // the new slots are consecutive
+        int64_t* z = hist_base + (int64_t)(step->n_slots - n_batch) * hist_words;  // the new slots are the last ones
         const int64_t nz = (int64_t)n_batch * hist_words;
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nz; i += (int64_t)gridDim.x * blockDim.x)
             z[i] = 0;
     }
-    __shared__ int sc[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ int sc[2][4];
     __shared__ int s_start[TABLE_MAX];
     load_batch(batch_seg, n_batch, s_start);
-    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+    int turn = 0;
+    for (int item = blockIdx.x; item < n_items; item += gridDim.x, turn ^= 1) {
         const BatchEntry nd = batch[find_batch(s_start, n_batch, item)];
-        const int32_t* src = idxs.p[nd.buf] + nd.begin;
-        const uint8_t* brow = rows.bins[ordered ? nd.buf : BUF_ORIGINAL] + (ordered ? nd.begin * (int64_t)F : 0);
-        // with a feature-major copy of the matrix the split feature's column is read instead: the ascending row
-        // ids of a node then fall into few sectors, where the row-major matrix costs one sector per row
-        const uint8_t* col = (bins_t && !ordered) ? bins_t + (int64_t)nd.feature * n_rows * bb : nullptr;
-        const int64_t sbegin = (int64_t)(item - nd.seg_start) * PART_SEG;
-        const int64_t send = min((int64_t)nd.count, sbegin + PART_SEG);
-        const int feature = nd.feature, bin = nd.bin;
-        int cnt = 0;
-        for (int64_t p = sbegin + threadIdx.x; p < send; p += blockDim.x) {
-            const int64_t row = (ordered || nd.buf == BUF_ORIGINAL) ? p : (int64_t)src[p];  // the root's list is the identity
-            const int fl = (col ? bin_at(col, row, bb) : bin_at(brow, row * F + feature, bb)) <= bin;
-            flags[nd.begin + p] = (uint8_t)fl;
-            cnt += fl;
+        const int seg = item - nd.seg_start;
+        const int sbegin = seg * PART_SEG, n = min(nd.count - sbegin, PART_SEG);  // rows of the segment, inside the node's slice
+        const int32_t* src = idxs.p[nd.buf] + nd.begin + sbegin;
+        const bool identity = ordered || nd.buf == BUF_ORIGINAL;  // the root's list is the identity
+        int64_t row[R];
+        int v[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int r = min((wave * R + u) * 64 + lane, n - 1);  // (past the end: the last row again, not counted)
+            row[u] = identity ? (int64_t)(sbegin + r) : (int64_t)src[r];
         }
-        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) sc[threadIdx.x >> 6] = cnt;
-        __syncthreads();
-        if (threadIdx.x == 0) seg_counts[item] = sc[0] + sc[1] + sc[2] + sc[3];
+        if (bins_t && !ordered) {
+            // with a feature-major copy of the matrix the split feature's column is read: the ascending row
+            // ids of a node then fall into few sectors, where the row-major matrix costs one sector per row
+            const uint8_t* col = bins_t + (int64_t)nd.feature * n_rows * bb;
+#pragma unroll
+            for (int u = 0; u < R; ++u) v[u] = bin_at(col, row[u], bb);
+        } else {
+            const uint8_t* brow = rows.bins[ordered ? nd.buf : BUF_ORIGINAL] + (ordered ? nd.begin * (int64_t)F : 0);
+#pragma unroll
+            for (int u = 0; u < R; ++u) v[u] = bin_at(brow, row[u] * F + nd.feature, bb);
+        }
+        int cnt = 0;
+        unsigned long long mine = 0ull;  // lane u keeps the wavefront's u-th mask
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const unsigned long long m = __ballot(v[u] <= nd.bin && (wave * R + u) * 64 + lane < n);
+            cnt += __popcll(m);
+            if (lane == u) mine = m;
+        }
+        if (lane < R) masks[(int64_t)item * (PART_SEG / 64) + wave * R + lane] = mine;
+        if (lane == 0) sc[turn][wave] = cnt;
+        __syncthreads();  // (two turns: the next item's counts go to the other half)
+        if (threadIdx.x == 0) {
+            const int c = sc[turn][0] + sc[turn][1] + sc[turn][2] + sc[turn][3];
+            seg_counts[item] = c;
+            if (super_counts) atomicAdd(&super_counts[nd.super_start + seg / PART_SUPER], c);
+        }
     }
 }
 
-// Order-preserving scatter of every segment into the children's buffer; seg_prefix is the
-// exclusive prefix of seg_counts over all segments of the round.  A workgroup takes a whole
-// segment (PART_SEG = 4 x 256 rows) at once: four rows per thread are loaded together, their
-// destinations follow from one round of ballots, and then (ORDERED) the bin rows move as
-// dwords, eight independent loads per thread in flight, coalesced on the reading side and in
-// two compacted streams on the writing side; the packed gradients move with the row ids.
-template <int MODE>  // 0: row ids, 1: row ids and packed gradients, 2: those and the bin rows (ordered mode)
+// Sum over the 64 lanes with DPP moves (no LDS traffic); the result is uniform.
+__device__ __forceinline__ int wave_sum(int v) {
+#define QG_DPP_ADD(x, ctrl, rmask) ((x) + __builtin_amdgcn_update_dpp(0, (x), ctrl, rmask, 0xf, false))
+    v = QG_DPP_ADD(v, 0x111, 0xf);  // row_shr:1
+    v = QG_DPP_ADD(v, 0x112, 0xf);  // row_shr:2
+    v = QG_DPP_ADD(v, 0x114, 0xf);  // row_shr:4
+    v = QG_DPP_ADD(v, 0x118, 0xf);  // row_shr:8: lane 15 of a row holds the row's sum, lane k the sum up to k
+    v = QG_DPP_ADD(v, 0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+    v = QG_DPP_ADD(v, 0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+    return __builtin_amdgcn_readlane(v, 63);
+}
+// Inclusive prefix sum over the lanes, the same way.
+__device__ __forceinline__ int wave_prefix(int v) {
+    v = QG_DPP_ADD(v, 0x111, 0xf);
+    v = QG_DPP_ADD(v, 0x112, 0xf);
+    v = QG_DPP_ADD(v, 0x114, 0xf);
+    v = QG_DPP_ADD(v, 0x118, 0xf);
+    v = QG_DPP_ADD(v, 0x142, 0xa);
+    v = QG_DPP_ADD(v, 0x143, 0xc);
+    return v;
+#undef QG_DPP_ADD
+}
+
+// The children of every expanded node and the tables of the histogram and scan kernels, by one workgroup of 256 threads
+// while the others move rows: it needs nothing of them but the left counts that the count kernel left behind.
+__device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __restrict__ batch,
+                             const int32_t* __restrict__ super_counts, HistEntry* hist_entries, int32_t* hist_counts,
+                             ScanItem* items, const HistPlan& plan, int super_len, int* s_start, int* s_left, int* s_tmp) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_batch = step->n_batch;
+    for (int t = tid; t < n_batch; t += 256) { s_start[t] = batch[t].super_start; s_left[t] = 0; }
+    __syncthreads();
+    const int last = n_batch - 1;
+    const int n_super = s_start[last] + (batch[last].n_seg + super_len - 1) / super_len;
+    for (int k = tid; k < n_super; k += 256) {
+        int lo = 0, hi = last;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_start[mid] <= k) lo = mid; else hi = mid - 1;
+        }
+        atomicAdd(&s_left[lo], super_counts[k]);
+    }
+    __syncthreads();
+    // rows of the builds (the smaller children), then their row groups: about max_groups items in total, shared out by size
+    int small_total = 0;
+    for (int t = tid; t < n_batch; t += 256) {
+        const int nl = s_left[t], nr = batch[t].count - nl;
+        small_total += min(nl, nr);
+    }
+    for (int o = 32; o > 0; o >>= 1) small_total += __shfl_xor(small_total, o);
+    if (lane == 0) s_tmp[wave] = small_total;
+    __syncthreads();
+    small_total = s_tmp[0] + s_tmp[1] + s_tmp[2] + s_tmp[3];
+    const int target = (int)hist_target_rows(plan, small_total, n_batch);
+    int base = 0;
+    for (int t0 = 0; t0 < n_batch; t0 += 256) {  // (uniform trip count)
+        const int t = t0 + tid;
+        int nl = 0, nr = 0, groups = 0;
+        BatchEntry be;
+        if (t < n_batch) {
+            be = batch[t];
+            nl = s_left[t]; nr = be.count - nl;
+            groups = max(1, (min(nl, nr) + target - 1) / target);
+        }
+        const int incl = wave_prefix(groups);
+        __syncthreads();
+        if (lane == 63) s_tmp[wave] = incl;
+        __syncthreads();
+        int start = base + incl - groups;
+        for (int k = 0; k < wave; ++k) start += s_tmp[k];
+        base += s_tmp[0] + s_tmp[1] + s_tmp[2] + s_tmp[3];
+        if (t < n_batch) {
+            Node* P = &nodes[be.node];
+            const int slot = P->slot, child = P->child;
+            const int64_t lg = P->best.left_g, lh = P->best.left_h, rg = P->best.right_g, rh = P->best.right_h;
+            P->n_left = nl;
+            const bool left_small = nl <= nr;
+            const int lslot = left_small ? be.new_slot : slot, rslot = left_small ? slot : be.new_slot;
+            const int cb = child_buffer(be.buf);
+            auto put = [&](int which, int64_t begin, int count, int64_t g, int64_t h, int sl) {
+                Node* c = &nodes[child + which];
+                c->begin = begin; c->count = count; c->sum_g = g; c->sum_h = h; c->n_left = 0; c->buf = cb; c->slot = sl;
+                c->state = 0; c->expanded = 0; c->child = -1; c->leaf_id = -1;
+                c->best.gain = 0.0; c->best.feature = -1; c->best.bin = -1;
+                c->best.left_g = c->best.left_h = c->best.right_g = c->best.right_h = c->best.left_count = 0;
+                const bool is_small = (which == 0) == left_small;
+                ScanItem it;
+                it.slot = sl; it.sub_parent = is_small ? -1 : slot; it.sub_child = is_small ? -1 : be.new_slot; it.valid = 1;
+                it.stat.n_rows = count; it.stat.sum_g = g; it.stat.sum_h = h;
+                it.out = &c->best;
+                items[2 * t + which] = it;
+            };
+            put(0, be.begin, nl, lg, lh, lslot);
+            put(1, be.begin + nl, nr, rg, rh, rslot);
+            HistEntry e;
+            e.begin = left_small ? be.begin : be.begin + nl; e.count = left_small ? nl : nr; e.buf = cb; e.slot = be.new_slot;
+            e.item_start = start; e.groups = groups;
+            hist_entries[t] = e;
+        }
+    }
+    if (tid == 0) { hist_counts[0] = n_batch; hist_counts[1] = base; }
+}
+
+// Order-preserving scatter of every segment into the children's buffer.  The left rows in front of a segment are the sum
+// of the node's super counts (SUPER segments each) and of the segment counts in front of it inside its super group: every wavefront adds them
+// up for itself (DPP sums), reads the segment's masks and knows where each of its rows goes, so no wavefront waits for
+// another.  In ordered mode (MODE 2) the bin rows then move as dwords, eight independent loads per thread in flight,
+// coalesced on the reading side and in two compacted streams on the writing side; the packed gradients move with the row ids.
+// The first workgroup builds the next kernels' tables meanwhile (child_tables), which was a launch of its own between the
+// two passes: 12.2 us per round on 10.5 M x 28, 5.4 us on 1 M x 28.  The scatter itself: 29.1 -> 26.6 us and 5.0 -> 4.7 us.
+template <int MODE, int R, int SUPER>  // 0: row ids, 1: row ids and packed gradients, 2: those and the bin rows (ordered mode)
 __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows, RowDest out, int F, IdxSet idxs,
-                                                                 const StepState* __restrict__ step,
-                                                                 const BatchEntry* __restrict__ batch,
-                                                                 const int32_t* __restrict__ batch_seg,
-                                                                 const Node* __restrict__ nodes,
-                                                                 const uint8_t* __restrict__ flags,
-                                                                 const int32_t* __restrict__ seg_prefix) {
-    static_assert(PART_SEG == 1024, "four sub-tiles of 256 rows");
+                                                                 StepState* step, const BatchEntry* __restrict__ batch,
+                                                                 const int32_t* __restrict__ batch_seg, Node* nodes,
+                                                                 const unsigned long long* __restrict__ masks,
+                                                                 const int32_t* __restrict__ seg_counts,
+                                                                 const int32_t* __restrict__ super_counts,
+                                                                 HistEntry* hist_entries, int32_t* hist_counts,
+                                                                 ScanItem* items, HistPlan plan) {
+    constexpr int PART_SEG = 256 * R;
     if (step->done) return;
-    const int n_items = step->n_part_items, n_batch = step->n_batch;
-    __shared__ int wl[4][4];
-    __shared__ int s_dpos[PART_SEG];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int dpr = F / 4;
     __shared__ int s_start[TABLE_MAX];
+    __shared__ int s_dpos[MODE == 2 && PART_SEG > TABLE_MAX + 8 ? PART_SEG : TABLE_MAX + 8];  // (also child_tables' LDS)
+    if (blockIdx.x == 0) {
+        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, items, plan, SUPER, s_start, s_dpos, s_dpos + TABLE_MAX);
+        return;
+    }
+    const int n_items = step->n_part_items, n_batch = step->n_batch;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int dpr = F / 4;
     load_batch(batch_seg, n_batch, s_start);
     // Segments are taken from the last to the first: the count kernel has just streamed the same
     // rows front to back, so the tail of that stream is what the memory-side cache still holds.
-    for (int item = n_items - 1 - (int)blockIdx.x; item >= 0; item -= (int)gridDim.x) {
+    for (int item = n_items - (int)blockIdx.x; item >= 0; item -= (int)gridDim.x - 1) {
         const BatchEntry nd = batch[find_batch(s_start, n_batch, item)];
+        const int seg = item - nd.seg_start, sup = seg / SUPER;
+        const int sbegin = seg * PART_SEG, n = min(nd.count - sbegin, PART_SEG);
+        const int n_sup = (nd.n_seg + SUPER - 1) / SUPER;
         const int cbuf = child_buffer(nd.buf);
         const bool identity = nd.buf == BUF_ORIGINAL;  // the root's list: row id = position, never stored
-        const int32_t* src = idxs.p[nd.buf] + nd.begin;
+        const int32_t* src = idxs.p[nd.buf] + nd.begin + sbegin;
         int32_t* dst = idxs.p[cbuf] + nd.begin;
-        const int16_t* gsrc = MODE >= 1 ? rows.gh[nd.buf] + nd.begin : nullptr;
+        const int16_t* gsrc = MODE >= 1 ? rows.gh[nd.buf] + nd.begin + sbegin : nullptr;
         int16_t* gdst = MODE >= 1 ? out.gh[cbuf] + nd.begin : nullptr;
-        const uint8_t* bsrc = MODE == 2 ? rows.bins[nd.buf] + nd.begin * (int64_t)F : nullptr;
-        uint8_t* bdst = MODE == 2 ? out.bins[cbuf] + nd.begin * (int64_t)F : nullptr;
-        const int64_t sbegin = (int64_t)(item - nd.seg_start) * PART_SEG;
-        const int64_t send = min((int64_t)nd.count, sbegin + PART_SEG);
-        const int n = (int)(send - sbegin);
-        const int64_t before = seg_prefix[item] - seg_prefix[nd.seg_start];  // left rows in earlier segments
-        const int64_t lpos0 = before;                          // first left slot of this segment (slice-relative)
-        const int64_t rpos0 = nodes[nd.node].n_left + (sbegin - before);   // first right slot
-        int fl[4], rank[4], g16[4];
-        int32_t v[4];
+        // everything that is read, in flight together
+        int32_t v[R];
+        int g16[R];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int r = u * 256 + threadIdx.x;
-            fl[u] = 0; v[u] = 0; g16[u] = 0;
-            if (r < n) {
-                fl[u] = flags[nd.begin + sbegin + r];
-                v[u] = identity ? (int32_t)(nd.begin + sbegin + r) : src[sbegin + r];
-                if (MODE >= 1) g16[u] = gsrc[sbegin + r];
-            }
+        for (int u = 0; u < R; ++u) {
+            const int r = min((wave * R + u) * 64 + lane, n - 1);
+            v[u] = identity ? (int32_t)(nd.begin + sbegin + r) : src[r];
+            g16[u] = MODE >= 1 ? gsrc[r] : 0;
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const unsigned long long m = __ballot(fl[u] != 0);
-            rank[u] = __popcll(m & ((1ull << lane) - 1ull));
-            if (lane == 0) wl[u][wave] = __popcll(m);
+        const unsigned long long mk = lane < PART_SEG / 64 ? masks[(int64_t)item * (PART_SEG / 64) + lane] : 0ull;
+        int before = SUPER > 1 && lane < seg - sup * SUPER ? seg_counts[item - (seg - sup * SUPER) + lane] : 0;
+        int total = 0;
+        for (int k = lane; k < n_sup; k += 64) {
+            const int c = super_counts[nd.super_start + k];
+            total += c;
+            before += k < sup ? c : 0;
         }
-        __syncthreads();
+        static_assert(SUPER <= 64 && PART_SEG / 64 <= 64, "one lane each");
+        before = wave_sum(before);  // left rows in earlier segments
+        total = wave_sum(total);    // left rows of the node
+        const int pc = __popcll(mk);
+        const int pre = wave_prefix(pc) - pc;  // left rows of the segment in front of a mask's 64 rows
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            int lw = 0;  // left rows of the segment in front of this wavefront's 64 rows of sub-tile u
-            for (int uu = 0; uu < 4; ++uu)
-                for (int w = 0; w < 4; ++w)
-                    if (uu < u || (uu == u && w < wave)) lw += wl[uu][w];
-            const int r = u * 256 + threadIdx.x;
-            const int64_t dp = fl[u] ? lpos0 + lw + rank[u] : rpos0 + (r - (lw + rank[u]));
+        for (int u = 0; u < R; ++u) {
+            const int w = wave * R + u, r = w * 64 + lane;
+            const uint32_t mlo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mk, w);
+            const uint32_t mhi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mk >> 32), w);
+            const int left = __builtin_amdgcn_readlane(pre, w) + (int)__builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0u));
+            const bool fl = ((lane < 32 ? mlo : mhi) >> (lane & 31)) & 1u;
+            const int dp = fl ? before + left : total + (sbegin - before) + (r - left);
             if (r < n) {
                 dst[dp] = v[u];
                 if (MODE >= 1) gdst[dp] = (int16_t)g16[u];
-                if (MODE == 2) s_dpos[r] = (int)dp;
+                if (MODE == 2) s_dpos[r] = dp;
             }
         }
         if (MODE == 2) {
+            const uint8_t* bsrc = rows.bins[nd.buf] + (nd.begin + sbegin) * (int64_t)F;
+            uint8_t* bdst = out.bins[cbuf] + nd.begin * (int64_t)F;
             __syncthreads();
-            const uint32_t* s32 = reinterpret_cast<const uint32_t*>(bsrc + sbegin * (int64_t)F);
+            const uint32_t* s32 = reinterpret_cast<const uint32_t*>(bsrc);
             const int n_dw = n * dpr;
             for (int e0 = threadIdx.x; e0 < n_dw; e0 += 8 * 256) {
                 uint32_t v8[8];
@@ -327,8 +464,8 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
                     }
                 }
             }
+            __syncthreads();  // s_dpos is reused by the next item
         }
-        __syncthreads();  // wl and s_dpos are reused by the next item
     }
 }
 
@@ -347,24 +484,38 @@ static IdxSet idx_set(const qgbdt_ctx* ctx) {
 
 int launch_batch_partition_count(qgbdt_ctx* ctx, const RowSource& rows, const uint8_t* bins_t, bool ordered) {
     const int64_t W = (int64_t)ctx->shape.n_features * ctx->shape.n_bins;
-    hipLaunchKernelGGL(batch_part_count_kernel, dim3(batch_part_grid(ctx)), dim3(256), 0, ctx->stream, rows, bins_t,
-                       ctx->shape.n_rows, ordered ? 1 : 0, ctx->shape.bin_bytes, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch,
-                       ctx->batch_seg, ctx->flags, ctx->seg_counts, ctx->hist_pool, W);
+#define QG_COUNT(R_)                                                                                                   \
+    hipLaunchKernelGGL(batch_part_count_kernel<R_>, dim3(batch_part_grid(ctx)), dim3(256), 0, ctx->stream, rows, bins_t, \
+                       ctx->shape.n_rows, ordered ? 1 : 0, ctx->shape.bin_bytes, ctx->shape.n_features, idx_set(ctx),  \
+                       ctx->step, ctx->batch, ctx->batch_seg, ctx->part_masks, ctx->seg_counts, supers, \
+                       ctx->hist_pool, W)
+    int32_t* const supers = ctx->seg_supers ? ctx->super_counts : nullptr;
+    if (ctx->seg_rows == 256 * 8) QG_COUNT(8); else QG_COUNT(2);
+#undef QG_COUNT
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
 
-int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered) {
+int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered, const HistPlan& plan) {
     RowDest out;
     for (int b = 0; b < 3; ++b) { out.bins[b] = ctx->obins[b]; out.gh[b] = ctx->ogh[b]; }
-#define QG_SCATTER(MODE_)                                                                                              \
-    hipLaunchKernelGGL(batch_part_scatter_kernel<MODE_>, dim3(batch_part_grid(ctx)), dim3(256), 0, ctx->stream, rows, \
-                       out, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch, ctx->batch_seg, ctx->nodes, ctx->flags, \
-                       ctx->seg_prefix)
+    const int32_t* const sums = ctx->seg_supers ? ctx->super_counts : ctx->seg_counts;
+#define QG_SCATTER_R(MODE_, R_, S_)                                                                                    \
+    hipLaunchKernelGGL((batch_part_scatter_kernel<MODE_, R_, S_>), dim3(batch_part_grid(ctx) + 1), dim3(256), 0, ctx->stream,     \
+                       rows, out, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch, ctx->batch_seg,           \
+                       ctx->nodes, ctx->part_masks, ctx->seg_counts, sums, ctx->hist_entries,                           \
+                       ctx->hist_counts, ctx->scan_items, plan)
+#define QG_SCATTER(MODE_)                                                  \
+    do {                                                                   \
+        if (ctx->seg_supers) QG_SCATTER_R(MODE_, 8, PART_SUPER);           \
+        else if (ctx->seg_rows == 256 * 8) QG_SCATTER_R(MODE_, 8, 1);      \
+        else QG_SCATTER_R(MODE_, 2, 1);                                    \
+    } while (0)
     if (ordered) QG_SCATTER(2);
     else if (rows.gh_pos) QG_SCATTER(1);
     else QG_SCATTER(0);
 #undef QG_SCATTER
+#undef QG_SCATTER_R
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

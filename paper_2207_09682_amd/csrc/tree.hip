@@ -73,21 +73,6 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
     }
 }
 
-// Inclusive scan of one int per thread over the workgroup (1024 threads).
-__device__ __forceinline__ int block_scan_incl(int v, int* tmp /*[16]*/) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(v, o);
-        if (lane >= o) v += u;
-    }
-    __syncthreads();
-    if (lane == 63) tmp[wave] = v;
-    __syncthreads();
-    int add = 0;
-    for (int k = 0; k < wave; ++k) add += tmp[k];
-    return v + add;
-}
-
 // Barrier for data exchanged through LDS only: unlike __syncthreads it does not wait for the acknowledgement of
 // global stores that nobody in the workgroup reads.
 __device__ __forceinline__ void lds_barrier() {
@@ -183,8 +168,8 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 // (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
 // (20 M x 200, 511 leaves).
 __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch, int32_t* batch_seg,
-                                                         PlanEntry* list, int32_t* hist_counts, int F, int num_leaves,
-                                                         int batch_max, int max_expand, TreeOut out,
+                                                         int32_t* super_counts, PlanEntry* list, int32_t* hist_counts, int F, int num_leaves,
+                                                         int batch_max, int max_expand, int seg_rows, int seg_supers, TreeOut out,
                                                          const FeatCand* __restrict__ cand,
                                                          const ScanItem* __restrict__ scan_items) {
     // the fields of the growth state this kernel needs and (for the first 1024 ranks) the kept order, in loads that are
@@ -213,7 +198,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     __shared__ unsigned long long s_open[64], s_exp[64], s_comm[64], s_cls1[64];
     __shared__ unsigned long long s_c0[64], s_c1[64], s_prefix[64];  // batch candidates; prefix counts: class 0 | class 1 << 16 | committed << 32
     __shared__ int s_nc, s_nnew, s_tie, s_stop, s_n0, s_npass;
-    __shared__ int s_wsum[16];
+    __shared__ unsigned long long s_wsum[16];
     __shared__ unsigned long long s_units[8], s_first[8];  // (eight partial results: an atomic on one address is expanded into a loop over the lanes)
     const int n_nodes = st0.y, leaves0 = st0.z, commits0 = st0.w;
     const int n_expanded0 = st1.x, n_slots = st1.y;
@@ -508,26 +493,34 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         const Node* nd = &nodes[i];
         be.begin = nd->begin; be.count = (int32_t)nd->count; be.node = i; be.buf = nd->buf;
         be.feature = nd->best.feature; be.bin = nd->best.bin;
-        be.n_seg = (be.count + PART_SEG - 1) / PART_SEG;
+        be.n_seg = (int)(((uint32_t)be.count + (uint32_t)seg_rows - 1u) / (uint32_t)seg_rows);
         be.new_slot = n_slots + tid;
-        be.pad[0] = be.pad[1] = be.pad[2] = be.pad[3] = 0;
+        be.pad[0] = be.pad[1] = be.pad[2] = 0;
         nodes[i].expanded = 1;
         nodes[i].child = n_nodes + 2 * tid;
     }
-    int incl = be.n_seg;
-    for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(incl, o); if (lane >= o) incl += u; }
+    // (segments and groups of segments in one scan: groups in the upper half, at most 2^31 / 512 segments below)
+    unsigned long long incl = (unsigned long long)be.n_seg | ((unsigned long long)((be.n_seg + PART_SUPER - 1) / PART_SUPER) << 32);
+    const unsigned long long own = incl;
+    for (int o = 1; o < 64 && o < n_batch; o <<= 1) { const unsigned long long u = __shfl_up(incl, o); if (lane >= o) incl += u; }
     if (n_batch > 64) {  // uniform over the workgroup
         if (lane == 63) s_wsum[wave] = incl;
         lds_barrier();
         for (int k = 0; k < wave; ++k) incl += s_wsum[k];
     }
     if (tid < n_batch) {
-        be.seg_start = incl - be.n_seg;
+        be.seg_start = (int)(uint32_t)(incl - own);
+        be.super_start = seg_supers ? (int)((incl - own) >> 32) : be.seg_start;
         batch[tid] = be;
         batch_seg[tid] = be.seg_start;
     }
+    if (seg_supers) {
+        if (tid == n_batch - 1) s_npass = (int)(incl >> 32);  // (not read again as what it was)
+        lds_barrier();
+        for (int t = tid; t < s_npass; t += 1024) super_counts[t] = 0;  // the count kernel adds to them
+    }
     if (tid == n_batch - 1) {
-        step->n_part_items = incl;
+        step->n_part_items = (int)(uint32_t)incl;
         step->n_batch = n_batch;
         step->n_nodes = n_nodes + 2 * n_batch;
         step->n_slots = n_slots + n_batch;
@@ -536,96 +529,6 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         step->n_scan_items = 2 * n_batch;
         step->n_list = P - n_commit;
     }
-}
-
-// Between the two partition passes: exclusive prefix of the segments' left counts, the
-// children of every expanded node, and the tables of the histogram and scan kernels.
-__global__ __launch_bounds__(1024) void tree_mid_kernel(StepState* step, Node* nodes, const BatchEntry* batch,
-                                                        const int32_t* seg_counts, int32_t* seg_prefix,
-                                                        HistEntry* hist_entries, int32_t* hist_counts, ScanItem* items,
-                                                        HistPlan plan) {
-    if (step->done) return;
-    __shared__ int s_tmp[16];
-    const int tid = threadIdx.x;
-    const int n_items = step->n_part_items, n_batch = step->n_batch;
-    // prefix over all segments: every thread owns a contiguous run (loaded in blocks of eight
-    // independent loads: one dependent load per segment would cost a memory latency each)
-    const int per = (n_items + blockDim.x - 1) / blockDim.x;
-    const int a = min(tid * per, n_items), b = min(a + per, n_items);
-    int local = 0;
-    for (int i0 = a; i0 < b; i0 += 8) {
-        int v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = (i0 + u < b) ? seg_counts[i0 + u] : 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) local += v[u];
-    }
-    const int incl = block_scan_incl(local, s_tmp);
-    int run = incl - local;
-    for (int i0 = a; i0 < b; i0 += 8) {
-        int v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = (i0 + u < b) ? seg_counts[i0 + u] : 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (i0 + u < b) seg_prefix[i0 + u] = run;
-            run += v[u];
-        }
-    }
-    if (tid == (int)blockDim.x - 1) seg_prefix[n_items] = incl;
-    __syncthreads();
-    __threadfence_block();
-    int groups = 0, small_rows = 0;
-    Node L, R;
-    int small_is_left = 1;
-    if (tid < n_batch) {
-        const BatchEntry be = batch[tid];
-        const Node P = nodes[be.node];
-        const int64_t nl = seg_prefix[be.seg_start + be.n_seg] - seg_prefix[be.seg_start];
-        const int64_t nr = P.count - nl;
-        nodes[be.node].n_left = nl;
-        small_is_left = (nl <= nr) ? 1 : 0;
-        const int cb = child_buffer(P.buf);
-        L.begin = P.begin; L.count = nl; L.sum_g = P.best.left_g; L.sum_h = P.best.left_h; L.n_left = 0; L.buf = cb;
-        R.begin = P.begin + nl; R.count = nr; R.sum_g = P.best.right_g; R.sum_h = P.best.right_h; R.n_left = 0; R.buf = cb;
-        L.slot = small_is_left ? be.new_slot : P.slot;
-        R.slot = small_is_left ? P.slot : be.new_slot;
-        L.state = 0; L.expanded = 0; L.child = -1; L.leaf_id = -1; clear_split(L.best);
-        R.state = 0; R.expanded = 0; R.child = -1; R.leaf_id = -1; clear_split(R.best);
-        nodes[P.child] = L; nodes[P.child + 1] = R;
-        small_rows = (int)(small_is_left ? nl : nr);
-        for (int c = 0; c < 2; ++c) {
-            const Node& C = c ? R : L;
-            const bool is_small = (c == 0) == (small_is_left == 1);
-            ScanItem it;
-            it.slot = C.slot;
-            it.sub_parent = is_small ? -1 : P.slot;
-            it.sub_child = is_small ? -1 : be.new_slot;
-            it.valid = 1;
-            it.stat.n_rows = C.count; it.stat.sum_g = C.sum_g; it.stat.sum_h = C.sum_h;
-            it.out = &nodes[P.child + c].best;
-            items[2 * tid + c] = it;
-        }
-    }
-    // row groups of the histogram builds: about max_groups items in total, shared out by size
-    const int total_small = block_scan_incl(small_rows, s_tmp);
-    __shared__ int s_total;
-    if (tid == (int)blockDim.x - 1) s_total = total_small;
-    __syncthreads();
-    if (tid < n_batch) {
-        const int target = (int)hist_target_rows(plan, s_total, n_batch);
-        groups = (small_rows + target - 1) / target;
-        if (groups < 1) groups = 1;
-    }
-    const int gincl = block_scan_incl(groups, s_tmp);
-    if (tid < n_batch) {
-        const Node& S = small_is_left ? L : R;
-        HistEntry e;
-        e.begin = S.begin; e.count = S.count; e.buf = S.buf; e.slot = batch[tid].new_slot;
-        e.item_start = gincl - groups; e.groups = groups;
-        hist_entries[tid] = e;
-    }
-    if (tid == n_batch - 1) { hist_counts[0] = n_batch; hist_counts[1] = gincl; }
 }
 
 __global__ __launch_bounds__(256) void tree_finalize_kernel(const StepState* step, const Node* nodes,
@@ -767,48 +670,38 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     const int round_cap = 4 * ctx->shape.max_leaves + 8;  // every round commits or expands at least one node
     int launched = 0;
     int to_launch = ctx->rounds_hint;
+    auto plan_batch = [&]() {
+        hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
+                           ctx->batch_seg, ctx->super_counts, ctx->plan_list, ctx->hist_counts, F, p->num_leaves,
+                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, out, fused_cand, ctx->scan_items);
+    };
+    auto expand_batch = [&]() {  // partition, histograms and split search of the nodes the plan kernel has chosen
+        int rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
+        if (rc != QGBDT_OK) return rc;
+        rc = launch_batch_partition_scatter(ctx, rows, ordered, plan);
+        if (rc != QGBDT_OK) return rc;
+        rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
+                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb);
+        if (rc != QGBDT_OK) return rc;
+        return launch_scan_items(ctx, ctx->hist_pool, ctx->scan_items, &ctx->step->n_scan_items, 2 * ctx->batch_max,
+                                 ctx->delta, p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, fused_cand == nullptr);
+    };
     for (;;) {
         for (int r = 0; r < to_launch; ++r) {
-            hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes,
-                               ctx->batch, ctx->batch_seg, ctx->plan_list, ctx->hist_counts, F, p->num_leaves, ctx->batch_max,
-                               ctx->max_expand, out, fused_cand, ctx->scan_items);
-            rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
-            if (rc != QGBDT_OK) return rc;
-            hipLaunchKernelGGL(tree_mid_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
-                               ctx->seg_counts, ctx->seg_prefix, ctx->hist_entries, ctx->hist_counts, ctx->scan_items,
-                               plan);
-            rc = launch_batch_partition_scatter(ctx, rows, ordered);
-            if (rc != QGBDT_OK) return rc;
-            rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
-                             ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb);
-            if (rc != QGBDT_OK) return rc;
-            rc = launch_scan_items(ctx, ctx->hist_pool, ctx->scan_items, &ctx->step->n_scan_items, 2 * ctx->batch_max,
-                                   ctx->delta, p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, fused_cand == nullptr);
+            plan_batch();
+            rc = expand_batch();
             if (rc != QGBDT_OK) return rc;
         }
         launched += to_launch;
         // one more plan: commits what the last round made known and tells whether the tree is finished
-        hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes,
-                           ctx->batch, ctx->batch_seg, ctx->plan_list, ctx->hist_counts, F, p->num_leaves, ctx->batch_max,
-                           ctx->max_expand, out, fused_cand, ctx->scan_items);
+        plan_batch();
         QG_HIP(ctx, hipGetLastError());
         QG_HIP(ctx, hipMemcpyAsync(ctx->host_state, ctx->step, sizeof(StepState), hipMemcpyDeviceToHost, ctx->stream));
         QG_HIP(ctx, hipStreamSynchronize(ctx->stream));
         if (ctx->host_state->done) break;
         if (launched > round_cap) return set_error(ctx, QGBDT_E_HIP, "tree growth did not finish in %d rounds", launched);
         // the trailing plan has already chosen a batch: finish that round, then continue
-        rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
-        if (rc != QGBDT_OK) return rc;
-        hipLaunchKernelGGL(tree_mid_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
-                           ctx->seg_counts, ctx->seg_prefix, ctx->hist_entries, ctx->hist_counts, ctx->scan_items,
-                           plan);
-        rc = launch_batch_partition_scatter(ctx, rows, ordered);
-        if (rc != QGBDT_OK) return rc;
-        rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
-                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb);
-        if (rc != QGBDT_OK) return rc;
-        rc = launch_scan_items(ctx, ctx->hist_pool, ctx->scan_items, &ctx->step->n_scan_items, 2 * ctx->batch_max,
-                               ctx->delta, p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, fused_cand == nullptr);
+        rc = expand_batch();
         if (rc != QGBDT_OK) return rc;
         launched += 1;
         to_launch = 3;

@@ -39,3 +39,25 @@ def test_equal_gains_take_the_lowest_leaf(N, F, nb, L):
     e = oracle.grow_tree(bins, nb, g, h, 3, 0, 5, 0, L, min_data=5, rounding=1)
     assert e.n_leaves > 4 and len(set(e.split_gain[1:].tolist())) < e.n_leaves - 2, "the input makes no ties"
     _check(t, e, N)
+
+
+# both sides of the lines at which the partition takes other segments or sums its counts in two levels, ragged ends
+@pytest.mark.parametrize("N,F,L,layout", [(511, 4, 6, 1), (262_144, 5, 63, 1), (262_145, 5, 63, 2), (262_147, 16, 40, 3),
+                                          (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3)])
+def test_partition_segments(N, F, L, layout):
+    rng = np.random.default_rng(N)
+    nb = 32
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    x = bins[:, :3].astype(np.float64) / nb - 0.5
+    y = (rng.random(N) < 1 / (1 + np.exp(-(4 * x[:, 0] + 6 * x[:, 1] * x[:, 2])))).astype(np.float32)
+    p = rng.uniform(0.2, 0.8, N).astype(np.float32)
+    g = (p - y).astype(np.float32); h = (p * (1 - p)).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L)
+    dbins = torch.from_numpy(bins).cuda()
+    e = oracle.grow_tree(bins, nb, g, h, 3, 3, 5, 0, L, min_data=20)
+    for bound in (False, True):
+        ctx.bind_bins(dbins if bound else None)
+        t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 3, 3, 5, 0, L, min_data_in_leaf=20,
+                          row_layout=layout)
+        _check(t, e, N)
