@@ -162,9 +162,9 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     k.take(&c->batch_seg, (size_t)c->batch_max);
     k.take(&c->cand, (size_t)2 * c->batch_max * F);
     k.take(&c->hist_entries, (size_t)c->batch_max);
-    k.take(&c->hist_counts, 2);
+    k.take(&c->hist_counts, 4);
     k.take(&c->pwork, 1);
-    k.take(&c->scan_items, (size_t)2 * c->batch_max);
+    k.take(&c->scan_pairs, (size_t)c->batch_max);
     k.take(&c->leaf_node, L);
     k.take(&c->refit_partial, L * REFIT_PARTS * 2);
     k.take(&c->tmp_i64, 8);
@@ -474,7 +474,7 @@ int qgbdt_find_best_splits(qgbdt_ctx* ctx, const int64_t* hist, int32_t n_hists,
     if (int rcw = require_workspace(ctx)) return rcw;
     if (n_hists < 0) return set_error(ctx, QGBDT_E_INVALID_ARG, "n_hists=%d", n_hists);
     return run_find_best_splits(ctx, hist, n_hists, stats, delta, min_data_in_leaf, min_sum_hessian, out,
-                                2 * ctx->batch_max, ctx->scan_items, ctx->cand, reinterpret_cast<int32_t*>(ctx->tmp_i64));
+                                2 * ctx->batch_max, ctx->scan_pairs, ctx->cand, reinterpret_cast<int32_t*>(ctx->tmp_i64));
 }
 
 int qgbdt_find_best_splits_static(qgbdt_ctx* ctx, const int64_t* hist, int32_t n_hists, const qgbdt_leafstat* stats,
@@ -483,20 +483,21 @@ int qgbdt_find_best_splits_static(qgbdt_ctx* ctx, const int64_t* hist, int32_t n
     if (!hist || !stats || !delta || !out) return set_error(ctx, QGBDT_E_INVALID_ARG, "null pointer");
     if (n_hists < 0) return set_error(ctx, QGBDT_E_INVALID_ARG, "n_hists=%d", n_hists);
     if (!ctx->static_scratch) return set_error(ctx, QGBDT_E_UNSUPPORTED, "no fixed scratch on device %d", ctx->device);
-    // the array holds: the item count [256 bytes], one item per histogram, one candidate per (histogram, feature)
+    // the array holds: the item count [256 bytes], one pair record per two histograms, one candidate per (histogram, tile
+    // of features); the limit is the stated one, 48 + 24 * n_features bytes per histogram, which is never less
+    static_assert(sizeof(ScanPair) / 2 + sizeof(FeatCand) <= 48 + 24, "a histogram of one feature fits the stated limit");
     const size_t F = (size_t)ctx->shape.n_features;
-    const size_t items_off = 256;
-    const size_t cand_off = (items_off + (size_t)n_hists * sizeof(ScanItem) + 255) & ~(size_t)255;
-    const size_t need = cand_off + (size_t)n_hists * F * sizeof(FeatCand);
+    const size_t pairs_off = 256;
+    const size_t cand_off = (pairs_off + ((size_t)n_hists + 1) / 2 * sizeof(ScanPair) + 255) & ~(size_t)255;
+    const size_t need = 512 + (size_t)n_hists * (48 + 24 * F);
     if (need > STATIC_SCRATCH_BYTES)
         return set_error(ctx, QGBDT_E_INVALID_ARG,
                          "n_hists=%d x %d features needs %zu bytes of scratch, the fixed array holds %zu (at most %zu histograms of this shape)",
-                         n_hists, ctx->shape.n_features, need, STATIC_SCRATCH_BYTES,
-                         (STATIC_SCRATCH_BYTES - 512) / (sizeof(ScanItem) + F * sizeof(FeatCand)));
+                         n_hists, ctx->shape.n_features, need, STATIC_SCRATCH_BYTES, (STATIC_SCRATCH_BYTES - 512) / (48 + 24 * F));
     if (n_hists == 0) return QGBDT_OK;
     unsigned char* base = static_cast<unsigned char*>(ctx->static_scratch);
     return run_find_best_splits(ctx, hist, n_hists, stats, delta, min_data_in_leaf, min_sum_hessian, out, n_hists,
-                                reinterpret_cast<ScanItem*>(base + items_off), reinterpret_cast<FeatCand*>(base + cand_off),
+                                reinterpret_cast<ScanPair*>(base + pairs_off), reinterpret_cast<FeatCand*>(base + cand_off),
                                 reinterpret_cast<int32_t*>(base));
 }
 

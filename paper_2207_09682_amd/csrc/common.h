@@ -66,12 +66,12 @@ struct PlanEntry {
     uint32_t leaf;           // leaf id, 0xffff: not an open leaf (its parent's split is not committed)
 };
 
-// Candidate of one (leaf, feature) pair produced by the scan kernel.
+// Best candidate of one (leaf, tile of features) pair produced by the scan kernel.
 struct FeatCand {
     double gain;
     int64_t left;  // packed prefix word (G_L | H_L)
     int32_t bin;   // -1: no valid candidate
-    int32_t pad;
+    int32_t feature;
 };
 
 // One histogram build: a row slice accumulated into one slot, cut into `groups` row groups
@@ -134,7 +134,7 @@ __host__ __device__ inline int64_t hist_target_rows(const HistPlan& p, int64_t t
     return t;
 }
 
-struct ScanItem;
+struct ScanPair;
 
 // Where the rows of a slice live.  Buffers 0..2 rotate with the depth of a node (the children
 // of buffer b live in buffer (b+1)%3, so a node's rows survive until its grandchildren are
@@ -211,9 +211,9 @@ struct qgbdt_ctx {
     int32_t* batch_seg;          // [batch_max] their first segments, for the search segment -> node
     qgbdt::FeatCand* cand;       // [2*batch_max][F]
     qgbdt::HistEntry* hist_entries;  // [batch_max]
-    int32_t* hist_counts;        // [2] entries, items
+    int32_t* hist_counts;        // [3] entries, items, 1: an entry has more than REDUCE_ABOVE groups
     qgbdt::PartWork* pwork;      // [1]
-    qgbdt::ScanItem* scan_items; // [2*batch_max]
+    qgbdt::ScanPair* scan_pairs; // [batch_max]
     int32_t* leaf_node;          // [max_leaves]
     double* refit_partial;       // [max_leaves][REFIT_PARTS][2]
     int64_t* tmp_i64;            // [8]
@@ -242,6 +242,11 @@ constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
 //    their device-wide atomics lengthen the count kernel by about 2 us: 1 M x 28 7.9 us with, 6.1 us without.
 inline int part_rows(int64_t n_rows) { return n_rows > ((int64_t)1 << 18) ? 8 : 2; }
 inline bool part_supers(int64_t n_rows) { return n_rows > ((int64_t)3 << 20); }
+// In tree growth the split search sums a build's slots itself when there are at most this many (a thread's loads of them are
+// all in flight at once); builds of more row groups are summed up by the reduce kernel, which spreads them over the
+// whole chip and otherwise returns at once.  Trees with 8 / 64: 400 k x 2000 1283 / 1396 us, 2 M x 40 of 16-bit bins
+// 924 / 980 us, 1 M x 28 the same.
+constexpr int REDUCE_ABOVE = 8;
 constexpr int PART_SUPER = 32;  // segments whose left rows are summed up in one counter
 // Most nodes expanded in one round = most builds of a histogram launch (the leaf budget; the growth bookkeeping
 // limits it to 658).  Kernels keep the first work item of every build / node in LDS and search there: a binary
@@ -272,16 +277,23 @@ int64_t max_rows_for_width(int bits_g, int bits_h, int w);
 int launch_set_hist_table(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count);
 int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, const IdxSet& idx, bool use_idx,
                 bool flat_ok, const HistEntry* entries, const int32_t* table_counts, int64_t* hist_base,
-                int64_t grid_items, StepState* step, const uint16_t* mfb = nullptr);
+                int64_t grid_items, StepState* step, const uint16_t* mfb = nullptr,
+                int reduce_above = 0);  // > 0: only builds of more row groups are added up by the reduce kernel
 int launch_fill_zero(qgbdt_ctx* ctx, int64_t* p, int64_t n_words);
 int launch_subtract(qgbdt_ctx* ctx, const int64_t* parent, const int64_t* child, int64_t* out, int64_t n);
-int launch_scan_items(qgbdt_ctx* ctx, int64_t* hist_base, const ScanItem* items, const int32_t* n_items, int max_items,
-                      const float* delta, int min_data, double min_sum_hess, FeatCand* cand, const uint16_t* mfb = nullptr,
-                      bool reduce = true);  // reduce = false: the caller's next kernel reduces the per-feature candidates
-// stand-alone search in batches of `cap` histograms; scratch: items [cap], cand [cap][F], n_items [1]
+// Best split of up to 2 * max_pairs histograms: candidates per (histogram, tile of features); `plan`: of the histogram launch
+// whose slots the pairs refer to
+int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs, const int32_t* n_items, int max_pairs,
+                      const float* delta, int min_data, double min_sum_hess, FeatCand* cand, const uint16_t* mfb,
+                      const HistPlan* plan);
+int scan_candidates(const qgbdt_shape& s);  // candidates per scanned histogram
+// candidates -> best splits, `stride` bytes apart from `out` on; step: growth state whose nodes' best splits are meant
+int launch_reduce_items(qgbdt_ctx* ctx, const FeatCand* cand, const ScanPair* pairs, const int32_t* n_items, int max_items,
+                        qgbdt_split* out, size_t stride, const StepState* step);
+// stand-alone search in batches of `cap` histograms; scratch: pairs [(cap + 1) / 2], cand [cap][scan_candidates], n_items [1]
 int run_find_best_splits(qgbdt_ctx* ctx, const int64_t* hist, int n_hists, const qgbdt_leafstat* stats,
                          const float* delta, int min_data, double min_sum_hess, qgbdt_split* out, int cap,
-                         ScanItem* items, FeatCand* cand, int32_t* n_items);
+                         ScanPair* pairs, FeatCand* cand, int32_t* n_items);
 int launch_partition_work(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* buf0, int32_t* buf1, const PartWork* work,
                           int64_t* n_left_out, int64_t max_count);
 int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, int64_t begin, int64_t count,

@@ -792,15 +792,17 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
 // Adds the slots of every build's row groups to the build's histogram.  Thread -> one word
 // of a tile's local bins; the launch's items are cut into gridDim.z runs, a thread walks its
 // run (consecutive items mostly belong to one build) and issues one 64-bit atomic per build
-// it meets.  `generic` slots have the pitch of their tile's width, the others plan.ftp.
+// it meets.  `generic` slots have the pitch of their tile's width, the others plan.ftp.  above > 0: builds of at most
+// that many row groups are left to the split search.
 template <int W>
 __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* __restrict__ partials,
                                                           const HistEntry* __restrict__ entries,
                                                           const int32_t* __restrict__ table_counts,
                                                           int64_t* hist_base, int F, int nb, HistPlan plan,
-                                                          int generic) {
+                                                          int generic, int above) {
     using word = typename Acc<W>::word;
     const int n_entries = table_counts[0], n_items = table_counts[1];
+    if (above > 0 && table_counts[2] == 0) return;  // the split search adds up every build of this launch itself
     const int hs = plan.hshift;
     const uint32_t hmask = (1u << hs) - 1u;
     const int per = (n_items + (int)gridDim.z - 1) / (int)gridDim.z;
@@ -823,6 +825,7 @@ __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* _
     int i = i0;
     while (i < i1) {
         const int iend = min(i1, entries[e].item_start + entries[e].groups);
+        if (above > 0 && entries[e].groups <= above) { i = iend; ++e; continue; }
         int64_t sg = 0, sh = 0;
         for (; i + 4 <= iend; i += 4) {
             word v[4];
@@ -1040,6 +1043,7 @@ __global__ void set_hist_table_kernel(HistEntry* entries, int32_t* counts, int64
         entries[0] = e;
         counts[0] = 1;
         counts[1] = count > 0 ? (int32_t)g : 0;
+        counts[2] = 1;
     }
 }
 
@@ -1088,7 +1092,7 @@ int prepare_hist_kernels(qgbdt_ctx* ctx) {
 // the number of work items; workgroups beyond the table's item count return at once.
 int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, const IdxSet& idx, bool use_idx,
                 bool flat_ok, const HistEntry* entries, const int32_t* table_counts, int64_t* hist_base,
-                int64_t grid_items, StepState* step, const uint16_t* mfb) {
+                int64_t grid_items, StepState* step, const uint16_t* mfb, int reduce_above) {
     const int F = ctx->shape.n_features, nb = ctx->shape.n_bins;
     unsigned char* partials = static_cast<unsigned char*>(ctx->hist_partials);
     // The kernels address slot (item, tile) for item < max_items of the plan they are given (the tables they read
@@ -1213,10 +1217,10 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         dim3 rgrid((unsigned)xb, (unsigned)plan.n_tiles, (unsigned)z);
         if (plan.acc_width == 16 && !plan.two_level)  // (two-level groups hand over 64-bit words)
             hipLaunchKernelGGL(hist_reduce_kernel<16>, rgrid, dim3(256), 0, ctx->stream, partials, entries, table_counts,
-                               hist_base, F, nb, plan, fast ? 0 : 1);
+                               hist_base, F, nb, plan, fast ? 0 : 1, reduce_above);
         else
             hipLaunchKernelGGL(hist_reduce_kernel<32>, rgrid, dim3(256), 0, ctx->stream, partials, entries, table_counts,
-                               hist_base, F, nb, plan, fast ? 0 : 1);
+                               hist_base, F, nb, plan, fast ? 0 : 1, reduce_above);
         QG_HIP(ctx, hipGetLastError());
     }
     if (e1) QG_HIP(ctx, hipEventRecord(e1, ctx->stream));

@@ -289,7 +289,7 @@ __device__ __forceinline__ int wave_prefix(int v) {
 // while the others move rows: it needs nothing of them but the left counts that the count kernel left behind.
 __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __restrict__ batch,
                              const int32_t* __restrict__ super_counts, HistEntry* hist_entries, int32_t* hist_counts,
-                             ScanItem* items, const HistPlan& plan, int super_len, int* s_start, int* s_left, int* s_tmp) {
+                             ScanPair* pairs, const HistPlan& plan, int super_len, int* s_start, int* s_left, int* s_tmp) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_batch = step->n_batch;
     for (int t = tid; t < n_batch; t += 256) { s_start[t] = batch[t].super_start; s_left[t] = 0; }
@@ -316,7 +316,7 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
     __syncthreads();
     small_total = s_tmp[0] + s_tmp[1] + s_tmp[2] + s_tmp[3];
     const int target = (int)hist_target_rows(plan, small_total, n_batch);
-    int base = 0;
+    int base = 0, big = 0;
     for (int t0 = 0; t0 < n_batch; t0 += 256) {  // (uniform trip count)
         const int t = t0 + tid;
         int nl = 0, nr = 0, groups = 0;
@@ -325,6 +325,7 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
             be = batch[t];
             nl = s_left[t]; nr = be.count - nl;
             groups = max(1, (min(nl, nr) + target - 1) / target);
+            if (groups > REDUCE_ABOVE) big = 1;
         }
         const int incl = wave_prefix(groups);
         __syncthreads();
@@ -347,12 +348,6 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
                 c->state = 0; c->expanded = 0; c->child = -1; c->leaf_id = -1;
                 c->best.gain = 0.0; c->best.feature = -1; c->best.bin = -1;
                 c->best.left_g = c->best.left_h = c->best.right_g = c->best.right_h = c->best.left_count = 0;
-                const bool is_small = (which == 0) == left_small;
-                ScanItem it;
-                it.slot = sl; it.sub_parent = is_small ? -1 : slot; it.sub_child = is_small ? -1 : be.new_slot; it.valid = 1;
-                it.stat.n_rows = count; it.stat.sum_g = g; it.stat.sum_h = h;
-                it.out = &c->best;
-                items[2 * t + which] = it;
             };
             put(0, be.begin, nl, lg, lh, lslot);
             put(1, be.begin + nl, nr, rg, rh, rslot);
@@ -360,9 +355,17 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
             e.begin = left_small ? be.begin : be.begin + nl; e.count = left_small ? nl : nr; e.buf = cb; e.slot = be.new_slot;
             e.item_start = start; e.groups = groups;
             hist_entries[t] = e;
+            ScanPair sp;
+            sp.slot_a = be.new_slot; sp.slot_b = slot; sp.parent = slot; sp.a_item = left_small ? 0 : 1;
+            sp.item_start = start; sp.groups = groups <= REDUCE_ABOVE ? groups : 0;
+            sp.merged = e.count > (int64_t)groups * plan.single_rows ? 1 : 0; sp.pad = 0;
+            const qgbdt_leafstat sl = {nl, lg, lh}, sr = {nr, rg, rh};
+            sp.stat[0] = left_small ? sl : sr; sp.stat[1] = left_small ? sr : sl;
+            pairs[t] = sp;
         }
     }
-    if (tid == 0) { hist_counts[0] = n_batch; hist_counts[1] = base; }
+    big = __syncthreads_or(big);
+    if (tid == 0) { hist_counts[0] = n_batch; hist_counts[1] = base; hist_counts[2] = big; }
 }
 
 // Order-preserving scatter of every segment into the children's buffer.  The left rows in front of a segment are the sum
@@ -380,13 +383,13 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
                                                                  const int32_t* __restrict__ seg_counts,
                                                                  const int32_t* __restrict__ super_counts,
                                                                  HistEntry* hist_entries, int32_t* hist_counts,
-                                                                 ScanItem* items, HistPlan plan) {
+                                                                 ScanPair* pairs, HistPlan plan) {
     constexpr int PART_SEG = 256 * R;
     if (step->done) return;
     __shared__ int s_start[TABLE_MAX];
     __shared__ int s_dpos[MODE == 2 && PART_SEG > TABLE_MAX + 8 ? PART_SEG : TABLE_MAX + 8];  // (also child_tables' LDS)
     if (blockIdx.x == 0) {
-        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, items, plan, SUPER, s_start, s_dpos, s_dpos + TABLE_MAX);
+        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, pairs, plan, SUPER, s_start, s_dpos, s_dpos + TABLE_MAX);
         return;
     }
     const int n_items = step->n_part_items, n_batch = step->n_batch;
@@ -504,7 +507,7 @@ int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool o
     hipLaunchKernelGGL((batch_part_scatter_kernel<MODE_, R_, S_>), dim3(batch_part_grid(ctx) + 1), dim3(256), 0, ctx->stream,     \
                        rows, out, ctx->shape.n_features, idx_set(ctx), ctx->step, ctx->batch, ctx->batch_seg,           \
                        ctx->nodes, ctx->part_masks, ctx->seg_counts, sums, ctx->hist_entries,                           \
-                       ctx->hist_counts, ctx->scan_items, plan)
+                       ctx->hist_counts, ctx->scan_pairs, plan)
 #define QG_SCATTER(MODE_)                                                  \
     do {                                                                   \
         if (ctx->seg_supers) QG_SCATTER_R(MODE_, 8, PART_SUPER);           \

@@ -2,6 +2,8 @@
 // enumeration of Sec. 3 with the quantized gain of Sec. 4.1 eq. (gain)).
 // Integer prefix sums over the packed words, fp64 gain; compiled with FMA
 // contraction off so that the gain is evaluated operation by operation.
+#include <type_traits>
+
 #include "split_device.h"
 
 namespace qgbdt {
@@ -22,324 +24,321 @@ int launch_subtract(qgbdt_ctx* ctx, const int64_t* parent, const int64_t* child,
     return QGBDT_OK;
 }
 
-__global__ void scan_items_from_stats_kernel(const qgbdt_leafstat* stats, int n, ScanItem* items, qgbdt_split* out,
-                                             int32_t* n_items) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        ScanItem it;
-        it.slot = i; it.sub_parent = -1; it.sub_child = -1; it.valid = 1; it.stat = stats[i]; it.out = out + i;
-        items[i] = it;
+__global__ void scan_pairs_from_stats_kernel(const qgbdt_leafstat* stats, int n, ScanPair* pairs, int32_t* n_items) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (2 * t < n) {
+        ScanPair sp;
+        sp.slot_a = 2 * t; sp.slot_b = 2 * t + 1 < n ? 2 * t + 1 : -1; sp.parent = -1; sp.a_item = 0;
+        sp.item_start = 0; sp.groups = 0; sp.merged = 0; sp.pad = 0;
+        sp.stat[0] = stats[2 * t]; sp.stat[1] = stats[min(2 * t + 1, n - 1)];
+        pairs[t] = sp;
     }
-    if (i == 0) *n_items = n;
+    if (t == 0) *n_items = n;
 }
 
-// One workgroup per (feature, histogram): thread b owns bin b.  Workgroup-wide
-// inclusive scan of the packed words (fields cannot overflow: every prefix is
-// bounded by the leaf totals), then each thread evaluates its threshold and the
-// workgroup keeps the feature's best one.
-__global__ __launch_bounds__(1024) void scan_kernel(int64_t* hist_base, const ScanItem* __restrict__ items,
-                                                   const int32_t* __restrict__ n_items_ptr, int F, int nb,
-                                                   const float* __restrict__ delta, int64_t min_data,
-                                                   double min_sum_hess, FeatCand* cand_base, int glog,
-                                                   const uint16_t* __restrict__ mfb) {
+// Largest unsigned value of the lanes with DPP moves (no LDS traffic); uniform.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define QG_DPP(ctrl, rmask) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rmask, 0xf, false))
+    QG_DPP(0x111, 0xf); QG_DPP(0x112, 0xf); QG_DPP(0x114, 0xf); QG_DPP(0x118, 0xf);  // row_shr: lane 15 of a row has its maximum
+    QG_DPP(0x142, 0xa); QG_DPP(0x143, 0xc);                                          // row_bcast:15, row_bcast:31
+#undef QG_DPP
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Where the row groups of a launch have left their local bins.
+struct SlotSource {
+    const unsigned char* partials;
+    int32_t elementwise;  // slots of the element-wise kernel: the pitch is the tile's own width
+    int32_t acc_width, hshift, ft, ftp, n_tiles, slot_bytes, pad16;
+};
+
+// Sum over a build's slots of the words of feature f and bins b .. b + KB - 1, as packed 32|32 words.
+template <int W, int KB>
+__device__ __forceinline__ void sum_slots(const SlotSource& s, int item_start, int groups, int b, int nb, int f, int F, int64_t (&out)[KB]) {
+    using word = typename std::conditional<W == 16, uint32_t, int64_t>::type;
+    const int tile = f / s.ft, fl = f - tile * s.ft;
+    const int pitch = s.elementwise ? min(s.ft, F - tile * s.ft) : s.ftp;
+    const int col = fl + (s.pad16 ? 4 * (fl >> 4) : 0);
+    const size_t stride = (size_t)s.n_tiles * (size_t)s.slot_bytes;
+    const unsigned char* p = s.partials + ((size_t)item_start * s.n_tiles + tile) * (size_t)s.slot_bytes;
+    uint32_t off[KB];  // of the bins (past the last one: the last one again, not used)
+#pragma unroll
+    for (int k = 0; k < KB; ++k) off[k] = (uint32_t)(min(b + k, nb - 1) * pitch + col) * (uint32_t)sizeof(word);
+    const uint32_t mask = (1u << s.hshift) - 1u;
+    int32_t g[KB] = {};
+    uint32_t h[KB] = {};
+    int64_t w64[KB] = {};
+    constexpr int U = (W == 16 ? 32 : 16) / KB < 8 ? (W == 16 ? 32 : 16) / KB : 8;  // slots whose loads are in flight together
+    for (int i = 0; i < groups; i += U) {
+        word x[U][KB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned char* q = p + (size_t)min(i + u, groups - 1) * stride;
+#pragma unroll
+            for (int k = 0; k < KB; ++k) x[u][k] = *reinterpret_cast<const word*>(q + off[k]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                const word v = i + u < groups ? x[u][k] : (word)0;
+                if (W == 16) { g[k] += (int32_t)(uint32_t)v >> s.hshift; h[k] += (uint32_t)v & mask; }
+                else w64[k] += (int64_t)v;
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < KB; ++k) out[k] = W == 16 ? (int64_t)g[k] * 4294967296LL + (int64_t)h[k] : w64[k];
+}
+
+// The winner of a set of candidates, one per lane: largest gain (> 0), ties to the lowest `code` (feature, then bin).  The
+// lane's index is returned (uniform), -1 if no lane has a gain.
+// (Gains are not negative, so their bits order like unsigned integers: upper halves first, then lower ones.)
+__device__ __forceinline__ int wave_argmax(double gain, uint32_t code) {
+    const uint64_t bits = (uint64_t)__double_as_longlong(gain);
+    const uint32_t hi = (uint32_t)(bits >> 32), lo = (uint32_t)bits;
+    const uint32_t mh = wave_max_u32(hi);
+    unsigned long long m = __ballot(hi == mh);
+    if (m & (m - 1ull)) {
+        const uint32_t ml = wave_max_u32(hi == mh ? lo : 0u);
+        m = __ballot(hi == mh && lo == ml);
+        if (mh == 0u && ml == 0u) return -1;
+    }
+    int win = __ffsll((long long)m) - 1;
+    uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)code, win);
+    for (m &= m - 1ull; m; m &= m - 1ull) {  // (equal gains are rare)
+        const int l = __ffsll((long long)m) - 1;
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)code, l);
+        if (c < low) { low = c; win = l; }
+    }
+    return win;
+}
+
+// Best split per tile of T features, for two histograms at a time, in tree growth the two children of a node.  The child
+// that was built from rows comes from its row groups' slots (or, when a reduce kernel has summed
+// them up, from the pool), its sibling is parent - child; both are written to the pool on the way.  A thread owns one feature
+// and KB consecutive bins of both histograms, a wavefront T features x 64 / T such segments: integer prefix sums (the
+// fields cannot overflow: every prefix is bounded by the leaf's totals) over the thread's bins, over the wavefront's segments and,
+// through LDS, over the wavefronts; then the fp64 gain of every threshold and the arg-max over the workgroup.
+// Bound by the instructions of a threshold (about 130, most of them two IEEE fp64 divisions) for wide matrices, by the
+// chain of latencies for narrow ones: one record per pair, the sums of slots and the parent's words loaded together, and
+// no branches between the thresholds, so that their dependent operations interleave.
+// Measured per launch with the reduce kernel's launch in front of it, against one workgroup per feature (or per 16 features and
+// 1024 threads) and histogram behind a full reduction: 1 M x 28, 255 bins 15.0 -> 12.6 us; 464 k x 90 28.1 -> 18.8 us;
+// 2 M x 40, 600 bins 38.1 -> 23.8 us; 400 k x 2000, 63 bins (and one launch less) 46.7 -> 28.6 us; 20 M x 200 34.1 -> 25.4 us.
+template <int T, int NB64, int KB>  // features per workgroup; bins, in units of 64; bins per thread
+__global__ __launch_bounds__(64 * T * NB64 / KB) void scan_pair_kernel(int64_t* hist_base, const ScanPair* __restrict__ pairs,
+                                                                  const int32_t* __restrict__ n_items_ptr, int max_pairs, SlotSource slots,
+                                                                  int F, int nb, const float* __restrict__ delta, int min_data,
+                                                                  double min_sum_hess, FeatCand* __restrict__ cand_base,
+                                                                  const uint16_t* __restrict__ mfb) {
+    constexpr int NW = T * NB64 / KB;  // wavefronts
     const int n_items = *n_items_ptr;
-    // Workgroup -> feature: histograms are [bin][feature], so the 16 features of a 128-byte line are
-    // read by 16 workgroups; consecutive workgroup ids go round-robin to the 8 XCDs, so the ids are
-    // dealt such that those 16 run next to each other behind one L2.
-    // (Fewer per group when there are too few features to keep all XCDs busy that way.)
-    const int xcd = blockIdx.x & 7, s = blockIdx.x >> 3;
-    const int f = ((s >> glog) * 8 + xcd) * (1 << glog) + (s & ((1 << glog) - 1));
-    if (f >= F) return;
-    const int b = threadIdx.x;
-    const int lane = b & 63, wave = b >> 6;
-    const int64_t W = (int64_t)F * nb;
-    const int64_t at = (int64_t)b * F + f;  // histograms are [bin][feature]
     const double dg = (double)delta[0], dh = (double)delta[1];
-    __shared__ int64_t wtot[16];
-    __shared__ double sg[16];
-    __shared__ int sb[16];
-    __shared__ int64_t sl[16];
-    for (int item = blockIdx.y; item < n_items; item += gridDim.y) {
-        const ScanItem it = items[item];
-        if (!it.valid) continue;
-        int64_t word = 0;
-        if (b < nb) {
-            if (it.sub_parent >= 0) {
-                word = hist_base[it.sub_parent * W + at] - hist_base[it.sub_child * W + at];
-                hist_base[it.slot * W + at] = word;
-            } else {
-                word = hist_base[it.slot * W + at];
+    const int n_ft = (F + T - 1) / T, n_pairs = (n_items + 1) / 2;
+    // consecutive workgroups go round-robin to the XCDs: the tiles of a pair, which share cache lines, stay on one
+    const int xcd = blockIdx.x & 7, sid = blockIdx.x >> 3;
+    const int tile = sid % n_ft;
+    const int64_t W = (int64_t)F * nb;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int fl = threadIdx.x % T, f = tile * T + fl, b0 = (int)threadIdx.x / T * KB;
+    __shared__ int64_t s_sum[2][NW][T];   // a wavefront's bins of a feature
+    __shared__ FeatCand s_cand[2][NW];
+    const int t0 = (sid / n_ft) * 8 + xcd;
+    ScanPair sp = pairs[min(t0, max_pairs - 1)];  // (in flight together with the number of items)
+    for (int t = t0; t < n_pairs; t += (int)(gridDim.x / (8 * n_ft)) * 8) {
+        if (t != t0) sp = pairs[t];
+        const bool has_b = sp.slot_b >= 0;
+        const int64_t at = (int64_t)b0 * F + f;  // histograms are [bin][feature]
+        int64_t v[2][KB] = {};                    // words, then inclusive prefix sums
+        if (f < F && b0 < nb) {
+            int64_t* const pa = hist_base + (int64_t)sp.slot_a * W + at;
+            if (has_b) {
+                const int64_t* p = hist_base + (int64_t)(sp.parent >= 0 ? sp.parent : sp.slot_b) * W + at;
+#pragma unroll
+                for (int k = 0; k < KB; ++k) if (b0 + k < nb) v[1][k] = p[(int64_t)k * F];
+            }
+            if (sp.groups > 0) {
+                if (slots.acc_width == 16) sum_slots<16, KB>(slots, sp.item_start, sp.groups, b0, nb, f, F, v[0]);
+                else sum_slots<32, KB>(slots, sp.item_start, sp.groups, b0, nb, f, F, v[0]);
+            }
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                if (b0 + k >= nb) v[0][k] = 0;
+                else if (sp.groups == 0 || sp.merged) v[0][k] += pa[(int64_t)k * F];
+            }
+            if (sp.groups > 0) {
+#pragma unroll
+                for (int k = 0; k < KB; ++k) if (b0 + k < nb) pa[(int64_t)k * F] = v[0][k];
+            }
+            if (sp.parent >= 0) {
+                int64_t* const pb = hist_base + (int64_t)sp.slot_b * W + at;
+#pragma unroll
+                for (int k = 0; k < KB; ++k) if (b0 + k < nb) { v[1][k] -= v[0][k]; pb[(int64_t)k * F] = v[1][k]; }
             }
         }
-        // inclusive scan
-        int64_t pre = word;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int64_t v = __shfl_up(pre, o);
-            if (lane >= o) pre += v;
+        int64_t before[2];  // the feature's bins in front of this thread's
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+#pragma unroll
+            for (int k = 1; k < KB; ++k) v[side][k] += v[side][k - 1];
+            int64_t incl = v[side][KB - 1];
+#pragma unroll
+            for (int o = T; o < 64; o <<= 1) {
+                const int64_t u = __shfl_up(incl, o);
+                if (lane >= o) incl += u;
+            }
+            before[side] = incl - v[side][KB - 1];
+            if (lane >= 64 - T) s_sum[side][wave][fl] = incl;
         }
-        if (lane == 63) wtot[wave] = pre;
         __syncthreads();
-        for (int k = 0; k < wave; ++k) pre += wtot[k];
-        if (mfb != nullptr) {
-            // The histogram kernels may have left out the feature's most frequent bin: the entry is then 0 and
-            // what is missing from the feature's sum over all bins -- the leaf's totals are known -- belongs to
-            // that bin.  (Nothing is missing when the bin was accumulated.)
-            const int mb = mfb[f];
-            int64_t all = 0;
-            for (int k = 0; k < (int)(blockDim.x >> 6); ++k) all += wtot[k];
-            const int64_t missing = (it.stat.sum_g * 4294967296LL + it.stat.sum_h) - all;
-            if (mb != 0xffff && b >= mb) pre += missing;
-        }
-
-        const int64_t Gs = it.stat.sum_g, Hs = it.stat.sum_h, n = it.stat.n_rows;
-        double gain = 0.0;
-        int bin = -1;
-        if (b + 1 < nb && Hs > 0) {
-            const int64_t GL = packed_g(pre), HL = packed_h(pre);
-            const int64_t GR = Gs - GL, HR = Hs - HL;
-            if (HL > 0 && HR > 0) {
-                const int64_t cl = count_estimate(HL, Hs, n), cr = n - cl;
-                if (cl >= min_data && cr >= min_data && !((double)HL * dh < min_sum_hess) &&
-                    !((double)HR * dh < min_sum_hess)) {
-                    const double parent = half_loss(Gs, Hs, dg, dh);
-                    const double gn = half_loss(GL, HL, dg, dh) + half_loss(GR, HR, dg, dh) - parent;
-                    if (gn > 0.0) { gain = gn; bin = b; }
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int64_t Gs = sp.stat[side].sum_g, Hs = sp.stat[side].sum_h, n = sp.stat[side].n_rows;
+            int64_t off = before[side], missing = 0;
+            int mb = 0xffff;
+#pragma unroll
+            for (int w = 0; w < NW - 1; ++w) off += w < wave ? s_sum[side][w][fl] : 0;
+            if (mfb != nullptr && f < F) {
+                // The histogram kernels may have left out the feature's most frequent bin: the entry is then 0 and
+                // what is missing from the feature's sum over all bins -- the leaf's totals are known -- belongs to
+                // that bin.  (Nothing is missing when the bin was accumulated.)
+                mb = mfb[f];
+                if (mb != 0xffff) {
+                    missing = Gs * 4294967296LL + Hs;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) missing -= s_sum[side][w][fl];
                 }
             }
+            // count_estimate(HL, Hs, n) = floor((2 HL n + Hs) / (2 Hs)) >= min_data, and <= n - min_data, without
+            // the division (2 HL n < 2^64: the fields and row counts have 32 and 31 bits)
+            const uint64_t n2 = 2ull * (uint64_t)n, uH = (uint64_t)Hs;
+            const uint64_t lo_lim = min_data > 0 ? (2ull * (uint64_t)min_data - 1ull) * uH : 0ull;
+            const uint64_t hi_lim = min_data <= 0 ? ~0ull : (n + 1 > (int64_t)min_data) ? (2ull * (uint64_t)(n - min_data + 1) - 1ull) * uH : 0ull;
+            const double parent = half_loss(Gs, Hs, dg, dh);
+            double gain = 0.0;
+            int bin = 0;
+            int64_t left = 0;
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {  // ascending bins: strict > keeps the lowest
+                int64_t pre = v[side][k] + off;
+                if (mfb != nullptr && b0 + k >= mb) pre += missing;
+                const int32_t GL = (int32_t)(pre >> 32);
+                const uint32_t HL = (uint32_t)pre;
+                const int64_t GR = Gs - GL, HR = Hs - (int64_t)HL;
+                const uint64_t x = (uint64_t)HL * n2;
+                const double hl = (double)HL * dh, hr = (double)HR * dh;
+                const double al = (double)GL * dg, ar = (double)GR * dg;
+                const double gn = (al * al) / (2.0 * hl) + (ar * ar) / (2.0 * hr) - parent;
+                const bool ok = (f < F) & (b0 + k + 1 < nb) & (HL > 0u) & (HR > 0) & (x >= lo_lim) & (x < hi_lim) &
+                                !(hl < min_sum_hess) & !(hr < min_sum_hess) & (gn > gain);
+                gain = ok ? gn : gain; bin = ok ? b0 + k : bin; left = ok ? pre : left;
+            }
+            const int win = wave_argmax(gain, ((uint32_t)fl << 16) | (uint32_t)bin);
+            if (lane == (win < 0 ? 0 : win)) {
+                FeatCand fc;
+                fc.gain = win < 0 ? 0.0 : gain; fc.left = left; fc.bin = win < 0 ? -1 : bin; fc.feature = f;
+                s_cand[side][wave] = fc;
+            }
         }
-        int64_t left = pre;
-        // arg-max: largest gain, ties to the lowest bin
-        for (int o = 32; o > 0; o >>= 1) {
-            const double og = __shfl_xor(gain, o);
-            const int ob = __shfl_xor(bin, o);
-            const int64_t ol = __shfl_xor(left, o);
-            if (ob >= 0 && (bin < 0 || og > gain || (og == gain && ob < bin))) { gain = og; bin = ob; left = ol; }
-        }
-        if (lane == 0) { sg[wave] = gain; sb[wave] = bin; sl[wave] = left; }
         __syncthreads();
-        if (b == 0) {
-            for (int k = 1; k < (int)(blockDim.x >> 6); ++k)
-                if (sb[k] >= 0 && (bin < 0 || sg[k] > gain || (sg[k] == gain && sb[k] < bin))) {
-                    gain = sg[k]; bin = sb[k]; left = sl[k];
-                }
-            FeatCand c;
-            c.gain = gain; c.left = left; c.bin = bin; c.pad = 0;
-            cand_base[(int64_t)item * F + f] = c;
+        if (wave < 2 && NW > 1 ? true : wave == 0) {  // the tile's best: one wavefront per histogram (both by the only one)
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                if (NW > 1 && side != wave) continue;
+                const FeatCand fc = s_cand[side][min(lane, NW - 1)];
+                const int win = wave_argmax(lane < NW && fc.bin >= 0 ? fc.gain : 0.0, ((uint32_t)(fc.feature - tile * T) << 16) | (uint32_t)fc.bin);
+                const int item = 2 * t + (side ^ sp.a_item);
+                if (lane == (win < 0 ? 0 : win) && (side == 0 || has_b)) cand_base[(int64_t)item * n_ft + tile] = fc;
+            }
         }
-        __syncthreads();
+        __syncthreads();  // (s_sum and s_cand are reused)
     }
 }
 
-// The same search for histograms of at most 64 * P bins (P = 1, 2, 4) and many features.  A workgroup of 16
-// wavefronts takes 16 consecutive features of an item: the [bin][16 features] tile (one 128-byte
-// line per bin) is read -- and, for a subtracted sibling, written back -- with coalesced accesses
-// and staged in LDS; wavefront w then scans feature w of the tile, lane l the bins l, l + 64, ...
-template <int P>
-__global__ __launch_bounds__(1024) void scan_tile_kernel(int64_t* hist_base, const ScanItem* __restrict__ items,
-                                                         const int32_t* __restrict__ n_items_ptr, int F, int nb,
-                                                         const float* __restrict__ delta, int64_t min_data,
-                                                         double min_sum_hess, FeatCand* cand_base,
-                                                         const uint16_t* __restrict__ mfb) {
-    const int n_items = *n_items_ptr;
-    const int f0 = blockIdx.x * 16;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t W = (int64_t)F * nb;
-    const double dg = (double)delta[0], dh = (double)delta[1];
-    __shared__ int64_t tile[64 * P * 17];  // [bin][feature], pitch 17 words: a wavefront's column walk spreads over the banks
-    const int tf = threadIdx.x & 15, tb = threadIdx.x >> 4;  // tile loader: feature and (first) bin of this thread
-    for (int item = blockIdx.y; item < n_items; item += gridDim.y) {
-        const ScanItem it = items[item];
-        if (!it.valid) continue;
-        int64_t word[P];
-#pragma unroll
-        for (int j = 0; j < P; ++j) {
-            const int b = tb + 64 * j;
-            word[j] = 0;
-            if (b < nb && f0 + tf < F) {
-                const int64_t at = (int64_t)b * F + f0 + tf;
-                if (it.sub_parent >= 0) word[j] = hist_base[it.sub_parent * W + at] - hist_base[it.sub_child * W + at];
-                else word[j] = hist_base[it.slot * W + at];
-            }
-        }
-        if (it.sub_parent >= 0) {
-#pragma unroll
-            for (int j = 0; j < P; ++j) {
-                const int b = tb + 64 * j;
-                if (b < nb && f0 + tf < F) hist_base[it.slot * W + (int64_t)b * F + f0 + tf] = word[j];
-            }
-        }
-        __syncthreads();  // the previous item's tile has been read
-#pragma unroll
-        for (int j = 0; j < P; ++j) tile[(tb + 64 * j) * 17 + tf] = word[j];
-        __syncthreads();
-        const int f = f0 + wave;
-        if (f >= F) continue;  // no barrier below depends on this wavefront
-        int64_t pre[P];
-        int64_t carry = 0;
-#pragma unroll
-        for (int j = 0; j < P; ++j) {
-            int64_t v = tile[(lane + 64 * j) * 17 + wave];
-            for (int o = 1; o < 64; o <<= 1) {
-                const int64_t u = __shfl_up(v, o);
-                if (lane >= o) v += u;
-            }
-            pre[j] = v + carry;
-            carry = __shfl(pre[j], 63);
-        }
-        if (mfb != nullptr) {  // the feature's most frequent bin may have been left out (see scan_kernel)
-            const int mb = mfb[f];
-            const int64_t missing = (it.stat.sum_g * 4294967296LL + it.stat.sum_h) - carry;
-#pragma unroll
-            for (int j = 0; j < P; ++j)
-                if (mb != 0xffff && lane + 64 * j >= mb) pre[j] += missing;
-        }
-        const int64_t Gs = it.stat.sum_g, Hs = it.stat.sum_h, n = it.stat.n_rows;
-        double gain = 0.0;
-        int bin = -1;
-        int64_t left = 0;
-#pragma unroll
-        for (int j = 0; j < P; ++j) {  // ascending bins: strict > keeps the lowest
-            const int b = lane + 64 * j;
-            if (b + 1 < nb && Hs > 0) {
-                const int64_t GL = packed_g(pre[j]), HL = packed_h(pre[j]);
-                const int64_t GR = Gs - GL, HR = Hs - HL;
-                if (HL > 0 && HR > 0) {
-                    const int64_t cl = count_estimate(HL, Hs, n), cr = n - cl;
-                    if (cl >= min_data && cr >= min_data && !((double)HL * dh < min_sum_hess) &&
-                        !((double)HR * dh < min_sum_hess)) {
-                        const double parent = half_loss(Gs, Hs, dg, dh);
-                        const double gn = half_loss(GL, HL, dg, dh) + half_loss(GR, HR, dg, dh) - parent;
-                        if (gn > 0.0 && gn > gain) { gain = gn; bin = b; left = pre[j]; }
-                    }
-                }
-            }
-        }
-        for (int o = 32; o > 0; o >>= 1) {  // arg-max: largest gain, ties to the lowest bin
-            const double og = __shfl_xor(gain, o);
-            const int ob = __shfl_xor(bin, o);
-            const int64_t ol = __shfl_xor(left, o);
-            if (ob >= 0 && (bin < 0 || og > gain || (og == gain && ob < bin))) { gain = og; bin = ob; left = ol; }
-        }
-        if (lane == 0) {
-            FeatCand c;
-            c.gain = gain; c.left = left; c.bin = bin; c.pad = 0;
-            cand_base[(int64_t)item * F + f] = c;
-        }
-    }
-}
-
-// Per-feature candidates -> best split of every scanned histogram, one wavefront per histogram.
+// Candidates (n_cand per histogram, one per tile of ascending features) -> best split of every scanned histogram, one
+// wavefront per histogram.
 __global__ __launch_bounds__(256) void reduce_items_kernel(const FeatCand* __restrict__ cand_base,
-                                                           const ScanItem* __restrict__ items,
-                                                           const int32_t* __restrict__ n_items_ptr, int F) {
+                                                           const ScanPair* __restrict__ pairs,
+                                                           const int32_t* __restrict__ n_items_ptr, int n_cand,
+                                                           unsigned char* out, int64_t stride, const StepState* step) {
     const int n_items = *n_items_ptr;
+    const int first = step ? step->n_nodes - n_items : 0;  // tree growth: the histograms are those of the newest nodes
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (F > 256) {
-        // many features: the four wavefronts share an item (a quarter of the features each, ascending)
-        __shared__ FeatCand part[4];
-        __shared__ int pf[4];
-        for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-            const ScanItem it = items[item];
-            if (!it.valid) continue;  // uniform over the workgroup
-            const FeatCand* cand = cand_base + (int64_t)item * F;
-            const int q = (F + 3) / 4, fb = wave * q, fe = min(F, fb + q);
-            double bg = 0.0;
-            int bf = -1;
-            for (int f = fb + lane; f < fe; f += 64) {
-                const FeatCand c = cand[f];
-                if (c.bin >= 0 && (c.gain > bg)) { bg = c.gain; bf = f; }
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const double og = __shfl_xor(bg, o);
-                const int of = __shfl_xor(bf, o);
-                if (of >= 0 && (bf < 0 || og > bg || (og == bg && of < bf))) { bg = og; bf = of; }
-            }
-            __syncthreads();
-            if (lane == 0) {
-                pf[wave] = bf;
-                if (bf >= 0) part[wave] = cand[bf];
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                int best = -1;
-                for (int k = 0; k < 4; ++k)  // ascending feature ranges: strict > keeps the lowest feature
-                    if (pf[k] >= 0 && (best < 0 || part[k].gain > part[best].gain)) best = k;
-                qgbdt_split sp;
-                sp.gain = 0.0; sp.feature = -1; sp.bin = -1;
-                sp.left_g = sp.left_h = sp.right_g = sp.right_h = sp.left_count = 0;
-                if (best >= 0) {
-                    const FeatCand c = part[best];
-                    sp.gain = c.gain; sp.feature = pf[best]; sp.bin = c.bin;
-                    sp.left_g = packed_g(c.left); sp.left_h = packed_h(c.left);
-                    sp.right_g = it.stat.sum_g - sp.left_g; sp.right_h = it.stat.sum_h - sp.left_h;
-                    sp.left_count = count_estimate(sp.left_h, it.stat.sum_h, it.stat.n_rows);
-                }
-                *it.out = sp;
-            }
-        }
-        return;
-    }
     for (int item = blockIdx.x * 4 + wave; item < n_items; item += gridDim.x * 4) {
-        const ScanItem it = items[item];
-        if (!it.valid) continue;
-        reduce_features_wave(cand_base + (int64_t)item * F, F, it.stat, it.out, lane);
+        const ScanPair* sp = &pairs[item >> 1];
+        reduce_features_wave(cand_base + (int64_t)item * n_cand, n_cand, sp->stat[sp->a_item == (item & 1) ? 0 : 1],
+                             reinterpret_cast<qgbdt_split*>(out + (int64_t)(first + item) * stride), lane);
     }
 }
 
-int launch_scan_items(qgbdt_ctx* ctx, int64_t* hist_base, const ScanItem* items, const int32_t* n_items, int max_items,
-                      const float* delta, int min_data, double min_sum_hess, FeatCand* cand, const uint16_t* mfb,
-                      bool reduce) {
-    const int F = ctx->shape.n_features, nb = ctx->shape.n_bins;
-    int threads = 64;
-    while (threads < nb) threads <<= 1;
-    // a workgroup walks the items gy apart one after the other, each a chain of dependent loads:
-    // enough workgroups that few items queue behind each other (about 32 K wavefronts at most)
-    int gy = 32768 / (F * (threads / 64));
-    if (gy < 2) gy = 2;
-    if (gy > max_items) gy = max_items;
-    if (gy < 1) gy = 1;
-    int glog = 0;  // features per XCD group: 16 (one 128-byte line) when F >= 128, fewer for narrow matrices
-    while (glog < 4 && (16 << glog) <= F) ++glog;
-    if (nb <= 256 && F >= 64) {
-        const int gx = (F + 15) / 16;
-        gy = 2048 / gx;
-        if (gy < 2) gy = 2;
-        if (gy > max_items) gy = max_items;
-        if (gy < 1) gy = 1;
-#define QG_SCAN_TILE(P_)                                                                                          \
-    hipLaunchKernelGGL(scan_tile_kernel<P_>, dim3(gx, gy), dim3(1024), 0, ctx->stream, hist_base, items, n_items, \
-                       F, nb, delta, (int64_t)min_data, min_sum_hess, cand, mfb)
-        if (nb <= 64) QG_SCAN_TILE(1);
-        else if (nb <= 128) QG_SCAN_TILE(2);
-        else QG_SCAN_TILE(4);
-#undef QG_SCAN_TILE
-    } else {
-        const int per = 8 << glog;
-        const int gx = (F + per - 1) / per * per;
-        hipLaunchKernelGGL(scan_kernel, dim3(gx, gy), dim3(threads), 0, ctx->stream, hist_base, items, n_items, F, nb,
-                           delta, (int64_t)min_data, min_sum_hess, cand, glog, mfb);
-    }
-    if (reduce) {  // (tree growth leaves the candidates of narrow matrices to its next kernel)
-        int gr = F > 256 ? max_items : (max_items + 3) / 4;
-        if (gr > 64) gr = 64;
-        hipLaunchKernelGGL(reduce_items_kernel, dim3(gr), dim3(256), 0, ctx->stream, cand, items, n_items, F);
-    }
+int launch_reduce_items(qgbdt_ctx* ctx, const FeatCand* cand, const ScanPair* pairs, const int32_t* n_items, int max_items,
+                        qgbdt_split* out, size_t stride, const StepState* step) {
+    int gr = (max_items + 3) / 4;
+    if (gr > 256) gr = 256;
+    hipLaunchKernelGGL(reduce_items_kernel, dim3(gr), dim3(256), 0, ctx->stream, cand, pairs, n_items,
+                       scan_candidates(ctx->shape), reinterpret_cast<unsigned char*>(out), (int64_t)stride, step);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
 
-// Stand-alone search over n_hists contiguous histograms, in batches of the item table it is given.
+// Features per tile of the split search: 16 (whole cache lines of the [bin][feature] histograms) for very wide matrices of
+// up to 256 bins, four or two for the others, whose few histograms of a round would leave compute units idle otherwise
+// (trees with tiles of 16 / of 4: 464 k x 90 775 / 745 us, 200 k x 136 968 / 897 us, 20 M x 200 14.9 / 14.7 ms).
+static int scan_tile_features(const qgbdt_shape& s) { return s.n_bins > 256 ? 2 : s.n_features >= 256 ? 16 : 4; }
+int scan_candidates(const qgbdt_shape& s) {
+    const int T = scan_tile_features(s);
+    return (s.n_features + T - 1) / T;
+}
+
+int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs, const int32_t* n_items, int max_pairs,
+                      const float* delta, int min_data, double min_sum_hess, FeatCand* cand, const uint16_t* mfb,
+                      const HistPlan* plan) {
+    const int F = ctx->shape.n_features, nb = ctx->shape.n_bins;
+    const int n_ft = scan_candidates(ctx->shape);
+    SlotSource src{};
+    if (plan) {
+        src.partials = static_cast<const unsigned char*>(ctx->hist_partials);
+        src.acc_width = plan->two_level ? 32 : plan->acc_width; src.hshift = plan->hshift; src.ft = plan->ft; src.ftp = plan->ftp;
+        src.n_tiles = plan->n_tiles; src.slot_bytes = plan->slot_bytes; src.pad16 = plan->pad16;
+        src.elementwise = plan->bytewise;
+    }
+    // one workgroup per (tile, pair) up to about 4096 of them, pairs in multiples of 8 (one per XCD)
+    int64_t lanes = max_pairs, most = 4096 / n_ft;
+    if (most < 8) most = 8;
+    if (lanes > most) lanes = most;
+    lanes = (lanes + 7) / 8 * 8;
+    const dim3 grid((unsigned)(lanes * n_ft));
+#define QG_SCAN(T_, N_, K_)                                                                                             \
+    hipLaunchKernelGGL((scan_pair_kernel<T_, N_, K_>), grid, dim3(64 * T_ * N_ / K_), 0, ctx->stream, hist_base, pairs, \
+                       n_items, max_pairs, src, F, nb, delta, min_data, min_sum_hess, cand, mfb)
+    // (bins per thread: few for narrow matrices, whose workgroups do not fill the chip; 1 M x 28 10.0 us per launch with four,
+    // 9.7 us with two)
+    if (nb > 512) QG_SCAN(2, 16, 4);
+    else if (nb > 256) QG_SCAN(2, 8, 2);
+    else if (scan_tile_features(ctx->shape) == 16) {
+        if (nb <= 64) QG_SCAN(16, 1, 4);
+        else if (nb <= 128) QG_SCAN(16, 2, 4);
+        else QG_SCAN(16, 4, 4);
+    } else if (nb <= 64) QG_SCAN(4, 1, 1);
+    else if (nb <= 128) QG_SCAN(4, 2, 1);
+    else if (F >= 64) QG_SCAN(4, 4, 4); else QG_SCAN(4, 4, 2);
+#undef QG_SCAN
+    QG_HIP(ctx, hipGetLastError());
+    return QGBDT_OK;
+}
+
+// Stand-alone search over n_hists contiguous histograms, in batches of the tables it is given.
 int run_find_best_splits(qgbdt_ctx* ctx, const int64_t* hist, int n_hists, const qgbdt_leafstat* stats,
                          const float* delta, int min_data, double min_sum_hess, qgbdt_split* out, int cap,
-                         ScanItem* items, FeatCand* cand, int32_t* n_items) {
-    const int F = ctx->shape.n_features, nb = ctx->shape.n_bins;
-    const int64_t W = (int64_t)F * nb;
+                         ScanPair* pairs, FeatCand* cand, int32_t* n_items) {
+    const int64_t W = (int64_t)ctx->shape.n_features * ctx->shape.n_bins;
     for (int h0 = 0; h0 < n_hists; h0 += cap) {
-        const int n = (n_hists - h0 < cap) ? (n_hists - h0) : cap;
-        hipLaunchKernelGGL(scan_items_from_stats_kernel, dim3((n + 63) / 64), dim3(64), 0, ctx->stream, stats + h0, n,
-                           items, out + h0, n_items);
-        int rc = launch_scan_items(ctx, const_cast<int64_t*>(hist) + h0 * W, items, n_items, n, delta,
-                                   min_data, min_sum_hess, cand);
+        const int n = (n_hists - h0 < cap) ? (n_hists - h0) : cap, np = (n + 1) / 2;
+        hipLaunchKernelGGL(scan_pairs_from_stats_kernel, dim3((np + 63) / 64), dim3(64), 0, ctx->stream, stats + h0, n, pairs, n_items);
+        int rc = launch_scan_pairs(ctx, const_cast<int64_t*>(hist) + h0 * W, pairs, n_items, np, delta, min_data, min_sum_hess,
+                                   cand, nullptr, nullptr);
+        if (rc != QGBDT_OK) return rc;
+        rc = launch_reduce_items(ctx, cand, pairs, n_items, n, out + h0, sizeof(qgbdt_split), nullptr);
         if (rc != QGBDT_OK) return rc;
     }
     return QGBDT_OK;

@@ -5,17 +5,25 @@
 
 namespace qgbdt {
 
-// One histogram to scan: where it lives, whether it is first formed as
-// parent - child (sibling subtraction), the totals of its leaf and where the
-// best split goes.
-struct ScanItem {
-    int32_t slot;        // histogram index relative to the base pointer
-    int32_t sub_parent;  // >= 0: hist[slot] = hist[sub_parent] - hist[sub_child] first
-    int32_t sub_child;
-    int32_t valid;       // 0: skip
-    qgbdt_leafstat stat;
-    qgbdt_split* out;
+// Two histograms to scan, in one record so that a workgroup of the split search needs a single load before it knows
+// everything: `a` was built from rows (or is given), `b` is formed as parent - a first (or is given, or absent).  In tree
+// growth they are the two children of a node; results are numbered 2 * pair + (0 or 1), `a` is number `a_item`.
+struct ScanPair {
+    int32_t slot_a, slot_b;  // histogram indices relative to the base pointer; slot_b < 0: no second histogram
+    int32_t parent;          // >= 0: hist[slot_b] = hist[parent] - hist[slot_a] first
+    int32_t a_item;
+    int32_t item_start;      // first slot of a's row groups
+    int32_t groups;          // > 0: a is the sum of that many slots, which the split search adds up; 0: it lies in hist[slot_a]
+    int32_t merged;          // (groups > 0) hist[slot_a] holds what long row groups have merged already, to be added
+    int32_t pad;
+    qgbdt_leafstat stat[2];  // totals of a, b
 };
+
+__device__ __forceinline__ long long readlane64(long long v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)v >> 32), lane);
+    return (long long)(((unsigned long long)hi << 32) | lo);
+}
 
 __device__ __forceinline__ int64_t packed_g(int64_t w) { return w >> 32; }
 __device__ __forceinline__ int64_t packed_h(int64_t w) { return w & 0xffffffffLL; }
@@ -34,7 +42,7 @@ __device__ __forceinline__ int64_t count_estimate(int64_t HL, int64_t Hs, int64_
     return (2 * HL * n + Hs) / (2 * Hs);
 }
 
-// Reduces the per-feature candidates of one leaf to its best split: largest gain,
+// Reduces the candidates of one leaf (F of them, one per tile of ascending features) to its best split: largest gain,
 // ties to the lowest feature.  Called by all 64 lanes of one wavefront; lane 0
 // writes the result.
 __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const qgbdt_leafstat& st, qgbdt_split* out,
@@ -56,7 +64,7 @@ __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const q
         s.left_g = s.left_h = s.right_g = s.right_h = s.left_count = 0;
         if (bf >= 0) {
             const FeatCand c = cand[bf];
-            s.gain = c.gain; s.feature = bf; s.bin = c.bin;
+            s.gain = c.gain; s.feature = c.feature; s.bin = c.bin;
             s.left_g = packed_g(c.left); s.left_h = packed_h(c.left);
             s.right_g = st.sum_g - s.left_g; s.right_h = st.sum_h - s.left_h;
             s.left_count = count_estimate(s.left_h, st.sum_h, st.n_rows);
@@ -72,7 +80,7 @@ __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const q
 __device__ inline void reduce_features_lanes(const FeatCand* cand, int F, const qgbdt_leafstat& st, qgbdt_split* out,
                                              int sl, int sub, double& gain, int& feature) {
     double bg = 0.0;
-    int bf = -1, bb = -1;
+    int bf = -1, bb = -1;  // (bf: the winner's feature)
     int64_t bl = 0;
     for (int f0 = sl; f0 < F; f0 += 4 * sub) {  // four loads in flight
         FeatCand c[4];
@@ -81,7 +89,7 @@ __device__ inline void reduce_features_lanes(const FeatCand* cand, int F, const 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {  // ascending features: strict > keeps the lowest
             const int f = f0 + u * sub;
-            if (f < F && c[u].bin >= 0 && (c[u].gain > bg)) { bg = c[u].gain; bf = f; bb = c[u].bin; bl = c[u].left; }
+            if (f < F && c[u].bin >= 0 && (c[u].gain > bg)) { bg = c[u].gain; bf = c[u].feature; bb = c[u].bin; bl = c[u].left; }
         }
     }
     for (int o = sub >> 1; o > 0; o >>= 1) {

@@ -47,7 +47,7 @@ __device__ __forceinline__ int hist_groups(int64_t count, const HistPlan& plan) 
 
 __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepState* step, Node* nodes,
                                                         const int64_t* qtotals, int root_buf, HistEntry* hist_entries,
-                                                        int32_t* hist_counts, ScanItem* items,
+                                                        int32_t* hist_counts, ScanPair* pairs,
                                                         int64_t* hist0, int64_t hist_words, HistPlan plan) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -64,12 +64,14 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
         HistEntry e;
         e.begin = 0; e.count = N; e.buf = root_buf; e.slot = 0; e.item_start = 0; e.groups = hist_groups(N, plan);
         hist_entries[0] = e;
-        hist_counts[0] = 1; hist_counts[1] = e.groups;
-        ScanItem it;
-        it.slot = 0; it.sub_parent = -1; it.sub_child = -1; it.valid = 1;
-        it.stat.n_rows = N; it.stat.sum_g = r.sum_g; it.stat.sum_h = r.sum_h;
-        it.out = &nodes[0].best;
-        items[0] = it;
+        hist_counts[0] = 1; hist_counts[1] = e.groups; hist_counts[2] = e.groups > REDUCE_ABOVE ? 1 : 0;
+        ScanPair sp;
+        sp.slot_a = 0; sp.slot_b = -1; sp.parent = -1; sp.a_item = 0; sp.item_start = 0;
+        sp.groups = e.groups <= REDUCE_ABOVE ? e.groups : 0;
+        sp.merged = N > (int64_t)e.groups * plan.single_rows ? 1 : 0; sp.pad = 0;
+        sp.stat[0].n_rows = N; sp.stat[0].sum_g = r.sum_g; sp.stat[0].sum_h = r.sum_h;
+        sp.stat[1] = sp.stat[0];
+        pairs[0] = sp;
     }
 }
 
@@ -145,8 +147,8 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 // Commit phase and choice of the round's batch.  One workgroup of 1024 threads, bound by the latency of its chain of
 // phases (about 0.1 us for a barrier, 0.06 us for a dependent LDS access), so everything that is a set of nodes is a
 // bit mask over gain ranks (64 ranks to a word, at most 64 words) or a pass with one thread per rank.
-//  0. (at most 256 features) The per-feature candidates of the histograms scanned last are reduced to their nodes'
-//     best splits, by groups of lanes just wide enough that one pass serves all of them, which saves the launch that
+//  0. (at most 256 candidates per histogram) The candidates of the histograms scanned last -- one per tile of features --
+//     are reduced to their nodes' best splits, by groups of lanes just wide enough that one pass serves all of them, which saves the launch that
 //     would do it.
 //  1. The known nodes that are not committed and have a gain are kept sorted by it in global memory; last round's
 //     children (node ids n_known ..) are merged in.  A node's place is a count of larger keys; every wavefront counts
@@ -168,10 +170,10 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 // (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
 // (20 M x 200, 511 leaves).
 __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch, int32_t* batch_seg,
-                                                         int32_t* super_counts, PlanEntry* list, int32_t* hist_counts, int F, int num_leaves,
+                                                         int32_t* super_counts, PlanEntry* list, int32_t* hist_counts, int F, int n_cand, int num_leaves,
                                                          int batch_max, int max_expand, int seg_rows, int seg_supers, TreeOut out,
                                                          const FeatCand* __restrict__ cand,
-                                                         const ScanItem* __restrict__ scan_items) {
+                                                         const ScanPair* __restrict__ scan_pairs) {
     // the fields of the growth state this kernel needs and (for the first 1024 ranks) the kept order, in loads that are
     // in flight together
     const int tid = threadIdx.x, lane = tid & 63;
@@ -217,12 +219,14 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     // Scanned histogram j belongs to node n_known + j: the best splits of last round's children.
     if (cand != nullptr) {
         int lg = 6;  // log2 of the lanes that share a histogram
-        while (lg > 0 && ((1 << (lg - 1)) >= F || (1024 >> lg) < n_scan)) --lg;
+        while (lg > 0 && ((1 << (lg - 1)) >= n_cand || (1024 >> lg) < n_scan)) --lg;
         const int sl = tid & ((1 << lg) - 1);
         for (int item = tid >> lg; item < n_scan; item += 1024 >> lg) {
             double gain = 0.0;
             int feature = -1;
-            reduce_features_lanes(cand + (int64_t)item * F, F, scan_items[item].stat, &nodes[n_known + item].best, sl, 1 << lg, gain, feature);
+            const ScanPair* sp = &scan_pairs[item >> 1];
+            reduce_features_lanes(cand + (int64_t)item * n_cand, n_cand, sp->stat[sp->a_item == (item & 1) ? 0 : 1],
+                                  &nodes[n_known + item].best, sl, 1 << lg, gain, feature);
             if (sl == 0)
                 nkey[item] = (feature >= 0 && gain > 0.0) ? (unsigned long long)__double_as_longlong(gain) : 0ull;
         }
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     if (done) {
         if (tid == 0) {
             step->done = 1; step->n_batch = 0; step->n_part_items = 0; step->n_scan_items = 0;
-            hist_counts[0] = 0; hist_counts[1] = 0;
+            hist_counts[0] = 0; hist_counts[1] = 0; hist_counts[2] = 0;
         }
         return;
     }
@@ -649,21 +653,28 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     // the root's rows are the original arrays under the identity list (array 0, which its great-grandchildren reuse)
     const int root_buf = BUF_ORIGINAL;
 
-    // up to 256 features the plan kernel reduces the scan's per-feature candidates itself (one launch less per round)
-    const FeatCand* fused_cand = F <= 256 ? ctx->cand : nullptr;
+    // up to 256 candidates per histogram the plan kernel reduces them itself (one launch less per round)
+    const int n_cand = scan_candidates(ctx->shape);
+    const FeatCand* fused_cand = n_cand <= 256 ? ctx->cand : nullptr;
     int blocks = (int)((W + 255) / 256);
     if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(tree_init_kernel, dim3(blocks), dim3(256), 0, ctx->stream, N, F, ctx->step,
-                       ctx->nodes, ctx->qtotals, root_buf, ctx->hist_entries, ctx->hist_counts, ctx->scan_items,
+                       ctx->nodes, ctx->qtotals, root_buf, ctx->hist_entries, ctx->hist_counts, ctx->scan_pairs,
                        ctx->hist_pool, W, root_plan);
     ctx->next_hist_is_root = 1;
     rc = launch_hist(ctx, root_plan, rows, idxs, false, ((uintptr_t)bins & 15) == 0,
                      ctx->hist_entries, ctx->hist_counts, ctx->hist_pool,
                      (N + hist_target_rows(root_plan, N, 1) - 1) / hist_target_rows(root_plan, N, 1),  // the build's row groups
-                     ctx->step, mfb);
+                     ctx->step, mfb, REDUCE_ABOVE);
     if (rc != QGBDT_OK) return rc;
-    rc = launch_scan_items(ctx, ctx->hist_pool, ctx->scan_items, &ctx->step->n_scan_items, 1, ctx->delta,
-                           p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, fused_cand == nullptr);
+    auto search_splits = [&](const HistPlan& hp, int max_pairs) {
+        int rc = launch_scan_pairs(ctx, ctx->hist_pool, ctx->scan_pairs, &ctx->step->n_scan_items, max_pairs, ctx->delta,
+                                   p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, &hp);
+        if (rc != QGBDT_OK || fused_cand) return rc;
+        return launch_reduce_items(ctx, ctx->cand, ctx->scan_pairs, &ctx->step->n_scan_items, 2 * max_pairs,
+                                   &ctx->nodes->best, sizeof(Node), ctx->step);
+    };
+    rc = search_splits(root_plan, 1);
     if (rc != QGBDT_OK) return rc;
 
     const size_t plan_lds = plan_kernel_lds(ctx, p->num_leaves);  // at most what prepare_tree_kernels allowed
@@ -672,8 +683,8 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     int to_launch = ctx->rounds_hint;
     auto plan_batch = [&]() {
         hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
-                           ctx->batch_seg, ctx->super_counts, ctx->plan_list, ctx->hist_counts, F, p->num_leaves,
-                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, out, fused_cand, ctx->scan_items);
+                           ctx->batch_seg, ctx->super_counts, ctx->plan_list, ctx->hist_counts, F, n_cand, p->num_leaves,
+                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, out, fused_cand, ctx->scan_pairs);
     };
     auto expand_batch = [&]() {  // partition, histograms and split search of the nodes the plan kernel has chosen
         int rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
@@ -681,10 +692,9 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         rc = launch_batch_partition_scatter(ctx, rows, ordered, plan);
         if (rc != QGBDT_OK) return rc;
         rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
-                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb);
+                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb, REDUCE_ABOVE);
         if (rc != QGBDT_OK) return rc;
-        return launch_scan_items(ctx, ctx->hist_pool, ctx->scan_items, &ctx->step->n_scan_items, 2 * ctx->batch_max,
-                                 ctx->delta, p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, fused_cand == nullptr);
+        return search_splits(plan, ctx->batch_max);
     };
     for (;;) {
         for (int r = 0; r < to_launch; ++r) {

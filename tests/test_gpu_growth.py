@@ -61,3 +61,35 @@ def test_partition_segments(N, F, L, layout):
         t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 3, 3, 5, 0, L, min_data_in_leaf=20,
                           row_layout=layout)
         _check(t, e, N)
+
+
+def _split_cases():
+    # bins and features around the edges of the search's tiles and of the bins a thread takes
+    return [(F, nb) for F, nb in [(1, 2), (3, 64), (4, 65), (5, 63), (7, 128), (29, 129), (63, 255), (64, 256), (66, 100), (255, 9),
+                                  (256, 64), (257, 65), (260, 129), (271, 255), (3, 257), (9, 512), (6, 513), (33, 1023), (2, 1024)]]
+
+
+@pytest.mark.parametrize("F,nb", _split_cases())
+def test_split_search_edges(F, nb):
+    from paper_2207_09682_amd import Context, binding
+    rng = np.random.default_rng(1000 * F + nb)
+    n = 5
+    G = rng.integers(-300, 300, (n, nb, F)).astype(np.int64)
+    H = rng.integers(0, 400, (n, nb, F)).astype(np.int64) * (rng.random((n, nb, F)) < 0.8)
+    tg = G.sum(axis=1).max(axis=1) + 10; th = H.sum(axis=1).max(axis=1) + 10
+    last = nb // 2  # every feature of a leaf sums to the leaf's totals
+    G[:, last, :] += tg[:, None] - G.sum(axis=1)
+    H[:, last, :] += th[:, None] - H.sum(axis=1)
+    rows = (th // 3 + 1).astype(np.int64)
+    hist = torch.from_numpy(((G << 32) + H).reshape(n, nb * F)).cuda()
+    stats = torch.from_numpy(np.stack([rows, tg, th], axis=1)).cuda()
+    d = np.array([0.25, 0.125], np.float32)
+    ctx = Context(1000, F, nb, max_leaves=3, bin_bytes=2 if nb > 256 else 1)   # batches of 6 histograms, an odd number here
+    for min_data, min_h in ((0, 0.0), (20, 0.0), (int(rows.min()) // 3, 5.0), (10**6, 0.0)):
+        got = binding.unpack_splits(ctx.find_best_splits(hist, stats, torch.from_numpy(d).cuda(), min_data, min_h))
+        for i in range(n):
+            o = np.stack([G[i].T, H[i].T], axis=-1).copy()
+            e = oracle.find_best_split(o, int(rows[i]), int(tg[i]), int(th[i]), d[0], d[1], min_data, min_h)
+            assert got[i]["feature"] == e.feature and got[i]["gain"] == e.gain, (min_data, i)
+            if e.feature >= 0:
+                assert all(got[i][k] == getattr(e, k) for k in ("bin", "GL", "HL", "GR", "HR", "cnt_left"))
