@@ -165,8 +165,9 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     k.take(&c->hist_counts, 4);
     k.take(&c->pwork, 1);
     k.take(&c->scan_pairs, (size_t)c->batch_max);
-    k.take(&c->leaf_node, L);
-    k.take(&c->refit_partial, L * REFIT_PARTS * 2);
+    k.take(&c->refit_units, L + REFIT_EXTRA);
+    k.take(&c->refit_leaves, L + 1);
+    k.take(&c->refit_partial, (size_t)refit_parts(sh.n_rows) * (L + REFIT_EXTRA) * 2);
     k.take(&c->tmp_i64, 8);
     // optional sections
     if (flags & QGBDT_WS_BIND) {
@@ -521,7 +522,7 @@ int qgbdt_refit_leaves(qgbdt_ctx* ctx, const float* g, const float* h, const int
     if (int rcw = require_workspace(ctx)) return rcw;
     if (n_leaves < 0 || n_leaves > ctx->shape.max_leaves)
         return set_error(ctx, QGBDT_E_INVALID_ARG, "n_leaves=%d outside 0..max_leaves", n_leaves);
-    return launch_refit(ctx, g, h, nullptr, row_idx, leaf_begin, leaf_count, n_leaves, nullptr, value_out);
+    return launch_refit(ctx, g, h, row_idx, leaf_begin, leaf_count, n_leaves, value_out);
 }
 
 int qgbdt_grow_tree(qgbdt_ctx* ctx, const void* bins, const float* g, const float* h, const qgbdt_params* p,
@@ -570,7 +571,7 @@ int qgbdt_update_scores(qgbdt_ctx* ctx, float* score, const int32_t* row_idx, co
     if (int rcw = require_workspace(ctx)) return rcw;
     if (n_leaves < 0 || n_leaves > ctx->shape.max_leaves)
         return set_error(ctx, QGBDT_E_INVALID_ARG, "n_leaves=%d outside 0..max_leaves", n_leaves);
-    return launch_update_scores(ctx, score, row_idx, leaf_begin, leaf_count, leaf_value, n_leaves, nullptr, learning_rate);
+    return launch_update_scores(ctx, score, row_idx, leaf_begin, leaf_count, leaf_value, n_leaves, false, learning_rate);
 }
 
 int qgbdt_lambdarank_gradients(qgbdt_ctx* ctx, const float* score, const float* relevance, int64_t n,
@@ -602,7 +603,7 @@ static int boost_iteration(qgbdt_ctx* ctx, int loss, int group_size, const void*
     rc = qgbdt_grow_tree(ctx, bins, ctx->gbuf, ctx->hbuf, p, iteration, t, row_idx_out);  // validates the rest
     if (rc != QGBDT_OK) return rc;
     return launch_update_scores(ctx, score, row_idx_out, t->leaf_begin, t->leaf_count, t->leaf_value,
-                                ctx->shape.max_leaves, t->n_leaves, learning_rate);
+                                ctx->shape.max_leaves, true, learning_rate);
 }
 
 int qgbdt_boost_iteration(qgbdt_ctx* ctx, const void* bins, const float* label, float* score, const qgbdt_params* p,

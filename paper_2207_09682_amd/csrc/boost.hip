@@ -1,6 +1,5 @@
-// The two steps around a tree that close the boosting loop on the device (Sec. 3): the loss
-// derivatives g_i, h_i of the current predictions (binary cross-entropy) and the prediction
-// update with the new tree's leaf values.  Both are HBM-bound streaming / gather kernels.
+// The loss derivatives g_i, h_i of the current predictions, which start a boosting iteration on
+// the device (Sec. 3): binary cross-entropy (HBM-bound streaming) and lambdarank.
 #include "common.h"
 
 namespace qgbdt {
@@ -33,25 +32,6 @@ __global__ __launch_bounds__(256) void logistic_grad_kernel(const float* __restr
         if (r < n) logistic_one(score[r], label[r], g[r], h[r]);
     } else {
         for (int64_t i = t0; i < n; i += stride) logistic_one(score[i], label[i], g[i], h[i]);
-    }
-}
-
-// score[row] += (float)(lr * value[leaf]) for the rows of every leaf: block (part, leaf) takes
-// a contiguous part of the leaf's slice of the leaf-ordered row list.
-__global__ __launch_bounds__(256) void update_scores_kernel(float* __restrict__ score,
-                                                            const int32_t* __restrict__ row_idx,
-                                                            const int64_t* __restrict__ leaf_begin,
-                                                            const int64_t* __restrict__ leaf_count,
-                                                            const double* __restrict__ leaf_value,
-                                                            const int32_t* __restrict__ n_leaves_dev, double lr) {
-    const int l = blockIdx.y;
-    if (n_leaves_dev && l >= *n_leaves_dev) return;
-    const int64_t begin = leaf_begin[l], count = leaf_count[l];
-    const float d = (float)(lr * leaf_value[l]);
-    const int64_t a = count * blockIdx.x / gridDim.x, b = count * (blockIdx.x + 1) / gridDim.x;
-    for (int64_t j = a + threadIdx.x; j < b; j += blockDim.x) {
-        const int64_t i = row_idx[begin + j];
-        score[i] += d;  // every row belongs to exactly one leaf: no two threads touch the same element
     }
 }
 
@@ -172,16 +152,6 @@ int launch_logistic_gradients(qgbdt_ctx* ctx, const float* score, const float* l
     if (blocks > 4096) blocks = 4096;
     if (vec) hipLaunchKernelGGL(logistic_grad_kernel<true>, dim3(blocks), dim3(256), 0, ctx->stream, score, label, n, g, h);
     else hipLaunchKernelGGL(logistic_grad_kernel<false>, dim3(blocks), dim3(256), 0, ctx->stream, score, label, n, g, h);
-    QG_HIP(ctx, hipGetLastError());
-    return QGBDT_OK;
-}
-
-int launch_update_scores(qgbdt_ctx* ctx, float* score, const int32_t* row_idx, const int64_t* leaf_begin,
-                         const int64_t* leaf_count, const double* leaf_value, int n_leaves,
-                         const int32_t* n_leaves_dev, double lr) {
-    if (n_leaves <= 0) return QGBDT_OK;
-    hipLaunchKernelGGL(update_scores_kernel, dim3(REFIT_PARTS, n_leaves), dim3(256), 0, ctx->stream, score, row_idx,
-                       leaf_begin, leaf_count, leaf_value, n_leaves_dev, lr);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

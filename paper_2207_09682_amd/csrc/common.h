@@ -134,6 +134,16 @@ __host__ __device__ inline int64_t hist_target_rows(const HistPlan& p, int64_t t
     return t;
 }
 
+// One unit of the passes over finished leaves (refit, score update): in every part of the row order, piece
+// (part * n + unit - first) of the leaf's rows, piece_rows long.
+struct RefitUnit {
+    int64_t begin, count;  // the leaf's rows
+    int64_t piece_rows;
+    int32_t first, n;      // the leaf's units of a part: [first, first + n)
+    int32_t leaf;
+    int32_t buf;           // index buffer that holds the leaf's rows (tree growth)
+};
+
 struct ScanPair;
 
 // Where the rows of a slice live.  Buffers 0..2 rotate with the depth of a node (the children
@@ -214,8 +224,9 @@ struct qgbdt_ctx {
     int32_t* hist_counts;        // [3] entries, items, 1: an entry has more than REDUCE_ABOVE groups
     qgbdt::PartWork* pwork;      // [1]
     qgbdt::ScanPair* scan_pairs; // [batch_max]
-    int32_t* leaf_node;          // [max_leaves]
-    double* refit_partial;       // [max_leaves][REFIT_PARTS][2]
+    qgbdt::RefitUnit* refit_units;  // [max_leaves + REFIT_EXTRA] of the leaves last laid out
+    int2* refit_leaves;          // [max_leaves + 1] first unit and units of a leaf; behind the leaves: number of units
+    double* refit_partial;       // [refit_parts][max_leaves + REFIT_EXTRA][2], a leaf's pieces consecutive
     int64_t* tmp_i64;            // [8]
     qgbdt::StepState* host_state;  // pinned host copy
     // profiling
@@ -231,7 +242,22 @@ struct qgbdt_ctx {
 namespace qgbdt {
 
 constexpr int PART_GROUPS = 512;
-constexpr int REFIT_PARTS = 32;
+// Passes over finished leaves gather and update 4 to 8 bytes per row, leaf by leaf, in places that lie about a cache line apart
+// or further.  Their work is cut into parts of the row order (a leaf's list ascends), a multiple of 8 of them, and the
+// workgroups of one part run side by side on one XCD: its L2 then serves all leaves' shares of a line after one fetch.
+// A part is 2^17 rows: 1 MB of (g, h) pairs, of which two to four parts in flight fit the 4 MB.
+// Against 32 parts per leaf spread over all XCDs (and a separate copy of the row lists): 20 M rows in 511 leaves, refit and copy
+// 430 -> 150 us, score update 635 -> 253 us (what is left is the rate of L2 requests, one per row and direction); 10.5 M
+// rows in 255 leaves 179 -> 77 us; two leaves of 3 M rows 95 -> 11 us, which used to have 64 workgroups.
+constexpr int REFIT_EXTRA = 256;  // most units of a part beyond one per leaf: large leaves are cut into several
+inline int refit_parts(int64_t n_rows) {
+    const int64_t p = 8 * ((n_rows + (1 << 20) - 1) >> 20);
+    return p < 8 ? 8 : p > 256 ? 256 : (int)p;
+}
+inline int refit_extra(int64_t n_rows) {  // about 512 rows per unit where a leaf is large enough
+    const int64_t x = n_rows / ((int64_t)refit_parts(n_rows) * 512);
+    return x > REFIT_EXTRA ? REFIT_EXTRA : (int)x;
+}
 constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
 // Rows per thread of a segment of the batched partition (256 threads; the loads of a thread's rows are in flight
 // together), and whether the left rows of PART_SUPER segments are summed up in one counter on the way.
@@ -307,15 +333,18 @@ int prepare_hist_kernels(qgbdt_ctx* ctx);  // once per context: dynamic-LDS limi
 int prepare_tree_kernels(qgbdt_ctx* ctx);
 // !ordered: row ids and, with rows.gh_pos, packed gradients; `plan`: of the histogram launch that follows
 int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered, const HistPlan& plan);
-int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const float2* pairs, const int32_t* row_idx,
-                 const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves,
-                 const int32_t* n_leaves_dev, double* value_out);
+// leaves -> units of the passes over their rows (ctx->refit_units); tree growth lays them out in its last kernel
+int launch_layout_leaves(qgbdt_ctx* ctx, const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves);
+int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* row_idx, const int64_t* leaf_begin,
+                 const int64_t* leaf_count, int n_leaves, double* value_out);
+// tree growth (leaves laid out): the row lists to the caller's, and the leaf values
+int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out);
 int launch_logistic_gradients(qgbdt_ctx* ctx, const float* score, const float* label, int64_t n, float* g, float* h);
 int launch_lambdarank_gradients(qgbdt_ctx* ctx, const float* score, const float* label, int64_t n, int group,
                                 float* g, float* h);
+// laid_out: by the tree that has just been grown (n_leaves: at most that many leaves)
 int launch_update_scores(qgbdt_ctx* ctx, float* score, const int32_t* row_idx, const int64_t* leaf_begin,
-                         const int64_t* leaf_count, const double* leaf_value, int n_leaves,
-                         const int32_t* n_leaves_dev, double lr);
+                         const int64_t* leaf_count, const double* leaf_value, int n_leaves, bool laid_out, double lr);
 int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const float* h,
                   const qgbdt_params* p, uint32_t iteration, const qgbdt_tree* out, int32_t* row_idx_out);
 

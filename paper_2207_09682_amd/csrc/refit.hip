@@ -1,72 +1,173 @@
 // Leaf-value refit with the original FP gradients (Sec. 3 eq. (leaf), Sec. 4.2):
 // one gather pass over g, h through the leaf-ordered row list, fp64 sums in a
-// fixed reduction order (so repeated runs give identical bits).
-#include "common.h"
+// fixed reduction order (so repeated runs give identical bits); and the layout of
+// finished leaves that it shares with the score update.
+#include "refit_device.h"
 
 namespace qgbdt {
 
-// PAIR: (g, h) of a row are read as one 8-byte pair from an interleaved copy (half the sectors
-// of two separate 4-byte gathers).
-template <bool PAIR>
+__global__ __launch_bounds__(1024) void layout_leaves_kernel(const int64_t* __restrict__ leaf_begin,
+                                                             const int64_t* __restrict__ leaf_count, int n_leaves,
+                                                             int parts, int extra, RefitUnit* units, int2* leaves,
+                                                             int max_leaves) {
+    __shared__ LeafLayout s;
+    for (int l = threadIdx.x; l < n_leaves; l += blockDim.x) {
+        s.begin[l] = leaf_begin[l]; s.count[l] = leaf_count[l]; s.buf[l] = 0;
+    }
+    __syncthreads();
+    layout_leaves(s, n_leaves, max_leaves, parts, extra, units, leaves);
+}
+
+// Sums of (g, h) over the pieces of all leaves; one wavefront per unit, four rows per lane in flight.
+// TREE: the rows come from the index buffer in which the leaf ended up and go to the caller's list on the way, and (g, h)
+// are read as one 8-byte pair from the quantizer's interleaved copy; otherwise row_idx is read and nothing is written.
+// Bound by the row lists and pairs once per line: see REFIT_EXTRA for the order of the units.
+template <bool TREE>
 __global__ __launch_bounds__(256) void refit_partial_kernel(const float* __restrict__ g, const float* __restrict__ h,
-                                                            const float2* __restrict__ pairs,
-                                                            const int32_t* __restrict__ row_idx,
-                                                            const int64_t* __restrict__ leaf_begin,
-                                                            const int64_t* __restrict__ leaf_count,
-                                                            const int32_t* __restrict__ n_leaves_dev,
+                                                            const float2* __restrict__ pairs, IdxSet idxs,
+                                                            const int32_t* __restrict__ row_idx, int32_t* __restrict__ out,
+                                                            const RefitUnit* __restrict__ units,
+                                                            const int32_t* __restrict__ n_units, int parts, int blocks_per_part,
                                                             double* __restrict__ partial) {
-    const int l = blockIdx.y;
-    if (n_leaves_dev && l >= *n_leaves_dev) return;
-    const int64_t begin = leaf_begin[l], count = leaf_count[l];
-    const int64_t a = count * blockIdx.x / gridDim.x, b = count * (blockIdx.x + 1) / gridDim.x;
+    int part, u;
+    if (!refit_unit_of(n_units, blocks_per_part, part, u)) return;
+    const RefitUnit un = units[u];
+    const int lane = threadIdx.x & 63;
+    const int64_t piece = (int64_t)part * un.n + (u - un.first);
+    const int64_t a = min(un.count, piece * un.piece_rows), b = min(un.count, a + un.piece_rows);
+    const bool identity = TREE && un.buf == BUF_ORIGINAL;  // a tree that is its root: the list was never stored
+    const int32_t* src = (TREE ? idxs.p[un.buf] : row_idx) + un.begin;
     double G = 0.0, H = 0.0;
-    for (int64_t j = a + threadIdx.x; j < b; j += blockDim.x) {
-        const int64_t i = row_idx[begin + j];
-        if (PAIR) {
-            const float2 v = pairs[i];
-            G += (double)v.x;
-            H += (double)v.y;
-        } else {
-            G += (double)g[i];
-            H += (double)h[i];
+    for (int64_t j0 = a; j0 < b; j0 += 256) {
+        int32_t r[4];
+        float2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t j = min(j0 + 64 * k + lane, b - 1);
+            r[k] = identity ? (int32_t)(un.begin + j) : src[j];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = TREE ? pairs[r[k]] : make_float2(g[r[k]], h[r[k]]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t j = j0 + 64 * k + lane;
+            if (j < b) {
+                if (TREE) out[un.begin + j] = r[k];
+                G += (double)v[k].x;
+                H += (double)v[k].y;
+            }
         }
     }
+    for (int o = 32; o > 0; o >>= 1) { G += __shfl_xor(G, o); H += __shfl_xor(H, o); }
+    if (lane == 0) reinterpret_cast<double2*>(partial)[(int64_t)parts * un.first + piece] = make_double2(G, H);
+}
+
+// One workgroup per leaf: the sums of its pieces.
+__global__ __launch_bounds__(256) void refit_final_kernel(const double* __restrict__ partial, int parts,
+                                                          const int2* __restrict__ leaves,
+                                                          const int32_t* __restrict__ n_leaves_dev, double* __restrict__ value) {
+    const int l = blockIdx.x;
+    if (n_leaves_dev && l >= *n_leaves_dev) {  // uniform over the workgroup
+        if (threadIdx.x == 0) value[l] = 0.0;
+        return;
+    }
+    const int2 lf = leaves[l];
+    const double2* p = reinterpret_cast<const double2*>(partial) + (int64_t)parts * lf.x;
+    const int n = parts * lf.y;
+    double G = 0.0, H = 0.0;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) { const double2 v = p[k]; G += v.x; H += v.y; }
     for (int o = 32; o > 0; o >>= 1) { G += __shfl_xor(G, o); H += __shfl_xor(H, o); }
     __shared__ double sg[4], sh[4];
     if ((threadIdx.x & 63) == 0) { sg[threadIdx.x >> 6] = G; sh[threadIdx.x >> 6] = H; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double* out = partial + ((int64_t)l * gridDim.x + blockIdx.x) * 2;
-        out[0] = ((sg[0] + sg[1]) + sg[2]) + sg[3];
-        out[1] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+        G = ((sg[0] + sg[1]) + sg[2]) + sg[3];
+        H = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+        value[l] = (H > 0.0) ? -G / H : 0.0;
     }
 }
 
-__global__ void refit_final_kernel(const double* __restrict__ partial, int parts, int n_leaves,
-                                   const int32_t* __restrict__ n_leaves_dev, double* __restrict__ value) {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= n_leaves) return;
-    if (n_leaves_dev && l >= *n_leaves_dev) { value[l] = 0.0; return; }
-    double G = 0.0, H = 0.0;
-    for (int k = 0; k < parts; ++k) {
-        G += partial[((int64_t)l * parts + k) * 2];
-        H += partial[((int64_t)l * parts + k) * 2 + 1];
+// score[row] += (float)(lr * value[leaf]) for the rows of every leaf, units as above.
+__global__ __launch_bounds__(256) void update_scores_kernel(float* __restrict__ score, const int32_t* __restrict__ row_idx,
+                                                            const double* __restrict__ leaf_value,
+                                                            const RefitUnit* __restrict__ units,
+                                                            const int32_t* __restrict__ n_units, int blocks_per_part,
+                                                            double lr) {
+    int part, u;
+    if (!refit_unit_of(n_units, blocks_per_part, part, u)) return;
+    const RefitUnit un = units[u];
+    const int lane = threadIdx.x & 63;
+    const float d = (float)(lr * leaf_value[un.leaf]);
+    const int64_t piece = (int64_t)part * un.n + (u - un.first);
+    const int64_t a = min(un.count, piece * un.piece_rows), b = min(un.count, a + un.piece_rows);
+    const int32_t* src = row_idx + un.begin;
+    for (int64_t j0 = a; j0 < b; j0 += 256) {
+        int32_t r[4];
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = src[min(j0 + 64 * k + lane, b - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = score[r[k]];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)  // every row belongs to exactly one leaf: no two threads touch the same element
+            if (j0 + 64 * k + lane < b) score[r[k]] = v[k] + d;
     }
-    value[l] = (H > 0.0) ? -G / H : 0.0;
 }
 
-int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const float2* pairs, const int32_t* row_idx,
-                 const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves,
-                 const int32_t* n_leaves_dev, double* value_out) {
+struct RefitGrid {
+    int parts, blocks_per_part;
+    dim3 grid() const { return dim3((unsigned)(parts * blocks_per_part)); }
+};
+static RefitGrid refit_grid(const qgbdt_ctx* ctx, int n_leaves) {
+    RefitGrid r;
+    r.parts = refit_parts(ctx->shape.n_rows);
+    r.blocks_per_part = (n_leaves + refit_extra(ctx->shape.n_rows) + 3) / 4;
+    return r;
+}
+static const int32_t* units_in_use(const qgbdt_ctx* ctx) { return &ctx->refit_leaves[ctx->shape.max_leaves].x; }
+
+int launch_layout_leaves(qgbdt_ctx* ctx, const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves) {
+    hipLaunchKernelGGL(layout_leaves_kernel, dim3(1), dim3(1024), 0, ctx->stream, leaf_begin, leaf_count, n_leaves,
+                       refit_parts(ctx->shape.n_rows), refit_extra(ctx->shape.n_rows), ctx->refit_units, ctx->refit_leaves,
+                       ctx->shape.max_leaves);
+    QG_HIP(ctx, hipGetLastError());
+    return QGBDT_OK;
+}
+
+int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* row_idx, const int64_t* leaf_begin,
+                 const int64_t* leaf_count, int n_leaves, double* value_out) {
     if (n_leaves <= 0) return QGBDT_OK;
-    if (pairs)
-        hipLaunchKernelGGL(refit_partial_kernel<true>, dim3(REFIT_PARTS, n_leaves), dim3(256), 0, ctx->stream, g, h,
-                           pairs, row_idx, leaf_begin, leaf_count, n_leaves_dev, ctx->refit_partial);
-    else
-        hipLaunchKernelGGL(refit_partial_kernel<false>, dim3(REFIT_PARTS, n_leaves), dim3(256), 0, ctx->stream, g, h,
-                           pairs, row_idx, leaf_begin, leaf_count, n_leaves_dev, ctx->refit_partial);
-    hipLaunchKernelGGL(refit_final_kernel, dim3((n_leaves + 63) / 64), dim3(64), 0, ctx->stream, ctx->refit_partial,
-                       REFIT_PARTS, n_leaves, n_leaves_dev, value_out);
+    int rc = launch_layout_leaves(ctx, leaf_begin, leaf_count, n_leaves);
+    if (rc != QGBDT_OK) return rc;
+    const RefitGrid rg = refit_grid(ctx, n_leaves);
+    hipLaunchKernelGGL(refit_partial_kernel<false>, rg.grid(), dim3(256), 0, ctx->stream, g, h, nullptr, IdxSet{}, row_idx,
+                       nullptr, ctx->refit_units, units_in_use(ctx), rg.parts, rg.blocks_per_part, ctx->refit_partial);
+    hipLaunchKernelGGL(refit_final_kernel, dim3(n_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial, rg.parts,
+                       ctx->refit_leaves, nullptr, value_out);
+    QG_HIP(ctx, hipGetLastError());
+    return QGBDT_OK;
+}
+
+int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out) {
+    const RefitGrid rg = refit_grid(ctx, ctx->shape.max_leaves);
+    hipLaunchKernelGGL(refit_partial_kernel<true>, rg.grid(), dim3(256), 0, ctx->stream, nullptr, nullptr, ctx->ghf, idx, nullptr,
+                       row_idx_out, ctx->refit_units, units_in_use(ctx), rg.parts, rg.blocks_per_part, ctx->refit_partial);
+    hipLaunchKernelGGL(refit_final_kernel, dim3(ctx->shape.max_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial,
+                       rg.parts, ctx->refit_leaves, n_leaves_dev, value_out);
+    QG_HIP(ctx, hipGetLastError());
+    return QGBDT_OK;
+}
+
+int launch_update_scores(qgbdt_ctx* ctx, float* score, const int32_t* row_idx, const int64_t* leaf_begin,
+                         const int64_t* leaf_count, const double* leaf_value, int n_leaves, bool laid_out, double lr) {
+    if (n_leaves <= 0) return QGBDT_OK;
+    if (!laid_out) {
+        const int rc = launch_layout_leaves(ctx, leaf_begin, leaf_count, n_leaves);
+        if (rc != QGBDT_OK) return rc;
+    }
+    const RefitGrid rg = refit_grid(ctx, n_leaves);
+    hipLaunchKernelGGL(update_scores_kernel, rg.grid(), dim3(256), 0, ctx->stream, score, row_idx, leaf_value,
+                       ctx->refit_units, units_in_use(ctx), rg.blocks_per_part, lr);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

@@ -24,6 +24,7 @@
 // number of rounds it reads one status word to learn whether more are needed.
 #include <algorithm>
 
+#include "refit_device.h"
 #include "split_device.h"
 
 namespace qgbdt {
@@ -535,15 +536,16 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     }
 }
 
-__global__ __launch_bounds__(256) void tree_finalize_kernel(const StepState* step, const Node* nodes,
-                                                            const float* delta, int32_t* leaf_node, TreeOut out) {
+__global__ __launch_bounds__(1024) void tree_finalize_kernel(const StepState* step, const Node* nodes,
+                                                             const float* delta, int parts, int extra, RefitUnit* units,
+                                                             int2* leaves, TreeOut out) {
+    __shared__ LeafLayout s;
     const int n = step->n_leaves;
     const double dg = (double)delta[0], dh = (double)delta[1];
     for (int l = threadIdx.x; l < out.max_leaves; l += blockDim.x) {
         if (l >= n) {
             out.t.leaf_begin[l] = 0; out.t.leaf_count[l] = 0; out.t.leaf_sum_g[l] = 0; out.t.leaf_sum_h[l] = 0;
             out.t.leaf_value_quant[l] = 0.0;
-            leaf_node[l] = -1;
         }
     }
     for (int i = threadIdx.x; i < step->n_nodes; i += blockDim.x) {
@@ -553,26 +555,15 @@ __global__ __launch_bounds__(256) void tree_finalize_kernel(const StepState* ste
         out.t.leaf_begin[l] = S.begin; out.t.leaf_count[l] = S.count;
         out.t.leaf_sum_g[l] = S.sum_g; out.t.leaf_sum_h[l] = S.sum_h;
         out.t.leaf_value_quant[l] = (S.sum_h > 0 && dh > 0.0) ? -((double)S.sum_g * dg) / ((double)S.sum_h * dh) : 0.0;
-        leaf_node[l] = i;
+        s.begin[l] = S.begin; s.count[l] = S.count; s.buf[l] = S.buf;
     }
     if (threadIdx.x == 0) {
         *out.t.n_leaves = n;
         out.t.delta[0] = delta[0]; out.t.delta[1] = delta[1];
         *out.t.hist_units = step->hist_units;
     }
-}
-
-// Copies every leaf's slice from the index buffer it ended up in to the output.
-__global__ __launch_bounds__(256) void tree_gather_rows_kernel(const StepState* step, const Node* nodes,
-                                                               const int32_t* __restrict__ leaf_node,
-                                                               IdxSet idxs, int32_t* __restrict__ out) {
-    const int l = blockIdx.y;
-    if (l >= step->n_leaves) return;
-    const Node S = nodes[leaf_node[l]];
-    const int32_t* src = idxs.p[S.buf];
-    const bool identity = S.buf == BUF_ORIGINAL;  // a tree that is its root: the list was never stored
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < S.count; j += (int64_t)gridDim.x * blockDim.x)
-        out[S.begin + j] = identity ? (int32_t)(S.begin + j) : src[S.begin + j];
+    __syncthreads();
+    layout_leaves(s, n, out.max_leaves, parts, extra, units, leaves);
 }
 
 // LDS of the plan kernel for this context's node capacity.
@@ -718,16 +709,10 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     }
     ctx->rounds_hint = ctx->host_state->rounds > 0 ? ctx->host_state->rounds : 1;
 
-    hipLaunchKernelGGL(tree_finalize_kernel, dim3(1), dim3(256), 0, ctx->stream, ctx->step, ctx->nodes, ctx->delta,
-                       ctx->leaf_node, out);
-    int gx = (int)((N / ctx->shape.max_leaves + 255) / 256);
-    if (gx < 1) gx = 1;
-    if (gx > 64) gx = 64;
-    hipLaunchKernelGGL(tree_gather_rows_kernel, dim3(gx, ctx->shape.max_leaves), dim3(256), 0, ctx->stream, ctx->step,
-                       ctx->nodes, ctx->leaf_node, idxs, row_idx_out);
+    hipLaunchKernelGGL(tree_finalize_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->delta,
+                       refit_parts(N), refit_extra(N), ctx->refit_units, ctx->refit_leaves, out);
     QG_HIP(ctx, hipGetLastError());
-    return launch_refit(ctx, g, h, ctx->ghf, row_idx_out, out.t.leaf_begin, out.t.leaf_count, ctx->shape.max_leaves,
-                        out.t.n_leaves, out.t.leaf_value);
+    return launch_gather_refit(ctx, idxs, row_idx_out, out.t.n_leaves, out.t.leaf_value);
 }
 
 }  // namespace qgbdt

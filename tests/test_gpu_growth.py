@@ -93,3 +93,31 @@ def test_split_search_edges(F, nb):
             assert got[i]["feature"] == e.feature and got[i]["gain"] == e.gain, (min_data, i)
             if e.feature >= 0:
                 assert all(got[i][k] == getattr(e, k) for k in ("bin", "GL", "HL", "GR", "HR", "cnt_left"))
+
+
+# leaves as units of work: one leaf, empty leaves, one that holds nearly all rows, both sides of the lines at which the row
+# order is cut into more parts, and more rows than the largest number of parts is made for
+@pytest.mark.parametrize("N,counts", [(1, [1]), (7, [0, 7, 0]), (5000, [1, 4990, 0, 9]), (2**20, [2**19] * 2),
+                                      (2**20 + 1, [2**20 - 600, 601]), (2**20 + 9, [3] * 657 + [2**20 - 1962]),
+                                      (2**25 + 5, [2**25 - 70_000, 70_000, 0, 5])])
+def test_refit_and_update_over_leaf_layouts(N, counts):
+    rng = np.random.default_rng(N)
+    L = len(counts)
+    g = rng.normal(size=N).astype(np.float32); h = rng.uniform(0.1, 0.25, N).astype(np.float32)
+    owner = np.repeat(np.arange(L, dtype=np.int16), counts); rng.shuffle(owner)
+    rows = np.argsort(owner, kind="stable").astype(np.int32)
+    count = np.asarray(counts, np.int64); begin = np.cumsum(count) - count
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, 4, 4, max_leaves=L)
+    drows, dbegin, dcount = (torch.from_numpy(a).cuda() for a in (rows, begin, count))
+    got = ctx.refit_leaves(torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), drows, dbegin, dcount).cpu().numpy()
+    G = np.bincount(owner, g.astype(np.float64), L); H = np.bincount(owner, h.astype(np.float64), L)
+    A = np.bincount(owner, np.abs(g.astype(np.float64)), L)
+    exp = np.where(H > 0, -G / np.where(H > 0, H, 1), 0.0)
+    # fp64 sums of n terms in another order: at most n 2^-53 of the sum of magnitudes
+    bound = 2.0**-52 * count * (A / np.where(H > 0, H, 1) + np.abs(exp)) + 1e-300
+    assert (np.abs(got - exp) <= bound).all()
+    score = rng.normal(size=N).astype(np.float32); value = rng.normal(size=L)
+    d = torch.from_numpy(score.copy()).cuda()
+    ctx.update_scores(d, drows, dbegin, dcount, torch.from_numpy(value).cuda(), 0.1)
+    assert np.array_equal(d.cpu().numpy(), score + (0.1 * value).astype(np.float32)[owner])
