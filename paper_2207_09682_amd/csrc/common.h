@@ -101,8 +101,8 @@ struct HistPlan {
     int32_t threads;     // workgroup size
     int32_t lds_bytes;
     int32_t chunk_rows;  // rows accumulated between two merges of the local bins
-    int32_t max_groups;  // row groups of one build: all its workgroups are resident at once
-    int32_t max_lanes;   // workgroups along the row axis of a launch with many builds (a multiple of 8)
+    int32_t max_groups;  // row groups whose workgroups are resident at once
+    int32_t max_lanes;   // most workgroups along the row axis of a launch (a multiple of 8)
     int32_t min_rows_per_group;
     int32_t acc_width;   // 16: packed 32-bit words in LDS (g~ sums above hshift, h~ sums below), 32: packed 32|32 words
     int32_t hshift;      // bits of the hessian field of a 32-bit local word: 16, or the split that takes more rows
@@ -120,12 +120,27 @@ struct HistPlan {
                           // (one large contiguous build: few, long row groups; slots hold the 64-bit words)
 };
 
-// Rows per row group when `total` rows of `n_entries` builds are shared out: about max_groups
-// groups in all, none smaller than min_rows_per_group unless its build is; and, when the item
-// table has room, no group larger than one chunk, so that no group merges through atomics.
+// Rows per row group when `total` rows of `n_entries` builds are shared out.
+//  - As many groups as workgroups are resident at once, and no more: every build ends with a group that is not full, so one
+//    place per build but the first is left for them.  (Without it a few workgroups took a second group when the others had
+//    ended: 10.5 M x 28 2169 -> 2050 us per tree, 400 k x 2000 1241 -> 1185 us, 2 M x 40 of 16-bit bins 906 -> 888 us.)
+//  - Twice as many where the matrix has several tiles of features and a group still has 4096 rows: the last tile is narrower,
+//    and what its workgroups leave idle goes to those that start later (20 M x 200 12040 -> 11705 us per tree; with 2400 rows per group,
+//    400 k x 2000, the bins handed over twice cost more: 1188 -> 1248 us).
+//  - Not fewer than min_rows_per_group rows, unless the launch would then have fewer than 64 workgroups: a group of
+//    2048 rows takes a wavefront through 16 dependent rounds of loads (100 k x 50 434 -> 385 us per tree with 650 rows; where
+//    the chip is busy smaller groups only have more bins to hand over, 1 M x 28 676 -> 690 us with 1024).
+//  - When the item table has room, no group is larger than one chunk, so that none merges through atomics.
 __host__ __device__ inline int64_t hist_target_rows(const HistPlan& p, int64_t total, int n_entries) {
-    int64_t t = (total + p.max_groups - 1) / p.max_groups;
-    if (t < p.min_rows_per_group) t = p.min_rows_per_group;
+    int64_t groups = p.max_groups;
+    if (p.n_tiles > 1 && total / (2 * groups) >= 4096) groups *= 2;
+    const int64_t places = groups - (n_entries - 1);
+    groups = places > (groups + 1) / 2 ? places : (groups + 1) / 2;
+    int64_t t = (total + groups - 1) / groups;
+    const int64_t few = total * p.n_tiles / 64;
+    int64_t least = p.min_rows_per_group;
+    if (few < least) least = few > 512 ? few : 512;
+    if (t < least) t = least;
     if (t > p.single_rows) {
         const int64_t room = (int64_t)p.max_items - n_entries - 1;
         if (total / p.single_rows < room) t = p.single_rows;

@@ -332,6 +332,9 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
 //          spread over all 32 banks, two lanes each.
 //  V = 8:  (tiles of at most 64 features, unpadded) half of the rows swap the two dwords of their
 //          piece, which together with the byte rotation spreads an instruction over 32 columns.
+// U = 2 instructions per block of a wavefront: the LDS atomics of 16 wavefronts cover the loads' latency, and smaller blocks
+// share a group's rows out more evenly (trees with 4 / 2: 400 k x 2000 1239 / 1212 us, 200 k x 136 947 / 931 us, 20 M x 200
+// 12190 / 12160 us; 8: 1283, 1045, 12920 us).
 template <int W, bool IDX, int V, int U, bool SKIP>
 __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet idxs,
                                                                     const HistEntry* __restrict__ entries,
@@ -968,14 +971,13 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
     if (by_waves < 1) by_waves = 1;
     if (per_cu > by_waves) per_cu = by_waves;
     if (per_cu < 1) per_cu = 1;
-    // Row-group lanes come in multiples of 8 (one per XCD).  One build (equal row groups, one per lane): rounded
-    // down, so that all workgroups are resident at once -- 7 tiles at 2 workgroups per CU: 72 x 7 = 504 instead
-    // of 80 x 7 = 560 workgroups for 512 places, whose last 48 would start when the first ones end (5 M x 200,
-    // 64-bit words: 403 against 485 us).  Many builds of different sizes per launch: rounded up, the workgroups
-    // end at different times anyway and the late ones fill in (20 M x 200: 13.06 against 13.13 ms per tree).
+    // Row-group lanes come in multiples of 8 (one per XCD).  The groups that are resident at once: rounded down -- 7 tiles
+    // at 2 workgroups per CU: 72 x 7 = 504 instead of 80 x 7 = 560 workgroups for 512 places, whose last 48 would
+    // start when the first ones end (5 M x 200, 64-bit words: 403 against 485 us).  Workgroups: with several tiles
+    // twice as many, for the launches that are cut finer (hist_target_rows); those without a group return at once.
     int groups = (256 * per_cu) / p.n_tiles;
     if (groups < 1) groups = 1;
-    p.max_lanes = (groups + 7) / 8 * 8;
+    p.max_lanes = (p.n_tiles > 1 ? 2 * groups + 7 : groups + 7) / 8 * 8;
     if (groups >= 8) groups = groups / 8 * 8;
     p.max_groups = groups;
     p.acc_width = w;
@@ -1058,7 +1060,7 @@ int launch_set_hist_table(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, i
 // of 64-bit words that frequent-bin skipping makes worthwhile): the runtime is told so once per context.
 template <int W, bool IDX, int V, bool S>
 static hipError_t allow_lds(int bytes) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(hist_wide_kernel<W, IDX, V, 4, S>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(hist_wide_kernel<W, IDX, V, 2, S>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
@@ -1154,7 +1156,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         if (mfb) QG_LAUNCH_WIDE_S(W_, IDX_, V_, U_, true); else QG_LAUNCH_WIDE_S(W_, IDX_, V_, U_, false);            \
     } while (0)
 #define QG_LAUNCH_WIDE_V(W_, IDX_) \
-    if (plan.wide_v == 16) QG_LAUNCH_WIDE(W_, IDX_, 16, 4); else QG_LAUNCH_WIDE(W_, IDX_, 8, 4)
+    if (plan.wide_v == 16) QG_LAUNCH_WIDE(W_, IDX_, 16, 2); else QG_LAUNCH_WIDE(W_, IDX_, 8, 2)
         if (plan.acc_width == 16) {
             if (use_idx) { QG_LAUNCH_WIDE_V(16, true); } else { QG_LAUNCH_WIDE_V(16, false); }
         } else {
