@@ -121,3 +121,42 @@ def test_refit_and_update_over_leaf_layouts(N, counts):
     d = torch.from_numpy(score.copy()).cuda()
     ctx.update_scores(d, drows, dbegin, dcount, torch.from_numpy(value).cuda(), 0.1)
     assert np.array_equal(d.cpu().numpy(), score + (0.1 * value).astype(np.float32)[owner])
+
+
+# one and several queries per workgroup, ragged last queries, group sizes around multiples of a wavefront and of the four
+# pairs that share a reciprocal, and the largest
+@pytest.mark.parametrize("n,group", [(5, 1), (7, 3), (131, 2), (1000, 5), (333, 20), (2001, 63), (2000, 64), (2600, 65), (3000, 127),
+                                     (3001, 150), (60_001, 100), (2049, 256), (2060, 257), (5111, 511), (2049, 513), (2500, 1000), (3333, 1024)])
+def test_lambdarank_group_sizes(n, group):
+    from paper_2207_09682_amd import Context
+    rng = np.random.default_rng(n * 7 + group)
+    s = np.round(rng.normal(size=n) * 8).astype(np.float32) / 8      # ties, and zeros of both signs
+    s[s == 0] *= rng.choice([-1.0, 1.0], int((s == 0).sum())).astype(np.float32)
+    rel = rng.choice([0, 0, 0, 1, 2, 4], n).astype(np.float32)
+    nq = (n + group - 1) // group
+    q = np.arange(n) // group
+    if nq > 8:  # score ranges on both sides of the line between the two forms, gains beyond 1e100, no relevant row
+        for at, width in ((1, 330.0), (3, 350.0), (5, 5000.0)):
+            s[q == at] = rng.uniform(-width / 2, width / 2, int((q == at).sum())).astype(np.float32)
+        rel[np.flatnonzero(q == 6)[0]] = 400.0
+        rel[q == 2] = 0.0
+    g, h = (a.cpu().numpy() for a in Context(n, 4, 16).lambdarank_gradients(torch.from_numpy(s).cuda(), torch.from_numpy(rel).cuda(), group))
+    eg, eh = oracle.lambdarank_gradients(s, rel, group)
+    # fp64 sums of at most `group` terms in another order, each term to a few 2^-52 (exp of |x| <= 170: 170 * 2^-53), and one
+    # rounding to fp32 (2^-24); sums of both signs cancel, so the bound is on the magnitudes, at most the query's largest h + |g|
+    top = np.zeros(nq); np.maximum.at(top, q, np.abs(eg)); tol = 2.0**-23
+    assert (np.abs(g - eg) <= tol * np.abs(eg) + group * 2.0**-43 * top[q]).all()
+    assert (np.abs(h - eh) <= tol * np.abs(eh) + group * 2.0**-43 * top[q]).all()
+
+
+def test_lambdarank_nan_score_stays_in_its_query():
+    from paper_2207_09682_amd import Context
+    rng = np.random.default_rng(3)
+    n, group = 700, 100
+    s = rng.normal(size=n).astype(np.float32); rel = rng.integers(0, 5, n).astype(np.float32)
+    eg, eh = oracle.lambdarank_gradients(s, rel, group)
+    s[250] = np.nan; s[503] = -np.float32(np.nan)
+    g, h = (a.cpu().numpy() for a in Context(n, 4, 16).lambdarank_gradients(torch.from_numpy(s).cuda(), torch.from_numpy(rel).cuda(), group))
+    bad = np.isin(np.arange(n) // group, (2, 5))
+    assert np.isnan(g[bad]).all() and np.isnan(h[bad]).all()
+    assert np.allclose(g[~bad], eg[~bad], rtol=1e-6, atol=1e-7) and np.allclose(h[~bad], eh[~bad], rtol=1e-6, atol=1e-7)
