@@ -485,12 +485,14 @@ int qgbdt_find_best_splits_static(qgbdt_ctx* ctx, const int64_t* hist, int32_t n
     if (n_hists < 0) return set_error(ctx, QGBDT_E_INVALID_ARG, "n_hists=%d", n_hists);
     if (!ctx->static_scratch) return set_error(ctx, QGBDT_E_UNSUPPORTED, "no fixed scratch on device %d", ctx->device);
     // the array holds: the item count [256 bytes], one pair record per two histograms, one candidate per (histogram, tile
-    // of features); the limit is the stated one, 48 + 24 * n_features bytes per histogram, which is never less
-    static_assert(sizeof(ScanPair) / 2 + sizeof(FeatCand) <= 48 + 24, "a histogram of one feature fits the stated limit");
+    // of features).  The limit is the stated one, 48 bytes per histogram (to whole 256 bytes) and 24 per feature of it,
+    // which is never less: up to four histograms the records of either size end in the same 256 bytes, from five on
+    // 80 bytes per pair are no more than 48 per histogram, and there are no more tiles than features.
+    static_assert(sizeof(ScanPair) <= 80 && sizeof(FeatCand) == 24, "the records fit the stated limit");
     const size_t F = (size_t)ctx->shape.n_features;
     const size_t pairs_off = 256;
     const size_t cand_off = (pairs_off + ((size_t)n_hists + 1) / 2 * sizeof(ScanPair) + 255) & ~(size_t)255;
-    const size_t need = 512 + (size_t)n_hists * (48 + 24 * F);
+    const size_t need = ((pairs_off + (size_t)n_hists * 48 + 255) & ~(size_t)255) + (size_t)n_hists * F * 24;
     if (need > STATIC_SCRATCH_BYTES)
         return set_error(ctx, QGBDT_E_INVALID_ARG,
                          "n_hists=%d x %d features needs %zu bytes of scratch, the fixed array holds %zu (at most %zu histograms of this shape)",

@@ -49,3 +49,20 @@ def test_static_split_search_equals_the_workspace_one(F, nb):
         sta.find_best_splits_static(hist1, stats1.expand(too_many, 3).contiguous(), delta,
                                     torch.empty((too_many, 56), dtype=torch.uint8, device="cuda"))
     assert "scratch" in str(ei.value)
+
+
+@pytest.mark.parametrize("F,most", [(25, 6472), (16, 9708), (28, 5824)])
+def test_static_split_search_at_the_limit_of_its_array(F, most):
+    """The largest n with roundup(256 + 48 n, 256) + 24 n F <= 4 MiB is served, one more is refused."""
+    from paper_2207_09682_amd import Context, QgbdtError
+    nb, size = 4, lambda n: (256 + 48 * n + 255) // 256 * 256 + 24 * n * F
+    assert size(most) <= 4 << 20 < size(most + 1)
+    rng = np.random.default_rng(F)
+    ctx = Context(1000, F, nb, max_leaves=31)
+    delta = torch.tensor([0.25, 0.125], dtype=torch.float32, device="cuda")
+    hist, stats = _histograms(rng, most, F, nb, "cuda")
+    out = torch.zeros((most + 1, 56), dtype=torch.uint8, device="cuda")
+    got = ctx.find_best_splits_static(hist, stats, delta, out[:most], min_data_in_leaf=5)
+    assert torch.equal(got, ctx.find_best_splits(hist, stats, delta, min_data_in_leaf=5))
+    with pytest.raises(QgbdtError):
+        ctx.find_best_splits_static(hist, torch.cat([stats, stats[:1]]), delta, out, min_data_in_leaf=5)
