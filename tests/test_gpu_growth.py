@@ -160,3 +160,20 @@ def test_lambdarank_nan_score_stays_in_its_query():
     bad = np.isin(np.arange(n) // group, (2, 5))
     assert np.isnan(g[bad]).all() and np.isnan(h[bad]).all()
     assert np.allclose(g[~bad], eg[~bad], rtol=1e-6, atol=1e-7) and np.allclose(h[~bad], eh[~bad], rtol=1e-6, atol=1e-7)
+
+
+# tiles of 2048 rows, at most 512 segments of them: around one tile, around the size from which segments hold more than one, a slice
+# that starts at an odd row, a list in no order, everything to one side
+@pytest.mark.parametrize("N,begin,count,bin_", [(2100, 3, 2047, 30), (2100, 0, 2048, 30), (2100, 1, 2049, 30), (300, 7, 257, 0),
+                                                (2**20 + 9, 0, 2**20, 31), (2**20 + 9, 5, 2**20 + 1, 31), (2_100_003, 1, 2_100_001, 12),
+                                                (2_100_003, 0, 2_100_003, 63)])
+def test_partition_rows_tiles(N, begin, count, bin_):
+    from paper_2207_09682_amd import Context
+    rng = np.random.default_rng(count)
+    bins = rng.integers(0, 64, (N, 5)).astype(np.uint8)
+    idx = rng.permutation(N).astype(np.int32)
+    exp, nl = oracle.partition_rows(bins, idx, begin, count, 3, bin_)
+    didx = torch.from_numpy(idx.copy()).cuda()
+    got = Context(N, 5, 64, max_leaves=2).partition_rows(torch.from_numpy(bins).cuda(), didx, begin, count, 3, bin_)
+    assert int(got.item()) == nl
+    assert np.array_equal(didx.cpu().numpy(), exp)
