@@ -164,8 +164,8 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 //     wavefront replays the selection split by split (a bit per open leaf at its rank, the first set bit is next;
 //     0.25 us per split).
 //  3. All threads write the outputs of the committed splits.
-//  4. The batch is chosen with popcounts over the masks: open leaves that are not expanded (class 0), then children of
-//     expanded open leaves (class 1; one level ahead only: a node's rows outlive the expansion of its children but
+//  4. The batch is chosen with popcounts over the masks: the leaf the selection stopped at, the other open leaves that are
+//     not expanded (class 0), then children of expanded open leaves (class 1; one level ahead only: a node's rows outlive the expansion of its children but
 //     not that of its grandchildren), by rank, if fewer than the remaining number of splits have a larger gain.
 // Measured per launch against the version that kept all nodes in the order and replayed every split: 20.6 -> 10.1 us
 // (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
@@ -442,7 +442,9 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         return;
     }
     // One expansion is certain (the leaf the selection stopped at); expansions beyond those
-    // that the remaining certain ones will need may be spent on speculation.
+    // that the remaining certain ones will need may be spent on speculation.  That leaf is always in the batch, so the
+    // next call commits at least one split and `spare` stays >= 0: never more than max_expand nodes are expanded, which
+    // the tables of nodes and histograms are made for.
     const int remaining = budget - n_commit;
     const int spare = (max_expand - n_expanded0) - remaining;
     int want = 1 + (spare > 0 ? spare : 0);
@@ -475,9 +477,10 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         const unsigned long long bit = 1ull << (p & 63), below = bit - 1ull, pre = s_prefix[w];
         const unsigned long long cw = s_comm[w], c0 = s_c0[w], c1 = s_c1[w];
         uint32_t id = ids[p];
-        if ((c0 | c1) & bit) {  // order of the batch: class 0 by gain, then class 1 by gain
-            const int o = (c0 & bit) ? (int)(pre & 0xffffu) + __popcll(c0 & below)
-                                     : n0 + (int)((pre >> 16) & 0xffffu) + __popcll(c1 & below);
+        if ((c0 | c1) & bit) {  // order of the batch: the leaf the selection stopped at, class 0 by gain, class 1 by gain
+            int o = (c0 & bit) ? (int)(pre & 0xffffu) + __popcll(c0 & below)
+                               : n0 + (int)((pre >> 16) & 0xffffu) + __popcll(c1 & below);
+            if (c0 & bit) o = p == stop ? 0 : p < stop ? o + 1 : o;  // (leaves of equal gain may be in front of it by rank)
             if (o < n_batch) {
                 chosen[o] = (uint16_t)p;
                 id = (id & 0xffffu) | ((uint32_t)(n_nodes + 2 * o) << 16);

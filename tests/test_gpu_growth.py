@@ -41,6 +41,24 @@ def test_equal_gains_take_the_lowest_leaf(N, F, nb, L):
     _check(t, e, N)
 
 
+def test_tied_leaf_the_selection_stops_at_is_expanded_first():
+    # Four blocks of 2 m rows, split by feature 0 (gain 2.25 m, in units of delta_g^2), then by feature 1 (4.5 m on the right,
+    # 2 m on the left); two of the four leaves have a last split by feature 2, of gain m exactly.  The one on the right comes
+    # first by node number, the one on the left by leaf id: the fifth leaf is the left one's, and nothing else is expanded.
+    m, gl = 64, [(3, 1), (0, 0), (-3, -1), (1, 1)]       # left: 2 +- 1 and 0, right: -2 +- 1 and 1
+    bins = np.array([[b >> 1, b & 1, k, 0] for b in range(4) for k in range(2) for _ in range(m)], np.uint8)
+    g = np.array([gl[b][k] for b in range(4) for k in range(2) for _ in range(m)], np.float32) * 0.25   # delta_g = 1/4
+    h = np.ones(len(g), np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(len(g), 4, 4, max_leaves=5)
+    t = ctx.grow_tree(torch.from_numpy(bins).cuda(), torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 3, 0, 5, 0, 5,
+                      min_data_in_leaf=5, rounding=1)
+    e = oracle.grow_tree(bins, 4, g, h, 3, 0, 5, 0, 5, min_data=5, rounding=1)
+    assert e.split_gain.tolist() == [2.25 * m / 16, 4.5 * m / 16, 2.0 * m / 16, m / 16] and e.split_leaf.tolist() == [0, 1, 0, 0]
+    _check(t, e, len(g))
+    assert ctx.tree_stats() == (3, 4, 4, 9)   # rounds, nodes expanded, splits, nodes
+
+
 # both sides of the lines at which the partition takes other segments or sums its counts in two levels, ragged ends
 @pytest.mark.parametrize("N,F,L,layout", [(511, 4, 6, 1), (262_144, 5, 63, 1), (262_145, 5, 63, 2), (262_147, 16, 40, 3),
                                           (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3)])
