@@ -46,8 +46,11 @@ __global__ __launch_bounds__(256) void logistic_grad_kernel(const float* __restr
 //    one exp per document, and t serves both derivatives: g takes F_x w t, h takes F_k F_j w t^2 (F_k after the loop);
 //  * four pairs share one reciprocal, that of the product of their sums: the hardware's estimate and one third-order
 //    step cost 7 instruction times, shared by four, and the products 9 (15 instruction times per pair
-//    in all, 26 before).  The product of four sums must stay finite and normal: queries with a score range of 340 or
-//    more, or gains beyond 1e100, take the direct form;
+//    in all, 26 before).  The product of four sums, and t^2 times a weight, must stay finite and normal: queries with a
+//    score range of 340 or more, or gains beyond 1e100, take one reciprocal per pair and the factors F_a t and F_b t
+//    themselves, which lie between 0 and 1 (2 M rows, queries of 100, scores in +-200: 407 us by the direct form, 157 us so;
+//    the four pairs' form takes 130); from 690 on exp(c - s) is no longer safe, and every pair takes its own exp and
+//    division (the direct form);
 //  * ranks are counted over 64-bit keys (order of the value, then of the position): one comparison and one add-with-
 //    carry per partner and rank instead of two comparisons in fp64, one of positions and the logic between them;
 //  * discounts come from a table made once per workgroup (log2 and a division per rank instead of two per document).
@@ -157,6 +160,14 @@ __global__ __launch_bounds__(1024) void lambdarank_grad_kernel(const float* __re
             }
             for (; j < m; ++j) pair(gain[at + j], disc[at + j], fac[at + j], recip(fk + fac[at + j]));
             H *= fk;
+        } else if ((smax - smin) < 690.0) {
+#pragma unroll 2
+            for (int j = 0; j < m; ++j) {
+                const double fj = fac[at + j], t = recip(fk + fj), a = fk * t, b = fj * t;
+                const double dg = gk - gain[at + j], u = dg * fabs(dk - disc[at + j]);
+                G = fma(-(dg > 0.0 ? a : b), u, G);
+                H = fma(a * b, fabs(u), H);
+            }
         } else {
             const double sd = (double)sk;
             for (int j = 0; j < m; ++j) {

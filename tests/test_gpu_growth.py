@@ -167,6 +167,28 @@ def test_lambdarank_group_sizes(n, group):
     assert (np.abs(h - eh) <= tol * np.abs(eh) + group * 2.0**-43 * top[q]).all()
 
 
+# score ranges and gains on both sides of the lines between the three forms of a pair (340, 690; 1e100, that is grade 332),
+# queries whose last pairs are not four, one and several queries per workgroup
+@pytest.mark.parametrize("group", [2, 37, 100, 150, 1023])
+def test_lambdarank_forms_of_a_pair(group):
+    from paper_2207_09682_amd import Context
+    rng = np.random.default_rng(group)
+    widths = [339.9, 340.1, 500.0, 689.9, 690.1, 2000.0, 1.0, 1.0, 500.0]
+    grades = [4, 4, 4, 4, 4, 4, 331, 333, 1000]
+    s = np.empty((len(widths), group), np.float32); rel = np.empty((len(widths), group), np.float32)
+    for i, (w, top) in enumerate(zip(widths, grades)):
+        s[i] = rng.uniform(-w / 2, w / 2, group); s[i, 0] = -w / 2; s[i, -1] = w / 2
+        rel[i] = rng.integers(0, 5, group); rel[i, 0] = top; rel[i, -1] = 0
+    s, rel = s.ravel(), rel.ravel()
+    g, h = (a.cpu().numpy() for a in Context(len(s), 4, 16).lambdarank_gradients(torch.from_numpy(s).cuda(), torch.from_numpy(rel).cuda(), group))
+    eg, eh = oracle.lambdarank_gradients(s, rel, group)
+    # as for the group sizes above; exp of |x| <= 345 here, and the largest magnitude of the query is that of its sums' terms
+    top = np.repeat(np.abs(eg).reshape(-1, group).max(axis=1), group); tol = 2.0**-23
+    assert (top > 0).all()
+    assert (np.abs(g - eg) <= tol * np.abs(eg) + group * 2.0**-42 * top).all()
+    assert (np.abs(h - eh) <= tol * np.abs(eh) + group * 2.0**-42 * top).all()
+
+
 def test_lambdarank_nan_score_stays_in_its_query():
     from paper_2207_09682_amd import Context
     rng = np.random.default_rng(3)
