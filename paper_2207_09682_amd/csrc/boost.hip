@@ -205,10 +205,14 @@ int launch_lambdarank_gradients(qgbdt_ctx* ctx, const float* score, const float*
     const int64_t n_queries = (n + group - 1) / group;
     const int queries = rank_queries(n_queries, group);
     const int threads = (queries * group + 63) / 64 * 64;
-    const int64_t batches = (n_queries + queries - 1) / queries;
     const size_t lds = sizeof(double) * (6 * (size_t)queries * rank_pitch(group) + (size_t)group);
-    hipLaunchKernelGGL(lambdarank_grad_kernel, dim3((unsigned)batches), dim3(threads), lds, ctx->stream,
-                       score, label, n, group, queries, g, h);
+    // a launch holds fewer than 2^32 work-items (queries of one row fill half of a wavefront): 2^31 at most, then the next one
+    const int64_t per_batch = (int64_t)queries * group, most = ((int64_t)1 << 31) / threads * per_batch;
+    for (int64_t first = 0; first < n; first += most) {
+        const int64_t rows = n - first < most ? n - first : most;
+        hipLaunchKernelGGL(lambdarank_grad_kernel, dim3((unsigned)((rows + per_batch - 1) / per_batch)), dim3(threads), lds,
+                           ctx->stream, score + first, label + first, rows, group, queries, g + first, h + first);
+    }
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

@@ -189,6 +189,32 @@ def test_lambdarank_forms_of_a_pair(group):
     assert (np.abs(h - eh) <= tol * np.abs(eh) + group * 2.0**-42 * top).all()
 
 
+def test_lambdarank_with_more_work_items_than_a_launch_may_have():
+    # queries of one row leave half of the lanes idle: 2^32 work-items for the largest number of rows; with three rows per
+    # query the second launch begins inside the rows and not at their last workgroup
+    from paper_2207_09682_amd import Context
+    n, period = 2**31 - 1, 3 * 2**16
+    ctx = Context(n, 1, 2, max_leaves=1, workspace_flags=0)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(1)
+    s0 = torch.randn(period, generator=gen, device="cuda"); r0 = torch.randint(0, 5, (period,), generator=gen, device="cuda").float()
+    times = n // period + 1
+    s, r = s0.repeat(times)[:n], r0.repeat(times)[:n]
+    for group in (1, 3):
+        eg, eh = ctx.lambdarank_gradients(s0, r0, group)
+        assert group == 1 or float(eg.abs().max()) > 0
+        g = torch.full((n,), float("nan"), device="cuda"); h = torch.full((n,), float("nan"), device="cuda")
+        ctx._chk(ctx.lib.qgbdt_lambdarank_gradients(ctx._h, s.data_ptr(), r.data_ptr(), n, group, g.data_ptr(), h.data_ptr()))
+        for got, exp in ((g, eg), (h, eh)):
+            whole = (times - 1) * period
+            assert bool((got[:whole].view(times - 1, period) == exp).all())
+            rest = (n - whole) // 3 * 3                     # (the last query may be a part of one)
+            assert torch.equal(got[whole:whole + rest], exp[:rest]) and bool(got[whole + rest:].isfinite().all())
+        del g, h, got
+    ctx.close()
+    del s, r
+    torch.cuda.empty_cache()
+
+
 def test_lambdarank_nan_score_stays_in_its_query():
     from paper_2207_09682_amd import Context
     rng = np.random.default_rng(3)
