@@ -256,6 +256,35 @@ struct qgbdt_ctx {
 
 namespace qgbdt {
 
+__device__ __forceinline__ long long readlane64(long long v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)v >> 32), lane);
+    return (long long)(((unsigned long long)hi << 32) | lo);
+}
+
+// Sum over the 64 lanes with DPP moves (no LDS traffic); the result is uniform.
+__device__ __forceinline__ int wave_sum(int v) {
+#define QG_DPP_ADD(x, ctrl, rmask) ((x) + __builtin_amdgcn_update_dpp(0, (x), ctrl, rmask, 0xf, false))
+    v = QG_DPP_ADD(v, 0x111, 0xf);  // row_shr:1
+    v = QG_DPP_ADD(v, 0x112, 0xf);  // row_shr:2
+    v = QG_DPP_ADD(v, 0x114, 0xf);  // row_shr:4
+    v = QG_DPP_ADD(v, 0x118, 0xf);  // row_shr:8: lane 15 of a row holds the row's sum, lane k the sum up to k
+    v = QG_DPP_ADD(v, 0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+    v = QG_DPP_ADD(v, 0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+    return __builtin_amdgcn_readlane(v, 63);
+}
+// Inclusive prefix sum over the lanes, the same way.
+__device__ __forceinline__ int wave_prefix(int v) {
+    v = QG_DPP_ADD(v, 0x111, 0xf);
+    v = QG_DPP_ADD(v, 0x112, 0xf);
+    v = QG_DPP_ADD(v, 0x114, 0xf);
+    v = QG_DPP_ADD(v, 0x118, 0xf);
+    v = QG_DPP_ADD(v, 0x142, 0xa);
+    v = QG_DPP_ADD(v, 0x143, 0xc);
+    return v;
+#undef QG_DPP_ADD
+}
+
 constexpr int PART_GROUPS = 512;
 // Passes over finished leaves gather and update 4 to 8 bytes per row, leaf by leaf, in places that lie about a cache line apart
 // or further.  Their work is cut into parts of the row order (a leaf's list ascends), a multiple of 8 of them, and the
@@ -348,8 +377,6 @@ int prepare_hist_kernels(qgbdt_ctx* ctx);  // once per context: dynamic-LDS limi
 int prepare_tree_kernels(qgbdt_ctx* ctx);
 // !ordered: row ids and, with rows.gh_pos, packed gradients; `plan`: of the histogram launch that follows
 int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered, const HistPlan& plan);
-// leaves -> units of the passes over their rows (ctx->refit_units); tree growth lays them out in its last kernel
-int launch_layout_leaves(qgbdt_ctx* ctx, const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves);
 int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* row_idx, const int64_t* leaf_begin,
                  const int64_t* leaf_count, int n_leaves, double* value_out);
 // tree growth (leaves laid out): the row lists to the caller's, and the leaf values

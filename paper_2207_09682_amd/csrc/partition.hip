@@ -290,29 +290,6 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
     }
 }
 
-// Sum over the 64 lanes with DPP moves (no LDS traffic); the result is uniform.
-__device__ __forceinline__ int wave_sum(int v) {
-#define QG_DPP_ADD(x, ctrl, rmask) ((x) + __builtin_amdgcn_update_dpp(0, (x), ctrl, rmask, 0xf, false))
-    v = QG_DPP_ADD(v, 0x111, 0xf);  // row_shr:1
-    v = QG_DPP_ADD(v, 0x112, 0xf);  // row_shr:2
-    v = QG_DPP_ADD(v, 0x114, 0xf);  // row_shr:4
-    v = QG_DPP_ADD(v, 0x118, 0xf);  // row_shr:8: lane 15 of a row holds the row's sum, lane k the sum up to k
-    v = QG_DPP_ADD(v, 0x142, 0xa);  // row_bcast:15 into rows 1 and 3
-    v = QG_DPP_ADD(v, 0x143, 0xc);  // row_bcast:31 into rows 2 and 3
-    return __builtin_amdgcn_readlane(v, 63);
-}
-// Inclusive prefix sum over the lanes, the same way.
-__device__ __forceinline__ int wave_prefix(int v) {
-    v = QG_DPP_ADD(v, 0x111, 0xf);
-    v = QG_DPP_ADD(v, 0x112, 0xf);
-    v = QG_DPP_ADD(v, 0x114, 0xf);
-    v = QG_DPP_ADD(v, 0x118, 0xf);
-    v = QG_DPP_ADD(v, 0x142, 0xa);
-    v = QG_DPP_ADD(v, 0x143, 0xc);
-    return v;
-#undef QG_DPP_ADD
-}
-
 // The children of every expanded node and the tables of the histogram and scan kernels, by one workgroup of 256 threads
 // while the others move rows: it needs nothing of them but the left counts that the count kernel left behind.
 __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __restrict__ batch,

@@ -1,42 +1,52 @@
 // Leaf-value refit with the original FP gradients (Sec. 3 eq. (leaf), Sec. 4.2):
 // one gather pass over g, h through the leaf-ordered row list, fp64 sums in a
-// fixed reduction order (so repeated runs give identical bits); and the layout of
-// finished leaves that it shares with the score update.
+// fixed reduction order (so repeated runs give identical bits); and the score update,
+// which shares the layout of finished leaves with it.
+#include <type_traits>
+
 #include "refit_device.h"
 
 namespace qgbdt {
 
-__global__ __launch_bounds__(1024) void layout_leaves_kernel(const int64_t* __restrict__ leaf_begin,
-                                                             const int64_t* __restrict__ leaf_count, int n_leaves,
-                                                             int parts, int extra, RefitUnit* units, int2* leaves,
-                                                             int max_leaves) {
-    __shared__ LeafLayout s;
-    for (int l = threadIdx.x; l < n_leaves; l += blockDim.x) {
-        s.begin[l] = leaf_begin[l]; s.count[l] = leaf_count[l]; s.buf[l] = 0;
-    }
-    __syncthreads();
-    layout_leaves(s, n_leaves, max_leaves, parts, extra, units, leaves);
-}
-
 // Sums of (g, h) over the pieces of all leaves; one wavefront per unit, four rows per lane in flight.
-// TREE: the rows come from the index buffer in which the leaf ended up and go to the caller's list on the way, and (g, h)
-// are read as one 8-byte pair from the quantizer's interleaved copy; otherwise row_idx is read and nothing is written.
+// After a tree the rows come from the index buffer in which the leaf ended up and go to the caller's list on the way, and (g, h)
+// are read as one 8-byte pair from the quantizer's interleaved copy; otherwise the caller's lists are read.
 // Bound by the row lists and pairs once per line: see REFIT_EXTRA for the order of the units.
-template <bool TREE>
-__global__ __launch_bounds__(256) void refit_partial_kernel(const float* __restrict__ g, const float* __restrict__ h,
-                                                            const float2* __restrict__ pairs, IdxSet idxs,
-                                                            const int32_t* __restrict__ row_idx, int32_t* __restrict__ out,
-                                                            const RefitUnit* __restrict__ units,
-                                                            const int32_t* __restrict__ n_units, int parts, int blocks_per_part,
-                                                            double* __restrict__ partial) {
+struct RefitTree {  // the tree that has just been grown
+    const float2* pairs;
+    IdxSet idxs;
+    int32_t* out;
+    const RefitUnit* units;
+    const int32_t* n_units;
+};
+struct RefitList {  // leaves that the caller lists
+    const float *g, *h;
+    const int32_t* row_idx;
+    LeafList list;
+    int2* leaves;  // their units, for the kernel that adds the pieces up
+};
+template <class SRC>
+__global__ __launch_bounds__(256) void refit_partial_kernel(SRC src, int parts, int blocks_per_part, double* __restrict__ partial) {
+    constexpr bool TREE = std::is_same<SRC, RefitTree>::value;
     int part, u;
-    if (!refit_unit_of(n_units, blocks_per_part, part, u)) return;
-    const RefitUnit un = units[u];
+    refit_unit_of(blocks_per_part, part, u);
+    RefitUnit un;
+    if constexpr (TREE) {
+        if (u >= *src.n_units) return;
+        un = src.units[u];
+    } else {
+        if (!find_unit(src.list, parts, u, un)) return;
+    }
     const int lane = threadIdx.x & 63;
     const int64_t piece = (int64_t)part * un.n + (u - un.first);
     const int64_t a = min(un.count, piece * un.piece_rows), b = min(un.count, a + un.piece_rows);
     const bool identity = TREE && un.buf == BUF_ORIGINAL;  // a tree that is its root: the list was never stored
-    const int32_t* src = (TREE ? idxs.p[un.buf] : row_idx) + un.begin;
+    const int32_t* ids;
+    if constexpr (TREE) ids = src.idxs.p[un.buf] + un.begin;
+    else {
+        ids = src.row_idx + un.begin;
+        if (piece == 0 && lane == 0) src.leaves[un.leaf] = make_int2(un.first, un.n);
+    }
     double G = 0.0, H = 0.0;
     for (int64_t j0 = a; j0 < b; j0 += 256) {
         int32_t r[4];
@@ -44,15 +54,18 @@ __global__ __launch_bounds__(256) void refit_partial_kernel(const float* __restr
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t j = min(j0 + 64 * k + lane, b - 1);
-            r[k] = identity ? (int32_t)(un.begin + j) : src[j];
+            r[k] = identity ? (int32_t)(un.begin + j) : ids[j];
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = TREE ? pairs[r[k]] : make_float2(g[r[k]], h[r[k]]);
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (TREE) v[k] = src.pairs[r[k]];
+            else v[k] = make_float2(src.g[r[k]], src.h[r[k]]);
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t j = j0 + 64 * k + lane;
             if (j < b) {
-                if (TREE) out[un.begin + j] = r[k];
+                if constexpr (TREE) src.out[un.begin + j] = r[k];
                 G += (double)v[k].x;
                 H += (double)v[k].y;
             }
@@ -87,15 +100,19 @@ __global__ __launch_bounds__(256) void refit_final_kernel(const double* __restri
     }
 }
 
-// score[row] += (float)(lr * value[leaf]) for the rows of every leaf, units as above.
+// score[row] += (float)(lr * value[leaf]) for the rows of every leaf, units as above (TREE: those of the tree just grown).
+template <bool TREE>
 __global__ __launch_bounds__(256) void update_scores_kernel(float* __restrict__ score, const int32_t* __restrict__ row_idx,
                                                             const double* __restrict__ leaf_value,
-                                                            const RefitUnit* __restrict__ units,
-                                                            const int32_t* __restrict__ n_units, int blocks_per_part,
-                                                            double lr) {
+                                                            const RefitUnit* __restrict__ units, const int32_t* __restrict__ n_units,
+                                                            LeafList list, int parts, int blocks_per_part, double lr) {
     int part, u;
-    if (!refit_unit_of(n_units, blocks_per_part, part, u)) return;
-    const RefitUnit un = units[u];
+    refit_unit_of(blocks_per_part, part, u);
+    RefitUnit un;
+    if (TREE) {
+        if (u >= *n_units) return;
+        un = units[u];
+    } else if (!find_unit(list, parts, u, un)) return;
     const int lane = threadIdx.x & 63;
     const float d = (float)(lr * leaf_value[un.leaf]);
     const int64_t piece = (int64_t)part * un.n + (u - un.first);
@@ -126,22 +143,13 @@ static RefitGrid refit_grid(const qgbdt_ctx* ctx, int n_leaves) {
 }
 static const int32_t* units_in_use(const qgbdt_ctx* ctx) { return &ctx->refit_leaves[ctx->shape.max_leaves].x; }
 
-int launch_layout_leaves(qgbdt_ctx* ctx, const int64_t* leaf_begin, const int64_t* leaf_count, int n_leaves) {
-    hipLaunchKernelGGL(layout_leaves_kernel, dim3(1), dim3(1024), 0, ctx->stream, leaf_begin, leaf_count, n_leaves,
-                       refit_parts(ctx->shape.n_rows), refit_extra(ctx->shape.n_rows), ctx->refit_units, ctx->refit_leaves,
-                       ctx->shape.max_leaves);
-    QG_HIP(ctx, hipGetLastError());
-    return QGBDT_OK;
-}
-
 int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* row_idx, const int64_t* leaf_begin,
                  const int64_t* leaf_count, int n_leaves, double* value_out) {
     if (n_leaves <= 0) return QGBDT_OK;
-    int rc = launch_layout_leaves(ctx, leaf_begin, leaf_count, n_leaves);
-    if (rc != QGBDT_OK) return rc;
     const RefitGrid rg = refit_grid(ctx, n_leaves);
-    hipLaunchKernelGGL(refit_partial_kernel<false>, rg.grid(), dim3(256), 0, ctx->stream, g, h, nullptr, IdxSet{}, row_idx,
-                       nullptr, ctx->refit_units, units_in_use(ctx), rg.parts, rg.blocks_per_part, ctx->refit_partial);
+    const RefitList src{g, h, row_idx, {leaf_begin, leaf_count, n_leaves, refit_extra(ctx->shape.n_rows)}, ctx->refit_leaves};
+    hipLaunchKernelGGL(refit_partial_kernel<RefitList>, rg.grid(), dim3(256), 0, ctx->stream, src, rg.parts, rg.blocks_per_part,
+                       ctx->refit_partial);
     hipLaunchKernelGGL(refit_final_kernel, dim3(n_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial, rg.parts,
                        ctx->refit_leaves, nullptr, value_out);
     QG_HIP(ctx, hipGetLastError());
@@ -150,8 +158,9 @@ int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* 
 
 int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out) {
     const RefitGrid rg = refit_grid(ctx, ctx->shape.max_leaves);
-    hipLaunchKernelGGL(refit_partial_kernel<true>, rg.grid(), dim3(256), 0, ctx->stream, nullptr, nullptr, ctx->ghf, idx, nullptr,
-                       row_idx_out, ctx->refit_units, units_in_use(ctx), rg.parts, rg.blocks_per_part, ctx->refit_partial);
+    const RefitTree src{ctx->ghf, idx, row_idx_out, ctx->refit_units, units_in_use(ctx)};
+    hipLaunchKernelGGL(refit_partial_kernel<RefitTree>, rg.grid(), dim3(256), 0, ctx->stream, src, rg.parts, rg.blocks_per_part,
+                       ctx->refit_partial);
     hipLaunchKernelGGL(refit_final_kernel, dim3(ctx->shape.max_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial,
                        rg.parts, ctx->refit_leaves, n_leaves_dev, value_out);
     QG_HIP(ctx, hipGetLastError());
@@ -161,13 +170,14 @@ int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, int32_t* row_idx_out,
 int launch_update_scores(qgbdt_ctx* ctx, float* score, const int32_t* row_idx, const int64_t* leaf_begin,
                          const int64_t* leaf_count, const double* leaf_value, int n_leaves, bool laid_out, double lr) {
     if (n_leaves <= 0) return QGBDT_OK;
-    if (!laid_out) {
-        const int rc = launch_layout_leaves(ctx, leaf_begin, leaf_count, n_leaves);
-        if (rc != QGBDT_OK) return rc;
-    }
     const RefitGrid rg = refit_grid(ctx, n_leaves);
-    hipLaunchKernelGGL(update_scores_kernel, rg.grid(), dim3(256), 0, ctx->stream, score, row_idx, leaf_value,
-                       ctx->refit_units, units_in_use(ctx), rg.blocks_per_part, lr);
+    if (laid_out)
+        hipLaunchKernelGGL(update_scores_kernel<true>, rg.grid(), dim3(256), 0, ctx->stream, score, row_idx, leaf_value,
+                           ctx->refit_units, units_in_use(ctx), LeafList{}, rg.parts, rg.blocks_per_part, lr);
+    else
+        hipLaunchKernelGGL(update_scores_kernel<false>, rg.grid(), dim3(256), 0, ctx->stream, score, row_idx, leaf_value, nullptr,
+                           nullptr, LeafList{leaf_begin, leaf_count, n_leaves, refit_extra(ctx->shape.n_rows)}, rg.parts,
+                           rg.blocks_per_part, lr);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

@@ -19,12 +19,6 @@ struct ScanPair {
     qgbdt_leafstat stat[2];  // totals of a, b
 };
 
-__device__ __forceinline__ long long readlane64(long long v, int lane) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)v >> 32), lane);
-    return (long long)(((unsigned long long)hi << 32) | lo);
-}
-
 __device__ __forceinline__ int64_t packed_g(int64_t w) { return w >> 32; }
 __device__ __forceinline__ int64_t packed_h(int64_t w) { return w & 0xffffffffLL; }
 

@@ -141,6 +141,25 @@ def test_refit_and_update_over_leaf_layouts(N, counts):
     assert np.array_equal(d.cpu().numpy(), score + (0.1 * value).astype(np.float32)[owner])
 
 
+# leaves on both sides of the 64 that a wavefront looks through at a time, the most leaves, lists that share rows (their counts
+# add up to more than the matrix has), empty leaves in front, at the end and between
+@pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 128, 129, 320, 658])
+@pytest.mark.parametrize("N", [900, 40_001])
+def test_refit_over_lists_that_share_rows(N, L):
+    rng = np.random.default_rng(N + L)
+    g = rng.normal(size=N).astype(np.float32); h = rng.uniform(0.1, 0.25, N).astype(np.float32)
+    count = rng.integers(0, N // 2, L) * (rng.random(L) < 0.7); count[L // 2] = N
+    begin = np.array([rng.integers(0, N - c + 1) for c in count])
+    rows = rng.permutation(N).astype(np.int32)
+    from paper_2207_09682_amd import Context
+    got = Context(N, 4, 4, max_leaves=L).refit_leaves(*(torch.from_numpy(a).cuda() for a in (g, h, rows, begin, count))).cpu().numpy()
+    for l in range(L):
+        r = rows[begin[l]:begin[l] + count[l]]
+        G, H, A = (float(a[r].astype(np.float64).sum()) for a in (g, h, np.abs(g)))
+        exp = -G / H if count[l] else 0.0
+        assert abs(got[l] - exp) <= 2.0**-52 * count[l] * (A / H + abs(exp)) if count[l] else got[l] == 0.0, l  # bound as above
+
+
 # one and several queries per workgroup, ragged last queries, group sizes around multiples of a wavefront and of the four
 # pairs that share a reciprocal, and the largest
 @pytest.mark.parametrize("n,group", [(5, 1), (7, 3), (131, 2), (1000, 5), (333, 20), (2001, 63), (2000, 64), (2600, 65), (3000, 127),
