@@ -81,6 +81,32 @@ def test_partition_segments(N, F, L, layout):
         _check(t, e, N)
 
 
+# both sides of the 256 candidates per histogram (a tile has 2 features above 256 bins, 16 for such wide 8-bit matrices) up to
+# which the plan kernel reduces them itself; above, a launch of its own does; columns that repeat tie between far tiles
+@pytest.mark.parametrize("F,nb,bb", [(512, 300, 2), (513, 300, 2), (1000, 300, 2), (4096, 12, 1), (4097, 12, 1)])
+def test_growth_with_candidates_reduced_apart(F, nb, bb):
+    N, L = 3001, 31
+    rng = np.random.default_rng(F)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint16 if bb == 2 else np.uint8)
+    bins[:, F - 1] = bins[:, 3]; bins[:, F // 2] = bins[:, F - 2]
+    x = bins[:, [3, F - 2, 40, F // 3]].astype(np.float64) / nb - 0.5
+    g = (x[:, 0] + 1.5 * x[:, 1] * (x[:, 0] > 0) + 2 * x[:, 2] * x[:, 3] + 0.1 * rng.normal(size=N)).astype(np.float32)
+    h = rng.uniform(0.1, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L, bin_bytes=bb)
+    dbins = torch.from_numpy(bins).cuda()
+    e = oracle.grow_tree(bins, nb, g, h, 3, 3, 5, 0, L, min_data=20)
+    used = e.split_feature[: e.n_leaves - 1]
+    assert e.n_leaves > 8 and F - 1 not in used and {3, F // 2} <= set(used.tolist())
+    for bound in (False, True):
+        ctx.bind_bins(dbins if bound else None)
+        for _ in range(2):  # the second tree with the first one's number of rounds
+            t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 3, 3, 5, 0, L, min_data_in_leaf=20)
+            _check(t, e, N)
+        assert np.array_equal(t.split_gain.cpu().numpy()[: e.n_leaves - 1], e.split_gain[: e.n_leaves - 1])
+    assert ctx.tree_stats()[0] > 2
+
+
 def _split_cases():
     # bins and features around the edges of the search's tiles and of the bins a thread takes
     return [(F, nb) for F, nb in [(1, 2), (3, 64), (4, 65), (5, 63), (7, 128), (29, 129), (63, 255), (64, 256), (66, 100), (255, 9),
