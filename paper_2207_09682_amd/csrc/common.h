@@ -88,8 +88,6 @@ struct HistEntry {
 struct PartWork {
     int64_t begin, count;
     int32_t feature, bin;
-    int32_t src_buf;    // which index buffer holds the slice; the result goes to the other one
-    int32_t zero_slot;  // unused by the stand-alone call
 };
 
 struct HistPlan {
@@ -108,7 +106,6 @@ struct HistPlan {
     int32_t hshift;      // bits of the hessian field of a 32-bit local word: 16, or the split that takes more rows
     int32_t flat_lanes;  // > 0: contiguous slices may use the flat 16-byte-load kernel with this many lanes
     int32_t flat_rows;   // rows per wavefront iteration of that kernel
-    int32_t flat_unroll;
     int32_t max_items;    // most work items (row groups) of one launch = slots of the partial-histogram buffer
     int32_t slot_bytes;   // bytes of one (item, tile) slot: the tile's local bins, padded to 16 bytes
     int32_t single_rows;  // a group of at most this many rows is accumulated in one chunk by every kernel variant
@@ -364,8 +361,6 @@ int launch_reduce_items(qgbdt_ctx* ctx, const FeatCand* cand, const ScanPair* pa
 int run_find_best_splits(qgbdt_ctx* ctx, const int64_t* hist, int n_hists, const qgbdt_leafstat* stats,
                          const float* delta, int min_data, double min_sum_hess, qgbdt_split* out, int cap,
                          ScanPair* pairs, FeatCand* cand, int32_t* n_items);
-int launch_partition_work(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* buf0, int32_t* buf1, const PartWork* work,
-                          int64_t* n_left_out, int64_t max_count);
 int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, int64_t begin, int64_t count,
                        int feature, int bin, int64_t* n_left_out);
 int launch_batch_partition_count(qgbdt_ctx* ctx, const RowSource& rows, const uint8_t* bins_t, bool ordered);

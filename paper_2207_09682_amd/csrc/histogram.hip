@@ -989,7 +989,6 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
         for (int l = 64; l >= 32; --l)
             if ((16 * l) % F == 0) { p.flat_lanes = l; p.flat_rows = 16 * l / F; break; }
     }
-    p.flat_unroll = 2;
     p.slot_bytes = (p.lds_bytes + 15) & ~15;
     p.max_items = 4 * p.max_groups;
     if (p.max_items < 2 * s.max_leaves + 64) p.max_items = 2 * s.max_leaves + 64;
@@ -1129,21 +1128,12 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     bool wide_ok = true;  // 16-byte loads need 16-byte aligned matrices (F is a multiple of 16 in that mode)
     for (int b = 0; b < 4; ++b) wide_ok = wide_ok && (((uintptr_t)rows.bins[b] & 15) == 0);
     if (flat) {
-#define QG_LAUNCH_FLAT(W_, U_)                                                                                   \
-    hipLaunchKernelGGL((hist_flat_kernel<W_, U_, false>), grid, block, plan.lds_bytes, ctx->stream, rows, entries, \
+#define QG_LAUNCH_FLAT(W_, TWO_)                                                                                  \
+    hipLaunchKernelGGL((hist_flat_kernel<W_, 2, TWO_>), grid, block, plan.lds_bytes, ctx->stream, rows, entries,  \
                        table_counts, hist_base, partials, F, nb, plan, step)
-        if (plan.two_level) {
-            hipLaunchKernelGGL((hist_flat_kernel<16, 2, true>), grid, block, plan.lds_bytes, ctx->stream, rows, entries,
-                               table_counts, hist_base, partials, F, nb, plan, step);
-        } else if (plan.acc_width == 16) {
-            if (plan.flat_unroll >= 4) QG_LAUNCH_FLAT(16, 4);
-            else if (plan.flat_unroll >= 2) QG_LAUNCH_FLAT(16, 2);
-            else QG_LAUNCH_FLAT(16, 1);
-        } else {
-            if (plan.flat_unroll >= 4) QG_LAUNCH_FLAT(32, 4);
-            else if (plan.flat_unroll >= 2) QG_LAUNCH_FLAT(32, 2);
-            else QG_LAUNCH_FLAT(32, 1);
-        }
+        if (plan.two_level) QG_LAUNCH_FLAT(16, true);
+        else if (plan.acc_width == 16) QG_LAUNCH_FLAT(16, false);
+        else QG_LAUNCH_FLAT(32, false);
 #undef QG_LAUNCH_FLAT
     } else if (fast && plan.wide_v > 0 && wide_ok) {
 #define QG_LAUNCH_WIDE_S(W_, IDX_, V_, U_, S_)                                                                        \

@@ -22,7 +22,7 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t v) {
 
 __global__ void set_part_work_kernel(PartWork* w, int64_t begin, int64_t count, int feature, int bin) {
     if (threadIdx.x == 0) {
-        w->begin = begin; w->count = count; w->feature = feature; w->bin = bin; w->src_buf = 0; w->zero_slot = -1;
+        w->begin = begin; w->count = count; w->feature = feature; w->bin = bin;
     }
 }
 
@@ -37,23 +37,10 @@ __device__ __forceinline__ int bin_at(const uint8_t* __restrict__ bins, int64_t 
 constexpr int PART_ROWS = 8;
 
 __global__ __launch_bounds__(256) void part_count_kernel(const uint8_t* __restrict__ bins, int bb, int F,
-                                                         const int32_t* __restrict__ buf0,
-                                                         const int32_t* __restrict__ buf1,
+                                                         const int32_t* __restrict__ src,
                                                          const PartWork* __restrict__ work,
-                                                         uint8_t* __restrict__ flags, int64_t* __restrict__ counts,
-                                                         int64_t* hist_base, int64_t hist_words) {
+                                                         uint8_t* __restrict__ flags, int64_t* __restrict__ counts) {
     const PartWork wk = *work;
-    if (wk.count <= 0) {
-        if (threadIdx.x == 0) counts[blockIdx.x] = 0;
-        return;
-    }
-    if (wk.zero_slot >= 0) {  // clear the histogram the smaller child will be accumulated into
-        int64_t* z = hist_base + (int64_t)wk.zero_slot * hist_words;
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < hist_words;
-             i += (int64_t)gridDim.x * blockDim.x)
-            z[i] = 0;
-    }
-    const int32_t* src = wk.src_buf ? buf1 : buf0;
     const int64_t seg = segment_len(wk.count, gridDim.x);
     const int64_t sbegin = (int64_t)blockIdx.x * seg;
     const int64_t send = min(wk.count, sbegin + seg);
@@ -82,15 +69,11 @@ __global__ __launch_bounds__(256) void part_count_kernel(const uint8_t* __restri
     if (threadIdx.x == 0) counts[blockIdx.x] = (int64_t)sc[0] + sc[1] + sc[2] + sc[3];
 }
 
-__global__ __launch_bounds__(256) void part_scatter_kernel(const int32_t* __restrict__ buf0r,
-                                                           const int32_t* __restrict__ buf1r, int32_t* buf0w,
-                                                           int32_t* buf1w, const PartWork* __restrict__ work,
+__global__ __launch_bounds__(256) void part_scatter_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst,
+                                                           const PartWork* __restrict__ work,
                                                            const uint8_t* __restrict__ flags,
                                                            const int64_t* __restrict__ counts, int64_t* n_left_out) {
     const PartWork wk = *work;
-    if (wk.count <= 0) return;
-    const int32_t* src = wk.src_buf ? buf1r : buf0r;
-    int32_t* dst = wk.src_buf ? buf0w : buf1w;
     // left rows before this segment, and in total
     int64_t before = 0, total = 0;
     for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
@@ -156,22 +139,6 @@ __global__ void copy_i32_kernel(const int32_t* __restrict__ src, int32_t* __rest
         dst[begin + i] = src[begin + i];
 }
 
-int launch_partition_work(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* buf0, int32_t* buf1, const PartWork* work,
-                          int64_t* n_left_out, int64_t max_count) {
-    const int F = ctx->shape.n_features;
-    int64_t g = (max_count + 2047) / 2048;
-    if (g > PART_GROUPS) g = PART_GROUPS;
-    if (g < 1) g = 1;
-    const int64_t W = (int64_t)F * ctx->shape.n_bins;
-    hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, bins, ctx->shape.bin_bytes, F, buf0,
-                       buf1, work,
-                       ctx->flags, ctx->part_counts, ctx->hist_pool, W);
-    hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, buf0, buf1, buf0, buf1,
-                       work, ctx->flags, ctx->part_counts, n_left_out);
-    QG_HIP(ctx, hipGetLastError());
-    return QGBDT_OK;
-}
-
 // Stand-alone call: row_idx is reordered in place (through the context's spare buffer).
 int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, int64_t begin, int64_t count,
                        int feature, int bin, int64_t* n_left_out) {
@@ -182,8 +149,12 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
         QG_HIP(ctx, hipGetLastError());
         return QGBDT_OK;
     }
-    int rc = launch_partition_work(ctx, bins, row_idx, ctx->idx[0], ctx->pwork, n_left_out, count);
-    if (rc != QGBDT_OK) return rc;
+    int64_t g = (count + 2047) / 2048;
+    if (g > PART_GROUPS) g = PART_GROUPS;
+    hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, bins, ctx->shape.bin_bytes,
+                       ctx->shape.n_features, row_idx, ctx->pwork, ctx->flags, ctx->part_counts);
+    hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, row_idx, ctx->idx[0], ctx->pwork,
+                       ctx->flags, ctx->part_counts, n_left_out);
     int blocks = (int)((count + 255) / 256);
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(copy_i32_kernel, dim3(blocks), dim3(256), 0, ctx->stream, ctx->idx[0], row_idx, begin, count);
