@@ -139,6 +139,31 @@ def test_split_search_edges(F, nb):
                 assert all(got[i][k] == getattr(e, k) for k in ("bin", "GL", "HL", "GR", "HR", "cnt_left"))
 
 
+# numbers of pairs on both sides of the lines between a whole pair per XCD and tiles spread over all of them (1 pair of 271 and
+# 1000 features, 9 of 40 and 17 of 90; never from 32 on), numbers of tiles and shares that are not multiples of 8
+@pytest.mark.parametrize("F,nb", [(1000, 65), (271, 255), (90, 255), (40, 600)])
+def test_split_search_spread_over_xcds(F, nb):
+    from paper_2207_09682_amd import Context, binding
+    rng = np.random.default_rng(F)
+    most = 70
+    G = rng.integers(-300, 300, (most, nb, F)).astype(np.int64)
+    H = rng.integers(0, 400, (most, nb, F)).astype(np.int64)
+    tg = G.sum(axis=1).max(axis=1) + 10; th = H.sum(axis=1).max(axis=1) + 10
+    G[:, -1, :] += tg[:, None] - G.sum(axis=1)
+    H[:, -1, :] += th[:, None] - H.sum(axis=1)
+    rows = (th // 3 + 1).astype(np.int64)
+    hist = torch.from_numpy(((G << 32) + H).reshape(most, nb * F)).cuda()
+    stats = torch.from_numpy(np.stack([rows, tg, th], axis=1)).cuda()
+    d = np.array([0.25, 0.125], np.float32)
+    exp = [oracle.find_best_split(np.stack([G[i].T, H[i].T], axis=-1).copy(), int(rows[i]), int(tg[i]), int(th[i]), d[0], d[1], 20, 0.0)
+           for i in range(most)]
+    ctx = Context(1000, F, nb, max_leaves=most // 2, bin_bytes=2 if nb > 256 else 1)
+    for n in (1, 2, 3, 15, 16, 17, 32, 33, 62, 63, 64, most):
+        got = binding.unpack_splits(ctx.find_best_splits(hist[:n], stats[:n], torch.from_numpy(d).cuda()))
+        for i in range(n):
+            assert all(got[i][k] == getattr(exp[i], k) for k in ("feature", "gain", "bin", "GL", "HL", "GR", "HR", "cnt_left")), (n, i)
+
+
 # leaves as units of work: one leaf, empty leaves, one that holds nearly all rows, both sides of the lines at which the row
 # order is cut into more parts, and more rows than the largest number of parts is made for
 @pytest.mark.parametrize("N,counts", [(1, [1]), (7, [0, 7, 0]), (5000, [1, 4990, 0, 9]), (2**20, [2**19] * 2),
