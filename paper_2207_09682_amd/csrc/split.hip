@@ -113,16 +113,16 @@ __device__ __forceinline__ int wave_argmax(double gain, uint32_t code) {
     return win;
 }
 
-// Whether the tiles of a launch's pairs are spread over all XCDs, instead of a whole pair on one: when the fullest XCD would get
-// more wavefronts (SPREAD_WAVES) than its 32 compute units run at full speed side by side, while others get a pair less or
-// none.  From 32 pairs on the shares differ by a quarter at most.  Calls of the stand-alone search with whole pairs / spread:
-// one histogram of 2000 features, 255 bins 51.9 / 17.8 us, 17 of them 98 / 65 us, two of 900 features, 300 bins 47.7 / 16.0 us,
-// 18 of 2000 features, 63 bins 24.6 / 20.7 us; trees of 40 k x 2000, 255 bins 1057 / 854 us, of 400 k x 2000, 63 bins 1225 /
-// 1195 us.  With 64 in place of 256 the same within 1 %; with 1024 the 18 histograms take 24.7 us, 200 k x 136 865 instead of 833 us.
-constexpr int SPREAD_WAVES = 256;
-__host__ __device__ __forceinline__ bool scan_spread(int n_tiles, int waves_per_tile, int n_pairs) {
-    return n_pairs < 32 && (int64_t)n_tiles * waves_per_tile * ((n_pairs + 7) >> 3) > SPREAD_WAVES;
+// Matrices whose tiles are spread over all XCDs when there are few pairs, instead of a whole pair on one: those of which a single
+// pair has more wavefronts than the 32 compute units of an XCD run at full speed side by side.  From 32 pairs on the XCDs'
+// shares differ by a quarter at most.  Calls of the stand-alone search with whole pairs / spread: one histogram of 2000 features,
+// 255 bins 51.9 / 17.8 us, 17 of them 98 / 65 us, two of 900 features, 300 bins 47.7 / 16.0 us, 18 of 2000 features, 63 bins
+// 24.6 / 20.7 us; trees of 40 k x 2000, 255 bins 1057 / 854 us, of 400 k x 2000, 63 bins 1225 / 1195 us.  Below the line a launch
+// of a tree would lose 0.3 to 0.6 us to the second order of the work and gain nothing (464 k x 90, 2 M x 40 of 600 bins).
+__host__ __device__ __forceinline__ bool scan_spread(int n_tiles, int waves_per_tile) {
+    return (int64_t)n_tiles * waves_per_tile > 256;
 }
+constexpr int SPREAD_PAIRS = 32;
 
 // Best split per tile of T features, for two histograms at a time, in tree growth the two children of a node.  The child
 // that was built from rows comes from its row groups' slots (or, when a reduce kernel has summed
@@ -136,7 +136,7 @@ __host__ __device__ __forceinline__ bool scan_spread(int n_tiles, int waves_per_
 // Measured per launch with the reduce kernel's launch in front of it, against one workgroup per feature (or per 16 features and
 // 1024 threads) and histogram behind a full reduction: 1 M x 28, 255 bins 15.0 -> 12.6 us; 464 k x 90 28.1 -> 18.8 us;
 // 2 M x 40, 600 bins 38.1 -> 23.8 us; 400 k x 2000, 63 bins (and one launch less) 46.7 -> 28.6 us; 20 M x 200 34.1 -> 25.4 us.
-template <int T, int NB64, int KB>  // features per workgroup; bins, in units of 64; bins per thread
+template <int T, int NB64, int KB, bool SPREAD>  // features per workgroup; bins, in units of 64; bins per thread; scan_spread
 __global__ __launch_bounds__(64 * T * NB64 / KB) void scan_pair_kernel(int64_t* hist_base, const ScanPair* __restrict__ pairs,
                                                                   const int32_t* __restrict__ n_items_ptr, int max_pairs, SlotSource slots,
                                                                   int F, int nb, const float* __restrict__ delta, int min_data,
@@ -146,31 +146,30 @@ __global__ __launch_bounds__(64 * T * NB64 / KB) void scan_pair_kernel(int64_t* 
     const int n_items = *n_items_ptr;
     const double dg = (double)delta[0], dh = (double)delta[1];
     const int n_ft = (F + T - 1) / T, n_pairs = (n_items + 1) / 2;
-    // Consecutive workgroups go round-robin to the XCDs: the tiles of a pair, which share cache lines, stay on one, and the
-    // pairs are dealt to the XCDs in turn.  Few pairs of a wide matrix are spread (scan_spread): every XCD takes an eighth
-    // of the tiles of all pairs, consecutive ones.
+    // Consecutive workgroups go round-robin to the XCDs: the tiles of a pair, which share cache lines, stay on one.  Few pairs of
+    // a wide matrix are spread: every XCD takes an eighth of the tiles of all pairs, consecutive ones.
     const int xcd = blockIdx.x & 7, sid = blockIdx.x >> 3;
-    const bool spread = scan_spread(n_ft, NW, n_pairs);
+    const bool spread = SPREAD && n_pairs < SPREAD_PAIRS;
     const int n_work = spread ? n_pairs * n_ft : 0, share = (n_work + 7) >> 3;
     const int64_t W = (int64_t)F * nb;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int fl = threadIdx.x % T, b0 = (int)threadIdx.x / T * KB;
     __shared__ int64_t s_sum[2][NW][T];   // a wavefront's bins of a feature
     __shared__ FeatCand s_cand[2][NW];
-    int at_pair = (sid / n_ft) * 8 + xcd;
-    ScanPair sp = pairs[min(at_pair, max_pairs - 1)];  // (in flight together with the number of items)
-    for (int w = sid;; w += (int)(gridDim.x >> 3)) {
-        int t, tile;
+    const int t0 = (sid / n_ft) * 8 + xcd;
+    int tile = sid % n_ft, w = sid;
+    ScanPair sp = pairs[min(t0, max_pairs - 1)];  // (in flight together with the number of items)
+    for (int t = t0;; t += (int)(gridDim.x / (8 * n_ft)) * 8) {
         if (spread) {
             const int i = xcd * share + w;
             if (w >= share || i >= n_work) break;
             t = i / n_ft; tile = i - t * n_ft;
+            w += (int)(gridDim.x >> 3);
+            sp = pairs[t];
         } else {
-            const int lane_of = w / n_ft;
-            t = lane_of * 8 + xcd; tile = w - lane_of * n_ft;
             if (t >= n_pairs) break;
+            if (t != t0) sp = pairs[t];
         }
-        if (t != at_pair) { sp = pairs[t]; at_pair = t; }
         const int f = tile * T + fl;
         const bool has_b = sp.slot_b >= 0;
         const int64_t at = (int64_t)b0 * F + f;  // histograms are [bin][feature]
@@ -333,12 +332,16 @@ int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs,
     if (lanes > most) lanes = most;
     lanes = (lanes + 7) / 8 * 8;
     // (where every number of pairs up to max_pairs is spread, no more than there are tiles)
+#define QG_SCAN_S(T_, N_, K_, S_)                                                                                       \
+    hipLaunchKernelGGL((scan_pair_kernel<T_, N_, K_, S_>), dim3((unsigned)((lanes * n_ft + 7) / 8 * 8)),                \
+                       dim3(64 * T_ * N_ / K_), 0, ctx->stream, hist_base, pairs, n_items, max_pairs, src, F, nb,       \
+                       delta, min_data, min_sum_hess, cand, mfb)
 #define QG_SCAN(T_, N_, K_)                                                                                             \
     do {                                                                                                                \
-        if (max_pairs < lanes && max_pairs < 32 && scan_spread(n_ft, T_ * N_ / K_, 1)) lanes = max_pairs;               \
-        hipLaunchKernelGGL((scan_pair_kernel<T_, N_, K_>), dim3((unsigned)((lanes * n_ft + 7) / 8 * 8)),                \
-                           dim3(64 * T_ * N_ / K_), 0, ctx->stream, hist_base, pairs, n_items, max_pairs, src, F, nb,   \
-                           delta, min_data, min_sum_hess, cand, mfb);                                                   \
+        if (scan_spread(n_ft, T_ * N_ / K_)) {                                                                          \
+            if (max_pairs < SPREAD_PAIRS && max_pairs < lanes) lanes = max_pairs;                                       \
+            QG_SCAN_S(T_, N_, K_, true);                                                                                \
+        } else QG_SCAN_S(T_, N_, K_, false);                                                                            \
     } while (0)
     // (bins per thread: few for narrow matrices, whose workgroups do not fill the chip; 1 M x 28 10.0 us per launch with four,
     // 9.7 us with two)
@@ -352,6 +355,7 @@ int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs,
     else if (nb <= 128) QG_SCAN(4, 2, 1);
     else if (F >= 64) QG_SCAN(4, 4, 4); else QG_SCAN(4, 4, 2);
 #undef QG_SCAN
+#undef QG_SCAN_S
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

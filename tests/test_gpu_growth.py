@@ -139,9 +139,9 @@ def test_split_search_edges(F, nb):
                 assert all(got[i][k] == getattr(e, k) for k in ("bin", "GL", "HL", "GR", "HR", "cnt_left"))
 
 
-# numbers of pairs on both sides of the lines between a whole pair per XCD and tiles spread over all of them (1 pair of 271 and
-# 1000 features, 9 of 40 and 17 of 90; never from 32 on), numbers of tiles and shares that are not multiples of 8
-@pytest.mark.parametrize("F,nb", [(1000, 65), (271, 255), (90, 255), (40, 600)])
+# both sides of the lines between a whole pair of histograms per XCD and tiles spread over all of them: more than 256 wavefronts per
+# pair (257 features of 255 bins, 65 of 300 and more), fewer than 32 pairs; numbers of tiles and shares that are no multiples of 8
+@pytest.mark.parametrize("F,nb", [(1000, 65), (271, 255), (256, 255), (64, 300), (65, 300), (67, 600)])
 def test_split_search_spread_over_xcds(F, nb):
     from paper_2207_09682_amd import Context, binding
     rng = np.random.default_rng(F)
