@@ -795,9 +795,11 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
 // Adds the slots of every build's row groups to the build's histogram.  Thread -> one word
 // of a tile's local bins; the launch's items are cut into gridDim.z runs, a thread walks its
 // run (consecutive items mostly belong to one build) and issues one 64-bit atomic per build
-// it meets.  `generic` slots have the pitch of their tile's width, the others plan.ftp.  above > 0: builds of at most
-// that many row groups are left to the split search.
-template <int W>
+// it meets.  `generic` slots have the pitch of their tile's width, the others plan.ftp.  LARGE: builds of at most
+// `above` row groups are left to the split search.  (A template parameter: the test on every build costs a stand-alone
+// build, which has one, 0.1 to 0.4 us.  LARGE launches test `above` all the same: without it the compiler orders the loads of the
+// counts one after the other, 4.9 -> 5.2 us per launch on 1 M x 28.)
+template <int W, bool LARGE>
 __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* __restrict__ partials,
                                                           const HistEntry* __restrict__ entries,
                                                           const int32_t* __restrict__ table_counts,
@@ -805,7 +807,7 @@ __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* _
                                                           int generic, int above) {
     using word = typename Acc<W>::word;
     const int n_entries = table_counts[0], n_items = table_counts[1];
-    if (above > 0 && table_counts[2] == 0) return;  // the split search adds up every build of this launch itself
+    if (LARGE && above > 0 && table_counts[2] == 0) return;  // the split search adds up every build of this launch itself
     const int hs = plan.hshift;
     const uint32_t hmask = (1u << hs) - 1u;
     const int per = (n_items + (int)gridDim.z - 1) / (int)gridDim.z;
@@ -828,7 +830,7 @@ __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* _
     int i = i0;
     while (i < i1) {
         const int iend = min(i1, entries[e].item_start + entries[e].groups);
-        if (above > 0 && entries[e].groups <= above) { i = iend; ++e; continue; }
+        if (LARGE && above > 0 && entries[e].groups <= above) { i = iend; ++e; continue; }
         int64_t sg = 0, sh = 0;
         for (; i + 4 <= iend; i += 4) {
             word v[4];
@@ -1034,23 +1036,20 @@ HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int ac
 }
 
 // One entry table for a stand-alone build.
-__global__ void set_hist_table_kernel(HistEntry* entries, int32_t* counts, int64_t begin, int64_t count, HistPlan plan) {
+__global__ void set_hist_table_kernel(HistEntry* entries, int32_t* counts, HistEntry e) {
     if (threadIdx.x == 0) {
-        const int64_t t = hist_target_rows(plan, count, 1);
-        int64_t g = (count + t - 1) / t;
-        if (g < 1) g = 1;
-        HistEntry e;
-        e.begin = begin; e.count = count; e.buf = BUF_ORIGINAL; e.slot = 0; e.item_start = 0; e.groups = (int32_t)g;
         entries[0] = e;
         counts[0] = 1;
-        counts[1] = count > 0 ? (int32_t)g : 0;
-        counts[2] = 1;
+        counts[1] = e.count > 0 ? e.groups : 0;
     }
 }
 
+// (The row groups are counted on the host: on the device their chain of 64-bit divisions took 0.3 us of every build.)
 int launch_set_hist_table(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count) {
-    hipLaunchKernelGGL(set_hist_table_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->hist_entries, ctx->hist_counts,
-                       begin, count, plan);
+    const int64_t t = hist_target_rows(plan, count, 1), g = (count + t - 1) / t;
+    HistEntry e;
+    e.begin = begin; e.count = count; e.buf = BUF_ORIGINAL; e.slot = 0; e.item_start = 0; e.groups = g < 1 ? 1 : (int32_t)g;
+    hipLaunchKernelGGL(set_hist_table_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->hist_entries, ctx->hist_counts, e);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
@@ -1207,12 +1206,15 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         if (z > items_bound) z = (int)items_bound;
         if (z < 1) z = 1;
         dim3 rgrid((unsigned)xb, (unsigned)plan.n_tiles, (unsigned)z);
-        if (plan.acc_width == 16 && !plan.two_level)  // (two-level groups hand over 64-bit words)
-            hipLaunchKernelGGL(hist_reduce_kernel<16>, rgrid, dim3(256), 0, ctx->stream, partials, entries, table_counts,
-                               hist_base, F, nb, plan, fast ? 0 : 1, reduce_above);
-        else
-            hipLaunchKernelGGL(hist_reduce_kernel<32>, rgrid, dim3(256), 0, ctx->stream, partials, entries, table_counts,
-                               hist_base, F, nb, plan, fast ? 0 : 1, reduce_above);
+#define QG_REDUCE(W_, LARGE_)                                                                                      \
+    hipLaunchKernelGGL((hist_reduce_kernel<W_, LARGE_>), rgrid, dim3(256), 0, ctx->stream, partials, entries,      \
+                       table_counts, hist_base, F, nb, plan, fast ? 0 : 1, reduce_above)
+        if (plan.acc_width == 16 && !plan.two_level) {  // (two-level groups hand over 64-bit words)
+            if (reduce_above > 0) QG_REDUCE(16, true); else QG_REDUCE(16, false);
+        } else {
+            if (reduce_above > 0) QG_REDUCE(32, true); else QG_REDUCE(32, false);
+        }
+#undef QG_REDUCE
         QG_HIP(ctx, hipGetLastError());
     }
     if (e1) QG_HIP(ctx, hipEventRecord(e1, ctx->stream));
