@@ -188,7 +188,7 @@ __global__ __launch_bounds__(1024) void lambdarank_grad_kernel(const float* __re
 
 // Queries per workgroup: what costs the busiest compute unit the fewest wavefronts -- whole wavefronts per workgroup times
 // its workgroups -- with at most 512 threads, or one query (20 M rows of queries of 100: five in 512 threads, 98 % of the
-// lanes in use, against 78 % for one in 128; 2000 queries: three in 320 threads).
+// lanes in use, against 78 % for one in 128; 2000 queries: four in 448 threads).
 static int rank_queries(int64_t n_queries, int group) {
     int best = 1;
     int64_t best_cost = INT64_MAX;

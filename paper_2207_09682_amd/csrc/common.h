@@ -44,7 +44,7 @@ struct StepState {
     int64_t prof_builds;                      // histogram builds served by those launches
 };
 
-// One node expanded in the current round, with everything the partition kernels need of it (one 64-byte record
+// One node expanded in the current round, with everything the partition kernels need of it (one 56-byte record
 // instead of a look-up in the node table that depends on it).
 struct BatchEntry {
     int64_t begin;      // the node's rows: slice of buffer `buf`
@@ -122,8 +122,10 @@ struct HistPlan {
 //    place per build but the first is left for them.  (Without it a few workgroups took a second group when the others had
 //    ended: 10.5 M x 28 2169 -> 2050 us per tree, 400 k x 2000 1241 -> 1185 us, 2 M x 40 of 16-bit bins 906 -> 888 us.)
 //  - Twice as many where the matrix has several tiles of features and a group still has 4096 rows: the last tile is narrower,
-//    and what its workgroups leave idle goes to those that start later (20 M x 200 12040 -> 11705 us per tree; with 2400 rows per group,
-//    400 k x 2000, the bins handed over twice cost more: 1188 -> 1248 us).
+//    and what its workgroups leave idle goes to those that start later; below 4096 the bins handed over twice cost more.  Time of
+//    a tree against never doubling, with the line at 512 / 4096 / 8192 rows per group: 4 M x 200 -4.5 / -4.7 / 0.0 %, 3 M x 500
+//    -2.2 / -2.7 / -3.1 %, 4 M x 136 (8-bit hessians) +4.5 / +0.7 / +0.2 %, 9 M x 40 of 16-bit bins -0.5 / -0.9 / -0.8 %; 20 M x 200
+//    -2.8 % with 4096, -2.5 % with 8192, -0.5 % with 16384; with 512 1 M x 200 +11 %, 1 M x 500 +5.6 %, 2 M x 40 +5.5 %, 400 k x 2000 +3.5 %.
 //  - Not fewer than min_rows_per_group rows, unless the launch would then have fewer than 64 workgroups: a group of
 //    2048 rows takes a wavefront through 16 dependent rounds of loads (100 k x 50 434 -> 385 us per tree with 650 rows; where
 //    the chip is busy smaller groups only have more bins to hand over, 1 M x 28 676 -> 690 us with 1024).
@@ -286,7 +288,8 @@ constexpr int PART_GROUPS = 512;
 // Passes over finished leaves gather and update 4 to 8 bytes per row, leaf by leaf, in places that lie about a cache line apart
 // or further.  Their work is cut into parts of the row order (a leaf's list ascends), a multiple of 8 of them, and the
 // workgroups of one part run side by side on one XCD: its L2 then serves all leaves' shares of a line after one fetch.
-// A part is 2^17 rows: 1 MB of (g, h) pairs, of which two to four parts in flight fit the 4 MB.
+// A part is at most 2^17 rows up to 2^25 rows in all (then there are 256, of more rows each): 1 MB of (g, h) pairs, of which two to
+// four parts in flight fit the 4 MB.
 // Against 32 parts per leaf spread over all XCDs (and a separate copy of the row lists): 20 M rows in 511 leaves, refit and copy
 // 430 -> 150 us, score update 635 -> 253 us (what is left is the rate of L2 requests, one per row and direction); 10.5 M
 // rows in 255 leaves 179 -> 77 us; two leaves of 3 M rows 95 -> 11 us, which used to have 64 workgroups.
@@ -306,7 +309,10 @@ constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
 //    kernel per round on 10 k x 28 in ordered mode: 17.0 us with 8, 10.0 us with 2); above that 8, which spreads a
 //    wavefront's fixed work per segment (1 M x 28: 10.8 us with 8, 14.6 us with 2).
 //  - The counters save the scatter kernel a walk over all of a node's segments (2 KB per wavefront and million rows), but
-//    their device-wide atomics lengthen the count kernel by about 2 us: 1 M x 28 7.9 us with, 6.1 us without.
+//    their device-wide atomics lengthen the count kernel by about 2 us: 1 M x 28 7.9 us with, 6.1 us without.  Trees in 255 leaves
+//    with / without: 1 M x 28 772 / 745 us, 3 M 1025 / 1003 us, 4 M 1174 / 1160 us, 5 M 1316 / 1300 us, 6 M 1416 / 1421 us, 7.5 M
+//    1652 / 1687 us, 10.5 M 2002 / 2073 us; matrix not bound: 4 M 1365 / 1362 us, 5 M 1584 / 1591 us, 7.5 M 2038 / 2095 us.  The
+//    two are level between 4 and 5.5 M rows; what the line gives away between it and there is 1 to 3 % of a bound tree.
 inline int part_rows(int64_t n_rows) { return n_rows > ((int64_t)1 << 18) ? 8 : 2; }
 inline bool part_supers(int64_t n_rows) { return n_rows > ((int64_t)3 << 20); }
 // In tree growth the split search sums a build's slots itself when there are at most this many (a thread's loads of them are
