@@ -136,7 +136,7 @@ typedef struct {
  * host-side context (and a few bytes of pinned host memory for the status word grow_tree reads back).
  *
  * qgbdt_workspace_bytes: bytes of device workspace a context of `shape` needs (host out), from the shape alone:
- * three row-index buffers and three lists of packed gradients that follow them, the quantized gradients, a pool of
+ * five row-index buffers and five lists of packed gradients that follow them, the quantized gradients, a pool of
  * 3 * max_leaves + 1 histograms, the slots of the histogram kernels' row groups, partition flags and small
  * descriptors, plus the optional sections named by `flags` (QGBDT_WS_*).
  *

@@ -135,8 +135,8 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     const size_t N = (size_t)sh.n_rows, F = (size_t)sh.n_features;
     const size_t W = F * (size_t)sh.n_bins;
     const size_t L = (size_t)sh.max_leaves;
-    for (int b = 0; b < 3; ++b) k.take(&c->idx[b], N);
-    for (int b = 0; b < 3; ++b) k.take(&c->ogh[b], N);
+    for (int b = 0; b < ROW_BUFS; ++b) k.take(&c->idx[b], N);
+    for (int b = 0; b < ROW_BUFS; ++b) k.take(&c->ogh[b], N);
     k.take(&c->gh, N);
     k.take(&c->ghf, N);
     k.take(&c->hist_pool, W * (size_t)(c->max_expand + 1));
@@ -175,8 +175,8 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
         k.take(&c->mfb, F);
     } else if (base) { c->bins_t = nullptr; c->mfb = nullptr; }
     if ((flags & QGBDT_WS_ROW_COPIES) && shape_allows_ordered(sh)) {
-        for (int b = 0; b < 3; ++b) k.take(&c->obins[b], N * F);
-    } else if (base) { c->obins[0] = c->obins[1] = c->obins[2] = nullptr; }
+        for (int b = 0; b < COPY_BUFS; ++b) k.take(&c->obins[b], N * F);
+    } else if (base) { for (int b = 0; b < COPY_BUFS; ++b) c->obins[b] = nullptr; }
     if (flags & QGBDT_WS_BOOST) {
         k.take(&c->gbuf, N);
         k.take(&c->hbuf, N);
@@ -421,7 +421,7 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
     RowSource rows;
     rows.gh_pos = 0;  // the caller's packed gradients are in original row order
     IdxSet idx;
-    for (int b = 0; b < 4; ++b) { rows.bins[b] = (const uint8_t*)bins; rows.gh[b] = gh; idx.p[b] = const_cast<int32_t*>(row_idx); }
+    for (int b = 0; b <= ROW_BUFS; ++b) { rows.bins[b] = (const uint8_t*)bins; rows.gh[b] = gh; idx.p[b] = const_cast<int32_t*>(row_idx); }
     rc = launch_hist(ctx, plan, rows, idx, row_idx != nullptr, ((uintptr_t)bins & 15) == 0,
                      ctx->hist_entries, ctx->hist_counts, hist_out,
                      (count + hist_target_rows(plan, count, 1) - 1) / hist_target_rows(plan, count, 1),  // the build's row groups

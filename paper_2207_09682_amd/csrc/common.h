@@ -56,7 +56,8 @@ struct BatchEntry {
     int32_t buf;
     int32_t feature, bin;  // its split
     int32_t super_start;   // first of its groups of PART_SUPER segments (without such counters: of its segments)
-    int32_t pad[3];
+    int32_t child_buf;     // buffer its children's rows go to
+    int32_t pad[2];
 };
 
 // One known node whose split is not committed yet and has a gain, in the gain order kept from round to round.
@@ -160,29 +161,35 @@ struct RefitUnit {
 
 struct ScanPair;
 
-// Where the rows of a slice live.  Buffers 0..2 rotate with the depth of a node (the children
-// of buffer b live in buffer (b+1)%3, so a node's rows survive until its grandchildren are
-// expanded); buffer 3 is the caller's data in original row order (bin matrix, quantized
-// gradients), where the root lives in ordered mode.  Row ids of buffer 3 use array 0.
-// In ordered mode (narrow rows) buffers 0..2 hold leaf-ordered copies of the bin rows and
+// Where the rows of a slice live.  A number of buffers rotates with the depth of a node (with n of them the children of
+// buffer b live in buffer (b+1)%n, so a node's rows survive until its descendants n - 1 levels below are expanded):
+// ROW_BUFS, in ordered mode COPY_BUFS.  Buffer BUF_ORIGINAL is the caller's data in original row order (bin matrix,
+// quantized gradients), where the root lives.
+// In ordered mode (narrow rows) the buffers hold leaf-ordered copies of the bin rows and
 // packed gradients.  Otherwise the bin rows are gathered from the original matrix by row id;
 // with `gh_pos` set the packed gradients still travel with the row ids (gh[b][p] belongs to
 // row idx[b][p]: 2 more bytes per moved row, and a gathered build reads them in sequence
 // instead of one more cache line per row), without it they are gathered from gh[BUF_ORIGINAL].
-constexpr int BUF_ORIGINAL = 3;
+// How many there are decides how far a tree may be grown ahead of its commits (tree_plan_kernel): nodes up to n - 2 levels
+// below an open leaf can be expanded while that leaf's rows are still there.  Five row lists cost 12 bytes per row more than
+// three; four would leave 20 M x 200 (lambdarank) 31 rounds per tree and five leave 23, six 20, three 50.  The leaf-ordered
+// copies of the rows themselves stay three.
+constexpr int ROW_BUFS = 5;
+constexpr int COPY_BUFS = 3;
+constexpr int BUF_ORIGINAL = ROW_BUFS;
 struct RowSource {
-    const uint8_t* bins[4];
-    const int16_t* gh[4];
+    const uint8_t* bins[ROW_BUFS + 1];
+    const int16_t* gh[ROW_BUFS + 1];
     int32_t gh_pos;
 };
 struct RowDest {
-    uint8_t* bins[3];
-    int16_t* gh[3];
+    uint8_t* bins[COPY_BUFS];
+    int16_t* gh[ROW_BUFS];
 };
 struct IdxSet {
-    int32_t* p[4];  // p[3] == p[0]
+    int32_t* p[ROW_BUFS + 1];  // (the root's list is the identity and never stored: the last one stands for it)
 };
-__host__ __device__ inline int child_buffer(int buf) { return buf == BUF_ORIGINAL ? 1 : (buf + 1) % 3; }
+__host__ __device__ inline int child_buffer(int buf, int n_bufs) { return buf == BUF_ORIGINAL ? 0 : (buf + 1) % n_bufs; }
 
 }  // namespace qgbdt
 
@@ -205,9 +212,9 @@ struct qgbdt_ctx {
     int rounds_hint;
     // workspace
     int ordered;           // the workspace holds leaf-ordered copies of the rows (narrow rows, QGBDT_WS_ROW_COPIES)
-    uint8_t* obins[3];     // [N][F] each (ordered mode), else null
-    int16_t* ogh[3];       // [N] each: packed gradients in the order of idx[b]
-    int32_t* idx[3];       // [N] each
+    uint8_t* obins[qgbdt::COPY_BUFS];  // [N][F] each (ordered mode), else null
+    int16_t* ogh[qgbdt::ROW_BUFS];     // [N] each: packed gradients in the order of idx[b]
+    int32_t* idx[qgbdt::ROW_BUFS];     // [N] each
     uint8_t* bins_t;       // [F][N] feature-major copy of the bound bin matrix (QGBDT_WS_BIND, filled by qgbdt_bind_bins), else null
     uint16_t* mfb;         // [F] most frequent bin of each feature of the bound matrix when it holds most rows, else 0xffff
     int mfb_features;      // features with such a bin (0: no skipping)

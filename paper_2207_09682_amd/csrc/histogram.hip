@@ -1125,7 +1125,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     if (plan.two_level && !flat)
         return set_error(ctx, QGBDT_E_INVALID_ARG, "two-level plan for rows that the byte-stream kernel cannot read");
     bool wide_ok = true;  // 16-byte loads need 16-byte aligned matrices (F is a multiple of 16 in that mode)
-    for (int b = 0; b < 4; ++b) wide_ok = wide_ok && (((uintptr_t)rows.bins[b] & 15) == 0);
+    for (int b = 0; b <= ROW_BUFS; ++b) wide_ok = wide_ok && (((uintptr_t)rows.bins[b] & 15) == 0);
     if (flat) {
 #define QG_LAUNCH_FLAT(W_, TWO_)                                                                                  \
     hipLaunchKernelGGL((hist_flat_kernel<W_, 2, TWO_>), grid, block, plan.lds_bytes, ctx->stream, rows, entries,  \

@@ -317,7 +317,7 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
             P->n_left = nl;
             const bool left_small = nl <= nr;
             const int lslot = left_small ? be.new_slot : slot, rslot = left_small ? slot : be.new_slot;
-            const int cb = child_buffer(be.buf);
+            const int cb = be.child_buf;
             auto put = [&](int which, int64_t begin, int count, int64_t g, int64_t h, int sl) {
                 Node* c = &nodes[child + which];
                 c->begin = begin; c->count = count; c->sum_g = g; c->sum_h = h; c->n_left = 0; c->buf = cb; c->slot = sl;
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
         const int seg = item - nd.seg_start, sup = seg / SUPER;
         const int sbegin = seg * PART_SEG, n = min(nd.count - sbegin, PART_SEG);
         const int n_sup = (nd.n_seg + SUPER - 1) / SUPER;
-        const int cbuf = child_buffer(nd.buf);
+        const int cbuf = nd.child_buf;
         const bool identity = nd.buf == BUF_ORIGINAL;  // the root's list: row id = position, never stored
         const int32_t* src = idxs.p[nd.buf] + nd.begin + sbegin;
         int32_t* dst = idxs.p[cbuf] + nd.begin;
@@ -457,7 +457,8 @@ static int batch_part_grid(const qgbdt_ctx* ctx) {
 
 static IdxSet idx_set(const qgbdt_ctx* ctx) {
     IdxSet s;
-    s.p[0] = ctx->idx[0]; s.p[1] = ctx->idx[1]; s.p[2] = ctx->idx[2]; s.p[3] = ctx->idx[0];
+    for (int b = 0; b < ROW_BUFS; ++b) s.p[b] = ctx->idx[b];
+    s.p[BUF_ORIGINAL] = ctx->idx[0];
     return s;
 }
 
@@ -477,7 +478,8 @@ int launch_batch_partition_count(qgbdt_ctx* ctx, const RowSource& rows, const ui
 
 int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered, const HistPlan& plan) {
     RowDest out;
-    for (int b = 0; b < 3; ++b) { out.bins[b] = ctx->obins[b]; out.gh[b] = ctx->ogh[b]; }
+    for (int b = 0; b < COPY_BUFS; ++b) out.bins[b] = ctx->obins[b];
+    for (int b = 0; b < ROW_BUFS; ++b) out.gh[b] = ctx->ogh[b];
     const int32_t* const sums = ctx->seg_supers ? ctx->super_counts : ctx->seg_counts;
 #define QG_SCATTER_R(MODE_, R_, S_)                                                                                    \
     hipLaunchKernelGGL((batch_part_scatter_kernel<MODE_, R_, S_>), dim3(batch_part_grid(ctx) + 1), dim3(256), 0, ctx->stream,     \

@@ -10,14 +10,14 @@
 //      expanded, and its children become open leaves; the replay stops at the first
 //      leaf that has not been expanded;
 //   2. expands that leaf and, speculatively, other nodes with large gains -- open leaves
-//      and, one level ahead, children of open leaves that are already expanded -- as
+//      and, up to three levels ahead, descendants of open leaves that are already expanded -- as
 //      far as the leaf budget can still reach them: one batched partition, one batched
 //      histogram build for the smaller children, one batched subtraction and split
 //      search for all children.
 // A speculative expansion that the replay never reaches is simply not part of the
 // tree: its node stays a leaf and its row slice is untouched, because children are
-// always written to another buffer (three buffers rotate with the depth, so a node's
-// rows survive the expansion of its children).  Split numbers and leaf ids are
+// always written to another buffer (buffers rotate with the depth, so a node's rows
+// survive the expansions of the levels below it that may run ahead).  Split numbers and leaf ids are
 // assigned at commit time, so the result equals the sequential one bit for bit.
 //
 // The host enqueues whole rounds without reading anything back; after the expected
@@ -131,9 +131,15 @@ __host__ __device__ __forceinline__ PlanLds plan_lds_layout(int max_nodes, int b
     return l;
 }
 
+// The rank whose order key is k: the last of its fields.
+__device__ __forceinline__ int key_rank(unsigned long long k) {
+    const int tz = __ffsll((long long)k) - 1;
+    return (int)((k >> (tz / 12 * 12)) & 0xfffull) - 1;
+}
+
 // Leaf id of the node at rank p once its parent is committed.  Left children take their parent's id, the right child
-// of the k-th committed split of this call is leaf leaves0 + k; the chain ends at the latest at the grandparent, which
-// was an open leaf before the call.
+// of the k-th committed split of this call is leaf leaves0 + k; the chain ends at the latest at the node that was an open
+// leaf before the call.
 __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* par, const unsigned long long* info,
                                           const uint16_t* corder, int leaves0, int p) {
     for (;;) {
@@ -158,21 +164,23 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 //     first that has not been expanded) without a replay: with distinct gains a node is selected when the *worst* rank
 //     on its path from an open leaf is reached, then the worst rank behind that one, and so on -- the order of
 //     selection is the lexicographic order of the running maxima of the ranks, read from the node upwards.  Paths are
-//     at most three nodes long (children are expanded one level ahead of the open leaves), so the order key is one
-//     64-bit word; the splits committed are the expanded nodes whose key is below that of every node that is not
+//     at most five nodes long (nodes are expanded up to three levels below the open leaves), so the order key is one
+//     64-bit word of five ranks; the splits committed are the expanded nodes whose key is below that of every node that is not
 //     expanded.  Equal gains are resolved by leaf ids, which depend on the order itself: if two known nodes tie, one
 //     wavefront replays the selection split by split (a bit per open leaf at its rank, the first set bit is next;
 //     0.25 us per split).
 //  3. All threads write the outputs of the committed splits.
 //  4. The batch is chosen with popcounts over the masks: the leaf the selection stopped at, the other open leaves that are
-//     not expanded (class 0), then children of expanded open leaves (class 1; one level ahead only: a node's rows outlive the expansion of its children but
-//     not that of its grandchildren), by rank, if fewer than the remaining number of splits have a larger gain.
+//     not expanded (class 0), then nodes up to n_bufs - 2 levels below expanded open leaves (class 1; a node's rows outlive the
+//     expansions of that many levels below it), by rank, if fewer than the remaining number of splits have a larger gain.
+//     One level ahead instead of three costs the data that peel a few rows off a large node at every split many rounds:
+//     rounds per tree 50 -> 23 (lambdarank 20 M x 200), 27 -> 21 (200 k x 136), 13 -> 11 (10.5 M x 28), 12 -> 10 (464 k x 90).
 // Measured per launch against the version that kept all nodes in the order and replayed every split: 20.6 -> 10.1 us
 // (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
 // (20 M x 200, 511 leaves).
 __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch, int32_t* batch_seg,
                                                          int32_t* super_counts, PlanEntry* list, int32_t* hist_counts, int F, int n_cand, int num_leaves,
-                                                         int batch_max, int max_expand, int seg_rows, int seg_supers, TreeOut out,
+                                                         int batch_max, int max_expand, int seg_rows, int seg_supers, int n_bufs, TreeOut out,
                                                          const FeatCand* __restrict__ cand,
                                                          const ScanPair* __restrict__ scan_pairs) {
     // the fields of the growth state this kernel needs and (for the first 1024 ranks) the kept order, in loads that are
@@ -306,18 +314,15 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     const int budget = num_leaves - 1 - commits0;
     unsigned long long* ckey = reinterpret_cast<unsigned long long*>(oids);
     if (!s_tie) {
-        // order key of rank p: running maxima of (rank + 1) on the path up to the open leaf, the largest first
+        // order key of rank p: running maxima of (rank + 1) on the path up to the open leaf, the largest first, 12 bits
+        // each; a path has at most n_bufs nodes
+        static_assert(ROW_BUFS <= 5 && 6 * MAX_TREE_LEAVES + 1 < 4096, "fields of the order key");
         auto order_key = [&](int p) {
-            unsigned long long k0 = (unsigned long long)(p + 1), k1 = 0, k2 = 0;  // up to three maxima, largest first
-            int q = par[p], top = p;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                if (q != (int)NO_NODE) {
-                    if (q > top) { k2 = k1; k1 = k0; k0 = (unsigned long long)(q + 1); top = q; }
-                    q = par[q];
-                }
-            }
-            return (k0 << 26) | (k1 << 13) | k2;
+            unsigned long long k = (unsigned long long)(p + 1) << 48;
+            int top = p;
+            for (int q = par[p]; q != (int)NO_NODE; q = par[q])
+                if (q > top) { k = (k >> 12) | ((unsigned long long)(q + 1) << 48); top = q; }
+            return k;
         };
         for (int p0 = wave * 64; p0 < P; p0 += 1024) {
             const int p = p0 + lane;
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         for (int p = tid; p < P; p += 1024) {
             if (!((info[p] >> 32) & 1ull)) continue;
             const unsigned long long k = order_key(p);
-            if (k < first) ckey[atomicAdd(&s_nc, 1)] = (k << 12) | (unsigned long long)p;
+            if (k < first) ckey[atomicAdd(&s_nc, 1)] = k;
         }
         lds_barrier();
         const int nc = s_nc;
@@ -338,7 +343,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
             const unsigned long long k = ckey[c];
             int o = 0;
             for (int u = 0; u < nc; ++u) o += ckey[u] < k ? 1 : 0;
-            const int p = (int)(k & 0xfffull);
+            const int p = key_rank(k);
             if (o < budget) { commit[o] = (uint16_t)p; corder[p] = (uint16_t)o; }
         }
     } else {
@@ -387,26 +392,22 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     for (int u = 1; u < 8; ++u) first_open = min(first_open, s_first[u]);
     const bool done = n_commit >= budget || first_open == ~0ull;  // (no leaf with a gain is left)
     // the leaf the selection stopped at (an order key ends with the node's own rank)
-    const int stop = s_tie ? s_stop
-                           : (int)((first_open & 0x1fffull) ? first_open & 0x1fffull : ((first_open >> 13) & 0x1fffull) ? (first_open >> 13) & 0x1fffull : first_open >> 26) - 1;
+    const int stop = s_tie ? s_stop : key_rank(first_open);
     // the masks after the commits
     for (int p0 = wave * 64; p0 < P; p0 += 1024) {
         const int p = p0 + lane;
-        bool open = false, expanded = false, committed = false;
+        bool open = false, expanded = false, committed = false, ahead = false;
         if (p < P) {
-            const unsigned long long inf = info[p];
-            expanded = (inf >> 32) & 1ull;
+            expanded = (info[p] >> 32) & 1ull;
             committed = corder[p] != NO_NODE;
-            const int q = par[p];
-            open = !committed && (q == (int)NO_NODE || corder[q] != NO_NODE);
-            if (open && expanded) {  // its children may be expanded one level ahead
-                const uint32_t rl = (uint32_t)inf & 0xffffu, rr = (uint32_t)inf >> 16;
-                if (rl != NO_NODE) atomicOr(&s_cls1[rl >> 6], 1ull << (rl & 63));
-                if (rr != NO_NODE) atomicOr(&s_cls1[rr >> 6], 1ull << (rr & 63));
-            }
+            int q = par[p], level = 0;  // levels below the open leaf
+            if (!committed)
+                for (; q != (int)NO_NODE && corder[q] == NO_NODE; q = par[q]) ++level;
+            open = !committed && level == 0;
+            ahead = level > 0 && level <= n_bufs - 2;
         }
-        const unsigned long long mo = __ballot(open), me = __ballot(expanded), mc = __ballot(committed);
-        if (lane == 0) { s_open[p0 >> 6] = mo; s_exp[p0 >> 6] = me; s_comm[p0 >> 6] = mc; }
+        const unsigned long long mo = __ballot(open), me = __ballot(expanded), mc = __ballot(committed), ma = __ballot(ahead);
+        if (lane == 0) { s_open[p0 >> 6] = mo; s_exp[p0 >> 6] = me; s_comm[p0 >> 6] = mc; s_cls1[p0 >> 6] = ma; }
     }
     // outputs and node states of the splits committed above
     for (int c = tid; c < n_commit; c += 1024) {
@@ -503,7 +504,8 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         be.feature = nd->best.feature; be.bin = nd->best.bin;
         be.n_seg = (int)(((uint32_t)be.count + (uint32_t)seg_rows - 1u) / (uint32_t)seg_rows);
         be.new_slot = n_slots + tid;
-        be.pad[0] = be.pad[1] = be.pad[2] = 0;
+        be.child_buf = child_buffer(be.buf, n_bufs);
+        be.pad[0] = be.pad[1] = 0;
         nodes[i].expanded = 1;
         nodes[i].child = n_nodes + 2 * tid;
     }
@@ -637,14 +639,14 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     const bool gh_lists = layout != QGBDT_ROWS_IDS;
     if (ordered && !ctx->ordered)
         return set_error(ctx, QGBDT_E_WORKSPACE, "the workspace has no room for leaf-ordered copies of the rows");
-    for (int b = 0; b < 3; ++b) {
-        rows.bins[b] = ordered ? ctx->obins[b] : bins;
+    for (int b = 0; b < ROW_BUFS; ++b) {
+        rows.bins[b] = ordered && b < COPY_BUFS ? ctx->obins[b] : bins;
         rows.gh[b] = gh_lists ? ctx->ogh[b] : ctx->gh;
         idxs.p[b] = ctx->idx[b];
     }
     rows.gh_pos = (gh_lists && !ordered) ? 1 : 0;
     rows.bins[BUF_ORIGINAL] = bins; rows.gh[BUF_ORIGINAL] = ctx->gh; idxs.p[BUF_ORIGINAL] = ctx->idx[0];
-    // the root's rows are the original arrays under the identity list (array 0, which its great-grandchildren reuse)
+    // the root's rows are the original arrays under the identity list
     const int root_buf = BUF_ORIGINAL;
 
     // up to 256 candidates per histogram the plan kernel reduces them itself (one launch less per round)
@@ -678,7 +680,8 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     auto plan_batch = [&]() {
         hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
                            ctx->batch_seg, ctx->super_counts, ctx->plan_list, ctx->hist_counts, F, n_cand, p->num_leaves,
-                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, out, fused_cand, ctx->scan_pairs);
+                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, ordered ? COPY_BUFS : ROW_BUFS, out,
+                           fused_cand, ctx->scan_pairs);
     };
     auto expand_batch = [&]() {  // partition, histograms and split search of the nodes the plan kernel has chosen
         int rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
