@@ -161,10 +161,9 @@ struct RefitUnit {
 
 struct ScanPair;
 
-// Where the rows of a slice live.  A number of buffers rotates with the depth of a node (with n of them the children of
-// buffer b live in buffer (b+1)%n, so a node's rows survive until its descendants n - 1 levels below are expanded):
-// ROW_BUFS, in ordered mode COPY_BUFS.  Buffer BUF_ORIGINAL is the caller's data in original row order (bin matrix,
-// quantized gradients), where the root lives.
+// Where the rows of a slice live: in one of ROW_BUFS buffers, in ordered mode of COPY_BUFS.  The children of a node share its
+// slice in another buffer, which holds the rows of no node above them that may yet stay a leaf (tree_plan_kernel).  Buffer
+// BUF_ORIGINAL is the caller's data in original row order (bin matrix, quantized gradients), where the root lives.
 // In ordered mode (narrow rows) the buffers hold leaf-ordered copies of the bin rows and
 // packed gradients.  Otherwise the bin rows are gathered from the original matrix by row id;
 // with `gh_pos` set the packed gradients still travel with the row ids (gh[b][p] belongs to
@@ -172,8 +171,8 @@ struct ScanPair;
 // instead of one more cache line per row), without it they are gathered from gh[BUF_ORIGINAL].
 // How many there are decides how far a tree may be grown ahead of its commits (tree_plan_kernel): nodes up to n - 2 levels
 // below an open leaf can be expanded while that leaf's rows are still there.  Five row lists cost 12 bytes per row more than
-// three; four would leave 20 M x 200 (lambdarank) 31 rounds per tree and five leave 23, six 20, three 50.  The leaf-ordered
-// copies of the rows themselves stay three.
+// three; a tree of 20 M x 200 (lambdarank) takes 51 rounds with three lists, 30 with four, 27 with five; six would save one or two
+// more (replayed on the host).  The leaf-ordered copies of the rows themselves stay three: five gain 1 % on 2.5 M x 28.
 constexpr int ROW_BUFS = 5;
 constexpr int COPY_BUFS = 3;
 constexpr int BUF_ORIGINAL = ROW_BUFS;
@@ -189,7 +188,6 @@ struct RowDest {
 struct IdxSet {
     int32_t* p[ROW_BUFS + 1];  // (the root's list is the identity and never stored: the last one stands for it)
 };
-__host__ __device__ inline int child_buffer(int buf, int n_bufs) { return buf == BUF_ORIGINAL ? 0 : (buf + 1) % n_bufs; }
 
 }  // namespace qgbdt
 

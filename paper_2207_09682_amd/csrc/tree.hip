@@ -90,18 +90,10 @@ __device__ __forceinline__ unsigned long long lane_bits(unsigned long long w, in
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// The lowest `k` set bits of m (k < popcount of m), by halving: six steps.
-__device__ __forceinline__ unsigned long long lowest_bits(unsigned long long m, int k) {
-    int at = 0;  // length of the prefix that is taken
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) {
-        const int c = __popcll(m & ((1ull << (at + s)) - 1ull));  // at + s <= 63
-        if (c <= k) at += s;
-    }
-    return m & ((1ull << at) - 1ull);
-}
-
 constexpr uint32_t NO_NODE = 0xffffu;
+constexpr uint32_t FAR_AHEAD = 0x8000u;  // of a candidate's bottleneck: the node is two or more levels below the open leaf
+constexpr uint32_t NODE_ID = 0xfffu;     // of a node's `ids`; the row buffer is in the four bits above
+static_assert(6 * MAX_TREE_LEAVES + 1 < 4096 && BUF_ORIGINAL < 16, "a node's id and buffer share 16 bits");
 
 // LDS of the plan kernel, as byte offsets into its dynamic LDS (offsets, not pointers: the compiler then sees LDS accesses
 // everywhere; through a struct of generic pointers they became flat ones, three times as slow).
@@ -109,13 +101,13 @@ constexpr uint32_t NO_NODE = 0xffffu;
 struct PlanLds {
     int key;      // u64 [p_max] gain bits in the new order
     int okey;     // u64 [p_max + 8] gain bits in the kept order; once merged: `info`, what the selection needs of a rank
-    int ids;      // u32 [p_max] node | left child << 16
+    int ids;      // u32 [p_max] node | row buffer << 12 | left child << 16
     int oids;     // u32 [p_max] the same in the kept order; once merged: `ckey`, u64 [p_max / 2], order of the splits committed now
     int leaf;     // u16 [p_max] leaf id of an open leaf, else NO_NODE
     int oleaf;    // u16 [p_max] the same in the kept order; once merged: `corder`, place among the splits committed now
     int rank_of;  // u16 [p_max] by node: its rank, NO_NODE: committed before or without a gain
     int par;      // u16 [p_max] rank of the parent, NO_NODE: an open leaf
-    int shift;    // i32 [p_max] larger new keys of an old entry, then places of the new ones
+    int shift;    // i32 [p_max] larger new keys of an old entry, then places of the new ones; after the merge: open splits by bottleneck
     int nkey;     // u64 [2*batch_max + 4] gain bits of last round's children (0: no split)
     int commit;   // u16 [num_leaves] ranks of the splits committed now, in order
     int chosen;   // u16 [batch_max] ranks of the nodes to expand
@@ -172,9 +164,12 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 //  3. All threads write the outputs of the committed splits.
 //  4. The batch is chosen with popcounts over the masks: the leaf the selection stopped at, the other open leaves that are
 //     not expanded (class 0), then nodes up to n_bufs - 2 levels below expanded open leaves (class 1; a node's rows outlive the
-//     expansions of that many levels below it), by rank, if fewer than the remaining number of splits have a larger gain.
+//     expansions of that many levels below it), by rank, if the selection can reach them with the splits that remain: a node
+//     comes after all nodes of a larger bottleneck, the smallest gain on the path from the open leaf to the node.  (Counting
+//     the nodes of a larger gain of their own instead puts off the descendants of small gains and takes others in their
+//     place: 21 against 15 rounds per tree on 200 k x 136.)
 //     One level ahead instead of three costs the data that peel a few rows off a large node at every split many rounds:
-//     rounds per tree 50 -> 23 (lambdarank 20 M x 200), 27 -> 21 (200 k x 136), 13 -> 11 (10.5 M x 28), 12 -> 10 (464 k x 90).
+//     rounds per tree 51 -> 27 (lambdarank 20 M x 200), 27 -> 15 (200 k x 136), 13 -> 11 (10.5 M x 28), 12 -> 10 (464 k x 90).
 // Measured per launch against the version that kept all nodes in the order and replayed every split: 20.6 -> 10.1 us
 // (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
 // (20 M x 200, 511 leaves).
@@ -206,22 +201,24 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     uint16_t* const par = reinterpret_cast<uint16_t*>(plan_lds + lay.par);
     uint16_t* const commit = reinterpret_cast<uint16_t*>(plan_lds + lay.commit);
     uint16_t* const chosen = reinterpret_cast<uint16_t*>(plan_lds + lay.chosen);
-    __shared__ unsigned long long s_open[64], s_exp[64], s_comm[64], s_cls1[64];
-    __shared__ unsigned long long s_c0[64], s_c1[64], s_prefix[64];  // batch candidates; prefix counts: class 0 | class 1 << 16 | committed << 32
-    __shared__ int s_nc, s_nnew, s_tie, s_stop, s_n0, s_npass;
+    __shared__ unsigned long long s_open[64], s_exp[64], s_comm[64];
+    __shared__ unsigned long long s_c0[64], s_c1[64];  // batch candidates of class 0 and 1
+    __shared__ int s_reach[64];                        // open splits by bottleneck, per 64 ranks
+    __shared__ int s_nc, s_nnew, s_tie, s_stop, s_nsup;
     __shared__ unsigned long long s_wsum[16];
     __shared__ unsigned long long s_units[8], s_first[8];  // (eight partial results: an atomic on one address is expanded into a loop over the lanes)
     const int n_nodes = st0.y, leaves0 = st0.z, commits0 = st0.w;
     const int n_expanded0 = st1.x, n_slots = st1.y;
     const int n_known = st2.z, n_list = st2.w, n_scan = st2.y;
     const int m_new = n_nodes - n_known;
+    const int new_buf = nodes[n_known + min(1023 - tid, m_new - 1)].buf;  // (used when the new nodes are ranked)
 
     for (int i = tid; i < n_nodes; i += 1024) { rank_of[i] = (uint16_t)NO_NODE; par[i] = (uint16_t)NO_NODE; shift[i] = 0; }
     for (int p = tid; p < n_list; p += 1024) {
         if (p >= 1024) mine = list[p];
         okey[p] = mine.key; oids[p] = mine.ids; oleaf[p] = (uint16_t)mine.leaf;
     }
-    if (tid < 64) { s_open[tid] = 0ull; s_exp[tid] = 0ull; s_comm[tid] = 0ull; s_cls1[tid] = 0ull; }
+    if (tid < 64) { s_open[tid] = 0ull; s_exp[tid] = 0ull; s_comm[tid] = 0ull; s_reach[tid] = 0; }
     if (tid == 0) { s_nc = 0; s_nnew = 0; s_tie = 0; s_stop = -1; }
     if (tid < 8) { s_units[tid] = 0ull; s_first[tid] = ~0ull; okey[n_list + tid] = 0ull; }
     if (tid < 4) nkey[m_new + tid] = 0ull;
@@ -281,13 +278,14 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         const uint32_t id = oids[p];
         const int q = p + shift[p];
         key[q] = okey[p]; ids[q] = id; leaf[q] = oleaf[p];
-        rank_of[id & 0xffffu] = (uint16_t)q;
+        rank_of[id & NODE_ID] = (uint16_t)q;
     }
     for (int t = 1023 - tid; t < m_new; t += 1024) {  // (from the last thread down: other wavefronts than the loop above, mostly)
         const unsigned long long kb = nkey[t];
         if (kb == 0ull) continue;
         const int q = shift[n_list + t];
-        key[q] = kb; ids[q] = (uint32_t)(n_known + t) | (NO_NODE << 16);
+        const int buf = t < 1024 ? new_buf : nodes[n_known + t].buf;
+        key[q] = kb; ids[q] = (uint32_t)(n_known + t) | ((uint32_t)buf << 12) | (NO_NODE << 16);
         leaf[q] = (uint16_t)(n_known + t == 0 ? 0u : NO_NODE);  // the root is an open leaf from the start
         rank_of[n_known + t] = (uint16_t)q;
     }
@@ -307,7 +305,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         }
         const uint32_t tie = (p + 1 < P && key[p + 1] == key[p]) ? 2u : 0u;
         info[p] = ((unsigned long long)(tie | (child != NO_NODE ? 1u : 0u)) << 32) | lo;
-        corder[p] = (uint16_t)NO_NODE;
+        corder[p] = (uint16_t)NO_NODE; shift[p] = 0;
         if (tie) s_tie = 1;
     }
     lds_barrier();
@@ -396,23 +394,27 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     // the masks after the commits
     for (int p0 = wave * 64; p0 < P; p0 += 1024) {
         const int p = p0 + lane;
-        bool open = false, expanded = false, committed = false, ahead = false;
+        bool open = false, expanded = false, committed = false;
         if (p < P) {
             expanded = (info[p] >> 32) & 1ull;
             committed = corder[p] != NO_NODE;
-            int q = par[p], level = 0;  // levels below the open leaf
-            if (!committed)
-                for (; q != (int)NO_NODE && corder[q] == NO_NODE; q = par[q]) ++level;
+            int worst = p, level = 0;  // the largest rank on the path to the open leaf, the levels on it
+            if (!committed) {
+                for (int q = par[p]; q != (int)NO_NODE && corder[q] == NO_NODE; q = par[q]) { ++level; worst = max(worst, q); }
+                atomicAdd(&shift[worst], 1);
+                atomicAdd(&s_reach[worst >> 6], 1);
+            }
             open = !committed && level == 0;
-            ahead = level > 0 && level <= n_bufs - 2;
+            const bool ahead = level > 0 && level <= n_bufs - 2 && !expanded;
+            reinterpret_cast<uint32_t*>(info)[2 * p + 1] = !ahead ? NO_NODE : (uint32_t)worst | (level > 1 ? FAR_AHEAD : 0u);  // (the flags are not read again)
         }
-        const unsigned long long mo = __ballot(open), me = __ballot(expanded), mc = __ballot(committed), ma = __ballot(ahead);
-        if (lane == 0) { s_open[p0 >> 6] = mo; s_exp[p0 >> 6] = me; s_comm[p0 >> 6] = mc; s_cls1[p0 >> 6] = ma; }
+        const unsigned long long mo = __ballot(open), me = __ballot(expanded), mc = __ballot(committed);
+        if (lane == 0) { s_open[p0 >> 6] = mo; s_exp[p0 >> 6] = me; s_comm[p0 >> 6] = mc; }
     }
     // outputs and node states of the splits committed above
     for (int c = tid; c < n_commit; c += 1024) {
         const int r = commit[c], lid = leaf_id_at(leaf, par, info, corder, leaves0, r), k = commits0 + c;
-        const int i = (int)(ids[r] & 0xffffu), ch = (int)(ids[r] >> 16);
+        const int i = (int)(ids[r] & NODE_ID), ch = (int)(ids[r] >> 16);
         const Node nd = nodes[i];
         out.t.split_leaf[k] = lid; out.t.split_feature[k] = nd.best.feature; out.t.split_bin[k] = nd.best.bin;
         out.t.split_gain[k] = nd.best.gain;
@@ -451,36 +453,42 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     int want = 1 + (spare > 0 ? spare : 0);
     if (want > remaining) want = remaining;
     if (want > batch_max) want = batch_max;
-    if (wave == 0) {
-        const int left = P - 64 * lane;
-        const unsigned long long used = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull;
-        const unsigned long long cw = s_comm[lane], ew = s_exp[lane], un = used & ~cw;
-        // A candidate is worth expanding if fewer than `remaining` nodes that can still be committed have a larger
-        // gain; the leaf the selection stopped at always is.
-        const int words = (P + 63) >> 6;
-        int nu = __popcll(un);
-        for (int o = 1; o < words; o <<= 1) { const int u = __shfl_up(nu, o); if (lane >= o) nu += u; }
-        const int before = nu - __popcll(un);
-        const unsigned long long pass = before >= remaining ? 0ull : nu <= remaining ? un : lowest_bits(un, remaining - before);
-        const unsigned long long c0 = s_open[lane] & ~ew & (pass | (lane == (stop >> 6) ? 1ull << (stop & 63) : 0ull));
-        const unsigned long long c1 = s_cls1[lane] & ~ew & pass;
-        const unsigned long long own = (unsigned long long)__popcll(c0) | ((unsigned long long)__popcll(c1) << 16) |
-                                       ((unsigned long long)__popcll(cw) << 32);
-        unsigned long long cnt = own;
-        for (int o = 1; o < words; o <<= 1) { const unsigned long long u = __shfl_up(cnt, o); if (lane >= o) cnt += u; }
-        s_c0[lane] = c0; s_c1[lane] = c1; s_prefix[lane] = cnt - own;
-        if (lane == words - 1) { s_n0 = (int)(cnt & 0xffffu); s_npass = (int)(cnt & 0xffffu) + (int)((cnt >> 16) & 0xffffu); }
+    // The last rank that the selection can reach as a bottleneck: fewer than `remaining` open splits have a better one.  Every
+    // wavefront finds it for itself, first the word of 64 ranks, then the rank.
+    // Nodes two or more levels ahead are guesses on guesses: while many splits remain they have to be within half of them.
+    // Rounds / expansions / time per tree with half and with all: 10.5 M x 28 10 / 283 / 2040 us and 10 / 319 / 2076 us,
+    // 20 M x 200 24 / 613 / 10.36 ms and 20 / 739 / 10.46 ms; the last 32 splits without that limit: 200 k x 136 699 -> 669 us.
+    const int in_front = wave_prefix(s_reach[lane]) - s_reach[lane];
+    auto last_reached = [&](int splits) {
+        auto last_below = [&](int n) { return 63 - __clzll((long long)__ballot(n < splits)); };  // (lane 0's always is)
+        const int w = last_below(in_front);
+        const int d = 64 * w + lane < P ? shift[64 * w + lane] : 0;
+        return 64 * w + last_below(__builtin_amdgcn_readlane(in_front, w) + wave_prefix(d) - d);
+    };
+    const int reach = last_reached(remaining), reach_far = last_reached(max(remaining / 2, min(remaining, 32)));
+    for (int p0 = wave * 64; p0 < P; p0 += 1024) {
+        const int p = p0 + lane, w = p0 >> 6;
+        const unsigned long long near = __ballot(p <= reach || p == stop);
+        const uint32_t worst = p < P ? (uint32_t)(info[p] >> 32) : NO_NODE;
+        const unsigned long long c1 = __ballot(worst != NO_NODE && (int)(worst & ~FAR_AHEAD) <= (worst & FAR_AHEAD ? reach_far : reach));
+        if (lane == 0) { s_c0[w] = s_open[w] & ~s_exp[w] & near; s_c1[w] = c1; }
     }
     lds_barrier();
-    const int n0 = s_n0, n_batch = min(s_npass, want);
-    for (int p = tid; p < P; p += 1024) {
-        const int w = p >> 6;
-        const unsigned long long bit = 1ull << (p & 63), below = bit - 1ull, pre = s_prefix[w];
+    // candidates of both classes (class 1 in the upper half) and committed splits in front of every word
+    const bool in = lane < ((P + 63) >> 6);
+    const int c01 = in ? __popcll(s_c0[lane]) | (__popcll(s_c1[lane]) << 16) : 0, cc = in ? __popcll(s_comm[lane]) : 0;
+    const int n_cls = wave_prefix(c01) - c01, n_comm = wave_prefix(cc) - cc;
+    const int n_all = __builtin_amdgcn_readlane(n_cls + c01, 63);
+    const int n0 = n_all & 0xffff, n_batch = min(n0 + (n_all >> 16), want);
+    for (int p0 = wave * 64; p0 < P; p0 += 1024) {
+        const int p = p0 + lane, w = p0 >> 6;
+        const int pre = __builtin_amdgcn_readlane(n_cls, w), gone = __builtin_amdgcn_readlane(n_comm, w);
+        if (p >= P) continue;
+        const unsigned long long bit = 1ull << lane, below = bit - 1ull;
         const unsigned long long cw = s_comm[w], c0 = s_c0[w], c1 = s_c1[w];
         uint32_t id = ids[p];
         if ((c0 | c1) & bit) {  // order of the batch: the leaf the selection stopped at, class 0 by gain, class 1 by gain
-            int o = (c0 & bit) ? (int)(pre & 0xffffu) + __popcll(c0 & below)
-                               : n0 + (int)((pre >> 16) & 0xffffu) + __popcll(c1 & below);
+            int o = (c0 & bit) ? (pre & 0xffff) + __popcll(c0 & below) : n0 + (pre >> 16) + __popcll(c1 & below);
             if (c0 & bit) o = p == stop ? 0 : p < stop ? o + 1 : o;  // (leaves of equal gain may be in front of it by rank)
             if (o < n_batch) {
                 chosen[o] = (uint16_t)p;
@@ -490,7 +498,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         if (!(cw & bit)) {
             PlanEntry e;
             e.key = key[p]; e.ids = id; e.leaf = (s_open[w] & bit) ? (uint32_t)leaf_id_at(leaf, par, info, corder, leaves0, p) : NO_NODE;
-            list[p - (int)((pre >> 32) & 0xffffu) - __popcll(cw & below)] = e;
+            list[p - gone - __popcll(cw & below)] = e;
         }
     }
     lds_barrier();
@@ -498,13 +506,18 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     BatchEntry be;
     be.n_seg = 0;
     if (tid < n_batch) {
-        const int i = (int)(ids[chosen[tid]] & 0xffffu);
+        const int p = chosen[tid], i = (int)(ids[p] & NODE_ID);
         const Node* nd = &nodes[i];
         be.begin = nd->begin; be.count = (int32_t)nd->count; be.node = i; be.buf = nd->buf;
         be.feature = nd->best.feature; be.bin = nd->best.bin;
         be.n_seg = (int)(((uint32_t)be.count + (uint32_t)seg_rows - 1u) / (uint32_t)seg_rows);
         be.new_slot = n_slots + tid;
-        be.child_buf = child_buffer(be.buf, n_bufs);
+        // the children's rows go to the first buffer that neither holds the node's own nor those of a node above it that
+        // may yet stay a leaf (at most n_bufs - 1 in all); with two in turn most of the time, rather than all in turn,
+        // the lists stay in the caches (2 M x 40 of 16-bit bins 1 %)
+        uint32_t taken = 1u << be.buf;
+        for (int q = par[p]; q != (int)NO_NODE && corder[q] == NO_NODE; q = par[q]) taken |= 1u << ((ids[q] >> 12) & 15u);
+        be.child_buf = __ffs((int)~taken) - 1;
         be.pad[0] = be.pad[1] = 0;
         nodes[i].expanded = 1;
         nodes[i].child = n_nodes + 2 * tid;
@@ -525,9 +538,9 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         batch_seg[tid] = be.seg_start;
     }
     if (seg_supers) {
-        if (tid == n_batch - 1) s_npass = (int)(incl >> 32);  // (not read again as what it was)
+        if (tid == n_batch - 1) s_nsup = (int)(incl >> 32);
         lds_barrier();
-        for (int t = tid; t < s_npass; t += 1024) super_counts[t] = 0;  // the count kernel adds to them
+        for (int t = tid; t < s_nsup; t += 1024) super_counts[t] = 0;  // the count kernel adds to them
     }
     if (tid == n_batch - 1) {
         step->n_part_items = (int)(uint32_t)incl;

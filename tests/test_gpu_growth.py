@@ -59,6 +59,34 @@ def test_tied_leaf_the_selection_stops_at_is_expanded_first():
     assert ctx.tree_stats() == (3, 4, 4, 9)   # rounds, nodes expanded, splits, nodes
 
 
+# Splits whose descendants have larger gains, several levels in a row (parity of features with a slight lead), and splits that
+# peel a few rows off a large node: what is expanded ahead of the commits, and whose rows have to outlive it.
+@pytest.mark.parametrize("kind,N,L", [("parity", 6000, 40), ("parity", 60_000, 255), ("peel", 20_000, 63), ("peel", 300_000, 255)])
+def test_growth_ahead_of_the_commits(kind, N, L):
+    F, nb = 16, 64
+    rng = np.random.default_rng(N + L)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    hi = bins >= nb // 2
+    if kind == "parity":
+        g = sum((-1.0) ** hi[:, 4 * k: 4 * k + 4].sum(1) * (1.0 + 0.1 * hi[:, 4 * k]) for k in range(3)) + 0.05 * hi[:, 0]
+    else:
+        g = np.exp(0.3 * (bins[:, :8] > nb - 6).sum(1) ** 2) - 0.05 * (bins[:, 8:12].sum(1) / nb) ** 2
+    g = (g + 0.1 * rng.normal(size=N)).astype(np.float32)
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L)
+    dbins = torch.from_numpy(bins).cuda()
+    e = oracle.grow_tree(bins, nb, g, h, 4, 4, 5, 0, L, min_data=20)
+    n = e.n_leaves
+    assert n > L // 2 and (np.diff(e.split_gain[: n - 1]) > 0).sum() > n // 10
+    for bound, layout in ((True, 1), (True, 2), (False, 3)):
+        ctx.bind_bins(dbins if bound else None)
+        t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 4, 4, 5, 0, L, min_data_in_leaf=20,
+                          row_layout=layout)
+        _check(t, e, N)
+        assert np.allclose(t.leaf_value.cpu().numpy()[:n], e.leaf_value[:n], rtol=1e-9, atol=1e-13)
+
+
 # both sides of the lines at which the partition takes other segments or sums its counts in two levels, ragged ends
 @pytest.mark.parametrize("N,F,L,layout", [(511, 4, 6, 1), (262_144, 5, 63, 1), (262_145, 5, 63, 2), (262_147, 16, 40, 3),
                                           (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3)])
