@@ -59,7 +59,8 @@ extern "C" {
 
 /* What moves when a leaf's rows are partitioned (results are identical for all of them). */
 #define QGBDT_ROWS_AUTO 0    /* ordered copies for an unbound matrix when the workspace holds them (QGBDT_WS_ROW_COPIES),
-                                else row ids, with the packed gradients when the matrix is 128 MB or more */
+                                else row ids with the quantized gradients in the same 32 bits where both fit, else row
+                                ids, with the packed gradients when the matrix is 128 MB or more */
 #define QGBDT_ROWS_IDS 1     /* row ids only; histogram builds gather bin rows and packed gradients */
 #define QGBDT_ROWS_IDS_GH 2  /* row ids and packed gradients; histogram builds gather the bin rows */
 #define QGBDT_ROWS_ORDERED 3 /* row ids, packed gradients and bin rows: every build reads contiguous memory

@@ -422,6 +422,7 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
     rows.gh_pos = 0;  // the caller's packed gradients are in original row order
     IdxSet idx;
     for (int b = 0; b <= ROW_BUFS; ++b) { rows.bins[b] = (const uint8_t*)bins; rows.gh[b] = gh; idx.p[b] = const_cast<int32_t*>(row_idx); }
+    rows.code = PLAIN_ROWS;
     rc = launch_hist(ctx, plan, rows, idx, row_idx != nullptr, ((uintptr_t)bins & 15) == 0,
                      ctx->hist_entries, ctx->hist_counts, hist_out,
                      (count + hist_target_rows(plan, count, 1) - 1) / hist_target_rows(plan, count, 1),  // the build's row groups

@@ -191,7 +191,7 @@ __device__ __forceinline__ uint32_t load_bins4(const uint8_t* p) {
     return *reinterpret_cast<const uint32_t*>(p);
 }
 
-template <int W, bool IDX, int U, bool RAG, int BB>
+template <int W, int IDX, int U, bool RAG, int BB>
 __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
                                                     const int32_t* __restrict__ table_counts, int64_t* hist_base,
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;  // row-group lanes (a multiple of 8)
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX != 0, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
@@ -262,6 +262,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
             __syncthreads();
             const int32_t* ib = IDX ? idx + cbegin : nullptr;
             const int64_t row_base = IDX ? 0 : en.begin + cbegin;
+            auto row_id = [&](int64_t e) { return IDX == 2 ? e & src.code.id_mask : e; };
             if (wave * S < crow) {
                 // three stages in flight per wavefront: row ids of block n+2, bin dwords and packed
                 // gradients of block n+1, LDS atomics of block n
@@ -273,29 +274,29 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = min(wave * S + u * rpi + r, crow - 1);
-                        rows[u] = IDX ? (int64_t)ib[p] : row_base + p;
+                        rows[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        d[u] = load_bins4<RAG>(colbase + rows[u] * row_bytes);
-                        gv[u] = gh[gpos ? cbegin + min(wave * S + u * rpi + r, crow - 1) : rows[u]];
+                        d[u] = load_bins4<RAG>(colbase + row_id(rows[u]) * row_bytes);
+                        gv[u] = IDX == 2 ? src.code.gh((uint32_t)rows[u]) : (int)gh[gpos ? cbegin + min(wave * S + u * rpi + r, crow - 1) : rows[u]];
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = min((wave + n_waves) * S + u * rpi + r, crow - 1);
-                        rown[u] = IDX ? (int64_t)ib[p] : row_base + p;
+                        rown[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
                     }
                 }
                 for (int ro = wave * S; ro < crow; ro += n_waves * S) {
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        dn[u] = load_bins4<RAG>(colbase + rown[u] * row_bytes);
-                        gn[u] = gh[gpos ? cbegin + min(ro + n_waves * S + u * rpi + r, crow - 1) : rown[u]];
+                        dn[u] = load_bins4<RAG>(colbase + row_id(rown[u]) * row_bytes);
+                        gn[u] = IDX == 2 ? src.code.gh((uint32_t)rown[u]) : (int)gh[gpos ? cbegin + min(ro + n_waves * S + u * rpi + r, crow - 1) : rown[u]];
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {  // row ids two blocks ahead (clamped when past the end)
                         const int p = min(ro + 2 * n_waves * S + u * rpi + r, crow - 1);
-                        rown[u] = IDX ? (int64_t)ib[p] : row_base + p;
+                        rown[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
                     }
                     // lanes without a place in the tile sit out (their loads alias lane 0's: atomics on the
                     // same words would serialize); rows past the end are not branched around, they add zero
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
 // 100 k x 50 11.1 -> 9.3 us, 2 M x 40 of 16-bit bins 28.8 -> 27.2 us.
 // The four dwords of a piece and the bins inside a dword are taken in an order that rotates with the row, so that the lanes of
 // an LDS atomic spread over 16 columns per piece.
-template <int W, bool IDX, bool RAG, int BB>
+template <int W, int IDX, bool RAG, int BB>
 __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
                                                     const int32_t* __restrict__ table_counts, int64_t* hist_base,
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX != 0, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);  // at least 16 bytes
@@ -410,13 +411,15 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
             const int64_t row_base = IDX ? 0 : en.begin + cbegin;
             if (wave * rpi < crow) {
                 // three stages in flight as in hist_kernel; rows past the end read the last one again and add zero
-                auto row_at = [&](int p) { return IDX ? (int64_t)ib[min(p, crow - 1)] : row_base + min(p, crow - 1); };
+                auto row_at = [&](int p) { return IDX ? (int64_t)(uint32_t)ib[min(p, crow - 1)] : row_base + min(p, crow - 1); };
                 auto load_row = [&](int64_t row) {
                     uint4 v;
-                    __builtin_memcpy(&v, colbase + row * row_bytes, 16);
+                    __builtin_memcpy(&v, colbase + (IDX == 2 ? row & src.code.id_mask : row) * row_bytes, 16);
                     return v;
                 };
-                auto load_gh = [&](int p, int64_t row) { return (int)gh[gpos ? cbegin + min(p, crow - 1) : row]; };
+                auto load_gh = [&](int p, int64_t row) {
+                    return IDX == 2 ? src.code.gh((uint32_t)row) : (int)gh[gpos ? cbegin + min(p, crow - 1) : row];
+                };
                 const int step_rows = n_waves * rpi;
                 int p = wave * rpi + r;
                 int64_t row = row_at(p), rown = row_at(p + step_rows);
@@ -462,7 +465,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
 // U = 2 instructions per block of a wavefront: the LDS atomics of 16 wavefronts cover the loads' latency, and smaller blocks
 // share a group's rows out more evenly (trees with 4 / 2: 400 k x 2000 1239 / 1212 us, 200 k x 136 947 / 931 us, 20 M x 200
 // 12190 / 12160 us; 8: 1283, 1045, 12920 us).
-template <int W, bool IDX, int V, int U, bool SKIP>
+template <int W, int IDX, int V, int U, bool SKIP>
 __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet idxs,
                                                                     const HistEntry* __restrict__ entries,
                                                                     const int32_t* __restrict__ table_counts,
@@ -481,7 +484,7 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX != 0, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);  // a multiple of V
@@ -549,6 +552,7 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
             __syncthreads();
             const int32_t* ib = IDX ? idx + cbegin : nullptr;
             const int64_t row_base = IDX ? 0 : en.begin + cbegin;
+            auto row_id = [&](int64_t e) { return IDX == 2 ? e & src.code.id_mask : e; };
             if (wave * S < crow) {
                 // three stages in flight: row ids of block n+2, bin pieces and packed gradients of
                 // block n+1, LDS atomics of block n; rows past the end re-read the last row and add zero
@@ -560,29 +564,29 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = min(wave * S + u * rpi + r, crow - 1);
-                        rows[u] = IDX ? (int64_t)ib[p] : row_base + p;
+                        rows[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        d[u] = *reinterpret_cast<const vec*>(colbase + rows[u] * F);
-                        gv[u] = gh[gpos ? cbegin + min(wave * S + u * rpi + r, crow - 1) : rows[u]];
+                        d[u] = *reinterpret_cast<const vec*>(colbase + row_id(rows[u]) * F);
+                        gv[u] = IDX == 2 ? src.code.gh((uint32_t)rows[u]) : (int)gh[gpos ? cbegin + min(wave * S + u * rpi + r, crow - 1) : rows[u]];
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = min((wave + n_waves) * S + u * rpi + r, crow - 1);
-                        rown[u] = IDX ? (int64_t)ib[p] : row_base + p;
+                        rown[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
                     }
                 }
                 for (int ro = wave * S; ro < crow; ro += n_waves * S) {
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        dn[u] = *reinterpret_cast<const vec*>(colbase + rown[u] * F);
-                        gn[u] = gh[gpos ? cbegin + min(ro + n_waves * S + u * rpi + r, crow - 1) : rown[u]];
+                        dn[u] = *reinterpret_cast<const vec*>(colbase + row_id(rown[u]) * F);
+                        gn[u] = IDX == 2 ? src.code.gh((uint32_t)rown[u]) : (int)gh[gpos ? cbegin + min(ro + n_waves * S + u * rpi + r, crow - 1) : rown[u]];
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = min(ro + 2 * n_waves * S + u * rpi + r, crow - 1);
-                        rown[u] = IDX ? (int64_t)ib[p] : row_base + p;
+                        rown[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
                     }
                     if (lane_on) {  // lanes beyond the tile's width sit out (their loads alias piece 0)
 #pragma unroll
@@ -907,8 +911,9 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
             const int64_t cend = min(gend, cbegin + (int64_t)plan.chunk_rows);
             __syncthreads();
             for (int64_t p = cbegin + wave * rpi + r; p < cend; p += n_waves * rpi) {
-                const int64_t i = idx ? (int64_t)idx[p] : en.begin + p;
-                const word v = Acc<W>::expand(gh[gpos ? p : i], hmul);
+                const uint32_t e = idx ? (uint32_t)idx[p] : 0u;
+                const int64_t i = idx ? (int64_t)(e & src.code.id_mask) : en.begin + p;
+                const word v = Acc<W>::expand(idx && src.code.on() ? src.code.gh(e) : (int)gh[gpos ? p : i], hmul);
                 const BIN* row = bins + i * F + f0;
                 for (int f = fl; f < ft; f += C) Acc<W>::add(&lds[(uint32_t)row[f] * ft + f], v);
             }
@@ -1184,7 +1189,7 @@ int launch_set_hist_table(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, i
 
 // The wide-row kernels may be given more local bins than the default limit of dynamic LDS (the 64-feature tiles
 // of 64-bit words that frequent-bin skipping makes worthwhile): the runtime is told so once per context.
-template <int W, bool IDX, int V, bool S>
+template <int W, int IDX, int V, bool S>
 static hipError_t allow_lds(int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(hist_wide_kernel<W, IDX, V, 2, S>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -1205,14 +1210,14 @@ int prepare_hist_kernels(qgbdt_ctx* ctx) {
             if (hp.wide_v > 0 && hp.lds_bytes > most) most = hp.lds_bytes;
         }
     if (most <= 64 * 1024) return QGBDT_OK;
-    QG_HIP(ctx, (allow_lds<16, false, 16, false>(most)));  QG_HIP(ctx, (allow_lds<16, false, 16, true>(most)));
-    QG_HIP(ctx, (allow_lds<16, true, 16, false>(most)));   QG_HIP(ctx, (allow_lds<16, true, 16, true>(most)));
-    QG_HIP(ctx, (allow_lds<16, false, 8, false>(most)));   QG_HIP(ctx, (allow_lds<16, false, 8, true>(most)));
-    QG_HIP(ctx, (allow_lds<16, true, 8, false>(most)));    QG_HIP(ctx, (allow_lds<16, true, 8, true>(most)));
-    QG_HIP(ctx, (allow_lds<32, false, 16, false>(most)));  QG_HIP(ctx, (allow_lds<32, false, 16, true>(most)));
-    QG_HIP(ctx, (allow_lds<32, true, 16, false>(most)));   QG_HIP(ctx, (allow_lds<32, true, 16, true>(most)));
-    QG_HIP(ctx, (allow_lds<32, false, 8, false>(most)));   QG_HIP(ctx, (allow_lds<32, false, 8, true>(most)));
-    QG_HIP(ctx, (allow_lds<32, true, 8, false>(most)));    QG_HIP(ctx, (allow_lds<32, true, 8, true>(most)));
+#define QG_ALLOW(W_, V_)                                                                                                  \
+    do {                                                                                                                  \
+        QG_HIP(ctx, (allow_lds<W_, 0, V_, false>(most))); QG_HIP(ctx, (allow_lds<W_, 0, V_, true>(most)));                \
+        QG_HIP(ctx, (allow_lds<W_, 1, V_, false>(most))); QG_HIP(ctx, (allow_lds<W_, 1, V_, true>(most)));                \
+        QG_HIP(ctx, (allow_lds<W_, 2, V_, false>(most))); QG_HIP(ctx, (allow_lds<W_, 2, V_, true>(most)));                \
+    } while (0)
+    QG_ALLOW(16, 16); QG_ALLOW(16, 8); QG_ALLOW(32, 16); QG_ALLOW(32, 8);
+#undef QG_ALLOW
     return QGBDT_OK;
 }
 
@@ -1240,6 +1245,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     const int64_t lanes = (groups + 7) / 8 * 8;
     dim3 grid((unsigned)(lanes * plan.n_tiles)), block(plan.threads);
     const bool fast = !plan.bytewise;
+    const int mode = !use_idx ? 0 : rows.code.on() ? 2 : 1;  // contiguous rows, row ids, row ids with their gradients
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->profiling && ctx->ev_used + 2 <= ctx->ev_cap) {
         for (int k = 0; k < 2; ++k)
@@ -1275,9 +1281,9 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #define QG_LAUNCH_WIDE_V(W_, IDX_) \
     if (plan.wide_v == 16) QG_LAUNCH_WIDE(W_, IDX_, 16, 2); else QG_LAUNCH_WIDE(W_, IDX_, 8, 2)
         if (plan.acc_width == 16) {
-            if (use_idx) { QG_LAUNCH_WIDE_V(16, true); } else { QG_LAUNCH_WIDE_V(16, false); }
+            if (mode == 2) { QG_LAUNCH_WIDE_V(16, 2); } else if (mode == 1) { QG_LAUNCH_WIDE_V(16, 1); } else { QG_LAUNCH_WIDE_V(16, 0); }
         } else {
-            if (use_idx) { QG_LAUNCH_WIDE_V(32, true); } else { QG_LAUNCH_WIDE_V(32, false); }
+            if (mode == 2) { QG_LAUNCH_WIDE_V(32, 2); } else if (mode == 1) { QG_LAUNCH_WIDE_V(32, 1); } else { QG_LAUNCH_WIDE_V(32, 0); }
         }
 #undef QG_LAUNCH_WIDE_V
 #undef QG_LAUNCH_WIDE
@@ -1295,9 +1301,9 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         else QG_LAUNCH_PIECE_K(W_, IDX_, true, 1);                                                                  \
     } while (0)
         if (plan.acc_width == 16) {
-            if (use_idx) QG_LAUNCH_PIECE(16, true); else QG_LAUNCH_PIECE(16, false);
+            if (mode == 2) QG_LAUNCH_PIECE(16, 2); else if (mode == 1) QG_LAUNCH_PIECE(16, 1); else QG_LAUNCH_PIECE(16, 0);
         } else {
-            if (use_idx) QG_LAUNCH_PIECE(32, true); else QG_LAUNCH_PIECE(32, false);
+            if (mode == 2) QG_LAUNCH_PIECE(32, 2); else if (mode == 1) QG_LAUNCH_PIECE(32, 1); else QG_LAUNCH_PIECE(32, 0);
         }
 #undef QG_LAUNCH_PIECE
 #undef QG_LAUNCH_PIECE_K
@@ -1323,9 +1329,9 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         default: QG_LAUNCH_HIST(W_, IDX_, 1); break;                                    \
     }
         if (plan.acc_width == 16) {
-            if (use_idx) { QG_LAUNCH_HIST_U(16, true) } else { QG_LAUNCH_HIST_U(16, false) }
+            if (mode == 2) { QG_LAUNCH_HIST_U(16, 2) } else if (mode == 1) { QG_LAUNCH_HIST_U(16, 1) } else { QG_LAUNCH_HIST_U(16, 0) }
         } else {
-            if (use_idx) { QG_LAUNCH_HIST_U(32, true) } else { QG_LAUNCH_HIST_U(32, false) }
+            if (mode == 2) { QG_LAUNCH_HIST_U(32, 2) } else if (mode == 1) { QG_LAUNCH_HIST_U(32, 1) } else { QG_LAUNCH_HIST_U(32, 0) }
         }
 #undef QG_LAUNCH_HIST_U
 #undef QG_LAUNCH_HIST

@@ -224,23 +224,28 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
         const int sbegin = seg * PART_SEG, n = min(nd.count - sbegin, PART_SEG);  // rows of the segment, inside the node's slice
         const int32_t* src = idxs.p[nd.buf] + nd.begin + sbegin;
         const bool identity = ordered || nd.buf == BUF_ORIGINAL;  // the root's list is the identity
-        int64_t row[R];
+        uint32_t row[R];
         int v[R];
+        // (rows past the end: the last one again, not counted; the entries are masked when all are on their way)
+        if (identity) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int r = min((wave * R + u) * 64 + lane, n - 1);  // (past the end: the last row again, not counted)
-            row[u] = identity ? (int64_t)(sbegin + r) : (int64_t)src[r];
+            for (int u = 0; u < R; ++u) row[u] = (uint32_t)(sbegin + min((wave * R + u) * 64 + lane, n - 1));
+        } else {
+#pragma unroll
+            for (int u = 0; u < R; ++u) row[u] = (uint32_t)src[min((wave * R + u) * 64 + lane, n - 1)];
+#pragma unroll
+            for (int u = 0; u < R; ++u) row[u] &= rows.code.id_mask;
         }
         if (bins_t && !ordered) {
             // with a feature-major copy of the matrix the split feature's column is read: the ascending row
             // ids of a node then fall into few sectors, where the row-major matrix costs one sector per row
             const uint8_t* col = bins_t + (int64_t)nd.feature * n_rows * bb;
 #pragma unroll
-            for (int u = 0; u < R; ++u) v[u] = bin_at(col, row[u], bb);
+            for (int u = 0; u < R; ++u) v[u] = bin_at(col, (int64_t)row[u], bb);
         } else {
             const uint8_t* brow = rows.bins[ordered ? nd.buf : BUF_ORIGINAL] + (ordered ? nd.begin * (int64_t)F : 0);
 #pragma unroll
-            for (int u = 0; u < R; ++u) v[u] = bin_at(brow, row[u] * F + nd.feature, bb);
+            for (int u = 0; u < R; ++u) v[u] = bin_at(brow, (int64_t)row[u] * F + nd.feature, bb);
         }
         int cnt = 0;
         unsigned long long mine = 0ull;  // lane u keeps the wavefront's u-th mask
@@ -393,6 +398,10 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
             const int r = min((wave * R + u) * 64 + lane, n - 1);
             v[u] = identity ? (int32_t)(nd.begin + sbegin + r) : src[r];
             g16[u] = MODE >= 1 ? gsrc[r] : 0;
+        }
+        if (MODE == 0 && identity && rows.code.on()) {  // the root's children are the first lists: entries with their gradients
+#pragma unroll
+            for (int u = 0; u < R; ++u) v[u] = (int32_t)rows.code.entry((uint32_t)v[u], rows.gh[BUF_ORIGINAL][v[u]]);
         }
         const unsigned long long mk = lane < PART_SEG / 64 ? masks[(int64_t)item * (PART_SEG / 64) + lane] : 0ull;
         int before = SUPER > 1 && lane < seg - sup * SUPER ? seg_counts[item - (seg - sup * SUPER) + lane] : 0;

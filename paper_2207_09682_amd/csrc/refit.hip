@@ -15,6 +15,7 @@ namespace qgbdt {
 struct RefitTree {  // the tree that has just been grown
     const float2* pairs;
     IdxSet idxs;
+    uint32_t id_mask;  // row id of a list's entry
     int32_t* out;
     const RefitUnit* units;
     const int32_t* n_units;
@@ -55,6 +56,7 @@ __global__ __launch_bounds__(256) void refit_partial_kernel(SRC src, int parts, 
         for (int k = 0; k < 4; ++k) {
             const int64_t j = min(j0 + 64 * k + lane, b - 1);
             r[k] = identity ? (int32_t)(un.begin + j) : ids[j];
+            if constexpr (TREE) r[k] &= (int32_t)src.id_mask;
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -156,9 +158,9 @@ int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* 
     return QGBDT_OK;
 }
 
-int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out) {
+int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, uint32_t id_mask, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out) {
     const RefitGrid rg = refit_grid(ctx, ctx->shape.max_leaves);
-    const RefitTree src{ctx->ghf, idx, row_idx_out, ctx->refit_units, units_in_use(ctx)};
+    const RefitTree src{ctx->ghf, idx, id_mask, row_idx_out, ctx->refit_units, units_in_use(ctx)};
     hipLaunchKernelGGL(refit_partial_kernel<RefitTree>, rg.grid(), dim3(256), 0, ctx->stream, src, rg.parts, rg.blocks_per_part,
                        ctx->refit_partial);
     hipLaunchKernelGGL(refit_final_kernel, dim3(ctx->shape.max_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial,

@@ -644,11 +644,20 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     // build then reads them in sequence, which takes one of the ~2.2 cache lines per sparse narrow row away.
     // A matrix that the caches hold gathers cheaply anyway and gains nothing from the move (1 M x 28: 1.15 to
     // 1.21 against 1.16 ms per tree).
+    // Where the row id and the quantized gradients fit 32 bits together the list's entries hold both (RowCode) and neither
+    // is gathered nor moved apart.
     int layout = p->row_layout;
     if (layout == QGBDT_ROWS_AUTO)
         layout = (ctx->ordered != 0 && !bins_t) ? QGBDT_ROWS_ORDERED
                  : ((int64_t)N * F * ctx->shape.bin_bytes >= (int64_t)128 << 20) ? QGBDT_ROWS_IDS_GH : QGBDT_ROWS_IDS;
     const bool ordered = layout == QGBDT_ROWS_ORDERED;
+    rows.code = PLAIN_ROWS;
+    int id_bits = 1;
+    while (((int64_t)1 << id_bits) < N) ++id_bits;
+    if (p->row_layout == QGBDT_ROWS_AUTO && !ordered && id_bits + p->bits_g + p->bits_h <= 32) {
+        rows.code = {(uint32_t)(((uint64_t)1 << id_bits) - 1), id_bits, p->bits_h, 32 - p->bits_g, p->bits_h == 0 ? 1 : 0};
+        layout = QGBDT_ROWS_IDS;
+    }
     const bool gh_lists = layout != QGBDT_ROWS_IDS;
     if (ordered && !ctx->ordered)
         return set_error(ctx, QGBDT_E_WORKSPACE, "the workspace has no room for leaf-ordered copies of the rows");
@@ -731,7 +740,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     hipLaunchKernelGGL(tree_finalize_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->delta,
                        refit_parts(N), refit_extra(N), ctx->refit_units, ctx->refit_leaves, out);
     QG_HIP(ctx, hipGetLastError());
-    return launch_gather_refit(ctx, idxs, row_idx_out, out.t.n_leaves, out.t.leaf_value);
+    return launch_gather_refit(ctx, idxs, rows.code.id_mask, row_idx_out, out.t.n_leaves, out.t.leaf_value);
 }
 
 }  // namespace qgbdt

@@ -87,6 +87,28 @@ def test_growth_ahead_of_the_commits(kind, N, L):
         assert np.allclose(t.leaf_value.cpu().numpy()[:n], e.leaf_value[:n], rtol=1e-9, atol=1e-13)
 
 
+# row lists whose entries carry the row's quantized gradients: id and gradients fill the 32 bits, miss them by one, constant
+# hessians; on the element-wise, the dword, the 16-byte-piece and both wide-row kernels
+@pytest.mark.parametrize("N,bits_g,bits_h", [(65_536, 8, 8), (65_537, 8, 8), (131_072, 8, 0), (16_385, 2, 8), (40_000, 8, 2)])
+@pytest.mark.parametrize("F,nb,bb", [(3, 64, 1), (13, 64, 1), (28, 64, 1), (45, 300, 2), (72, 255, 1), (80, 63, 1)])
+def test_row_entries_with_gradients(N, bits_g, bits_h, F, nb, bb):
+    L = 24
+    rng = np.random.default_rng(N + F + bits_g)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint16 if bb == 2 else np.uint8)
+    x = bins[:, :3].astype(np.float64) / nb - 0.5
+    g = (2 * x[:, 0] + 3 * x[:, 1] * x[:, 2] + 0.5 * rng.normal(size=N)).astype(np.float32)
+    h = np.full(N, 0.25, np.float32) if bits_h == 0 else rng.uniform(0.0, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L, bin_bytes=bb)
+    dbins = torch.from_numpy(bins).cuda()
+    e = oracle.grow_tree(bins, nb, g, h, bits_g, bits_h, 5, 0, L, min_data=20)
+    assert e.n_leaves == L
+    ctx.bind_bins(dbins)
+    t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), bits_g, bits_h, 5, 0, L, min_data_in_leaf=20)
+    _check(t, e, N)
+    assert np.allclose(t.leaf_value.cpu().numpy()[:L], e.leaf_value[:L], rtol=1e-9, atol=1e-13)
+
+
 # both sides of the lines at which the partition takes other segments or sums its counts in two levels, ragged ends
 @pytest.mark.parametrize("N,F,L,layout", [(511, 4, 6, 1), (262_144, 5, 63, 1), (262_145, 5, 63, 2), (262_147, 16, 40, 3),
                                           (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3)])
