@@ -185,7 +185,7 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
 }
 
 static void free_host(qgbdt_ctx* c) {
-    if (c->host_state) (void)hipHostFree(c->host_state);
+    if (c->report) (void)hipHostFree(c->report);
     if (c->ev) {
         for (int i = 0; i < c->ev_cap; ++i)
             if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
@@ -292,8 +292,9 @@ int qgbdt_create(qgbdt_ctx** out, const qgbdt_shape* shape, void* stream) {
         }
         c->static_scratch = g_static_scratch_ptr[c->device];
     }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->host_state), sizeof(StepState), hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->report), sizeof(TreeReport), hipHostMallocDefault) != hipSuccess)
         rc = set_error(c, QGBDT_E_ALLOC, "hipHostMalloc failed");
+    else *c->report = TreeReport{};
     // kernels whose local bins or bookkeeping exceed the default limit of dynamic LDS are told so once
     if (rc == QGBDT_OK) rc = prepare_hist_kernels(c);
     if (rc == QGBDT_OK) rc = prepare_tree_kernels(c);
@@ -747,9 +748,9 @@ int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g, int32_t b
 }
 
 int qgbdt_tree_stats(const qgbdt_ctx* ctx, int32_t* out4) {
-    if (!ctx || !out4 || !ctx->host_state) return QGBDT_E_INVALID_ARG;
-    out4[0] = ctx->host_state->rounds; out4[1] = ctx->host_state->n_expanded;
-    out4[2] = ctx->host_state->n_commits; out4[3] = ctx->host_state->n_nodes;
+    if (!ctx || !out4 || !ctx->report) return QGBDT_E_INVALID_ARG;
+    out4[0] = ctx->report->rounds; out4[1] = ctx->report->n_expanded;
+    out4[2] = ctx->report->n_commits; out4[3] = ctx->report->n_nodes;
     return QGBDT_OK;
 }
 

@@ -44,6 +44,13 @@ struct StepState {
     int64_t prof_builds;                      // histogram builds served by those launches
 };
 
+// What a plan kernel tells the host when it is asked to, in pinned memory: how far the tree is, and behind it the number of the
+// request with the answer to "is it finished" in the lowest bit.
+struct TreeReport {
+    int32_t rounds, n_expanded, n_commits, n_nodes;
+    uint64_t answer;
+};
+
 // One node expanded in the current round, with everything the partition kernels need of it (one 56-byte record
 // instead of a look-up in the node table that depends on it).
 struct BatchEntry {
@@ -267,7 +274,8 @@ struct qgbdt_ctx {
     int2* refit_leaves;          // [max_leaves + 1] first unit and units of a leaf; behind the leaves: number of units
     double* refit_partial;       // [refit_parts][max_leaves + REFIT_EXTRA][2], a leaf's pieces consecutive
     int64_t* tmp_i64;            // [8]
-    qgbdt::StepState* host_state;  // pinned host copy
+    qgbdt::TreeReport* report;     // pinned host memory
+    uint64_t report_seq;           // requests so far
     // profiling
     int profiling;
     hipEvent_t* ev;
@@ -405,7 +413,7 @@ int prepare_tree_kernels(qgbdt_ctx* ctx);
 int launch_batch_partition_scatter(qgbdt_ctx* ctx, const RowSource& rows, bool ordered, const HistPlan& plan);
 int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* row_idx, const int64_t* leaf_begin,
                  const int64_t* leaf_count, int n_leaves, double* value_out);
-// tree growth (leaves laid out): the row lists to the caller's, and the leaf values
+// tree growth (leaves laid out; nothing happens while the tree is not finished): the row lists to the caller's, and the leaf values
 int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, uint32_t id_mask, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out);
 int launch_logistic_gradients(qgbdt_ctx* ctx, const float* score, const float* label, int64_t n, float* g, float* h);
 int launch_lambdarank_gradients(qgbdt_ctx* ctx, const float* score, const float* label, int64_t n, int group,

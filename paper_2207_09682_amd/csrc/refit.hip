@@ -19,6 +19,7 @@ struct RefitTree {  // the tree that has just been grown
     int32_t* out;
     const RefitUnit* units;
     const int32_t* n_units;
+    const int32_t* done;  // 0: the tree is not finished and its leaves are not laid out
 };
 struct RefitList {  // leaves that the caller lists
     const float *g, *h;
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(256) void refit_partial_kernel(SRC src, int parts, 
     refit_unit_of(blocks_per_part, part, u);
     RefitUnit un;
     if constexpr (TREE) {
-        if (u >= *src.n_units) return;
+        if (*src.done == 0 || u >= *src.n_units) return;
         un = src.units[u];
     } else {
         if (!find_unit(src.list, parts, u, un)) return;
@@ -80,8 +81,10 @@ __global__ __launch_bounds__(256) void refit_partial_kernel(SRC src, int parts, 
 // One workgroup per leaf: the sums of its pieces.
 __global__ __launch_bounds__(256) void refit_final_kernel(const double* __restrict__ partial, int parts,
                                                           const int2* __restrict__ leaves,
-                                                          const int32_t* __restrict__ n_leaves_dev, double* __restrict__ value) {
+                                                          const int32_t* __restrict__ n_leaves_dev,
+                                                          const int32_t* __restrict__ done, double* __restrict__ value) {
     const int l = blockIdx.x;
+    if (done && *done == 0) return;
     if (n_leaves_dev && l >= *n_leaves_dev) {  // uniform over the workgroup
         if (threadIdx.x == 0) value[l] = 0.0;
         return;
@@ -153,18 +156,18 @@ int launch_refit(qgbdt_ctx* ctx, const float* g, const float* h, const int32_t* 
     hipLaunchKernelGGL(refit_partial_kernel<RefitList>, rg.grid(), dim3(256), 0, ctx->stream, src, rg.parts, rg.blocks_per_part,
                        ctx->refit_partial);
     hipLaunchKernelGGL(refit_final_kernel, dim3(n_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial, rg.parts,
-                       ctx->refit_leaves, nullptr, value_out);
+                       ctx->refit_leaves, nullptr, nullptr, value_out);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
 
 int launch_gather_refit(qgbdt_ctx* ctx, const IdxSet& idx, uint32_t id_mask, int32_t* row_idx_out, const int32_t* n_leaves_dev, double* value_out) {
     const RefitGrid rg = refit_grid(ctx, ctx->shape.max_leaves);
-    const RefitTree src{ctx->ghf, idx, id_mask, row_idx_out, ctx->refit_units, units_in_use(ctx)};
+    const RefitTree src{ctx->ghf, idx, id_mask, row_idx_out, ctx->refit_units, units_in_use(ctx), &ctx->step->done};
     hipLaunchKernelGGL(refit_partial_kernel<RefitTree>, rg.grid(), dim3(256), 0, ctx->stream, src, rg.parts, rg.blocks_per_part,
                        ctx->refit_partial);
     hipLaunchKernelGGL(refit_final_kernel, dim3(ctx->shape.max_leaves), dim3(256), 0, ctx->stream, ctx->refit_partial,
-                       rg.parts, ctx->refit_leaves, n_leaves_dev, value_out);
+                       rg.parts, ctx->refit_leaves, n_leaves_dev, &ctx->step->done, value_out);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

@@ -20,9 +20,11 @@
 // survive the expansions of the levels below it that may run ahead).  Split numbers and leaf ids are
 // assigned at commit time, so the result equals the sequential one bit for bit.
 //
-// The host enqueues whole rounds without reading anything back; after the expected
-// number of rounds it reads one status word to learn whether more are needed.
+// The host enqueues whole rounds without reading anything back, as many as the last
+// tree took, and behind them the passes over the finished leaves, which return at once
+// if the tree is not finished; a word in pinned memory tells it whether more rounds are needed.
 #include <algorithm>
+#include <chrono>
 
 #include "refit_device.h"
 #include "split_device.h"
@@ -33,6 +35,13 @@ struct TreeOut {
     qgbdt_tree t;
     int32_t max_leaves;
 };
+
+// The answer to the host's request `seq` (0: none).
+__device__ __forceinline__ void report_to_host(TreeReport* r, uint64_t seq, bool done, int rounds, int n_expanded, int n_commits, int n_nodes) {
+    if (seq == 0) return;
+    r->rounds = rounds; r->n_expanded = n_expanded; r->n_commits = n_commits; r->n_nodes = n_nodes;
+    __hip_atomic_store(&r->answer, seq * 2 + (done ? 1 : 0), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 __device__ __forceinline__ void clear_split(qgbdt_split& s) {
     s.gain = 0.0; s.feature = -1; s.bin = -1;
@@ -175,7 +184,7 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 // (20 M x 200, 511 leaves).
 __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch, int32_t* batch_seg,
                                                          int32_t* super_counts, PlanEntry* list, int32_t* hist_counts, int F, int n_cand, int num_leaves,
-                                                         int batch_max, int max_expand, int seg_rows, int seg_supers, int n_bufs, TreeOut out,
+                                                         int batch_max, int max_expand, int seg_rows, int seg_supers, int n_bufs, TreeReport* report, uint64_t report_seq, TreeOut out,
                                                          const FeatCand* __restrict__ cand,
                                                          const ScanPair* __restrict__ scan_pairs) {
     // the fields of the growth state this kernel needs and (for the first 1024 ranks) the kept order, in loads that are
@@ -186,7 +195,10 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     const int4* sp = reinterpret_cast<const int4*>(step);
     const int4 st0 = sp[0], st1 = sp[1], st2 = sp[2];
     PlanEntry mine = list[min(tid, max_nodes - 1)];
-    if (st0.x) return;  // done
+    if (st0.x) {  // done
+        if (tid == 0) report_to_host(report, report_seq, true, st1.w, st1.x, st0.w, st0.y);
+        return;
+    }
     extern __shared__ unsigned char plan_lds[];
     const PlanLds lay = plan_lds_layout(max_nodes, batch_max, num_leaves);
     unsigned long long* const key = reinterpret_cast<unsigned long long*>(plan_lds + lay.key);
@@ -441,9 +453,11 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         if (tid == 0) {
             step->done = 1; step->n_batch = 0; step->n_part_items = 0; step->n_scan_items = 0;
             hist_counts[0] = 0; hist_counts[1] = 0; hist_counts[2] = 0;
+            report_to_host(report, report_seq, true, st1.w, n_expanded0, commits0 + n_commit, n_nodes);
         }
         return;
     }
+    if (tid == 0) report_to_host(report, report_seq, false, st1.w, n_expanded0, commits0 + n_commit, n_nodes);
     // One expansion is certain (the leaf the selection stopped at); expansions beyond those
     // that the remaining certain ones will need may be spent on speculation.  That leaf is always in the batch, so the
     // next call commits at least one split and `spare` stays >= 0: never more than max_expand nodes are expanded, which
@@ -558,6 +572,7 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(const StepState* st
                                                              const float* delta, int parts, int extra, RefitUnit* units,
                                                              int2* leaves, TreeOut out) {
     __shared__ LeafLayout s;
+    if (step->done == 0) return;  // (uniform) the host enqueues this pass before it knows
     const int n = step->n_leaves;
     const double dg = (double)delta[0], dh = (double)delta[1];
     for (int l = threadIdx.x; l < out.max_leaves; l += blockDim.x) {
@@ -598,6 +613,30 @@ int prepare_tree_kernels(qgbdt_ctx* ctx) {
         QG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_plan_kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan_lds));
     return QGBDT_OK;
+}
+
+// Waits for the answer to request `seq` in pinned memory: the stream's work behind it goes on meanwhile.  (Copying the status word
+// and waiting for the stream left the GPU idle for 15 to 25 us at the end of every tree.)  The stream is asked now and then whether it is still at work, so that an error ends the wait.
+static int wait_for_report(qgbdt_ctx* ctx, uint64_t seq, bool* done) {
+    const auto answered = [&]() {
+        const uint64_t a = __atomic_load_n(&ctx->report->answer, __ATOMIC_ACQUIRE);
+        *done = a & 1;
+        return a >> 1 == seq;
+    };
+    for (auto next = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);;) {
+        for (int k = 0; k < 64; ++k) {
+            if (answered()) return QGBDT_OK;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::steady_clock::now() < next) continue;
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        if (e == hipSuccess) {
+            if (answered()) return QGBDT_OK;
+            return set_error(ctx, QGBDT_E_HIP, "the plan kernel left no answer");
+        }
+        if (e != hipErrorNotReady) return set_error(ctx, QGBDT_E_HIP, "hipStreamQuery failed: %s", hipGetErrorString(e));
+        next = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    }
 }
 
 int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const float* h, const qgbdt_params* p,
@@ -699,11 +738,11 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     const int round_cap = 4 * ctx->shape.max_leaves + 8;  // every round commits or expands at least one node
     int launched = 0;
     int to_launch = ctx->rounds_hint;
-    auto plan_batch = [&]() {
+    auto plan_batch = [&](uint64_t report_seq) {
         hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
                            ctx->batch_seg, ctx->super_counts, ctx->plan_list, ctx->hist_counts, F, n_cand, p->num_leaves,
-                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, ordered ? COPY_BUFS : ROW_BUFS, out,
-                           fused_cand, ctx->scan_pairs);
+                           ctx->batch_max, ctx->max_expand, ctx->seg_rows, ctx->seg_supers, ordered ? COPY_BUFS : ROW_BUFS, ctx->report,
+                           report_seq, out, fused_cand, ctx->scan_pairs);
     };
     auto expand_batch = [&]() {  // partition, histograms and split search of the nodes the plan kernel has chosen
         int rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
@@ -717,30 +756,33 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     };
     for (;;) {
         for (int r = 0; r < to_launch; ++r) {
-            plan_batch();
+            plan_batch(0);
             rc = expand_batch();
             if (rc != QGBDT_OK) return rc;
         }
         launched += to_launch;
-        // one more plan: commits what the last round made known and tells whether the tree is finished
-        plan_batch();
+        // one more plan: commits what the last round made known and tells whether the tree is finished; behind it, what is
+        // left to do if it is
+        const uint64_t seq = ++ctx->report_seq;
+        plan_batch(seq);
+        hipLaunchKernelGGL(tree_finalize_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->delta,
+                           refit_parts(N), refit_extra(N), ctx->refit_units, ctx->refit_leaves, out);
         QG_HIP(ctx, hipGetLastError());
-        QG_HIP(ctx, hipMemcpyAsync(ctx->host_state, ctx->step, sizeof(StepState), hipMemcpyDeviceToHost, ctx->stream));
-        QG_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        if (ctx->host_state->done) break;
+        rc = launch_gather_refit(ctx, idxs, rows.code.id_mask, row_idx_out, out.t.n_leaves, out.t.leaf_value);
+        if (rc != QGBDT_OK) return rc;
+        bool done = false;
+        rc = wait_for_report(ctx, seq, &done);
+        if (rc != QGBDT_OK) return rc;
+        if (done) break;
         if (launched > round_cap) return set_error(ctx, QGBDT_E_HIP, "tree growth did not finish in %d rounds", launched);
-        // the trailing plan has already chosen a batch: finish that round, then continue
+        // the trailing plan has already chosen a batch: finish that round, then ask again
         rc = expand_batch();
         if (rc != QGBDT_OK) return rc;
         launched += 1;
-        to_launch = 3;
+        to_launch = 0;
     }
-    ctx->rounds_hint = ctx->host_state->rounds > 0 ? ctx->host_state->rounds : 1;
-
-    hipLaunchKernelGGL(tree_finalize_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->delta,
-                       refit_parts(N), refit_extra(N), ctx->refit_units, ctx->refit_leaves, out);
-    QG_HIP(ctx, hipGetLastError());
-    return launch_gather_refit(ctx, idxs, rows.code.id_mask, row_idx_out, out.t.n_leaves, out.t.leaf_value);
+    ctx->rounds_hint = ctx->report->rounds > 0 ? ctx->report->rounds : 1;
+    return QGBDT_OK;
 }
 
 }  // namespace qgbdt

@@ -109,6 +109,29 @@ def test_row_entries_with_gradients(N, bits_g, bits_h, F, nb, bb):
     assert np.allclose(t.leaf_value.cpu().numpy()[:L], e.leaf_value[:L], rtol=1e-9, atol=1e-13)
 
 
+def test_trees_of_very_different_depth_in_turn():
+    # the number of rounds enqueued up front is the last tree's: too few and too many of them, on one context, without a
+    # synchronisation of the caller's between the trees
+    N, F, nb, L = 20_000, 12, 64, 127
+    rng = np.random.default_rng(3)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    x = bins.astype(np.float64) / nb
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    gs = [(x[:, 0] - 0.5).astype(np.float32), np.exp(0.3 * (bins[:, :8] > nb - 6).sum(1) ** 2).astype(np.float32), np.zeros(N, np.float32),
+          (x[:, 1] * x[:, 2] - x[:, 3] + 0.1 * rng.normal(size=N)).astype(np.float32)]
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L)
+    dbins, dh, dg = torch.from_numpy(bins).cuda(), torch.from_numpy(h).cuda(), [torch.from_numpy(g).cuda() for g in gs]
+    order = [0, 1, 2, 3, 1, 0, 3, 2, 2, 1]
+    leaves = [L, 2, L, L, L, L, 5, L, 3, L]
+    trees = [ctx.grow_tree(dbins, dg[k], dh, 3, 3, 5, i, l, min_data_in_leaf=20) for i, (k, l) in enumerate(zip(order, leaves))]
+    for i, (k, l, t) in enumerate(zip(order, leaves, trees)):
+        e = oracle.grow_tree(bins, nb, gs[k], h, 3, 3, 5, i, l, min_data=20)
+        _check(t, e, N)
+        n = e.n_leaves
+        assert np.allclose(t.leaf_value.cpu().numpy()[:n], e.leaf_value[:n], rtol=1e-9, atol=1e-13)
+
+
 # both sides of the lines at which the partition takes other segments or sums its counts in two levels, ragged ends
 @pytest.mark.parametrize("N,F,L,layout", [(511, 4, 6, 1), (262_144, 5, 63, 1), (262_145, 5, 63, 2), (262_147, 16, 40, 3),
                                           (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3)])
