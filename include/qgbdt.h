@@ -50,16 +50,16 @@ extern "C" {
 /* Optional sections of the workspace (qgbdt_workspace_bytes / qgbdt_set_workspace). */
 #define QGBDT_WS_BIND 1u       /* feature-major copy of a bound matrix: qgbdt_bind_bins (n_rows * n_features * bin_bytes) */
 #define QGBDT_WS_ROW_COPIES 2u /* three leaf-ordered copies of the bin rows: row_layout QGBDT_ROWS_ORDERED, and what
-                                  QGBDT_ROWS_AUTO takes for an unbound matrix of 16..64 uint8 features (a multiple of 4);
-                                  ignored for other shapes (3 * n_rows * n_features) */
+                                  QGBDT_ROWS_AUTO takes for a large unbound matrix of up to 32 uint8 features (16..64
+                                  uint8 features, a multiple of 4; ignored for other shapes; 3 * n_rows * n_features) */
 #define QGBDT_WS_BOOST 4u      /* loss derivatives of qgbdt_boost_iteration* (2 * 4 bytes per row) */
 
 #define QGBDT_ROUND_STOCHASTIC 0 /* SR of Sec. 4.2 */
 #define QGBDT_ROUND_NEAREST 1    /* RN of Sec. 4.2 (half rounds up) */
 
 /* What moves when a leaf's rows are partitioned (results are identical for all of them). */
-#define QGBDT_ROWS_AUTO 0    /* ordered copies for an unbound matrix when the workspace holds them (QGBDT_WS_ROW_COPIES),
-                                else row ids with the quantized gradients in the same 32 bits where both fit, else row
+#define QGBDT_ROWS_AUTO 0    /* ordered copies for a large unbound matrix of short rows when the workspace holds them
+                                (QGBDT_WS_ROW_COPIES), else row ids with the quantized gradients in the same 32 bits where both fit, else row
                                 ids, with the packed gradients when the matrix is 128 MB or more */
 #define QGBDT_ROWS_IDS 1     /* row ids only; histogram builds gather bin rows and packed gradients */
 #define QGBDT_ROWS_IDS_GH 2  /* row ids and packed gradients; histogram builds gather the bin rows */

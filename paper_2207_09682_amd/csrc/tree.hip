@@ -675,10 +675,12 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     IdxSet idxs;
     // the feature-major copy serves only the matrix it was made from
     const uint8_t* bins_t = (ctx->bins_t && ctx->bound_bins == (const void*)bins) ? ctx->bins_t : nullptr;
-    // Narrow rows are kept in leaf order (every level moves them) when the partition would otherwise gather a
-    // sector of the row-major matrix per row; with the feature-major copy the partition is cheap without
-    // moving rows, and gathering the rows of the smaller children costs less than moving all rows
-    // (10.5 M x 28: 3.58 against 3.97 ms per tree).
+    // Without the feature-major copy the partition's count gathers a line of the row-major matrix per row, once per level; keeping
+    // the rows in leaf order reads and writes the whole row at every level instead.  Rows of 36 bytes and more are cheaper to
+    // gather, shorter ones too while the matrix is in the caches.  Index / ordered, ms per tree: 20 M x 48 5.99 / 7.45, 20 M x 36
+    // 5.21 / 5.54, 60 M x 32 16.6 / 15.7, 8 M x 32 1.87 / 1.94, 20 M x 28 4.76 / 4.57, 6 M x 28 1.73 / 1.68, 5 M x 28 1.45 / 1.47, 2.5 M x 28
+    // 0.84 / 0.84, 1 M x 28 0.70 / 0.75, 7 M x 20 1.48 / 1.34, 5 M x 16 1.11 / 1.03, 1 M x 16 0.51 / 0.53, 10 k x 28 0.205 / 0.219.  (With the
+    // feature-major copy moving row ids wins throughout: 10.5 M x 28 1.85 against 2.54 ms.)
     // Without ordered rows the packed gradients still move with the row ids (2 bytes per moved row): a gathered
     // build then reads them in sequence, which takes one of the ~2.2 cache lines per sparse narrow row away.
     // A matrix that the caches hold gathers cheaply anyway and gains nothing from the move (1 M x 28: 1.15 to
@@ -687,7 +689,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     // is gathered nor moved apart.
     int layout = p->row_layout;
     if (layout == QGBDT_ROWS_AUTO)
-        layout = (ctx->ordered != 0 && !bins_t) ? QGBDT_ROWS_ORDERED
+        layout = (ctx->ordered != 0 && !bins_t && N * F * (36 - F) > (int64_t)1000 << 20) ? QGBDT_ROWS_ORDERED
                  : ((int64_t)N * F * ctx->shape.bin_bytes >= (int64_t)128 << 20) ? QGBDT_ROWS_IDS_GH : QGBDT_ROWS_IDS;
     const bool ordered = layout == QGBDT_ROWS_ORDERED;
     rows.code = PLAIN_ROWS;
