@@ -116,6 +116,7 @@ struct HistPlan {
     int32_t flat_rows;   // rows per wavefront iteration of that kernel
     int32_t max_items;    // most work items (row groups) of one launch = slots of the partial-histogram buffer
     int32_t slot_bytes;   // bytes of one (item, tile) slot: the tile's local bins, padded to 16 bytes
+    int32_t search_sums;  // tree growth: builds of at most this many row groups are added up by the split search (0x7fffffff: all)
     int32_t single_rows;  // a group of at most this many rows is accumulated in one chunk by every kernel variant
     int32_t pad16;        // local bins keep 4 unused words after every 16 features (wide rows, 16-byte loads)
     int32_t wide_v;       // > 0: wide rows are read in pieces of this many bytes per lane (8 or 16)
@@ -352,7 +353,12 @@ inline bool part_supers(int64_t n_rows) { return n_rows > ((int64_t)3 << 20); }
 // all in flight at once); builds of more row groups are summed up by the reduce kernel, which spreads them over the
 // whole chip and otherwise returns at once.  Trees with 8 / 64: 400 k x 2000 1283 / 1396 us, 2 M x 40 of 16-bit bins
 // 924 / 980 us, 1 M x 28 the same.
+// Where no build can have more than about 32 groups (hist_target_rows: 2^14 rows in one tile, 2^17 rows times tiles in several) the
+// search adds them all up and the reduce kernel, 3 us of every round with the gap in front of it, is not launched.  Trees with / without
+// it: 10 k x 28 196 / 187 us, 16 k x 28 281 / 272 us, 60 k x 100 284 / 270 us, 8 k x 500 452 / 436 us; beyond the line 30 k x 28 267 / 269 us, 100 k x 50
+// 311 / 332 us.
 constexpr int REDUCE_ABOVE = 8;
+constexpr int ALL_GROUPS = 0x7fffffff;
 constexpr int PART_SUPER = 32;  // segments whose left rows are summed up in one counter
 // Most nodes expanded in one round = most builds of a histogram launch (the leaf budget; the growth bookkeeping
 // limits it to 658).  Kernels keep the first work item of every build / node in LDS and search there: a binary

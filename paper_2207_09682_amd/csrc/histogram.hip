@@ -1124,6 +1124,7 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
             if ((16 * l) % F == 0) { p.flat_lanes = l; p.flat_rows = 16 * l / F; break; }
     }
     p.pieces = (fast && !wide_ft && p.ft * s.bin_bytes >= 16) ? (p.ft * s.bin_bytes + 15) / 16 : 0;
+    p.search_sums = s.n_rows * p.n_tiles <= (p.n_tiles > 1 ? 1 << 17 : 1 << 14) ? ALL_GROUPS : REDUCE_ABOVE;
     p.slot_bytes = (p.lds_bytes + 15) & ~15;
     p.max_items = 4 * p.max_groups;
     if (p.max_items < 2 * s.max_leaves + 64) p.max_items = 2 * s.max_leaves + 64;
@@ -1348,7 +1349,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #undef QG_LAUNCH_GENERIC
     }
     QG_HIP(ctx, hipGetLastError());
-    {
+    if (reduce_above != ALL_GROUPS) {
         // the slots of the row groups are added to the histograms
         const int tile_words = nb * (fast ? plan.ftp : plan.ft);
         const int xb = (tile_words + 255) / 256;

@@ -306,7 +306,7 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
             be = batch[t];
             nl = s_left[t]; nr = be.count - nl;
             groups = max(1, (min(nl, nr) + target - 1) / target);
-            if (groups > REDUCE_ABOVE) big = 1;
+            if (groups > plan.search_sums) big = 1;
         }
         const int incl = wave_prefix(groups);
         __syncthreads();
@@ -338,7 +338,7 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
             hist_entries[t] = e;
             ScanPair sp;
             sp.slot_a = be.new_slot; sp.slot_b = slot; sp.parent = slot; sp.a_item = left_small ? 0 : 1;
-            sp.item_start = start; sp.groups = groups <= REDUCE_ABOVE ? groups : 0;
+            sp.item_start = start; sp.groups = groups <= plan.search_sums ? groups : 0;
             sp.merged = e.count > (int64_t)groups * plan.single_rows ? 1 : 0; sp.pad = 0;
             const qgbdt_leafstat sl = {nl, lg, lh}, sr = {nr, rg, rh};
             sp.stat[0] = left_small ? sl : sr; sp.stat[1] = left_small ? sr : sl;

@@ -74,10 +74,10 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
         HistEntry e;
         e.begin = 0; e.count = N; e.buf = root_buf; e.slot = 0; e.item_start = 0; e.groups = hist_groups(N, plan);
         hist_entries[0] = e;
-        hist_counts[0] = 1; hist_counts[1] = e.groups; hist_counts[2] = e.groups > REDUCE_ABOVE ? 1 : 0;
+        hist_counts[0] = 1; hist_counts[1] = e.groups; hist_counts[2] = e.groups > plan.search_sums ? 1 : 0;
         ScanPair sp;
         sp.slot_a = 0; sp.slot_b = -1; sp.parent = -1; sp.a_item = 0; sp.item_start = 0;
-        sp.groups = e.groups <= REDUCE_ABOVE ? e.groups : 0;
+        sp.groups = e.groups <= plan.search_sums ? e.groups : 0;
         sp.merged = N > (int64_t)e.groups * plan.single_rows ? 1 : 0; sp.pad = 0;
         sp.stat[0].n_rows = N; sp.stat[0].sum_g = r.sum_g; sp.stat[0].sum_h = r.sum_h;
         sp.stat[1] = sp.stat[0];
@@ -724,7 +724,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     rc = launch_hist(ctx, root_plan, rows, idxs, false, ((uintptr_t)bins & 15) == 0,
                      ctx->hist_entries, ctx->hist_counts, ctx->hist_pool,
                      (N + hist_target_rows(root_plan, N, 1) - 1) / hist_target_rows(root_plan, N, 1),  // the build's row groups
-                     ctx->step, mfb, REDUCE_ABOVE);
+                     ctx->step, mfb, root_plan.search_sums);
     if (rc != QGBDT_OK) return rc;
     auto search_splits = [&](const HistPlan& hp, int max_pairs) {
         int rc = launch_scan_pairs(ctx, ctx->hist_pool, ctx->scan_pairs, &ctx->step->n_scan_items, max_pairs, ctx->delta,
@@ -752,7 +752,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         rc = launch_batch_partition_scatter(ctx, rows, ordered, plan);
         if (rc != QGBDT_OK) return rc;
         rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
-                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb, REDUCE_ABOVE);
+                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb, plan.search_sums);
         if (rc != QGBDT_OK) return rc;
         return search_splits(plan, ctx->batch_max);
     };
