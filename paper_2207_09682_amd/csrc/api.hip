@@ -163,7 +163,6 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     k.take(&c->cand, (size_t)2 * c->batch_max * F);
     k.take(&c->hist_entries, (size_t)c->batch_max);
     k.take(&c->hist_counts, 4);
-    k.take(&c->pwork, 1);
     k.take(&c->scan_pairs, (size_t)c->batch_max);
     k.take(&c->refit_units, L + REFIT_EXTRA);
     k.take(&c->refit_leaves, L + 1);
@@ -409,15 +408,13 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
         if (tot[1] > 0xffffffffLL || tot[2] > 0x7fffffffLL)
             return set_error(ctx, QGBDT_E_OVERFLOW_RISK, "sums of %lld rows do not fit 32|32 packed bins", (long long)count);
     }
-    rc = launch_fill_zero(ctx, hist_out, W);
-    if (rc != QGBDT_OK) return rc;
-    if (count == 0) return QGBDT_OK;
+    if (count == 0) return launch_fill_zero(ctx, hist_out, W);
     // most frequent bins of the bound matrix are left out by the wide-row kernels and filled in afterwards
     const uint16_t* mfb = (ctx->mfb_features > 0 && ctx->bound_bins == bins) ? ctx->mfb : nullptr;
     const HistPlan plan = make_hist_plan_for(ctx->shape, bits_g, bits_h, acc_width, count, mfb != nullptr,
                                              row_idx == nullptr && ((uintptr_t)bins & 15) == 0);
     if (mfb && plan.wide_v == 0) mfb = nullptr;  // only those kernels skip
-    rc = launch_set_hist_table(ctx, plan, begin, count);
+    rc = launch_begin_build(ctx, plan, begin, count, hist_out, W);
     if (rc != QGBDT_OK) return rc;
     RowSource rows;
     rows.gh_pos = 0;  // the caller's packed gradients are in original row order

@@ -269,7 +269,6 @@ struct qgbdt_ctx {
     qgbdt::FeatCand* cand;       // [2*batch_max][F]
     qgbdt::HistEntry* hist_entries;  // [batch_max]
     int32_t* hist_counts;        // [3] entries, items, 1: an entry has more than REDUCE_ABOVE groups
-    qgbdt::PartWork* pwork;      // [1]
     qgbdt::ScanPair* scan_pairs; // [batch_max]
     qgbdt::RefitUnit* refit_units;  // [max_leaves + REFIT_EXTRA] of the leaves last laid out
     int2* refit_leaves;          // [max_leaves + 1] first unit and units of a leaf; behind the leaves: number of units
@@ -316,6 +315,20 @@ __device__ __forceinline__ int wave_prefix(int v) {
     v = QG_DPP_ADD(v, 0x143, 0xc);
     return v;
 #undef QG_DPP_ADD
+}
+
+// Totals of the quantizer's workgroups (sum g~, sum h~, sum |g~|), by a workgroup of 256 threads; every thread gets them.
+__device__ __forceinline__ void sum_totals(const int64_t* __restrict__ part, int n_part, int64_t (&s)[3]) {
+    __shared__ int64_t t[3][4];
+    s[0] = s[1] = s[2] = 0;
+    for (int i = threadIdx.x; i < n_part; i += 256)
+        for (int k = 0; k < 3; ++k) s[k] += part[3 * i + k];
+    for (int k = 0; k < 3; ++k) {
+        for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_xor(s[k], o);
+        if ((threadIdx.x & 63) == 0) t[k][threadIdx.x >> 6] = s[k];
+    }
+    __syncthreads();
+    for (int k = 0; k < 3; ++k) s[k] = t[k][0] + t[k][1] + t[k][2] + t[k][3];
 }
 
 constexpr int PART_GROUPS = 512;
@@ -381,12 +394,13 @@ int set_error(qgbdt_ctx* ctx, int code, const char* fmt, ...);
 // launchers (each defined next to its kernels)
 int launch_quantize(qgbdt_ctx* ctx, const float* g, const float* h, int64_t n, int bits_g, int bits_h,
                     uint64_t seed, uint32_t iteration, int rounding, int16_t* gh, float* delta_out,
-                    int64_t* totals_out, float2* pairs_out);
+                    int64_t* totals_out, float2* pairs_out);  // totals_out null: only the workgroups' totals (quantize_parts of them)
+int quantize_parts(const float* g, const float* h, const int16_t* gh, int64_t n);
 HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, bool skew = false);
 HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, int64_t rows, bool skew = false,
                             bool stream_ok = false);  // stream_ok: contiguous rows of a 16-byte aligned matrix
 int64_t max_rows_for_width(int bits_g, int bits_h, int w);
-int launch_set_hist_table(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count);
+int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, int64_t* hist, int64_t n_words);
 int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, const IdxSet& idx, bool use_idx,
                 bool flat_ok, const HistEntry* entries, const int32_t* table_counts, int64_t* hist_base,
                 int64_t grid_items, StepState* step, const uint16_t* mfb = nullptr,

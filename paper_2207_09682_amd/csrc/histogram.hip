@@ -1169,21 +1169,25 @@ HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int ac
     return p;
 }
 
-// One entry table for a stand-alone build.
-__global__ void set_hist_table_kernel(HistEntry* entries, int32_t* counts, HistEntry e) {
-    if (threadIdx.x == 0) {
+// The table of a stand-alone build, and its histogram cleared.
+__global__ void begin_build_kernel(HistEntry* entries, int32_t* counts, HistEntry e, int64_t* hist, int64_t n_words) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = t; i < n_words; i += (int64_t)gridDim.x * blockDim.x) hist[i] = 0;
+    if (t == 0) {
         entries[0] = e;
         counts[0] = 1;
-        counts[1] = e.count > 0 ? e.groups : 0;
+        counts[1] = e.groups;
     }
 }
 
 // (The row groups are counted on the host: on the device their chain of 64-bit divisions took 0.3 us of every build.)
-int launch_set_hist_table(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count) {
+int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, int64_t* hist, int64_t n_words) {
     const int64_t t = hist_target_rows(plan, count, 1), g = (count + t - 1) / t;
     HistEntry e;
     e.begin = begin; e.count = count; e.buf = BUF_ORIGINAL; e.slot = 0; e.item_start = 0; e.groups = g < 1 ? 1 : (int32_t)g;
-    hipLaunchKernelGGL(set_hist_table_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->hist_entries, ctx->hist_counts, e);
+    const int64_t blocks = (n_words + 255) / 256;
+    hipLaunchKernelGGL(begin_build_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks)), dim3(256), 0, ctx->stream, ctx->hist_entries,
+                       ctx->hist_counts, e, hist, n_words);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

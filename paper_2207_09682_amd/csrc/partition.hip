@@ -20,12 +20,6 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t v) {
     if (threadIdx.x == 0) *p = v;
 }
 
-__global__ void set_part_work_kernel(PartWork* w, int64_t begin, int64_t count, int feature, int bin) {
-    if (threadIdx.x == 0) {
-        w->begin = begin; w->count = count; w->feature = feature; w->bin = bin;
-    }
-}
-
 // Bin of (row, feature) in a row-major matrix of 8-bit (bb = 1) or 16-bit (bb = 2) bins.
 __device__ __forceinline__ int bin_at(const uint8_t* __restrict__ bins, int64_t at, int bb) {
     return bb == 2 ? (int)reinterpret_cast<const uint16_t*>(bins)[at] : (int)bins[at];
@@ -38,9 +32,8 @@ constexpr int PART_ROWS = 8;
 
 __global__ __launch_bounds__(256) void part_count_kernel(const uint8_t* __restrict__ bins, int bb, int F,
                                                          const int32_t* __restrict__ src,
-                                                         const PartWork* __restrict__ work,
-                                                         uint8_t* __restrict__ flags, int64_t* __restrict__ counts) {
-    const PartWork wk = *work;
+                                                         PartWork wk, uint8_t* __restrict__ flags,
+                                                         int64_t* __restrict__ counts) {
     const int64_t seg = segment_len(wk.count, gridDim.x);
     const int64_t sbegin = (int64_t)blockIdx.x * seg;
     const int64_t send = min(wk.count, sbegin + seg);
@@ -70,10 +63,8 @@ __global__ __launch_bounds__(256) void part_count_kernel(const uint8_t* __restri
 }
 
 __global__ __launch_bounds__(256) void part_scatter_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst,
-                                                           const PartWork* __restrict__ work,
-                                                           const uint8_t* __restrict__ flags,
+                                                           PartWork wk, const uint8_t* __restrict__ flags,
                                                            const int64_t* __restrict__ counts, int64_t* n_left_out) {
-    const PartWork wk = *work;
     // left rows before this segment, and in total
     int64_t before = 0, total = 0;
     for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
@@ -142,8 +133,7 @@ __global__ void copy_i32_kernel(const int32_t* __restrict__ src, int32_t* __rest
 // Stand-alone call: row_idx is reordered in place (through the context's spare buffer).
 int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, int64_t begin, int64_t count,
                        int feature, int bin, int64_t* n_left_out) {
-    hipLaunchKernelGGL(set_part_work_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->pwork, begin, count, feature,
-                       bin);
+    const PartWork work = {begin, count, feature, bin};
     if (count == 0) {
         hipLaunchKernelGGL(fill_i64_kernel, dim3(1), dim3(64), 0, ctx->stream, n_left_out, (int64_t)0);
         QG_HIP(ctx, hipGetLastError());
@@ -152,8 +142,8 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
     int64_t g = (count + 2047) / 2048;
     if (g > PART_GROUPS) g = PART_GROUPS;
     hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, bins, ctx->shape.bin_bytes,
-                       ctx->shape.n_features, row_idx, ctx->pwork, ctx->flags, ctx->part_counts);
-    hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, row_idx, ctx->idx[0], ctx->pwork,
+                       ctx->shape.n_features, row_idx, work, ctx->flags, ctx->part_counts);
+    hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, row_idx, ctx->idx[0], work,
                        ctx->flags, ctx->part_counts, n_left_out);
     int blocks = (int)((count + 255) / 256);
     if (blocks > 1024) blocks = 1024;

@@ -182,16 +182,17 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__
 // Sums the workgroups' partial totals: sum g~, sum h~, sum |g~|.
 __global__ __launch_bounds__(256) void quantize_totals_kernel(const int64_t* __restrict__ part, int n_part,
                                                               int64_t* totals) {
-    int64_t s[3] = {0, 0, 0};
-    for (int i = threadIdx.x; i < n_part; i += blockDim.x)
-        for (int k = 0; k < 3; ++k) s[k] += part[3 * i + k];
-    __shared__ int64_t t[3][4];
-    for (int k = 0; k < 3; ++k) {
-        for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_xor(s[k], o);
-        if ((threadIdx.x & 63) == 0) t[k][threadIdx.x >> 6] = s[k];
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) totals[threadIdx.x] = t[threadIdx.x][0] + t[threadIdx.x][1] + t[threadIdx.x][2] + t[threadIdx.x][3];
+    int64_t s[3];
+    sum_totals(part, n_part, s);
+    if (threadIdx.x == 0) { totals[0] = s[0]; totals[1] = s[1]; totals[2] = s[2]; }
+}
+
+static bool quantize_vec(const float* g, const float* h, const int16_t* gh) {
+    return (((uintptr_t)g | (uintptr_t)h) & 15) == 0 && ((uintptr_t)gh & 7) == 0;
+}
+int quantize_parts(const float* g, const float* h, const int16_t* gh, int64_t n) {
+    const int64_t blocks = ((quantize_vec(g, h, gh) ? (n + 3) / 4 : n) + 255) / 256;
+    return blocks > QUANT_PARTS ? QUANT_PARTS : blocks < 1 ? 1 : (int)blocks;
 }
 
 int launch_quantize(qgbdt_ctx* ctx, const float* g, const float* h, int64_t n, int bits_g, int bits_h,
@@ -199,11 +200,8 @@ int launch_quantize(qgbdt_ctx* ctx, const float* g, const float* h, int64_t n, i
                     int64_t* totals_out, float2* pairs_out) {
     // bits_h == 0: constant hessians are not quantized (kh = 0 tells the kernel: h~ = 1, delta_h = max h)
     const int kg = (1 << (bits_g - 1)) - 1, kh = bits_h == 0 ? 0 : (1 << bits_h) - 2;
-    int64_t* totals = totals_out ? totals_out : ctx->qtotals;
-    const bool vec = (((uintptr_t)g | (uintptr_t)h) & 15) == 0 && ((uintptr_t)gh & 7) == 0;
-    int blocks = (int)(((vec ? (n + 3) / 4 : n) + 255) / 256);
-    if (blocks > QUANT_PARTS) blocks = QUANT_PARTS;
-    if (blocks < 1) blocks = 1;
+    const bool vec = quantize_vec(g, h, gh);
+    const int blocks = quantize_parts(g, h, gh, n);
     if (vec) {
         hipLaunchKernelGGL(absmax_kernel<true>, dim3(blocks), dim3(256), 0, ctx->stream, g, h, n, ctx->absmax_part);
         hipLaunchKernelGGL(quantize_kernel<true>, dim3(blocks), dim3(256), 0, ctx->stream, g, h, n, ctx->absmax_part,
@@ -215,7 +213,8 @@ int launch_quantize(qgbdt_ctx* ctx, const float* g, const float* h, int64_t n, i
                            blocks, kg, kh, (uint32_t)seed, (uint32_t)(seed >> 32), iteration, rounding, gh, delta_out,
                            ctx->qtotals_part, pairs_out);
     }
-    hipLaunchKernelGGL(quantize_totals_kernel, dim3(1), dim3(256), 0, ctx->stream, ctx->qtotals_part, blocks, totals);
+    if (totals_out)
+        hipLaunchKernelGGL(quantize_totals_kernel, dim3(1), dim3(256), 0, ctx->stream, ctx->qtotals_part, blocks, totals_out);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

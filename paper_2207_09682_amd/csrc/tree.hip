@@ -56,18 +56,21 @@ __device__ __forceinline__ int hist_groups(int64_t count, const HistPlan& plan) 
 }
 
 __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepState* step, Node* nodes,
-                                                        const int64_t* qtotals, int root_buf, HistEntry* hist_entries,
+                                                        const int64_t* qtotals_part, int n_part, int root_buf, HistEntry* hist_entries,
                                                         int32_t* hist_counts, ScanPair* pairs,
                                                         int64_t* hist0, int64_t hist_words, HistPlan plan) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = t; i < hist_words; i += stride) hist0[i] = 0;  // (the root's row list is the identity: never stored)
+    if (blockIdx.x != 0) return;
+    int64_t total[3];  // (a launch of its own for them took 3 us of every tree)
+    sum_totals(qtotals_part, n_part, total);
     if (t == 0) {
         step->done = 0; step->n_known = 0; step->n_list = 0; step->n_nodes = 1; step->n_leaves = 1; step->n_commits = 0; step->n_expanded = 0;
         step->n_slots = 1; step->n_batch = 0; step->rounds = 0; step->n_part_items = 0; step->n_scan_items = 1;
         step->hist_units = N * (int64_t)F;
         Node r;
-        r.begin = 0; r.count = N; r.sum_g = qtotals[0]; r.sum_h = qtotals[1]; r.n_left = 0; r.buf = root_buf; r.slot = 0;
+        r.begin = 0; r.count = N; r.sum_g = total[0]; r.sum_h = total[1]; r.n_left = 0; r.buf = root_buf; r.slot = 0;
         r.state = 1; r.expanded = 0; r.child = -1; r.leaf_id = 0;
         clear_split(r.best);
         nodes[0] = r;
@@ -648,11 +651,12 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     out.t = *tout;
     out.max_leaves = ctx->shape.max_leaves;
 
-    int rc = launch_quantize(ctx, g, h, N, p->bits_g, p->bits_h, p->seed, iteration, p->rounding, ctx->gh,
-                             ctx->delta, ctx->qtotals, ctx->ghf);
-    if (rc != QGBDT_OK) return rc;
     // 32|32 words of the total histograms must hold the root's sums
-    if (N > max_rows_for_width(p->bits_g, p->bits_h, 32)) {
+    const bool check_totals = N > max_rows_for_width(p->bits_g, p->bits_h, 32);
+    int rc = launch_quantize(ctx, g, h, N, p->bits_g, p->bits_h, p->seed, iteration, p->rounding, ctx->gh,
+                             ctx->delta, check_totals ? ctx->qtotals : nullptr, ctx->ghf);
+    if (rc != QGBDT_OK) return rc;
+    if (check_totals) {
         int64_t tot[3];
         QG_HIP(ctx, hipMemcpyAsync(tot, ctx->qtotals, sizeof(tot), hipMemcpyDeviceToHost, ctx->stream));
         QG_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -718,7 +722,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     int blocks = (int)((W + 255) / 256);
     if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(tree_init_kernel, dim3(blocks), dim3(256), 0, ctx->stream, N, F, ctx->step,
-                       ctx->nodes, ctx->qtotals, root_buf, ctx->hist_entries, ctx->hist_counts, ctx->scan_pairs,
+                       ctx->nodes, ctx->qtotals_part, quantize_parts(g, h, ctx->gh, N), root_buf, ctx->hist_entries, ctx->hist_counts, ctx->scan_pairs,
                        ctx->hist_pool, W, root_plan);
     ctx->next_hist_is_root = 1;
     rc = launch_hist(ctx, root_plan, rows, idxs, false, ((uintptr_t)bins & 15) == 0,
