@@ -25,7 +25,6 @@
 // the four features of a dword is rotated per row so that lanes of one instruction
 // spread over the features.  Lanes that have no place in a tile are masked for the
 // atomics (they would otherwise hit one word together and serialize).
-#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -1071,12 +1070,18 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
                 if (dpr > 64) continue;
                 const int rpi = 64 / dpr;
                 const int tiles = (F + ft - 1) / ft;
-                if (F - (tiles - 1) * ft < std::min(F, 16 / s.bin_bytes)) continue;  // every tile row holds a piece (a short row: a dword)
+                if (F - (tiles - 1) * ft < npd) continue;  // every tile row holds at least one dword
                 const double score = ((double)(rpi * dpr) / 64.0) * ((double)F / ((double)tiles * ft));
                 if (score > best_score + 1e-9) { best_score = score; best_ft = ft; }
             }
         }
         if (best_ft == 0 && aligned && (int64_t)pitch_of(npd) * nb * wbytes <= lds_budget) best_ft = npd;
+        if (best_ft > 0) {
+            // as many tiles, of more even widths, where the last one's rows would be shorter than a 16-byte piece (F = 68: 36 + 32, not 64 + 4)
+            const int tiles = (F + best_ft - 1) / best_ft, piece = 16 / s.bin_bytes;
+            const int even = ((F + tiles - 1) / tiles + npd - 1) / npd * npd;
+            if (F - (tiles - 1) * best_ft < piece && even < best_ft && F - (tiles - 1) * even >= piece) best_ft = even;
+        }
         if (best_ft == 0) fast = false;
         p.ft = best_ft;
         p.ftp = pitch_of(best_ft > 0 ? best_ft : 1);
@@ -1123,7 +1128,7 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
         for (int l = 64; l >= 32; --l)
             if ((16 * l) % F == 0) { p.flat_lanes = l; p.flat_rows = 16 * l / F; break; }
     }
-    p.pieces = (fast && !wide_ft && p.ft * s.bin_bytes >= 16) ? (p.ft * s.bin_bytes + 15) / 16 : 0;
+    p.pieces = (fast && !wide_ft && (F - (p.n_tiles - 1) * p.ft) * s.bin_bytes >= 16) ? (p.ft * s.bin_bytes + 15) / 16 : 0;
     p.search_sums = s.n_rows * p.n_tiles <= (p.n_tiles > 1 ? 1 << 17 : 1 << 14) ? ALL_GROUPS : REDUCE_ABOVE;
     p.slot_bytes = (p.lds_bytes + 15) & ~15;
     p.max_items = 4 * p.max_groups;

@@ -90,7 +90,7 @@ def test_growth_ahead_of_the_commits(kind, N, L):
 # row lists whose entries carry the row's quantized gradients: id and gradients fill the 32 bits, miss them by one, constant
 # hessians; on the element-wise, the dword, the 16-byte-piece and both wide-row kernels
 @pytest.mark.parametrize("N,bits_g,bits_h", [(65_536, 8, 8), (65_537, 8, 8), (131_072, 8, 0), (16_385, 2, 8), (40_000, 8, 2)])
-@pytest.mark.parametrize("F,nb,bb", [(3, 64, 1), (13, 64, 1), (28, 64, 1), (45, 300, 2), (72, 255, 1), (80, 63, 1)])
+@pytest.mark.parametrize("F,nb,bb", [(3, 64, 1), (13, 64, 1), (28, 64, 1), (36, 255, 1), (45, 300, 2), (68, 255, 1), (72, 255, 1), (80, 63, 1)])
 def test_row_entries_with_gradients(N, bits_g, bits_h, F, nb, bb):
     L = 24
     rng = np.random.default_rng(N + F + bits_g)

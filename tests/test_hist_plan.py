@@ -242,21 +242,21 @@ def test_the_launch_shape_of_an_old_unexplained_fault_is_in_bounds():
                 assert (gend - 1) * F + off + nbytes <= N * F
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
+@pytest.mark.parametrize("shape", SHAPES + [(9000, F, nb, 31, 2) for F in (8, 9, 10, 13, 26, 41) for nb in (400, 1024)] +
+                         [(9000, F, 255, 31, 1) for F in (15, 17, 65, 68, 70, 97, 129)], ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
 def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
     # lane -> (row, piece) of the kernel that reads 16 bytes per lane: loads inside the row, every bin of the tile row in one
     # lane's sixteen (eight) atomics exactly once, whatever the row's rotation of their order
     N, F, nb, L, bb = shape
     for key, p in _plans(shape):
-        if p["bytewise"] or p["wide_v"] or p["ft"] * bb < 16:
-            continue
+        if p["bytewise"] or p["wide_v"] or (F - (p["n_tiles"] - 1) * p["ft"]) * bb < 16:
+            continue                                                 # other kernels
         P, npd = -(-p["ft"] * bb // 16), 4 // bb
         rpi = 64 // P
         assert rpi >= 1, key
         for tile in range(p["n_tiles"]):
             f0 = tile * p["ft"]
             ft = min(p["ft"], F - f0)
-            assert ft * bb >= 16, (key, tile)
             for r in range(rpi):
                 seen = []
                 for c in range(P):
@@ -272,6 +272,7 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
                             if j >= (16 * c - at) // bb:
                                 seen.append(at // bb + j)
                 assert sorted(seen) == list(range(ft)), (key, tile, r)
+        assert not (F * bb >= 16 and p["bytewise"]), key
         whole = p["ft"] * bb % 16 == 0 and F % p["ft"] * bb % 16 == 0
         if whole:   # the variant without the test for bins held twice
             assert all(min(p["ft"], F - t * p["ft"]) * bb % 16 == 0 for t in range(p["n_tiles"])), key
