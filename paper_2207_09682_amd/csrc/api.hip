@@ -91,7 +91,6 @@ static void derive_sizes(qgbdt_ctx* c) {
     c->max_expand = 3 * L;
     c->max_nodes = 2 * c->max_expand + 1;
     c->seg_rows = 256 * part_rows(c->shape.n_rows);
-    c->seg_supers = part_supers(c->shape.n_rows) ? 1 : 0;
     c->max_seg = (int)(c->shape.n_rows / c->seg_rows) + c->batch_max + 2;
     c->max_super = c->max_seg / PART_SUPER + c->batch_max + 2;
 }

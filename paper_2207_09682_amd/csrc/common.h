@@ -232,7 +232,7 @@ struct qgbdt_ctx {
     int max_expand;  // most expansions per tree (sequential ones plus speculative ones)
     int max_nodes;
     int seg_rows;   // rows per segment of the batched partition
-    int seg_supers; // 1: with counters per PART_SUPER segments
+    int seg_supers; // 1: with counters per PART_SUPER segments (of the tree being grown)
     int max_seg;
     int max_super;
     int rounds_hint;
@@ -356,12 +356,12 @@ constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
 //    kernel per round on 10 k x 28 in ordered mode: 17.0 us with 8, 10.0 us with 2); above that 8, which spreads a
 //    wavefront's fixed work per segment (1 M x 28: 10.8 us with 8, 14.6 us with 2).
 //  - The counters save the scatter kernel a walk over all of a node's segments (2 KB per wavefront and million rows), but
-//    their device-wide atomics lengthen the count kernel by about 2 us: 1 M x 28 7.9 us with, 6.1 us without.  Trees in 255 leaves
-//    with / without: 1 M x 28 772 / 745 us, 3 M 1025 / 1003 us, 4 M 1174 / 1160 us, 5 M 1316 / 1300 us, 6 M 1416 / 1421 us, 7.5 M
-//    1652 / 1687 us, 10.5 M 2002 / 2073 us; matrix not bound: 4 M 1365 / 1362 us, 5 M 1584 / 1591 us, 7.5 M 2038 / 2095 us.  The
-//    two are level between 4 and 5.5 M rows; what the line gives away between it and there is 1 to 3 % of a bound tree.
+//    their device-wide atomics lengthen the count kernel by about 2 us (1 M x 28: 7.9 us with, 6.1 us without).  Trees
+//    with / without, matrix bound: 3.3 M x 28 907 / 887 us, 4 M 993 / 979 us, 4.7 M 1088 / 1079 us, 5.5 M 1198 / 1201 us, 6.2 M
+//    1289 / 1302 us, 4 M x 100 1096 / 1077 us, 5.5 M x 100 1683 / 1687 us; not bound: 3.5 M x 60 1463 / 1482 us, 4.5 M x 60 1496 / 1519 us,
+//    5.5 M x 20 1145 / 1154 us.  The lines lie where the two are level: between 4.7 and 5.5 M rows bound, below 3.5 M not bound.
 inline int part_rows(int64_t n_rows) { return n_rows > ((int64_t)1 << 18) ? 8 : 2; }
-inline bool part_supers(int64_t n_rows) { return n_rows > ((int64_t)3 << 20); }
+inline bool part_supers(int64_t n_rows, bool bound) { return n_rows > ((int64_t)(bound ? 5 : 3) << 20); }
 // In tree growth the split search sums a build's slots itself when there are at most this many (a thread's loads of them are
 // all in flight at once); builds of more row groups are summed up by the reduce kernel, which spreads them over the
 // whole chip and otherwise returns at once.  Trees with 8 / 64: 400 k x 2000 1283 / 1396 us, 2 M x 40 of 16-bit bins

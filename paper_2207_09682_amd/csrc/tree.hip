@@ -679,6 +679,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     IdxSet idxs;
     // the feature-major copy serves only the matrix it was made from
     const uint8_t* bins_t = (ctx->bins_t && ctx->bound_bins == (const void*)bins) ? ctx->bins_t : nullptr;
+    ctx->seg_supers = part_supers(N, bins_t != nullptr) ? 1 : 0;
     // Without the feature-major copy the partition's count gathers a line of the row-major matrix per row, once per level; keeping
     // the rows in leaf order reads and writes the whole row at every level instead.  Rows of 36 bytes and more are cheaper to
     // gather, shorter ones too while the matrix is in the caches.  Index / ordered, ms per tree: 20 M x 48 5.99 / 7.45, 20 M x 36

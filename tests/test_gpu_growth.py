@@ -134,7 +134,8 @@ def test_trees_of_very_different_depth_in_turn():
 
 # both sides of the lines at which the partition takes other segments or sums its counts in two levels, ragged ends
 @pytest.mark.parametrize("N,F,L,layout", [(511, 4, 6, 1), (262_144, 5, 63, 1), (262_145, 5, 63, 2), (262_147, 16, 40, 3),
-                                          (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3)])
+                                          (3 * 2**20, 4, 31, 1), (3 * 2**20 + 1, 4, 255, 2), (3_300_001, 16, 31, 3),
+                                          (5 * 2**20, 4, 15, 0), (5 * 2**20 + 1, 4, 15, 0)])
 def test_partition_segments(N, F, L, layout):
     rng = np.random.default_rng(N)
     nb = 32
