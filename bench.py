@@ -279,7 +279,10 @@ def main():
     esz = bins.element_size()
     committed_builds = sum(x[2] for x in stats) + K
     rows_committed = total_units // F
-    bytes_committed = K * N * (F * esz + 2) + (rows_committed - K * N) * (F * esz + 2 + 4) + committed_builds * F * nb * 8
+    # what a build below the root reads per row beside the bin row, by what the trees moved
+    layout = ctx.tree_layout()
+    beside = {qb.ROWS_IDS: 6, qb.ROWS_IDS_GH: 6, qb.ROWS_IDS_CODED: 4, qb.ROWS_ORDERED: 2}[layout]
+    bytes_committed = K * N * (F * esz + 2) + (rows_committed - K * N) * (F * esz + beside) + committed_builds * F * nb * 8
     achieved_all = (hist_bytes / hist_launches) / (hist_ms / hist_launches * 1e-3) / 1e9 if hist_launches and hist_ms > 0 else 0.0
     achieved = bytes_committed / (hist_ms * 1e-3) / 1e9 if hist_ms > 0 else 0.0
     # HBM bytes per histogram launch from the rocprofv3 counter runs (FETCH_SIZE, WRITE_SIZE scaled by a plain
@@ -308,9 +311,11 @@ def main():
                    "acc_width": args.acc_width or "auto", "leaves_last_tree": n_leaves_last,
                    "hist_units_per_tree": total_units / K,
                    "bins_bound": bind_ms is not None, "bind_ms_once": bind_ms,
-                   "rows": ("in place: row ids (and, for matrices beyond the caches, the packed gradients) move, the bin rows of the "
-                            "smaller children are gathered (the faster of the two layouts for whole trees)") if (bind_ms is not None or F > 64 or F % 4 or F < 16)
-                           else "kept in leaf order: every level moves the rows, builds stream contiguous memory"},
+                   "rows": {qb.ROWS_IDS: "in place: row ids move, bin rows and packed gradients of the smaller children are gathered",
+                            qb.ROWS_IDS_GH: "in place: row ids and packed gradients move, the bin rows of the smaller children are gathered",
+                            qb.ROWS_IDS_CODED: "in place: row ids with the quantized gradients in the same 32 bits move, the bin rows of "
+                                               "the smaller children are gathered",
+                            qb.ROWS_ORDERED: "kept in leaf order: every level moves the rows, builds stream contiguous memory"}[layout]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "traffic_source": "rocprofv3 FETCH_SIZE + WRITE_SIZE runs of another process on this workload "

@@ -66,6 +66,8 @@ extern "C" {
 #define QGBDT_ROWS_ORDERED 3 /* row ids, packed gradients and bin rows: every build reads contiguous memory
                                 (uint8 bins, 16..64 features that are a multiple of 4, else QGBDT_E_UNSUPPORTED;
                                 needs QGBDT_WS_ROW_COPIES) */
+#define QGBDT_ROWS_IDS_CODED 4 /* (qgbdt_tree_layout's answer, not a choice) row ids with the quantized gradients in the
+                                  same 32 bits; histogram builds gather the bin rows */
 
 typedef struct qgbdt_ctx qgbdt_ctx;
 
@@ -334,6 +336,11 @@ QGBDT_API int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g,
  * batched expansion, nodes expanded (committed splits plus speculative ones), committed
  * splits, nodes created.  For callers that time or tune; no paper quantity. */
 QGBDT_API int qgbdt_tree_stats(const qgbdt_ctx* ctx, int32_t* out4);
+
+/* What the last grow_tree call on this context moved when it partitioned a leaf's rows (host out): QGBDT_ROWS_IDS, _IDS_GH,
+ * _ORDERED or _IDS_CODED; QGBDT_ROWS_AUTO before the first tree.  A histogram build then reads per row, beside the bin row:
+ * a row id and the packed gradients (6 bytes; 2 for _ORDERED, whose rows are contiguous) or one entry (4 bytes). */
+QGBDT_API int qgbdt_tree_layout(const qgbdt_ctx* ctx, int32_t* layout);
 
 /* Streaming-read rate of this device as a plain kernel reaches it: `buf` (dev, 16-byte aligned, `bytes` a
  * multiple of 16, at least 16) is read `reps` times with 16-byte loads by one grid-stride kernel per repetition,

@@ -19,6 +19,7 @@ LIB_PATH = os.path.join(_PKG, "libqgbdt.so")
 ROUND_STOCHASTIC = 0
 ROUND_NEAREST = 1
 ROWS_AUTO, ROWS_IDS, ROWS_IDS_GH, ROWS_ORDERED = 0, 1, 2, 3
+ROWS_IDS_CODED = 4  # told by Context.tree_layout, not to be asked for
 WS_BIND, WS_ROW_COPIES, WS_BOOST = 1, 2, 4
 E_WORKSPACE = -6
 
@@ -30,7 +31,7 @@ EXPORTS = [
     "qgbdt_logistic_gradients", "qgbdt_lambdarank_gradients", "qgbdt_update_scores", "qgbdt_boost_iteration",
     "qgbdt_boost_iteration_lambdarank",
     "qgbdt_set_profiling", "qgbdt_read_profile", "qgbdt_read_profile_roots", "qgbdt_tree_stats", "qgbdt_bind_bins",
-    "qgbdt_measure_stream_read", "qgbdt_describe_hist_plan",
+    "qgbdt_measure_stream_read", "qgbdt_describe_hist_plan", "qgbdt_tree_layout",
 ]
 
 
@@ -98,6 +99,7 @@ def load_library() -> C.CDLL:
         lib.qgbdt_read_profile.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double)]
         lib.qgbdt_read_profile_roots.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
         lib.qgbdt_tree_stats.argtypes = [C.c_void_p, C.POINTER(C.c_int32)]
+        lib.qgbdt_tree_layout.argtypes = [C.c_void_p, C.POINTER(C.c_int32)]
         lib.qgbdt_bind_bins.argtypes = [C.c_void_p, C.c_void_p]
         lib.qgbdt_measure_stream_read.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.POINTER(C.c_double),
                                                   C.POINTER(C.c_int32)]
@@ -445,6 +447,16 @@ def _tree_stats(self):
 
 
 Context.tree_stats = _tree_stats
+
+
+def _tree_layout(self):
+    """Row layout of the last grow_tree call: ROWS_IDS, ROWS_IDS_GH, ROWS_ORDERED or ROWS_IDS_CODED."""
+    out = C.c_int32(0)
+    self._chk(self.lib.qgbdt_tree_layout(self._h, C.byref(out)))
+    return out.value
+
+
+Context.tree_layout = _tree_layout
 
 
 def unpack_splits(raw: torch.Tensor):

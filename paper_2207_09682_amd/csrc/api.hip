@@ -662,13 +662,15 @@ int qgbdt_read_profile(qgbdt_ctx* ctx, double* hist_ms, int64_t* hist_launches, 
     StepState st;
     QG_HIP(ctx, hipMemcpy(&st, ctx->step, sizeof(st), hipMemcpyDeviceToHost));
     const double F = ctx->shape.n_features, nb = ctx->shape.n_bins;
-    // algorithmic bytes: a bin row and a packed (g~,h~) per row, a row id when gathered, one histogram per build
+    // algorithmic bytes: a bin row and a packed (g~,h~) per row, a row id when gathered (or one entry that holds both), one
+    // histogram per build
     *hist_bytes = (double)st.prof_rows_contig * (F + 2.0) + (double)st.prof_rows_idx * (F + 2.0 + 4.0) +
+                  (double)st.prof_rows_code * (F + 4.0) +
                   (double)st.prof_builds * F * nb * 8.0;
     *hist_ms = ms;
     *hist_launches = st.prof_launches;
     ctx->ev_used = 0;
-    st.prof_rows_contig = 0; st.prof_rows_idx = 0; st.prof_launches = 0; st.prof_builds = 0;
+    st.prof_rows_contig = 0; st.prof_rows_idx = 0; st.prof_rows_code = 0; st.prof_launches = 0; st.prof_builds = 0;
     QG_HIP(ctx, hipMemcpy(ctx->step, &st, sizeof(st), hipMemcpyHostToDevice));
     return QGBDT_OK;
 }
@@ -750,5 +752,10 @@ int qgbdt_tree_stats(const qgbdt_ctx* ctx, int32_t* out4) {
     return QGBDT_OK;
 }
 
+int qgbdt_tree_layout(const qgbdt_ctx* ctx, int32_t* layout) {
+    if (!ctx || !layout) return QGBDT_E_INVALID_ARG;
+    *layout = ctx->tree_layout;
+    return QGBDT_OK;
+}
 
 }  // extern "C"

@@ -39,7 +39,8 @@ struct StepState {
     int32_t n_known;       // nodes that have passed through tree_plan_kernel (all but the last round's children)
     int32_t n_list;        // entries of the kept gain order (see tree_plan_kernel)
     int64_t hist_units;    // rows*features of the histogram builds the sequential algorithm performs
-    int64_t prof_rows_contig, prof_rows_idx;  // rows seen by histogram launches
+    // rows seen by histogram launches: contiguous, gathered by row id, gathered by entries that hold their gradients (RowCode)
+    int64_t prof_rows_contig, prof_rows_idx, prof_rows_code;
     int64_t prof_launches;                    // histogram launches that had rows
     int64_t prof_builds;                      // histogram builds served by those launches
 };
@@ -236,6 +237,7 @@ struct qgbdt_ctx {
     int max_seg;
     int max_super;
     int rounds_hint;
+    int tree_layout;  // QGBDT_ROWS_* that the last tree was grown with
     // workspace
     int ordered;           // the workspace holds leaf-ordered copies of the rows (narrow rows, QGBDT_WS_ROW_COPIES)
     uint8_t* obins[qgbdt::COPY_BUFS];  // [N][F] each (ordered mode), else null

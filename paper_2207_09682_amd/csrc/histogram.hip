@@ -95,11 +95,12 @@ __device__ __forceinline__ int find_entry(const int* s_start, int n_entries, int
     return lo;
 }
 
-__device__ __forceinline__ void count_profile(const HistEntry* __restrict__ entries, int n_entries, bool idx,
+// mode: 0 contiguous rows, 1 gathered by row id, 2 gathered by entries that hold their gradients
+__device__ __forceinline__ void count_profile(const HistEntry* __restrict__ entries, int n_entries, int mode,
                                               StepState* step) {
     int64_t rows = 0;
     for (int e = 0; e < n_entries; ++e) rows += entries[e].count;
-    if (idx) step->prof_rows_idx += rows; else step->prof_rows_contig += rows;
+    if (mode == 2) step->prof_rows_code += rows; else if (mode == 1) step->prof_rows_idx += rows; else step->prof_rows_contig += rows;
     step->prof_launches += 1;
     step->prof_builds += n_entries;
 }
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;  // row-group lanes (a multiple of 8)
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX != 0, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX != 0, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);  // at least 16 bytes
@@ -483,7 +484,7 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX != 0, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);  // a multiple of V
@@ -646,7 +647,7 @@ __global__ __launch_bounds__(TWO ? 1024 : HIST_THREADS, TWO ? 1 : HIST_WAVES) vo
     const int n_entries = table_counts[0], n_items = table_counts[1];
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     if ((int)blockIdx.x >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, false, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, 0, step);
 
     const int RPI = plan.flat_rows, L = plan.flat_lanes;
     const int BR = U * RPI;  // rows of one block of U iterations
@@ -883,7 +884,7 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, use_idx != 0, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, !use_idx ? 0 : src.code.on() ? 2 : 1, step);
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
     const int lds_words = ft * nb;

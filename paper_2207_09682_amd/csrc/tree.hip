@@ -707,6 +707,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     const bool gh_lists = layout != QGBDT_ROWS_IDS;
     if (ordered && !ctx->ordered)
         return set_error(ctx, QGBDT_E_WORKSPACE, "the workspace has no room for leaf-ordered copies of the rows");
+    ctx->tree_layout = rows.code.on() ? QGBDT_ROWS_IDS_CODED : layout;
     for (int b = 0; b < ROW_BUFS; ++b) {
         rows.bins[b] = ordered && b < COPY_BUFS ? ctx->obins[b] : bins;
         rows.gh[b] = gh_lists ? ctx->ogh[b] : ctx->gh;
