@@ -661,11 +661,11 @@ int qgbdt_read_profile(qgbdt_ctx* ctx, double* hist_ms, int64_t* hist_launches, 
     }
     StepState st;
     QG_HIP(ctx, hipMemcpy(&st, ctx->step, sizeof(st), hipMemcpyDeviceToHost));
-    const double F = ctx->shape.n_features, nb = ctx->shape.n_bins;
+    const double F = ctx->shape.n_features, nb = ctx->shape.n_bins, row = F * ctx->shape.bin_bytes;
     // algorithmic bytes: a bin row and a packed (g~,h~) per row, a row id when gathered (or one entry that holds both), one
     // histogram per build
-    *hist_bytes = (double)st.prof_rows_contig * (F + 2.0) + (double)st.prof_rows_idx * (F + 2.0 + 4.0) +
-                  (double)st.prof_rows_code * (F + 4.0) +
+    *hist_bytes = (double)st.prof_rows_contig * (row + 2.0) + (double)st.prof_rows_idx * (row + 2.0 + 4.0) +
+                  (double)st.prof_rows_code * (row + 4.0) +
                   (double)st.prof_builds * F * nb * 8.0;
     *hist_ms = ms;
     *hist_launches = st.prof_launches;

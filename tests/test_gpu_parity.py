@@ -852,15 +852,15 @@ def test_profile_separates_root_builds_from_the_rounds_builds():
 
 
 # one split: the root build and the smaller child's, counted as the layout of the row lists reads them
-@pytest.mark.parametrize("N,F,bits,row_layout,layout,per_row", [(20_000, 3, 3, 0, 4, 4), (20_000, 16, 3, 0, 4, 4), (20_000, 80, 3, 0, 4, 4),
-                                                                 (20_000, 16, 3, 1, 1, 6), (20_000, 80, 3, 2, 2, 6), (20_000, 16, 3, 3, 3, 2),
-                                                                 (70_000, 16, 8, 0, 1, 6)])
-def test_profile_counts_what_the_row_layout_reads(N, F, bits, row_layout, layout, per_row):
+@pytest.mark.parametrize("N,F,bits,row_layout,layout,per_row,bb", [
+    (20_000, 3, 3, 0, 4, 4, 1), (20_000, 16, 3, 0, 4, 4, 1), (20_000, 80, 3, 0, 4, 4, 1), (20_000, 16, 3, 1, 1, 6, 1), (20_000, 80, 3, 2, 2, 6, 1),
+    (20_000, 16, 3, 3, 3, 2, 1), (70_000, 16, 8, 0, 1, 6, 1), (20_000, 16, 3, 0, 4, 4, 2), (20_000, 9, 3, 1, 1, 6, 2)])
+def test_profile_counts_what_the_row_layout_reads(N, F, bits, row_layout, layout, per_row, bb):
     nb = 32
     rng = np.random.default_rng(F)
-    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint16 if bb == 2 else np.uint8)
     g = (bins[:, 1] / nb - 0.3 + 0.1 * rng.normal(size=N)).astype(np.float32)
-    ctx = _ctx(N, F, nb, L=4)
+    ctx = _ctx16(N, F, nb, L=4) if bb == 2 else _ctx(N, F, nb, L=4)
     ctx.set_profiling(True)
     ctx.read_profile()
     t = ctx.grow_tree(torch.from_numpy(bins).cuda(), torch.from_numpy(g).cuda(), torch.ones(N, device="cuda"), bits, bits, 0, 0, 2, row_layout=row_layout)
@@ -868,7 +868,7 @@ def test_profile_counts_what_the_row_layout_reads(N, F, bits, row_layout, layout
     ctx.set_profiling(False)
     small = int(t.leaf_count[:2].min().item())
     assert ctx.tree_layout() == layout and ctx.tree_stats() == (1, 1, 1, 3) and n == 2 and 0 < small < N // 2
-    assert nbytes == N * (F + 2) + small * (F + per_row) + 2 * F * nb * 8
+    assert nbytes == N * (F * bb + 2) + small * (F * bb + per_row) + 2 * F * nb * 8
 
 
 # ----------------------------------------------------------------------------
