@@ -368,11 +368,13 @@ inline bool part_supers(int64_t n_rows, bool bound) { return n_rows > ((int64_t)
 // all in flight at once); builds of more row groups are summed up by the reduce kernel, which spreads them over the
 // whole chip and otherwise returns at once.  Trees with 8 / 64: 400 k x 2000 1283 / 1396 us, 2 M x 40 of 16-bit bins
 // 924 / 980 us, 1 M x 28 the same.
-// Where no build can have more than about 32 groups (hist_target_rows: 2^14 rows in one tile, 2^17 rows times tiles in several) the
-// search adds them all up and the reduce kernel, 3 us of every round with the gap in front of it, is not launched.  Trees with / without
-// it: 10 k x 28 196 / 187 us, 16 k x 28 281 / 272 us, 60 k x 100 284 / 270 us, 8 k x 500 452 / 436 us; beyond the line 30 k x 28 267 / 269 us, 100 k x 50
-// 311 / 332 us.
+// Where no build can have more than 32 groups the search adds them all up and the reduce kernel, 3 us of every round with the gap in
+// front of it, is not launched: up to 2^14 rows in one tile, 2^17 rows times tiles in several (hist_target_rows), unless the bits
+// of a forced word width allow short groups only.  Trees with / without the launch: 10 k x 28 196 / 187 us, 16 k x 28 281 / 272 us,
+// 60 k x 100 284 / 270 us, 8 k x 500 452 / 436 us; beyond the lines 30 k x 28 267 / 269 us, 100 k x 50 311 / 332 us, and with 8 bits in 32-bit
+// words (groups of 129 rows) 16 k x 28 280 / 308 us, 30 k x 100 410 / 518 us, 65 k x 68 339 / 540 us.
 constexpr int REDUCE_ABOVE = 8;
+constexpr int SEARCH_SUMS_MOST = 33;  // (32 and one that rounding may add)
 constexpr int ALL_GROUPS = 0x7fffffff;
 constexpr int PART_SUPER = 32;  // segments whose left rows are summed up in one counter
 // Most nodes expanded in one round = most builds of a histogram launch (the leaf budget; the growth bookkeeping

@@ -1130,12 +1130,14 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
             if ((16 * l) % F == 0) { p.flat_lanes = l; p.flat_rows = 16 * l / F; break; }
     }
     p.pieces = (fast && !wide_ft && (F - (p.n_tiles - 1) * p.ft) * s.bin_bytes >= 16) ? (p.ft * s.bin_bytes + 15) / 16 : 0;
-    p.search_sums = s.n_rows * p.n_tiles <= (p.n_tiles > 1 ? 1 << 17 : 1 << 14) ? ALL_GROUPS : REDUCE_ABOVE;
     p.slot_bytes = (p.lds_bytes + 15) & ~15;
     p.max_items = 4 * p.max_groups;
     if (p.max_items < 2 * s.max_leaves + 64) p.max_items = 2 * s.max_leaves + 64;
     p.single_rows = p.chunk_rows >= 1024 ? p.chunk_rows - 320 : p.chunk_rows / 2;
     if (p.single_rows < 1) p.single_rows = 1;
+    const int64_t t = hist_target_rows(p, s.n_rows, 1);
+    const bool few = s.n_rows * p.n_tiles <= (p.n_tiles > 1 ? 1 << 17 : 1 << 14) && (s.n_rows + t - 1) / t <= SEARCH_SUMS_MOST;
+    p.search_sums = few ? ALL_GROUPS : REDUCE_ABOVE;
     return p;
 }
 

@@ -109,6 +109,21 @@ def test_row_entries_with_gradients(N, bits_g, bits_h, F, nb, bb):
     assert np.allclose(t.leaf_value.cpu().numpy()[:L], e.leaf_value[:L], rtol=1e-9, atol=1e-13)
 
 
+# 32-bit working words and 8-bit gradients: groups of 129 rows, on both sides of where the split search adds them all up itself
+@pytest.mark.parametrize("N,F", [(4000, 28), (4400, 28), (2000, 100), (12_000, 100)])
+def test_small_trees_of_many_short_row_groups(N, F):
+    nb, L = 255, 31
+    rng = np.random.default_rng(N)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    g = (bins[:, 0] / nb * (bins[:, 1] > 99) - 0.3 + 0.1 * rng.normal(size=N)).astype(np.float32)
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L)
+    e = oracle.grow_tree(bins, nb, g, h, 8, 8, 5, 0, L, min_data=20)
+    t = ctx.grow_tree(torch.from_numpy(bins).cuda(), torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 8, 8, 5, 0, L, min_data_in_leaf=20, acc_width=16)
+    _check(t, e, N)
+
+
 def test_trees_of_very_different_depth_in_turn():
     # the number of rounds enqueued up front is the last tree's: too few and too many of them, on one context, without a
     # synchronisation of the caller's between the trees

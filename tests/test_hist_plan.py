@@ -276,3 +276,29 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
         whole = p["ft"] * bb % 16 == 0 and F % p["ft"] * bb % 16 == 0
         if whole:   # the variant without the test for bins held twice
             assert all(min(p["ft"], F - t * p["ft"]) * bb % 16 == 0 for t in range(p["n_tiles"])), key
+
+
+@pytest.mark.parametrize("shape", SHAPES + [(16_384, 28, 255, 31, 1), (16_385, 28, 255, 31, 1), (65_536, 68, 255, 31, 1), (65_537, 68, 255, 31, 1),
+                                            (30_000, 100, 255, 63, 1), (4100, 28, 255, 31, 1)], ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
+def test_the_search_adds_up_few_row_groups_only(shape):
+    # where a tree's builds are not reduced by a launch of their own, none of them has more than 32 row groups (33 by rounding), whatever the
+    # bits and the width allow a group to hold, and however the rows are spread over the builds of a launch
+    N, F, nb, L, bb = shape
+    for key, p in _plans(shape):
+        if p["search_sums"] == 8:
+            continue
+        assert p["search_sums"] == 2 ** 31 - 1, key
+        for n_builds in {1, 2, min(L, 17), L}:
+            for total in {1, 700, N // 3 + 1, N}:
+                t = describe_hist_plan(N, F, nb, L, bb, key[0], key[1], key[2], key[3], rows=total, n_builds=n_builds)["target_rows"]
+                if n_builds > 1 or not p["flat_lanes"]:
+                    assert -(-total // t) <= 33, (key, n_builds, total, t)
+
+
+def test_small_trees_with_long_row_groups_need_no_reduction():
+    rng = np.random.default_rng(0)
+    for N in [1, 2, 511, 512, 513, 16_383, 16_384, 16_385, 65_535, 65_536] + rng.integers(1, 140_000, 200).tolist():
+        for F, bits in ((28, 2), (28, 5), (68, 3), (100, 3), (100, 8), (500, 4)):
+            p = describe_hist_plan(N, F, 255, 31, 1, bits, bits)
+            small = N * p["n_tiles"] <= (2 ** 17 if p["n_tiles"] > 1 else 2 ** 14)
+            assert p["search_sums"] == (2 ** 31 - 1 if small else 8), (N, F, bits)
