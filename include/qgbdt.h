@@ -136,7 +136,7 @@ typedef struct {
 /* ---- lifecycle ---------------------------------------------------------- */
 
 /* Device memory: the caller owns all of it.  The library allocates no device memory anywhere; it owns only the
- * host-side context (and a few bytes of pinned host memory for the status word grow_tree reads back).
+ * host-side context (and a few bytes of pinned host memory, to which the GPU reports whether a tree is finished).
  *
  * qgbdt_workspace_bytes: bytes of device workspace a context of `shape` needs (host out), from the shape alone:
  * five row-index buffers and five lists of packed gradients that follow them, the quantized gradients, a pool of
@@ -250,9 +250,9 @@ QGBDT_API int qgbdt_refit_leaves(qgbdt_ctx* ctx, const float* g, const float* h,
  * The result is that of this sequential procedure; the work is done in rounds that
  * expand several leaves at once (the one the procedure needs next plus leaves it is
  * likely to need), and the order of the splits is replayed on the device.  The host
- * waits on the stream once per batch of rounds to read a 'finished' flag (normally
- * once per tree) and, when n_rows exceeds what a 32-bit field surely holds, once
- * more after quantization to check the quantized totals (QGBDT_E_OVERFLOW_RISK).
+ * enqueues as many rounds as the last tree took, waits until the GPU reports whether
+ * the tree is finished, enqueues further rounds while it is not, and, when n_rows
+ * exceeds what a 32-bit field surely holds, waits once more after quantization to check the quantized totals (QGBDT_E_OVERFLOW_RISK).
  * bins: dev; g, h: dev float[n_rows]; row_idx_out: dev int32[n_rows], leaf-ordered
  * rows (ascending inside each leaf). */
 QGBDT_API int qgbdt_grow_tree(qgbdt_ctx* ctx, const void* bins, const float* g, const float* h,
@@ -337,6 +337,11 @@ QGBDT_API int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g,
  * batched expansion, nodes expanded (committed splits plus speculative ones), committed
  * splits, nodes created.  For callers that time or tune; no paper quantity. */
 QGBDT_API int qgbdt_tree_stats(const qgbdt_ctx* ctx, int32_t* out4);
+
+/* Launches enqueued for the last grow_tree call on this context (host out int32[2]): rounds, of which those beyond the
+ * rounds of qgbdt_tree_stats found the tree finished, and passes over its leaves (1 to 4; more than 1 when the number of
+ * rounds enqueued up front, that of the tree before, was too small).  For callers that time or tune. */
+QGBDT_API int qgbdt_tree_launches(const qgbdt_ctx* ctx, int32_t* out2);
 
 /* What the last grow_tree call on this context moved when it partitioned a leaf's rows (host out): QGBDT_ROWS_IDS, _IDS_GH,
  * _ORDERED or _IDS_CODED; QGBDT_ROWS_AUTO before the first tree.  A histogram build then reads per row, beside the bin row:

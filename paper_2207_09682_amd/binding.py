@@ -32,6 +32,7 @@ EXPORTS = [
     "qgbdt_boost_iteration_lambdarank",
     "qgbdt_set_profiling", "qgbdt_read_profile", "qgbdt_read_profile_roots", "qgbdt_tree_stats", "qgbdt_bind_bins",
     "qgbdt_measure_stream_read", "qgbdt_describe_hist_plan", "qgbdt_tree_layout",
+    "qgbdt_tree_launches",
 ]
 
 
@@ -99,6 +100,7 @@ def load_library() -> C.CDLL:
         lib.qgbdt_read_profile.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double)]
         lib.qgbdt_read_profile_roots.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
         lib.qgbdt_tree_stats.argtypes = [C.c_void_p, C.POINTER(C.c_int32)]
+        lib.qgbdt_tree_launches.argtypes = [C.c_void_p, C.POINTER(C.c_int32)]
         lib.qgbdt_tree_layout.argtypes = [C.c_void_p, C.POINTER(C.c_int32)]
         lib.qgbdt_bind_bins.argtypes = [C.c_void_p, C.c_void_p]
         lib.qgbdt_measure_stream_read.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.POINTER(C.c_double),
@@ -457,6 +459,16 @@ def _tree_layout(self):
 
 
 Context.tree_layout = _tree_layout
+
+
+def _tree_launches(self):
+    """(rounds, passes over the leaves) enqueued for the last grow_tree call."""
+    out = (C.c_int32 * 2)()
+    self._chk(self.lib.qgbdt_tree_launches(self._h, out))
+    return tuple(int(x) for x in out)
+
+
+Context.tree_launches = _tree_launches
 
 
 def unpack_splits(raw: torch.Tensor):

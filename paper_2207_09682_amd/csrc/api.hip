@@ -754,6 +754,12 @@ int qgbdt_tree_stats(const qgbdt_ctx* ctx, int32_t* out4) {
     return QGBDT_OK;
 }
 
+int qgbdt_tree_launches(const qgbdt_ctx* ctx, int32_t* out2) {
+    if (!ctx || !out2) return QGBDT_E_INVALID_ARG;
+    out2[0] = ctx->tree_rounds; out2[1] = ctx->tree_passes;
+    return QGBDT_OK;
+}
+
 int qgbdt_tree_layout(const qgbdt_ctx* ctx, int32_t* layout) {
     if (!ctx || !layout) return QGBDT_E_INVALID_ARG;
     *layout = ctx->tree_layout;

@@ -238,6 +238,7 @@ struct qgbdt_ctx {
     int max_super;
     int rounds_hint;
     int tree_layout;  // QGBDT_ROWS_* that the last tree was grown with
+    int tree_rounds, tree_passes;  // rounds and passes over its leaves that were enqueued for it
     // workspace
     int ordered;           // the workspace holds leaf-ordered copies of the rows (narrow rows, QGBDT_WS_ROW_COPIES)
     uint8_t* obins[qgbdt::COPY_BUFS];  // [N][F] each (ordered mode), else null

@@ -618,13 +618,13 @@ int prepare_tree_kernels(qgbdt_ctx* ctx) {
     return QGBDT_OK;
 }
 
-// Waits for the answer to request `seq` in pinned memory: the stream's work behind it goes on meanwhile.  (Copying the status word
+// Waits for the answer to request `seq` or a later one in pinned memory: the stream's work behind it goes on meanwhile.  (Copying the status word
 // and waiting for the stream left the GPU idle for 15 to 25 us at the end of every tree.)  The stream is asked now and then whether it is still at work, so that an error ends the wait.
 static int wait_for_report(qgbdt_ctx* ctx, uint64_t seq, bool* done) {
     const auto answered = [&]() {
         const uint64_t a = __atomic_load_n(&ctx->report->answer, __ATOMIC_ACQUIRE);
         *done = a & 1;
-        return a >> 1 == seq;
+        return a >> 1 >= seq;
     };
     for (auto next = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);;) {
         for (int k = 0; k < 64; ++k) {
@@ -744,8 +744,6 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
 
     const size_t plan_lds = plan_kernel_lds(ctx, p->num_leaves);  // at most what prepare_tree_kernels allowed
     const int round_cap = 4 * ctx->shape.max_leaves + 8;  // every round commits or expands at least one node
-    int launched = 0;
-    int to_launch = ctx->rounds_hint;
     auto plan_batch = [&](uint64_t report_seq) {
         hipLaunchKernelGGL(tree_plan_kernel, dim3(1), dim3(1024), plan_lds, ctx->stream, ctx->step, ctx->nodes, ctx->batch,
                            ctx->batch_seg, ctx->super_counts, ctx->plan_list, ctx->hist_counts, F, n_cand, p->num_leaves,
@@ -762,32 +760,58 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         if (rc != QGBDT_OK) return rc;
         return search_splits(plan, ctx->batch_max);
     };
-    for (;;) {
-        for (int r = 0; r < to_launch; ++r) {
-            plan_batch(0);
-            rc = expand_batch();
-            if (rc != QGBDT_OK) return rc;
-        }
-        launched += to_launch;
-        // one more plan: commits what the last round made known and tells whether the tree is finished; behind it, what is
-        // left to do if it is
-        const uint64_t seq = ++ctx->report_seq;
-        plan_batch(seq);
+    auto leaf_passes = [&]() {  // what is left to do when the tree is finished; returns at once while it is not
+        ctx->tree_passes += 1;
         hipLaunchKernelGGL(tree_finalize_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->step, ctx->nodes, ctx->delta,
                            refit_parts(N), refit_extra(N), ctx->refit_units, ctx->refit_leaves, out);
         QG_HIP(ctx, hipGetLastError());
-        rc = launch_gather_refit(ctx, idxs, rows.code.id_mask, row_idx_out, out.t.n_leaves, out.t.leaf_value);
-        if (rc != QGBDT_OK) return rc;
-        bool done = false;
-        rc = wait_for_report(ctx, seq, &done);
-        if (rc != QGBDT_OK) return rc;
-        if (done) break;
-        if (launched > round_cap) return set_error(ctx, QGBDT_E_HIP, "tree growth did not finish in %d rounds", launched);
-        // the trailing plan has already chosen a batch: finish that round, then ask again
+        return launch_gather_refit(ctx, idxs, rows.code.id_mask, row_idx_out, out.t.n_leaves, out.t.leaf_value);
+    };
+    ctx->tree_rounds = 0;
+    ctx->tree_passes = 0;
+    for (; ctx->tree_rounds < ctx->rounds_hint; ++ctx->tree_rounds) {
+        plan_batch(0);
         rc = expand_batch();
         if (rc != QGBDT_OK) return rc;
-        launched += 1;
-        to_launch = 0;
+    }
+    // One more plan commits what the last round made known and tells whether the tree is finished; behind it, what is left to do
+    // if it is.  A tree that needs a round or two more than the last one gets each after the answer to the one before.
+    bool done = false;
+    for (int missing = 0;; ++missing) {
+        plan_batch(++ctx->report_seq);
+        rc = leaf_passes();
+        if (rc != QGBDT_OK) return rc;
+        rc = wait_for_report(ctx, ctx->report_seq, &done);
+        if (rc != QGBDT_OK) return rc;
+        if (done || missing == 2) break;
+        rc = expand_batch();  // (the plan has chosen a batch already)
+        if (rc != QGBDT_OK) return rc;
+        ctx->tree_rounds += 1;
+    }
+    if (!done) {
+        // From the third missing round on a round is enqueued before the host has read the answer of the one in front of it, so that
+        // the GPU does not wait for the host, and the leaf passes at the end; the last round finds the tree finished (9 us).  Each
+        // after the answer, with the leaf passes behind it, cost 5 us per missing round.  First tree of a context (10 rounds enqueued up
+        // front), each after the answer / one ahead / three per answer: 100 k x 50 with 56 rounds 2216 / 2030 / 2068 us, 20 M x 200 with
+        // 21 rounds 10.76 / 10.66 / 10.71 ms; one round missing: 1 M x 28 658 / 673 / 700 us, 464 k x 90 702 / 711 / 742 us.
+        auto one_more = [&]() {
+            const int rc = expand_batch();
+            ctx->tree_rounds += 1;
+            plan_batch(++ctx->report_seq);
+            return rc;
+        };
+        rc = one_more();
+        while (rc == QGBDT_OK && !done) {
+            if (ctx->tree_rounds > round_cap) return set_error(ctx, QGBDT_E_HIP, "tree growth did not finish in %d rounds", ctx->tree_rounds);
+            rc = one_more();
+            if (rc == QGBDT_OK) rc = wait_for_report(ctx, ctx->report_seq - 1, &done);
+        }
+        if (rc != QGBDT_OK) return rc;
+        rc = leaf_passes();
+        if (rc != QGBDT_OK) return rc;
+        // (nothing that is still to run writes the report when the call returns)
+        rc = wait_for_report(ctx, ctx->report_seq, &done);
+        if (rc != QGBDT_OK) return rc;
     }
     ctx->rounds_hint = ctx->report->rounds > 0 ? ctx->report->rounds : 1;
     return QGBDT_OK;

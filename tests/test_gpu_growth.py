@@ -109,6 +109,31 @@ def test_row_entries_with_gradients(N, bits_g, bits_h, F, nb, bb):
     assert np.allclose(t.leaf_value.cpu().numpy()[:L], e.leaf_value[:L], rtol=1e-9, atol=1e-13)
 
 
+def test_rounds_beyond_those_enqueued_up_front():
+    # a tree of more rounds than the one before it: whatever is missing, at most one round too many is enqueued and the passes over
+    # the leaves at most four times
+    N, F, nb, L = 20_000, 12, 64, 255
+    rng = np.random.default_rng(3)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    g = np.exp(0.3 * (bins[:, :8] > nb - 6).sum(1) ** 2).astype(np.float32) + 0.1 * rng.normal(size=N).astype(np.float32)
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L)
+    dbins, dg, dh = torch.from_numpy(bins).cuda(), torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda()
+    up_front = 10   # of a context's first tree
+    seen = set()
+    for i, l in enumerate((L, L, 2, L, 3, 5, 40, 2, 4, 6, 8, 10, 12, 2, 3, 2, 6, 2, 8)):
+        t = ctx.grow_tree(dbins, dg, dh, 3, 3, 5, 0, l, min_data_in_leaf=20)
+        _check(t, oracle.grow_tree(bins, nb, g, h, 3, 3, 5, 0, l, min_data=20), N)
+        rounds = ctx.tree_stats()[0]
+        assert i > 0 or rounds > up_front + 3
+        missing = rounds - up_front
+        assert ctx.tree_launches() == ((up_front, 1) if missing <= 0 else (rounds, missing + 1) if missing <= 2 else (rounds + 1, 4)), (i, l, rounds)
+        seen.add(min(missing, 3))
+        up_front = rounds
+    assert {0, 1, 2, 3} <= seen, seen
+
+
 # 32-bit working words and 8-bit gradients: groups of 129 rows, on both sides of where the split search adds them all up itself
 @pytest.mark.parametrize("N,F", [(4000, 28), (4400, 28), (2000, 100), (12_000, 100)])
 def test_small_trees_of_many_short_row_groups(N, F):
