@@ -134,6 +134,27 @@ def test_rounds_beyond_those_enqueued_up_front():
     assert {0, 1, 2, 3} <= seen, seen
 
 
+# what the automatic choice takes for a matrix that is not bound, and that the choice does not change the tree
+@pytest.mark.parametrize("N,F,L,layout", [(1_600_000, 20, 255, 4), (1_700_000, 20, 255, 3), (1_600_000, 16, 255, 4), (1_700_000, 16, 255, 3),
+                                          (2_100_000, 16, 64, 4), (2_200_000, 20, 64, 3), (3_200_000, 16, 5, 4), (3_300_000, 16, 5, 3), (2_000_000, 24, 255, 4)])
+def test_layout_of_an_unbound_matrix(N, F, L, layout):
+    nb = 32
+    rng = np.random.default_rng(F)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint8)
+    g = (bins[:, 0] / nb * (bins[:, 1] > 9) - 0.3 * (bins[:, 2] > 20) + 0.1 * rng.normal(size=N)).astype(np.float32)
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L)
+    dbins, dg, dh = torch.from_numpy(bins).cuda(), torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda()
+    trees = []
+    for asked, took in ((0, layout), (1, 1)):
+        t = ctx.grow_tree(dbins, dg, dh, 3, 3, 5, 0, L, row_layout=asked)
+        assert ctx.tree_layout() == took
+        trees.append({k: getattr(t, k).cpu() for k in ("n_leaves", "split_feature", "split_bin", "split_gain", "leaf_sum_g", "leaf_sum_h", "leaf_value", "row_idx")})
+    for k, v in trees[0].items():
+        assert torch.equal(v, trees[1][k]), k
+
+
 # 32-bit working words and 8-bit gradients: groups of 129 rows, on both sides of where the split search adds them all up itself
 @pytest.mark.parametrize("N,F", [(4000, 28), (4400, 28), (2000, 100), (12_000, 100)])
 def test_small_trees_of_many_short_row_groups(N, F):
