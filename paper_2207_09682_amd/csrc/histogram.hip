@@ -1130,6 +1130,12 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
             if ((16 * l) % F == 0) { p.flat_lanes = l; p.flat_rows = 16 * l / F; break; }
     }
     p.pieces = (fast && !wide_ft && (F - (p.n_tiles - 1) * p.ft) * s.bin_bytes >= 16) ? (p.ft * s.bin_bytes + 15) / 16 : 0;
+    // Contiguous rows in one tile of two or three pieces whose last one has at most four bytes of its own stay with the dword
+    // kernel: a third to a half of the piece kernel's atomics would be for bins that it leaves out.  Dwords / pieces, one build of
+    // 8 M rows: 17 features 74 / 77 us (5 bits 79 / 90), 19 73 / 76 (81 / 86), 34 118 / 123 (137 / 135), 9 of 16-bit bins 60 / 64 us; beyond
+    // the line 21 features 81 / 77 us, 37 126 / 127, 49 169 / 155.  (Gathered rows: pieces throughout, they cost one line each.)
+    const int tail = p.ft * s.bin_bytes % 16;
+    p.dword_pieces = p.n_tiles == 1 && tail >= 1 && tail <= 4 ? 3 : 0;
     p.slot_bytes = (p.lds_bytes + 15) & ~15;
     p.max_items = 4 * p.max_groups;
     if (p.max_items < 2 * s.max_leaves + 64) p.max_items = 2 * s.max_leaves + 64;
@@ -1301,7 +1307,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #undef QG_LAUNCH_WIDE_V
 #undef QG_LAUNCH_WIDE
 #undef QG_LAUNCH_WIDE_S
-    } else if (fast && plan.pieces > 0) {
+    } else if (fast && plan.pieces > (mode == 0 ? plan.dword_pieces : 0)) {
 #define QG_LAUNCH_PIECE_K(W_, IDX_, RAG_, BB_)                                                                      \
     hipLaunchKernelGGL((hist_piece_kernel<W_, IDX_, RAG_, BB_>), grid, block, plan.lds_bytes, ctx->stream, \
                        rows, idx, entries, table_counts, hist_base, partials, F, nb, plan, step)

@@ -1119,6 +1119,32 @@ def test_random_histogram_slices(seed):
         del ctx
 
 
+# rows of a few bytes more than one or two 16-byte pieces: by dwords where they are contiguous, by pieces where they are gathered
+@pytest.mark.parametrize("F,bb", [(17, 1), (18, 1), (19, 1), (20, 1), (21, 1), (33, 1), (36, 1), (37, 1), (49, 1), (9, 2), (10, 2), (11, 2), (17, 2), (18, 2), (25, 2)])
+def test_rows_of_a_few_bytes_more_than_whole_pieces(F, bb):
+    from paper_2207_09682_amd import Context
+    N, nb = 30_011, 200 if bb == 1 else 400
+    rng = np.random.default_rng(F)
+    mat = rng.integers(0, nb, (N, F)).astype(np.uint16 if bb == 2 else np.uint8)
+    ctx = Context(N, F, nb, max_leaves=4, bin_bytes=bb)
+    idx = np.sort(rng.choice(N, N // 3, replace=False)).astype(np.int32)
+    for off in (0, 4):   # a matrix that is 16-byte aligned, one that is 4-byte aligned
+        dbuf = torch.zeros(N * F * bb + 16, dtype=torch.uint8, device="cuda")
+        dmat = dbuf[off:off + N * F * bb]
+        dmat.copy_(torch.from_numpy(mat.view(np.uint8).reshape(-1)))
+        dmat = (dmat.view(torch.uint16) if bb == 2 else dmat).view(N, F)
+        for bits in ((3, 3), (5, 5), (8, 8)):
+            gq, hq, gh = _rand_gh(rng, N, *bits, "cuda")
+            for acc in (0, 16, 32):
+                for kw in (dict(), dict(begin=5, count=N - 77), dict(row_idx=idx)):
+                    exp = _pack_hist(oracle.build_histograms(mat, nb, gq, hq, **kw))
+                    gkw = dict(kw)
+                    if "row_idx" in gkw:
+                        gkw.update(row_idx=torch.from_numpy(idx).cuda(), count=idx.size)
+                    got = ctx.build_histograms(dmat, gh, bits_g=bits[0], bits_h=bits[1], acc_width=acc, **gkw).cpu().numpy().reshape(nb, F)
+                    assert np.array_equal(got, exp), (off, bits, acc, list(kw))
+
+
 # ----------------------------------------------------------------------------
 # most-frequent-bin skipping (bound, skewed wide matrices)
 # ----------------------------------------------------------------------------

@@ -295,6 +295,18 @@ def test_the_search_adds_up_few_row_groups_only(shape):
                     assert -(-total // t) <= 33, (key, n_builds, total, t)
 
 
+@pytest.mark.parametrize("F,bb,most", [(16, 1, 0), (17, 1, 3), (20, 1, 3), (21, 1, 0), (32, 1, 0), (33, 1, 3), (36, 1, 3), (37, 1, 0), (8, 2, 0), (9, 2, 3),
+                                       (10, 2, 3), (11, 2, 0), (17, 2, 3), (19, 2, 0), (65, 1, 0), (28, 1, 0)])
+def test_contiguous_rows_that_are_read_by_dwords(F, bb, most):
+    # a last piece of one to four bytes of its own: contiguous rows of at most three pieces take the dword kernel
+    for (bg, bh), acc in itertools.product(BITS, (0, 16, 32)):
+        p = describe_hist_plan(50_000, F, 255 if bb == 1 else 400, 15, bb, bg, bh, acc)
+        if p["n_tiles"] == 1:
+            assert p["dword_pieces"] == most and p["pieces"] == -(-F * bb // 16), (bg, bh, acc)
+        else:
+            assert p["dword_pieces"] == 0
+
+
 def test_small_trees_with_long_row_groups_need_no_reduction():
     rng = np.random.default_rng(0)
     for N in [1, 2, 511, 512, 513, 16_383, 16_384, 16_385, 65_535, 65_536] + rng.integers(1, 140_000, 200).tolist():
