@@ -290,7 +290,8 @@ int qgbdt_create(qgbdt_ctx** out, const qgbdt_shape* shape, void* stream) {
         }
         c->static_scratch = g_static_scratch_ptr[c->device];
     }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->report), sizeof(TreeReport), hipHostMallocDefault) != hipSuccess)
+    // (coherent by name, not by a default that the environment can change: the host reads it while the stream is at work)
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->report), sizeof(TreeReport), hipHostMallocCoherent) != hipSuccess)
         rc = set_error(c, QGBDT_E_ALLOC, "hipHostMalloc failed");
     else *c->report = TreeReport{};
     // kernels whose local bins or bookkeeping exceed the default limit of dynamic LDS are told so once
