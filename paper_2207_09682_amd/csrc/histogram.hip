@@ -1078,7 +1078,8 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
         }
         if (best_ft == 0 && aligned && (int64_t)pitch_of(npd) * nb * wbytes <= lds_budget) best_ft = npd;
         if (best_ft > 0) {
-            // as many tiles, of more even widths, where the last one's rows would be shorter than a 16-byte piece (F = 68: 36 + 32, not 64 + 4)
+            // as many tiles, of more even widths, where the last one's rows would be shorter than a 16-byte piece (36 features in
+            // 64-bit words: 20 + 16, not 32 + 4)
             const int tiles = (F + best_ft - 1) / best_ft, piece = 16 / s.bin_bytes;
             const int even = ((F + tiles - 1) / tiles + npd - 1) / npd * npd;
             if (F - (tiles - 1) * best_ft < piece && even < best_ft && F - (tiles - 1) * even >= piece) best_ft = even;

@@ -249,9 +249,12 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
     # lane's sixteen (eight) atomics exactly once, whatever the row's rotation of their order
     N, F, nb, L, bb = shape
     for key, p in _plans(shape):
-        if p["bytewise"] or p["wide_v"] or (F - (p["n_tiles"] - 1) * p["ft"]) * bb < 16:
+        last = (F - (p["n_tiles"] - 1) * p["ft"]) * bb
+        assert (p["pieces"] > 0) == (not p["bytewise"] and not p["wide_v"] and last >= 16), key
+        if p["pieces"] == 0:
             continue                                                 # other kernels
-        P, npd = -(-p["ft"] * bb // 16), 4 // bb
+        P, npd = p["pieces"], 4 // bb
+        assert P == -(-p["ft"] * bb // 16)
         rpi = 64 // P
         assert rpi >= 1, key
         for tile in range(p["n_tiles"]):
@@ -272,10 +275,17 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
                             if j >= (16 * c - at) // bb:
                                 seen.append(at // bb + j)
                 assert sorted(seen) == list(range(ft)), (key, tile, r)
-        assert not (F * bb >= 16 and p["bytewise"]), key
-        whole = p["ft"] * bb % 16 == 0 and F % p["ft"] * bb % 16 == 0
-        if whole:   # the variant without the test for bins held twice
-            assert all(min(p["ft"], F - t * p["ft"]) * bb % 16 == 0 for t in range(p["n_tiles"])), key
+
+
+# which widths the piece kernel serves: (tiles, features per tile, pieces); 0 pieces: the last tile is narrower than one
+@pytest.mark.parametrize("F,nb,bb,bits,plan", [
+    (15, 255, 1, 3, (1, 15, 0)), (16, 255, 1, 3, (1, 16, 1)), (17, 255, 1, 3, (1, 17, 2)), (28, 255, 1, 3, (1, 28, 2)), (50, 255, 1, 4, (1, 50, 4)),
+    (68, 255, 1, 3, (2, 40, 3)), (90, 255, 1, 3, (3, 32, 2)), (28, 255, 1, 5, (1, 28, 2)), (36, 255, 1, 5, (2, 20, 2)), (68, 255, 1, 5, (3, 24, 2)),
+    (40, 600, 2, 3, (5, 8, 1)), (38, 600, 2, 3, (19, 2, 0)),
+    (42, 600, 2, 3, (21, 2, 0)), (44, 600, 2, 3, (11, 4, 0)), (33, 255, 1, 5, (3, 12, 0)), (72, 255, 1, 3, (2, 64, 0))])
+def test_widths_that_are_read_in_sixteen_byte_pieces(F, nb, bb, bits, plan):
+    p = describe_hist_plan(2_000_000, F, nb, 127, bb, bits, bits)
+    assert (p["n_tiles"], p["ft"], p["pieces"]) == plan
 
 
 @pytest.mark.parametrize("shape", SHAPES + [(16_384, 28, 255, 31, 1), (16_385, 28, 255, 31, 1), (65_536, 68, 255, 31, 1), (65_537, 68, 255, 31, 1),
