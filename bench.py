@@ -108,7 +108,7 @@ def main():
     K, W = args.steps, args.warmup
     sys.stderr.write(f"[bench] workload {cfg.name}: {N} x {F}, {nb} bins, generated in {time.time() - t0:.1f}s\n")
 
-    # the matrix of all trees of the run: bound once, like binning part of the set-up (no effect for narrow rows)
+    # the matrix of all trees of the run: bound once, like binning part of the set-up
     bind_ms = None
     if not args.no_bind:
         torch.cuda.synchronize()
@@ -286,7 +286,7 @@ def main():
     achieved_all = (hist_bytes / hist_launches) / (hist_ms / hist_launches * 1e-3) / 1e9 if hist_launches and hist_ms > 0 else 0.0
     achieved = bytes_committed / (hist_ms * 1e-3) / 1e9 if hist_ms > 0 else 0.0
     # HBM bytes per histogram launch from the rocprofv3 counter runs (FETCH_SIZE, WRITE_SIZE scaled by a plain
-    # copy; see profiles/): measured offline on this workload, so only reported for it
+    # copy; see profiles/): measured offline on the first tree of this workload, so only reported for it
     traffic, root_traffic = None, None
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic_cfg3.json")
     if args.config == 2 and not args.rows and args.bits == 3 and os.path.exists(tpath):

@@ -16,10 +16,10 @@ namespace qgbdt {
 // expanded (partitioned, histograms built, best split searched); a node becomes an
 // open leaf when its parent's split is committed in best-first order.
 struct Node {
-    int64_t begin, count;  // slice of the index buffer `buf`
+    int64_t begin, count;  // slice of the row list `buf`
     int64_t sum_g, sum_h;  // quantized totals
     int64_t n_left;        // rows sent left by this node's split (valid once expanded)
-    int32_t buf;           // which of the two index buffers holds the slice
+    int32_t buf;           // which of the row lists holds the slice (RowSource)
     int32_t slot;          // histogram slot in the pool
     int32_t state;         // 0 waiting for its parent's commit, 1 open leaf, 2 internal (split committed)
     int32_t expanded;      // children exist (their rows, histograms and best splits are known)
@@ -71,7 +71,7 @@ struct BatchEntry {
 // One known node whose split is not committed yet and has a gain, in the gain order kept from round to round.
 struct PlanEntry {
     unsigned long long key;  // bits of the gain (> 0): ordered like the gain
-    uint32_t ids;            // node id, left child's id in the upper half (0xffff: not expanded)
+    uint32_t ids;            // node id in 12 bits, row list in the next four, left child's id in the upper half (0xffff: not expanded)
     uint32_t leaf;           // leaf id, 0xffff: not an open leaf (its parent's split is not committed)
 };
 
@@ -272,7 +272,7 @@ struct qgbdt_ctx {
     int32_t* batch_seg;          // [batch_max] their first segments, for the search segment -> node
     qgbdt::FeatCand* cand;       // [2*batch_max][F]
     qgbdt::HistEntry* hist_entries;  // [batch_max]
-    int32_t* hist_counts;        // [3] entries, items, 1: an entry has more than REDUCE_ABOVE groups
+    int32_t* hist_counts;        // [3] entries, items, 1: an entry has more groups than the split search adds up (HistPlan::search_sums)
     qgbdt::ScanPair* scan_pairs; // [batch_max]
     qgbdt::RefitUnit* refit_units;  // [max_leaves + REFIT_EXTRA] of the leaves last laid out
     int2* refit_leaves;          // [max_leaves + 1] first unit and units of a leaf; behind the leaves: number of units

@@ -473,8 +473,8 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     // The last rank that the selection can reach as a bottleneck: fewer than `remaining` open splits have a better one.  Every
     // wavefront finds it for itself, first the word of 64 ranks, then the rank.
     // Nodes two or more levels ahead are guesses on guesses: while many splits remain they have to be within half of them.
-    // Rounds / expansions / time per tree with half and with all: 10.5 M x 28 10 / 283 / 2040 us and 10 / 319 / 2076 us,
-    // 20 M x 200 24 / 613 / 10.36 ms and 20 / 739 / 10.46 ms; the last 32 splits without that limit: 200 k x 136 699 -> 669 us.
+    // Rounds / expansions / time per tree with half and with all: 10.5 M x 28 11 / 285 / 1885 us and 10 / 324 / 1911 us,
+    // 20 M x 200 27 / 620 / 10.91 ms and 23 / 761 / 11.01 ms; the last 32 splits without that limit: 200 k x 136 699 -> 669 us.
     const int in_front = wave_prefix(s_reach[lane]) - s_reach[lane];
     auto last_reached = [&](int splits) {
         auto last_below = [&](int n) { return 63 - __clzll((long long)__ballot(n < splits)); };  // (lane 0's always is)
@@ -673,8 +673,8 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     const HistPlan root_plan = make_hist_plan_for(ctx->shape, p->bits_g, p->bits_h, p->acc_width, N, skip_ok,
                                                   ((uintptr_t)bins & 15) == 0);  // the root's build alone: contiguous rows
     const uint16_t* mfb = skip_ok ? ctx->mfb : nullptr;
-    // Row sources: buffer 3 = the caller's matrix and the quantized gradients in original order;
-    // buffers 0..2 are what the partition writes (see RowSource).
+    // Row sources: buffer BUF_ORIGINAL = the caller's matrix and the quantized gradients in original order;
+    // the others are what the partition writes (see RowSource).
     RowSource rows;
     IdxSet idxs;
     // the feature-major copy serves only the matrix it was made from
