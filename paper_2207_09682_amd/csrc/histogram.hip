@@ -334,7 +334,10 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
 // Per gathered launch against hist_kernel: 1 M x 28 14.4 -> 12.9 us, 10.5 M x 28 70.4 -> 66.1 us, 464 k x 90 17.0 -> 15.3 us,
 // 100 k x 50 11.1 -> 9.3 us, 2 M x 40 of 16-bit bins 28.8 -> 27.2 us.
 // The four dwords of a piece and the bins inside a dword are taken in an order that rotates with the row, so that the lanes of
-// an LDS atomic spread over 16 columns per piece.
+// an LDS atomic spread over 16 columns per piece, and from one 32 columns of a tile to the next by as many places as half a wavefront
+// has rows: where the pitch is a multiple of 32 words a column's bank is the same in every bin, and half a wavefront then covers all of
+// them.  (By the row alone tiles of 64 and 128 features met 2 and 4 lanes per bank: one build of 393 k x 1017 in 64-bit words 365 -> 143 us,
+// by row list 139 -> 67, a tree 1480 -> 723 us; 2 M x 97 136 -> 91, 56 -> 46, 819 -> 690; 32-bit words by row list 60 -> 51 us.)
 template <int W, int IDX, bool RAG, int BB>
 __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
@@ -371,7 +374,8 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
     if (!lane_on) { c = 0; r = 0; }
     const int at = min(16 * c, ft * BB - 16);   // first byte of the lane's piece in the tile row
     const int dup = (16 * c - at) / BB;         // its bins that the piece in front of it holds
-    const int rot = (r * BB) & 15;              // bytes by which the lane's order is rotated
+    // bytes by which the lane's order is rotated: by the row, and by the rows of half a wavefront from one 32 columns to the next
+    const int rot = ((r + c / (2 * BB) * (32 / P)) * BB) & 15;
     const bool rot8 = rot & 8, rot4 = rot & 4;
     uint32_t sh[NPD], fl[4][NPD];  // bit offset of the k-th bin in a dword; byte offset in LDS of the (i, k)-th bin's column
     bool okk[4][NPD];

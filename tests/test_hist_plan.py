@@ -268,13 +268,38 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
                     at = min(16 * c, ft * bb - 16)
                     assert 0 <= at and f0 * bb + at + 16 <= F * bb
                     assert at % bb == 0 and (16 * c - at) % bb == 0
-                    rot = (r * bb) & 15
+                    rot = ((r + c // (2 * bb) * (32 // P)) * bb) & 15
                     for i in range(4):
                         for k in range(npd):
                             j = ((i + (rot >> 2)) & 3) * npd + ((k + (rot & 3) // bb) & (npd - 1))
                             if j >= (16 * c - at) // bb:
                                 seen.append(at // bb + j)
                 assert sorted(seen) == list(range(ft)), (key, tile, r)
+
+
+@pytest.mark.parametrize("F,nb,bb", [(32, 255, 1), (64, 255, 1), (97, 63, 1), (100, 127, 1), (190, 127, 1), (500, 15, 1), (1017, 63, 1), (1020, 31, 1), (96, 300, 2), (128, 400, 2)])
+def test_pieces_spread_over_the_lds_banks(F, nb, bb):
+    # a pitch of whole 32 words: the bank of a column is the same in every bin, and the lanes that an LDS atomic serves at once (half a
+    # wavefront) meet every bank at most once
+    seen = 0
+    for (bg, bh), acc in itertools.product(BITS, (16, 32)):
+        p = describe_hist_plan(300_000, F, nb, 15, bb, bg, bh, acc)
+        P, npd = p["pieces"], 4 // bb
+        if P < 32 * bb // 16 or P & (P - 1) or p["ftp"] % 32 or p["ft"] * bb % 16:
+            continue
+        seen += 1
+        rpi = 64 // P
+        for half in (range(32), range(32, 64)):
+            for i in range(4):
+                for k in range(npd):
+                    banks = []
+                    for lane in half:
+                        c, r = lane % P, lane // P
+                        rot = ((r + c // (2 * bb) * (32 // P)) * bb) & 15
+                        kk = (k + (rot & 3) // bb) & (npd - 1)
+                        banks.append((16 * c // bb + ((i + (rot >> 2)) & 3) * npd + kk) % 32)
+                    assert r < rpi and len(set(banks)) == 32, (bg, bh, acc, i, k)
+    assert seen or nb == 400
 
 
 # which widths the piece kernel serves: (tiles, features per tile, pieces); 0 pieces: the last tile is narrower than one
