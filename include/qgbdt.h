@@ -321,7 +321,7 @@ QGBDT_API int qgbdt_read_profile_roots(qgbdt_ctx* ctx, double* root_ms, int64_t*
 /* The launch plan the histogram kernels would be given for a shape (host-only: no context, no GPU call), for
  * callers and tests that check the plan against its invariants.  rows / n_builds: the rows a launch serves and
  * the number of builds they belong to (1 with rows > 0: a stand-alone build of that many contiguous rows of a
- * 16-byte aligned matrix).  out (host int64 [n_out], n_out >= 25; 28 values are known): features per tile, tile pitch in LDS words, dwords per tile row, rows per wavefront step, feature tiles,
+ * 16-byte aligned matrix).  out (host int64 [n_out], n_out >= 25; 30 values are known): features per tile, tile pitch in LDS words, dwords per tile row, rows per wavefront step, feature tiles,
  * threads per workgroup, bytes of local bins, rows per chunk (width rule of Sec. 7.4.3), row groups of one build,
  * row-group lanes of a launch, least rows per group, word width of the local bins (16: 32-bit words, 32: 64-bit),
  * bits of the hessian field of a 32-bit word, lanes / rows per step of the byte-stream kernel (0: not used), most
@@ -329,8 +329,9 @@ QGBDT_API int qgbdt_read_profile_roots(qgbdt_ctx* ctx, double* root_ms, int64_t*
  * lane of the wide-row kernels (0: not used), unaligned-row flag, element-wise flag, rows per row group for
  * (rows, n_builds), bytes of the workspace section that holds the slots, two-level flag (32-bit working words folded
  * into 64-bit words in LDS after every chunk: the slots then hold 64-bit words), 16-byte pieces per tile row (0: the
- * kernel that reads such pieces does not apply), most row groups of a build that a tree's split search adds up itself, most pieces at
- * which contiguous rows are read by dwords all the same. */
+ * kernel that reads such pieces does not apply), most row groups of a build that a tree's split search adds up itself, 1 where
+ * contiguous rows are read by dwords all the same, rows by which the order of a piece's bins moves on from one 32 columns to
+ * the next for gathered and for contiguous rows. */
 QGBDT_API int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g, int32_t bits_h, int32_t acc_width,
                              int32_t skewed, int64_t rows, int32_t n_builds, int64_t* out, int32_t n_out);
 

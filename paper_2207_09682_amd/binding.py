@@ -114,7 +114,8 @@ def load_library() -> C.CDLL:
 PLAN_FIELDS = ("ft", "ftp", "dpr", "rows_per_it", "n_tiles", "threads", "lds_bytes", "chunk_rows", "max_groups",
                "max_lanes", "min_rows_per_group", "acc_width", "hshift", "flat_lanes", "flat_rows", "max_items",
                "slot_bytes", "single_rows", "pad16", "wide_v", "ragged", "bytewise", "target_rows", "partial_bytes",
-               "two_level", "pieces", "search_sums", "dword_pieces")
+               "two_level", "pieces", "search_sums", "contig_dwords", "turn",
+               "contig_turn")
 
 
 def describe_hist_plan(n_rows, n_features, n_bins, max_leaves=255, bin_bytes=1, bits_g=3, bits_h=3, acc_width=0,

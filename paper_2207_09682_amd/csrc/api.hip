@@ -738,12 +738,12 @@ int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g, int32_t b
     // words); else the plan of the batched launches of a tree
     const HistPlan p = (n_builds == 1 && rows > 0) ? make_hist_plan_for(*shape, bits_g, bits_h, acc_width, rows, skewed != 0, true)
                                                    : make_hist_plan(*shape, bits_g, bits_h, acc_width, skewed != 0);
-    constexpr int PLAN_VALUES = 28;
+    constexpr int PLAN_VALUES = 30;
     const int64_t v[PLAN_VALUES] = {p.ft, p.ftp, p.dpr, p.rows_per_it, p.n_tiles, p.threads, p.lds_bytes, p.chunk_rows,
                            p.max_groups, p.max_lanes, p.min_rows_per_group, p.acc_width, p.hshift, p.flat_lanes,
                            p.flat_rows, p.max_items, p.slot_bytes, p.single_rows, p.pad16, p.wide_v, p.ragged,
                            p.bytewise, hist_target_rows(p, rows, n_builds), (int64_t)partial_slot_bytes(*shape), p.two_level,
-                           p.pieces, p.search_sums, p.dword_pieces};
+                           p.pieces, p.search_sums, p.contig_dwords, p.turn, p.contig_turn};
     for (int i = 0; i < PLAN_VALUES && i < n_out; ++i) out[i] = v[i];
     return QGBDT_OK;
 }

@@ -121,8 +121,9 @@ struct HistPlan {
     int32_t single_rows;  // a group of at most this many rows is accumulated in one chunk by every kernel variant
     int32_t pad16;        // local bins keep 4 unused words after every 16 features (wide rows, 16-byte loads)
     int32_t wide_v;       // > 0: wide rows are read in pieces of this many bytes per lane (8 or 16)
-    int32_t pieces;       // > 0: 16-byte pieces per tile row (tile rows of at least 16 bytes)
-    int32_t dword_pieces; // contiguous rows of at most so many pieces are read by dwords all the same
+    int32_t pieces;        // > 0: 16-byte pieces per tile row, of the kernel that reads such pieces
+    int32_t turn, contig_turn; // of that kernel: rows by which the order of a piece's bins moves on from one 32 columns of a tile to the next
+    int32_t contig_dwords; // 1: contiguous rows are read by dwords all the same
     int32_t ragged;       // feature count not a multiple of 4: unaligned dword loads, last dword of a tile row partial
     int32_t bytewise;     // no dword kernel applies (rows or a tile narrower than 4 bytes): one byte load per bin
     int32_t two_level;    // byte-stream kernel with 32-bit working words folded into 64-bit words in LDS after every chunk

@@ -374,8 +374,8 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
     if (!lane_on) { c = 0; r = 0; }
     const int at = min(16 * c, ft * BB - 16);   // first byte of the lane's piece in the tile row
     const int dup = (16 * c - at) / BB;         // its bins that the piece in front of it holds
-    // bytes by which the lane's order is rotated: by the row, and by the rows of half a wavefront from one 32 columns to the next
-    const int rot = ((r + c / (2 * BB) * (32 / P)) * BB) & 15;
+    // bytes by which the lane's order is rotated: by the row, and by `turn` rows from one 32 columns to the next
+    const int rot = ((r + c / (2 * BB) * (IDX ? plan.turn : plan.contig_turn)) * BB) & 15;
     const bool rot8 = rot & 8, rot4 = rot & 4;
     uint32_t sh[NPD], fl[4][NPD];  // bit offset of the k-th bin in a dword; byte offset in LDS of the (i, k)-th bin's column
     bool okk[4][NPD];
@@ -1135,12 +1135,34 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
             if ((16 * l) % F == 0) { p.flat_lanes = l; p.flat_rows = 16 * l / F; break; }
     }
     p.pieces = (fast && !wide_ft && (F - (p.n_tiles - 1) * p.ft) * s.bin_bytes >= 16) ? (p.ft * s.bin_bytes + 15) / 16 : 0;
-    // Contiguous rows in one tile of two or three pieces whose last one has at most four bytes of its own stay with the dword
-    // kernel: a third to a half of the piece kernel's atomics would be for bins that it leaves out.  Dwords / pieces, one build of
-    // 8 M rows: 17 features 74 / 77 us (5 bits 79 / 90), 19 73 / 76 (81 / 86), 34 118 / 123 (137 / 135), 9 of 16-bit bins 60 / 64 us; beyond
-    // the line 21 features 81 / 77 us, 37 126 / 127, 49 169 / 155.  (Gathered rows: pieces throughout, they cost one line each.)
+    // Where the dword kernel is the better one all the same:
+    //  - Contiguous rows in one tile of two or three pieces whose last one has at most four bytes of its own: a third to a half of the
+    //    piece kernel's atomics would be for bins that it leaves out.  Dwords / pieces, one build of 8 M rows: 17 features 74 / 77 us
+    //    (5 bits 79 / 90), 19 73 / 76 (81 / 86), 34 118 / 123 (137 / 135), 9 of 16-bit bins 60 / 64 us; beyond the line 21 features 81 / 77 us,
+    //    37 126 / 127, 49 169 / 155.
+    //  - Contiguous rows of whole dwords in several tiles of 64 or 128 bytes that they fill (the dword kernel then has no idle lane), with
+    //    32-bit words that leave room for four (tiles of 128 bytes: three) workgroups per CU, whose wavefronts cover its shorter loads.
+    //    One build of 300 MB: 500 features, 160 bins 109 / 121 us, 100 bins 101 / 113 us, 700 features, 63 bins 99 / 104 us, 128 of 16-bit
+    //    bins 100 / 108 us; beyond the line 100 features, which fill 78 % of two tiles, 106 / 98 us, 116 features (91 %) 99 / 93 us, 500
+    //    features of 127 bins (two workgroups per CU) 98 / 91 us, in 64-bit words 123 / 120 us, 112 of 16-bit bins in tiles of 40 100 / 94 us.
+    //  - Contiguous rows in tiles of 128 bytes of 64-bit words, and gathered ones too where they are whole dwords that fill the tiles: 1020
+    //    features, 63 bins 114 / 127 us, by row list 47 / 50 us, 1017 features 118 / 123 us (by row list 48 / 47 us: pieces).
     const int tail = p.ft * s.bin_bytes % 16;
-    p.dword_pieces = p.n_tiles == 1 && tail >= 1 && tail <= 4 ? 3 : 0;
+    p.contig_dwords = p.n_tiles == 1 && tail >= 1 && tail <= 4 && p.pieces <= 3 ? 1 : 0;
+    const bool fills = 16 * F >= 15 * p.n_tiles * p.ft || (p.n_tiles >= 3 && 8 * F >= 7 * p.n_tiles * p.ft);
+    if (p.n_tiles > 1 && aligned && fills && w == 16 && (p.pieces == 4 || p.pieces == 8) && p.lds_bytes * (p.pieces == 8 ? 3 : 4) <= 160 * 1024)
+        p.contig_dwords = 1;
+    if (p.n_tiles > 1 && w == 32 && p.pieces == 8) {
+        p.contig_dwords = 1;
+        if (aligned && fills) p.pieces = 0;
+    }
+    // How far the order of a piece's bins moves on from one 32 columns of a tile to the next: by the rows of half a wavefront where
+    // the pitch keeps the bank of a column the same from bin to bin, or from every second one (hist_piece_kernel).  Not with other
+    // pitches (skewed bins in tiles of 40 features, 64-bit words: 172 / 181 us without / with it), and not for contiguous 32-bit words
+    // that come from beyond the memory-side cache with three and more workgroups per CU: one build of 1017 features, 31 bins, 200 k rows
+    // 87 / 71 us, 246 k 88 / 77, 393 k 123 / 134, 787 k 212 / 225; 127 bins (two workgroups) 393 k 137 / 118 us.
+    p.turn = p.pieces > 0 && p.ftp % 16 == 0 ? 32 / p.pieces : 0;
+    p.contig_turn = w == 32 || p.lds_bytes * 3 > 160 * 1024 || s.n_rows * F * s.bin_bytes <= (int64_t)256 << 20 ? p.turn : 0;
     p.slot_bytes = (p.lds_bytes + 15) & ~15;
     p.max_items = 4 * p.max_groups;
     if (p.max_items < 2 * s.max_leaves + 64) p.max_items = 2 * s.max_leaves + 64;
@@ -1312,7 +1334,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #undef QG_LAUNCH_WIDE_V
 #undef QG_LAUNCH_WIDE
 #undef QG_LAUNCH_WIDE_S
-    } else if (fast && plan.pieces > (mode == 0 ? plan.dword_pieces : 0)) {
+    } else if (fast && plan.pieces > 0 && !(mode == 0 && plan.contig_dwords)) {
 #define QG_LAUNCH_PIECE_K(W_, IDX_, RAG_, BB_)                                                                      \
     hipLaunchKernelGGL((hist_piece_kernel<W_, IDX_, RAG_, BB_>), grid, block, plan.lds_bytes, ctx->stream, \
                        rows, idx, entries, table_counts, hist_base, partials, F, nb, plan, step)

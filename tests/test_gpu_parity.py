@@ -1120,10 +1120,13 @@ def test_random_histogram_slices(seed):
 
 
 # rows of a few bytes more than one or two 16-byte pieces: by dwords where they are contiguous, by pieces where they are gathered
-@pytest.mark.parametrize("F,bb", [(17, 1), (18, 1), (19, 1), (20, 1), (21, 1), (33, 1), (36, 1), (37, 1), (49, 1), (9, 2), (10, 2), (11, 2), (17, 2), (18, 2), (25, 2)])
-def test_rows_of_a_few_bytes_more_than_whole_pieces(F, bb):
+@pytest.mark.parametrize("F,nb,bb", [(17, 200, 1), (18, 200, 1), (19, 200, 1), (20, 200, 1), (21, 200, 1), (33, 200, 1), (36, 200, 1), (37, 200, 1), (49, 200, 1),
+                                     (9, 400, 2), (10, 400, 2), (11, 400, 2), (17, 400, 2), (18, 400, 2), (25, 400, 2),
+                                     # several tiles of 64 and 128 bytes, filled and not
+                                     (97, 63, 1), (100, 127, 1), (124, 63, 1), (500, 63, 1), (380, 127, 1), (513, 31, 1), (505, 15, 1), (128, 257, 2), (95, 300, 2)])
+def test_rows_of_a_few_bytes_more_than_whole_pieces(F, nb, bb):
     from paper_2207_09682_amd import Context
-    N, nb = 30_011, 200 if bb == 1 else 400
+    N = 30_011 if F < 64 else 5003
     rng = np.random.default_rng(F)
     mat = rng.integers(0, nb, (N, F)).astype(np.uint16 if bb == 2 else np.uint8)
     ctx = Context(N, F, nb, max_leaves=4, bin_bytes=bb)

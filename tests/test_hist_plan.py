@@ -250,7 +250,8 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
     N, F, nb, L, bb = shape
     for key, p in _plans(shape):
         last = (F - (p["n_tiles"] - 1) * p["ft"]) * bb
-        assert (p["pieces"] > 0) == (not p["bytewise"] and not p["wide_v"] and last >= 16), key
+        if not (bb == 1 and F % 4 == 0 and p["ft"] == 128 and p["acc_width"] == 32):   # (such tiles, where the rows fill them, stay with the dword kernel)
+            assert (p["pieces"] > 0) == (not p["bytewise"] and not p["wide_v"] and last >= 16), key
         if p["pieces"] == 0:
             continue                                                 # other kernels
         P, npd = p["pieces"], 4 // bb
@@ -260,7 +261,7 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
         for tile in range(p["n_tiles"]):
             f0 = tile * p["ft"]
             ft = min(p["ft"], F - f0)
-            for r in range(rpi):
+            for r, turn in itertools.product(range(rpi), {p["turn"], p["contig_turn"]}):
                 seen = []
                 for c in range(P):
                     if 16 * c >= ft * bb:
@@ -268,7 +269,7 @@ def test_sixteen_byte_pieces_cover_every_bin_of_a_tile_row_once(shape):
                     at = min(16 * c, ft * bb - 16)
                     assert 0 <= at and f0 * bb + at + 16 <= F * bb
                     assert at % bb == 0 and (16 * c - at) % bb == 0
-                    rot = ((r + c // (2 * bb) * (32 // P)) * bb) & 15
+                    rot = ((r + c // (2 * bb) * turn) * bb) & 15
                     for i in range(4):
                         for k in range(npd):
                             j = ((i + (rot >> 2)) & 3) * npd + ((k + (rot & 3) // bb) & (npd - 1))
@@ -287,6 +288,7 @@ def test_pieces_spread_over_the_lds_banks(F, nb, bb):
         P, npd = p["pieces"], 4 // bb
         if P < 32 * bb // 16 or P & (P - 1) or p["ftp"] % 32 or p["ft"] * bb % 16:
             continue
+        assert p["turn"] == 32 // P and p["contig_turn"] == (32 // P if p["acc_width"] == 32 or p["lds_bytes"] * 3 > 160 * 1024 or 300_000 * F * bb <= 2 ** 28 else 0)
         seen += 1
         rpi = 64 // P
         for half in (range(32), range(32, 64)):
@@ -295,7 +297,7 @@ def test_pieces_spread_over_the_lds_banks(F, nb, bb):
                     banks = []
                     for lane in half:
                         c, r = lane % P, lane // P
-                        rot = ((r + c // (2 * bb) * (32 // P)) * bb) & 15
+                        rot = ((r + c // (2 * bb) * p["turn"]) * bb) & 15
                         kk = (k + (rot & 3) // bb) & (npd - 1)
                         banks.append((16 * c // bb + ((i + (rot >> 2)) & 3) * npd + kk) % 32)
                     assert r < rpi and len(set(banks)) == 32, (bg, bh, acc, i, k)
@@ -330,16 +332,27 @@ def test_the_search_adds_up_few_row_groups_only(shape):
                     assert -(-total // t) <= 33, (key, n_builds, total, t)
 
 
-@pytest.mark.parametrize("F,bb,most", [(16, 1, 0), (17, 1, 3), (20, 1, 3), (21, 1, 0), (32, 1, 0), (33, 1, 3), (36, 1, 3), (37, 1, 0), (8, 2, 0), (9, 2, 3),
-                                       (10, 2, 3), (11, 2, 0), (17, 2, 3), (19, 2, 0), (65, 1, 0), (28, 1, 0)])
-def test_contiguous_rows_that_are_read_by_dwords(F, bb, most):
-    # a last piece of one to four bytes of its own: contiguous rows of at most three pieces take the dword kernel
+@pytest.mark.parametrize("F,bb,dwords", [(16, 1, 0), (17, 1, 1), (20, 1, 1), (21, 1, 0), (32, 1, 0), (33, 1, 1), (36, 1, 1), (37, 1, 0), (49, 1, 0), (8, 2, 0), (9, 2, 1),
+                                         (10, 2, 1), (11, 2, 0), (17, 2, 1), (19, 2, 0), (25, 2, 0), (28, 1, 0)])
+def test_contiguous_rows_of_one_tile_that_are_read_by_dwords(F, bb, dwords):
+    # a last piece of one to four bytes of its own, three pieces at most
     for (bg, bh), acc in itertools.product(BITS, (0, 16, 32)):
         p = describe_hist_plan(50_000, F, 255 if bb == 1 else 400, 15, bb, bg, bh, acc)
         if p["n_tiles"] == 1:
-            assert p["dword_pieces"] == most and p["pieces"] == -(-F * bb // 16), (bg, bh, acc)
+            assert p["contig_dwords"] == dwords and p["pieces"] == -(-F * bb // 16), (bg, bh, acc)
         else:
-            assert p["dword_pieces"] == 0
+            assert p["contig_dwords"] == 0
+
+
+# several tiles of 64 or 128 bytes: (pieces, contiguous rows by dwords); both sides of every condition of the rule
+@pytest.mark.parametrize("F,nb,bb,acc,plan", [
+    (124, 63, 1, 16, (4, 1)), (116, 63, 1, 16, (4, 0)), (100, 63, 1, 16, (4, 0)), (172, 63, 1, 16, (4, 1)), (300, 160, 1, 16, (4, 1)),
+    (300, 161, 1, 16, (4, 0)), (300, 63, 1, 32, (4, 0)), (190, 127, 1, 16, (4, 0)), (500, 100, 1, 16, (8, 1)), (500, 127, 1, 16, (8, 0)), (1017, 63, 1, 16, (8, 0)),
+    (1020, 63, 1, 32, (0, 1)), (1017, 63, 1, 32, (8, 1)), (128, 257, 2, 16, (4, 1)), (128, 400, 2, 16, (4, 0)), (127, 257, 2, 16, (4, 0)), (60, 300, 2, 16, (4, 1)),
+    (56, 300, 2, 16, (4, 0)), (80, 300, 2, 16, (5, 0))])
+def test_rows_of_several_tiles_that_are_read_by_dwords(F, nb, bb, acc, plan):
+    p = describe_hist_plan(300_000, F, nb, 15, bb, 3, 3, acc)
+    assert p["n_tiles"] > 1 and (p["pieces"], p["contig_dwords"]) == plan
 
 
 def test_small_trees_with_long_row_groups_need_no_reduction():
