@@ -873,8 +873,8 @@ __global__ __launch_bounds__(TWO ? 1024 : HIST_THREADS, TWO ? 1 : HIST_WAVES) vo
 // bins and rows or tiles narrower than a dword.  lane -> (row r of the iteration, feature f of the
 // tile); a wavefront covers 64/C rows per iteration, C = the tile width rounded up to a power of two
 // (tiles wider than 64 features are walked in steps of 64).
-template <int W, typename BIN>
-__global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource src, IdxSet idxs, int use_idx,
+template <int W, int IDX, typename BIN>
+__global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource src, IdxSet idxs,
                                                             const HistEntry* __restrict__ entries,
                                                             const int32_t* __restrict__ table_counts,
                                                             int64_t* hist_base, unsigned char* partials, int F,
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, !use_idx ? 0 : src.code.on() ? 2 : 1, step);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
     const int lds_words = ft * nb;
@@ -907,17 +907,17 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
         const int64_t gend = min(en.count, gbegin + rows_per_group);
         int64_t* hist = hist_base + (int64_t)en.slot * F * nb;
         unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
-        const int32_t* idx = use_idx ? (idxs.p[en.buf] + en.begin) : nullptr;
-        const BIN* bins = reinterpret_cast<const BIN*>(src.bins[use_idx ? BUF_ORIGINAL : en.buf]);
-        const bool gpos = use_idx && src.gh_pos != 0;
-        const int16_t* gh = gpos ? src.gh[en.buf] + en.begin : src.gh[use_idx ? BUF_ORIGINAL : en.buf];
+        const int32_t* idx = IDX ? (idxs.p[en.buf] + en.begin) : nullptr;
+        const BIN* bins = reinterpret_cast<const BIN*>(src.bins[IDX ? BUF_ORIGINAL : en.buf]);
+        const bool gpos = IDX && src.gh_pos != 0;
+        const int16_t* gh = gpos ? src.gh[en.buf] + en.begin : src.gh[IDX ? BUF_ORIGINAL : en.buf];
         for (int64_t cbegin = gbegin; cbegin < gend || cbegin == gbegin; cbegin += plan.chunk_rows) {
             const int64_t cend = min(gend, cbegin + (int64_t)plan.chunk_rows);
             __syncthreads();
             for (int64_t p = cbegin + wave * rpi + r; p < cend; p += n_waves * rpi) {
-                const uint32_t e = idx ? (uint32_t)idx[p] : 0u;
-                const int64_t i = idx ? (int64_t)(e & src.code.id_mask) : en.begin + p;
-                const word v = Acc<W>::expand(idx && src.code.on() ? src.code.gh(e) : (int)gh[gpos ? p : i], hmul);
+                const uint32_t e = IDX ? (uint32_t)idx[p] : 0u;
+                const int64_t i = IDX == 2 ? (int64_t)(e & src.code.id_mask) : IDX ? (int64_t)e : en.begin + p;
+                const word v = Acc<W>::expand(IDX == 2 ? src.code.gh(e) : (int)gh[gpos ? p : i], hmul);
                 const BIN* row = bins + i * F + f0;
                 for (int f = fl; f < ft; f += C) Acc<W>::add(&lds[(uint32_t)row[f] * ft + f], v);
             }
@@ -1383,15 +1383,18 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #undef QG_LAUNCH_HIST
 #undef QG_LAUNCH_HIST_K
     } else {
-#define QG_LAUNCH_GENERIC(W_, BIN_)                                                                              \
-    hipLaunchKernelGGL((hist_generic_kernel<W_, BIN_>), grid, block, plan.lds_bytes, ctx->stream, rows, idx, \
-                       use_idx ? 1 : 0, entries, table_counts, hist_base, partials, F, nb, plan, step)
+#define QG_LAUNCH_GENERIC_K(W_, IDX_, BIN_)                                                                        \
+    hipLaunchKernelGGL((hist_generic_kernel<W_, IDX_, BIN_>), grid, block, plan.lds_bytes, ctx->stream, rows, idx, \
+                       entries, table_counts, hist_base, partials, F, nb, plan, step)
+#define QG_LAUNCH_GENERIC(W_, BIN_) \
+    if (mode == 2) QG_LAUNCH_GENERIC_K(W_, 2, BIN_); else if (mode == 1) QG_LAUNCH_GENERIC_K(W_, 1, BIN_); else QG_LAUNCH_GENERIC_K(W_, 0, BIN_)
         if (ctx->shape.bin_bytes == 2) {
-            if (plan.acc_width == 16) QG_LAUNCH_GENERIC(16, uint16_t); else QG_LAUNCH_GENERIC(32, uint16_t);
+            if (plan.acc_width == 16) { QG_LAUNCH_GENERIC(16, uint16_t); } else { QG_LAUNCH_GENERIC(32, uint16_t); }
         } else {
-            if (plan.acc_width == 16) QG_LAUNCH_GENERIC(16, uint8_t); else QG_LAUNCH_GENERIC(32, uint8_t);
+            if (plan.acc_width == 16) { QG_LAUNCH_GENERIC(16, uint8_t); } else { QG_LAUNCH_GENERIC(32, uint8_t); }
         }
 #undef QG_LAUNCH_GENERIC
+#undef QG_LAUNCH_GENERIC_K
     }
     QG_HIP(ctx, hipGetLastError());
     if (reduce_above != ALL_GROUPS) {
