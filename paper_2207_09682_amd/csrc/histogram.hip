@@ -334,9 +334,9 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
 // Per gathered launch against hist_kernel: 1 M x 28 14.4 -> 12.9 us, 10.5 M x 28 70.4 -> 66.1 us, 464 k x 90 17.0 -> 15.3 us,
 // 100 k x 50 11.1 -> 9.3 us, 2 M x 40 of 16-bit bins 28.8 -> 27.2 us.
 // The four dwords of a piece and the bins inside a dword are taken in an order that rotates with the row, so that the lanes of
-// an LDS atomic spread over 16 columns per piece, and from one 32 columns of a tile to the next by as many places as half a wavefront
-// has rows: where the pitch is a multiple of 32 words a column's bank is the same in every bin, and half a wavefront then covers all of
-// them.  (By the row alone tiles of 64 and 128 features met 2 and 4 lanes per bank: one build of 393 k x 1017 in 64-bit words 365 -> 143 us,
+// an LDS atomic spread over 16 columns per piece, and (HistPlan::turn) from one 32 columns of a tile to the next by as many places as
+// half a wavefront has rows: where the pitch is a multiple of 32 words a column's bank is the same in every bin, and half a wavefront
+// then covers all of them.  (By the row alone tiles of 64 and 128 features met 2 and 4 lanes per bank: one build of 393 k x 1017 in 64-bit words 365 -> 143 us,
 // by row list 139 -> 67, a tree 1480 -> 723 us; 2 M x 97 136 -> 91, 56 -> 46, 819 -> 690; 32-bit words by row list 60 -> 51 us.)
 template <int W, int IDX, bool RAG, int BB>
 __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(RowSource src, IdxSet idxs,
