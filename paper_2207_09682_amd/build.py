@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libqgbdt.so")
 SOURCES = ["api.hip", "quantize.hip", "histogram.hip", "split.hip", "partition.hip", "refit.hip", "tree.hip", "boost.hip"]
-HEADERS = ["common.h", "split_device.h", "refit_device.h", os.path.join("..", "..", "include", "qgbdt.h")]
+HEADERS = ["common.h", "split_device.h", "partition_device.h", "refit_device.h", os.path.join("..", "..", "include", "qgbdt.h")]
 
 # -ffp-contract=off: the split gain is evaluated operation by operation (no FMA), like its definition.
 # packed-fp32 ops are switched off for the whole library.

@@ -158,7 +158,7 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
     k.take(&c->plan_list, (size_t)c->max_nodes);
     k.take(&c->step, 1);
     k.take(&c->batch, (size_t)c->batch_max);
-    k.take(&c->batch_seg, (size_t)c->batch_max);
+    k.take(&c->batch_seg, (size_t)TABLE_MAX);
     k.take(&c->cand, (size_t)2 * c->batch_max * F);
     k.take(&c->hist_entries, (size_t)c->batch_max);
     k.take(&c->hist_counts, 4);
@@ -414,7 +414,7 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
     const HistPlan plan = make_hist_plan_for(ctx->shape, bits_g, bits_h, acc_width, count, mfb != nullptr,
                                              row_idx == nullptr && ((uintptr_t)bins & 15) == 0);
     if (mfb && plan.wide_v == 0) mfb = nullptr;  // only those kernels skip
-    rc = launch_begin_build(ctx, plan, begin, count, hist_out, W);
+    rc = launch_begin_build(ctx, plan, begin, count, row_idx != nullptr, hist_out, W);
     if (rc != QGBDT_OK) return rc;
     RowSource rows;
     rows.gh_pos = 0;  // the caller's packed gradients are in original row order
@@ -424,7 +424,7 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
     rc = launch_hist(ctx, plan, rows, idx, row_idx != nullptr, ((uintptr_t)bins & 15) == 0,
                      ctx->hist_entries, ctx->hist_counts, hist_out,
                      (count + hist_target_rows(plan, count, 1) - 1) / hist_target_rows(plan, count, 1),  // the build's row groups
-                     ctx->step, mfb);
+                     mfb);
     if (rc != QGBDT_OK || !mfb) return rc;
     hipLaunchKernelGGL(zero3_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->tmp_i64);
     hipLaunchKernelGGL(gh_totals_kernel, dim3(512), dim3(256), 0, ctx->stream, gh, row_idx, begin, count, ctx->tmp_i64);
@@ -665,13 +665,13 @@ int qgbdt_read_profile(qgbdt_ctx* ctx, double* hist_ms, int64_t* hist_launches, 
     const double F = ctx->shape.n_features, nb = ctx->shape.n_bins, row = F * ctx->shape.bin_bytes;
     // algorithmic bytes: a bin row and a packed (g~,h~) per row, a row id when gathered (or one entry that holds both), one
     // histogram per build
-    *hist_bytes = (double)st.prof_rows_contig * (row + 2.0) + (double)st.prof_rows_idx * (row + 2.0 + 4.0) +
-                  (double)st.prof_rows_code * (row + 4.0) +
-                  (double)st.prof_builds * F * nb * 8.0;
+    *hist_bytes = (double)st.prof.rows[HistProfile::CONTIGUOUS] * (row + 2.0) + (double)st.prof.rows[HistProfile::IDS] * (row + 2.0 + 4.0) +
+                  (double)st.prof.rows[HistProfile::CODED] * (row + 4.0) +
+                  (double)st.prof.builds * F * nb * 8.0;
     *hist_ms = ms;
-    *hist_launches = st.prof_launches;
+    *hist_launches = (int64_t)st.prof.launches;
     ctx->ev_used = 0;
-    st.prof_rows_contig = 0; st.prof_rows_idx = 0; st.prof_rows_code = 0; st.prof_launches = 0; st.prof_builds = 0;
+    st.prof = HistProfile{};
     QG_HIP(ctx, hipMemcpy(ctx->step, &st, sizeof(st), hipMemcpyHostToDevice));
     return QGBDT_OK;
 }

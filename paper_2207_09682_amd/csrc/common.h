@@ -28,6 +28,22 @@ struct Node {
     qgbdt_split best;      // best split of this node (feature < 0: none)
 };
 
+// What the histogram launches have had to do, counted where their tables are made.  (By a thread of the histogram kernels, which
+// walked the table, one load after the other, in front of its workgroup's first barrier, it held up every launch of many builds.)
+struct HistProfile {
+    enum { CONTIGUOUS = 0, IDS = 1, CODED = 2 };  // rows: contiguous, gathered by row id, gathered by entries that hold their gradients (RowCode)
+    unsigned long long rows[3];
+    unsigned long long launches;  // histogram launches that had rows
+    unsigned long long builds;    // histogram builds served by those launches
+    __device__ __forceinline__ void add(int kind, int64_t n_rows, int n_builds) {  // (atomics: nothing waits for the old values)
+        atomicAdd(&rows[kind], (unsigned long long)n_rows);
+        atomicAdd(&launches, 1ull);
+        atomicAdd(&builds, (unsigned long long)n_builds);
+    }
+};
+
+struct ScanPair;
+
 // State of the growth of one tree.
 struct StepState {
     int32_t done;        // 1: tree finished, later kernels return at once
@@ -39,10 +55,7 @@ struct StepState {
     int32_t n_known;       // nodes that have passed through tree_plan_kernel (all but the last round's children)
     int32_t n_list;        // entries of the kept gain order (see tree_plan_kernel)
     int64_t hist_units;    // rows*features of the histogram builds the sequential algorithm performs
-    // rows seen by histogram launches: contiguous, gathered by row id, gathered by entries that hold their gradients (RowCode)
-    int64_t prof_rows_contig, prof_rows_idx, prof_rows_code;
-    int64_t prof_launches;                    // histogram launches that had rows
-    int64_t prof_builds;                      // histogram builds served by those launches
+    HistProfile prof;
 };
 
 // What a plan kernel tells the host when it is asked to, in pinned memory: how far the tree is, and behind it the number of the
@@ -65,7 +78,8 @@ struct BatchEntry {
     int32_t feature, bin;  // its split
     int32_t super_start;   // first of its groups of PART_SUPER segments (without such counters: of its segments)
     int32_t child_buf;     // buffer its children's rows go to
-    int32_t pad[2];
+    int32_t built_left;    // (counting build) 1: the left child's histogram is built from its rows, 0: the right one's
+    int32_t pad;
 };
 
 // One known node whose split is not committed yet and has a gain, in the gain order kept from round to round.
@@ -161,6 +175,18 @@ __host__ __device__ inline int64_t hist_target_rows(const HistPlan& p, int64_t t
     return t;
 }
 
+// Counting build (CountSource): workgroups of 1024 threads, one per CU, and row-group lanes in multiples of 8.
+constexpr int COUNT_THREADS = 1024;
+__host__ __device__ inline int count_lanes(const HistPlan& p) { return 256 / p.n_tiles >= 16 ? 256 / p.n_tiles / 8 * 8 : 8; }
+// Segments per work item, `total` of them in the round's `n_entries` builds: no more items than workgroups, with a place left for the item
+// of every build that is not full (a CU with two of them takes twice as long: 1 M x 28 19 -> 25 us), of at least 1024 rows (512 or 2048
+// rows: within 3 % on 10 k to 1 M rows) and of one chunk, so that nothing is merged.
+__host__ __device__ inline int count_item_segs(const HistPlan& p, int total, int n_entries, int seg_rows) {
+    const int lanes = count_lanes(p), places = max(lanes - (n_entries - 1), (lanes + 1) / 2);
+    const int k = max((total + places - 1) / places, (1024 + seg_rows - 1) / seg_rows);
+    return max(min(k, p.single_rows / seg_rows), 1);
+}
+
 // One unit of the passes over finished leaves (refit, score update): in every part of the row order, piece
 // (part * n + unit - first) of the leaf's rows, piece_rows long.
 struct RefitUnit {
@@ -171,7 +197,7 @@ struct RefitUnit {
     int32_t buf;           // index buffer that holds the leaf's rows (tree growth)
 };
 
-struct ScanPair;
+struct RowMover;
 
 // Where the rows of a slice live: in one of ROW_BUFS buffers, in ordered mode of COPY_BUFS.  The children of a node share its
 // slice in another buffer, which holds the rows of no node above them that may yet stay a leaf (tree_plan_kernel).  Buffer
@@ -212,6 +238,23 @@ struct RowSource {
     int32_t gh_pos;
     RowCode code;
 };
+// A histogram launch over the rows of a round's nodes that finds out itself which of them go to the child that it builds, and leaves
+// the masks and counts of the left rows behind for whoever moves them.  bins_t null: no feature-major copy.
+struct CountSource {
+    const uint8_t* bins_t;
+    int64_t n_rows;
+    const StepState* step;
+    const Node* nodes;
+    const BatchEntry* batch;
+    const int32_t* batch_seg;
+    unsigned long long* masks;
+    int32_t* seg_counts;
+    HistEntry* entries;  // tables of the reduce kernel and the search, which it makes on the way
+    int32_t* counts;
+    ScanPair* pairs;
+    int32_t seg_rows, batch_max;
+};
+constexpr int SELECT_ROWS = 4096;  // rows of a parent that a workgroup goes through at a time
 struct RowDest {
     uint8_t* bins[COPY_BUFS];
     int16_t* gh[ROW_BUFS];
@@ -322,6 +365,17 @@ __device__ __forceinline__ int wave_prefix(int v) {
 #undef QG_DPP_ADD
 }
 
+// The last of the n ascending `starts` (in LDS, the first one 0) that is not above `at`, by a whole wavefront: 64 of them are compared
+// at a time (a binary search is a chain of LDS accesses of about 0.05 us each).
+__device__ __forceinline__ int find_start(const int* starts, int n, int at) {
+    int c = 0;
+    for (int k = 0; k < n; k += 64) {
+        const int i = k + (int)(threadIdx.x & 63);
+        c += __popcll(__ballot(i < n && starts[min(i, n - 1)] <= at));
+    }
+    return c - 1;
+}
+
 // Totals of the quantizer's workgroups (sum g~, sum h~, sum |g~|), by a workgroup of 256 threads; every thread gets them.
 __device__ __forceinline__ void sum_totals(const int64_t* __restrict__ part, int n_part, int64_t (&s)[3]) {
     __shared__ int64_t t[3][4];
@@ -403,22 +457,23 @@ int launch_quantize(qgbdt_ctx* ctx, const float* g, const float* h, int64_t n, i
                     uint64_t seed, uint32_t iteration, int rounding, int16_t* gh, float* delta_out,
                     int64_t* totals_out, float2* pairs_out);  // totals_out null: only the workgroups' totals (quantize_parts of them)
 int quantize_parts(const float* g, const float* h, const int16_t* gh, int64_t n);
+bool counting_build_ok(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows);  // a launch of `plan` can count the round's rows itself
 HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, bool skew = false);
 HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, int64_t rows, bool skew = false,
                             bool stream_ok = false);  // stream_ok: contiguous rows of a 16-byte aligned matrix
 int64_t max_rows_for_width(int bits_g, int bits_h, int w);
-int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, int64_t* hist, int64_t n_words);
+int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, bool gathered, int64_t* hist, int64_t n_words);
 int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, const IdxSet& idx, bool use_idx,
                 bool flat_ok, const HistEntry* entries, const int32_t* table_counts, int64_t* hist_base,
-                int64_t grid_items, StepState* step, const uint16_t* mfb = nullptr,
-                int reduce_above = 0);  // > 0: only builds of more row groups are added up by the reduce kernel
+                int64_t grid_items, const uint16_t* mfb = nullptr,
+                int reduce_above = 0, const CountSource* count = nullptr);  // > 0: only builds of more row groups are added up by the reduce kernel
 int launch_fill_zero(qgbdt_ctx* ctx, int64_t* p, int64_t n_words);
 int launch_subtract(qgbdt_ctx* ctx, const int64_t* parent, const int64_t* child, int64_t* out, int64_t n);
 // Best split of up to 2 * max_pairs histograms: candidates per (histogram, tile of features); `plan`: of the histogram launch
 // whose slots the pairs refer to
 int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs, const int32_t* n_items, int max_pairs,
                       const float* delta, int min_data, double min_sum_hess, FeatCand* cand, const uint16_t* mfb,
-                      const HistPlan* plan);
+                      const HistPlan* plan, const RowMover* mover = nullptr);
 int scan_candidates(const qgbdt_shape& s);  // candidates per scanned histogram
 // candidates -> best splits, `stride` bytes apart from `out` on; step: growth state whose nodes' best splits are meant
 int launch_reduce_items(qgbdt_ctx* ctx, const FeatCand* cand, const ScanPair* pairs, const int32_t* n_items, int max_items,

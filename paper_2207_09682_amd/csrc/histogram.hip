@@ -27,7 +27,7 @@
 // atomics (they would otherwise hit one word together and serialize).
 #include <type_traits>
 
-#include "common.h"
+#include "split_device.h"
 
 namespace qgbdt {
 
@@ -86,25 +86,6 @@ __device__ __forceinline__ void load_item_starts(const HistEntry* __restrict__ e
     for (int t = threadIdx.x; t < n_entries; t += blockDim.x) s_start[t] = entries[t].item_start;
     __syncthreads();
 }
-__device__ __forceinline__ int find_entry(const int* s_start, int n_entries, int item) {
-    int lo = 0, hi = n_entries - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s_start[mid] <= item) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// mode: 0 contiguous rows, 1 gathered by row id, 2 gathered by entries that hold their gradients
-__device__ __forceinline__ void count_profile(const HistEntry* __restrict__ entries, int n_entries, int mode,
-                                              StepState* step) {
-    int64_t rows = 0;
-    for (int e = 0; e < n_entries; ++e) rows += entries[e].count;
-    if (mode == 2) step->prof_rows_code += rows; else if (mode == 1) step->prof_rows_idx += rows; else step->prof_rows_contig += rows;
-    step->prof_launches += 1;
-    step->prof_builds += n_entries;
-}
-
 // Workgroup -> (feature tile, row-group lane) for launches with several feature tiles.  The
 // hardware deals consecutive workgroups round-robin to the 8 XCDs (each with its own L2), so
 // the T workgroups that read the T tiles of the same rows are made consecutive *within one
@@ -162,6 +143,161 @@ __device__ __forceinline__ void store_partial(typename Acc<W>::word* lds, int ld
     }
 }
 
+// ---- counting build (IDX 3) ----
+//
+// The rows of the nodes of a round are those of their parents' lists that go to the built child: a workgroup reads its share of
+// a list and the split feature's bins, leaves the masks and counts of the left rows behind, puts the rows to build on a list in
+// LDS and accumulates them, SELECT_ROWS of the parent's rows at a time, the next ones on their way meanwhile.
+// Bound by a chain: tables 2.5 us, list entries and bins 2 us (a line per one or two of them below the first levels), rows and atomics 1 to
+// 6 us for 500 to 4000 rows, local bins handed over 0.6 us.  One workgroup of 1024 threads per CU; two of 512 took 18.7 us per launch
+// on 1 M x 28 where one takes 18.2.  Per round against the count, scatter and histogram launches it replaces (the scatter goes beside
+// the split search): 10 k x 28 13.0 -> 8.6 us, 100 k x 50 17.2 -> 13.2, 1 M x 28 24.3 -> 18.2, 2.5 M x 28 not bound 58.5 -> 46.1, 464 k x 90 25.2 -> 22.9,
+// 200 k x 136 (64-bit words) 19.8 -> 14.4.  Which child is built follows from the hessians, not from the rows, which are not known yet: the
+// histograms are the same, only their cost is not.
+
+// The first items of the round's builds (in LDS), segments per item and number of items, from the segments that the plan kernel has
+// numbered.  Ends with a barrier.  Of the nodes' records as many as there is room for are copied into `s_row` on the way.
+constexpr int COUNT_RECORDS = SELECT_ROWS * 4 / (int)sizeof(BatchEntry);
+__device__ __forceinline__ int count_starts(const CountSource& cs, const HistPlan& plan, int* s_start, uint32_t* s_row, int* s_tmp, int& n_batch, int& segs) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    static_assert(sizeof(BatchEntry) % 8 == 0 && COUNT_RECORDS * (int)sizeof(BatchEntry) / 16 <= COUNT_THREADS, "one load per thread");
+    const bool mine = t < min(cs.batch_max, COUNT_RECORDS) * (int)sizeof(BatchEntry) / 16;
+    const uint4 record = mine ? reinterpret_cast<const uint4*>(cs.batch)[t] : make_uint4(0u, 0u, 0u, 0u);
+    const int first = t < TABLE_MAX ? cs.batch_seg[t] : 0;  // (in flight together with the number of nodes; the section has TABLE_MAX places)
+    int next = t + 1 < TABLE_MAX ? cs.batch_seg[t + 1] : 0;
+    n_batch = cs.step->n_batch;
+    const int n_segs = cs.step->n_part_items;
+    if (n_batch <= 0) return 0;  // (uniform)
+    if (t == n_batch - 1) next = n_segs;
+    segs = count_item_segs(plan, n_segs, n_batch, cs.seg_rows);
+    const int groups = t < n_batch ? (next - first + segs - 1) / segs : 0;
+    int incl = wave_prefix(groups);
+    if (n_batch > 64) {  // uniform
+        if (lane == 63) s_tmp[wave] = incl;
+        __syncthreads();
+        for (int k = 0; k < wave; ++k) incl += s_tmp[k];
+    }
+    if (t < n_batch) s_start[t] = incl - groups;
+    if (t == n_batch - 1) s_start[TABLE_MAX] = incl;
+    if (mine) reinterpret_cast<uint4*>(s_row)[t] = record;
+    __syncthreads();
+    return s_start[TABLE_MAX];
+}
+
+// A node's record out of LDS, in scalar registers (what the build needs of it).
+__device__ __forceinline__ void read_record(const BatchEntry* r, BatchEntry& e) {
+    e.begin = (int64_t)readlane64(r->begin, 0);
+    e.count = __builtin_amdgcn_readfirstlane(r->count);
+    e.seg_start = __builtin_amdgcn_readfirstlane(r->seg_start);
+    e.new_slot = __builtin_amdgcn_readfirstlane(r->new_slot);
+    e.buf = __builtin_amdgcn_readfirstlane(r->buf);
+    e.feature = __builtin_amdgcn_readfirstlane(r->feature);
+    e.bin = __builtin_amdgcn_readfirstlane(r->bin);
+    e.built_left = __builtin_amdgcn_readfirstlane(r->built_left);
+}
+
+// The tables of the kernels behind, by a workgroup of its own.
+__device__ __forceinline__ void count_tables(const CountSource& cs, const HistPlan& plan, const int* s_start, int n_batch, int n_items) {
+    const int t = threadIdx.x;
+    int large = 0;
+    if (t < n_batch) {
+        const BatchEntry be = cs.batch[t];
+        const Node* P = &cs.nodes[be.node];
+        HistEntry e;
+        e.begin = be.begin; e.count = be.count; e.buf = be.buf; e.slot = be.new_slot;
+        e.item_start = s_start[t]; e.groups = (t + 1 < n_batch ? s_start[t + 1] : n_items) - e.item_start;
+        large = e.groups > plan.search_sums ? 1 : 0;
+        cs.entries[t] = e;
+        ScanPair sp;
+        sp.slot_a = be.new_slot; sp.slot_b = P->slot; sp.parent = P->slot; sp.a_item = be.built_left ? 0 : 1;
+        sp.item_start = e.item_start; sp.groups = large ? 0 : e.groups; sp.merged = 0; sp.seg_start = be.seg_start;
+        const bool left = be.built_left != 0;  // (selected number by number: whole records go through scratch memory)
+        const int64_t lg = P->best.left_g, lh = P->best.left_h, rg = P->best.right_g, rh = P->best.right_h;
+        sp.stat[0].n_rows = be.count; sp.stat[0].sum_g = left ? lg : rg; sp.stat[0].sum_h = left ? lh : rh;
+        sp.stat[1].n_rows = be.count; sp.stat[1].sum_g = left ? rg : lg; sp.stat[1].sum_h = left ? rh : lh;
+        cs.pairs[t] = sp;
+    }
+    large = __syncthreads_or(large);
+    if (t == 0) { cs.counts[0] = n_batch; cs.counts[1] = n_items; cs.counts[2] = large; }
+}
+
+struct RowSelect {
+    static constexpr int R = SELECT_ROWS / COUNT_THREADS;
+    uint32_t e[R];
+    int v[R], g[R];
+    // list entries of the node's rows from r0 on; rows past the end: the last one again
+    __device__ __forceinline__ void load_list(const IdxSet& idxs, const BatchEntry& nd, int r0, int n, int wave, int lane) {
+        const int32_t* list = idxs.p[nd.buf] + nd.begin + r0;
+        const bool identity = nd.buf == BUF_ORIGINAL;
+        if (wave * R * 64 >= n) return;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int r = min((wave * R + u) * 64 + lane, n - 1);
+            e[u] = identity ? (uint32_t)(nd.begin + r0 + r) : (uint32_t)list[r];
+        }
+    }
+    __device__ __forceinline__ void load_bins(const RowSource& src, const CountSource& cs, const BatchEntry& nd, int n, int wave, int F, int bb) {
+        if (wave * R * 64 >= n) return;
+        const bool identity = nd.buf == BUF_ORIGINAL;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int64_t row = identity ? e[u] : e[u] & src.code.id_mask;
+            const uint8_t* p = cs.bins_t ? cs.bins_t + ((int64_t)nd.feature * cs.n_rows + row) * bb : src.bins[BUF_ORIGINAL] + (row * F + nd.feature) * bb;
+            v[u] = bb == 2 ? (int)*reinterpret_cast<const uint16_t*>(p) : (int)*p;
+            g[u] = identity ? (int)src.gh[BUF_ORIGINAL][row] : 0;
+        }
+    }
+    // The rows to build on the list, in any order; the masks, and the wavefront's left rows in s_seg, if `write` is set.
+    __device__ __forceinline__ void emit(const RowSource& src, const CountSource& cs, const BatchEntry& nd, int r0, int n, int wave, int lane, bool write,
+                                         uint32_t* s_row, int16_t* s_gh, int* s_n, int* s_seg) {
+        const bool identity = nd.buf == BUF_ORIGINAL;
+        unsigned long long mine = 0ull, sel[R];  // lane u keeps the wavefront's u-th mask
+        int left = 0, taken = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const bool in = (wave * R + u) * 64 + lane < n;
+            const unsigned long long ml = __ballot(in && v[u] <= nd.bin);
+            left += __popcll(ml);
+            if (lane == u) mine = ml;
+            sel[u] = nd.built_left ? ml : __ballot(in && v[u] > nd.bin);
+            taken += __popcll(sel[u]);
+        }
+        int at = 0;
+        if (lane == 0 && taken > 0) at = atomicAdd(s_n, taken);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int o = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(sel[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sel[u], 0u));
+            if ((sel[u] >> lane) & 1ull) {
+                const uint32_t row = identity ? e[u] : e[u] & src.code.id_mask;
+                s_row[o] = row;
+                s_gh[o] = (int16_t)(identity ? g[u] : src.code.on() ? src.code.gh(e[u]) : (int)src.gh[BUF_ORIGINAL][row]);
+            }
+            at += __popcll(sel[u]);
+        }
+        if (!write) return;
+        // (whole segments: of the last one also the masks behind the node's end)
+        const int words = (n + cs.seg_rows - 1) / cs.seg_rows * (cs.seg_rows / 64);
+        if (lane < R && wave * R + lane < words) cs.masks[(int64_t)nd.seg_start * (cs.seg_rows / 64) + r0 / 64 + wave * R + lane] = mine;
+        if (lane == 0) s_seg[wave] = left;
+    }
+    // (behind a barrier) the left rows of the segments
+    __device__ __forceinline__ void write_counts(const CountSource& cs, const BatchEntry& nd, int r0, int n, const int* s_seg) {
+        const int per = cs.seg_rows / (64 * R), t = threadIdx.x;  // wavefronts per segment
+        if (t * cs.seg_rows >= n) return;
+        int c = 0;
+        for (int w = 0; w < per; ++w) c += s_seg[t * per + w];
+        cs.seg_counts[nd.seg_start + r0 / cs.seg_rows + t] = c;
+    }
+};
+
+// A counting build's histogram is cleared by its items if the reduce kernel will add to it.
+__device__ __forceinline__ void clear_large(int local, int groups, const HistPlan& plan, int tile, int64_t* hist, int64_t words) {
+    if (groups <= plan.search_sums) return;
+    const int64_t step = (int64_t)groups * plan.n_tiles * COUNT_THREADS;
+    for (int64_t i = ((int64_t)local * plan.n_tiles + tile) * COUNT_THREADS + threadIdx.x; i < words; i += step) hist[i] = 0;
+}
+
 // Fast path (feature count a multiple of 4), any row set.  lane -> (row r of the
 // iteration, dword q of the row's feature tile); U row-iterations (U*rows_per_it
 // <= 64 rows) form one block of a wavefront.  All loads of a block are issued before
@@ -195,11 +331,10 @@ template <int W, int IDX, int U, bool RAG, int BB>
 __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
                                                     const int32_t* __restrict__ table_counts, int64_t* hist_base,
-                                                    unsigned char* partials, int F, int nb, HistPlan plan,
-                                                    StepState* step) {
+                                                    unsigned char* partials, int F, int nb, HistPlan plan) {
     using word = typename Acc<W>::word;
     constexpr int NPD = 4 / BB;  // bins per dword
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
     const int n_entries = table_counts[0], n_items = table_counts[1];
@@ -208,7 +343,6 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;  // row-group lanes (a multiple of 8)
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
@@ -242,7 +376,7 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
     const int64_t row_bytes = (int64_t)F * BB;
 
     for (int item = glane; item < n_items; item += n_lanes) {
-        const HistEntry en = entries[find_entry(s_start, n_entries, item)];
+        const HistEntry en = entries[find_start(s_start, n_entries, item)];
         const int64_t rows_per_group = (en.count + en.groups - 1) / en.groups;
         const int64_t gbegin = min(en.count, (int64_t)(item - en.item_start) * rows_per_group);
         const int64_t gend = min(en.count, gbegin + rows_per_group);
@@ -339,31 +473,44 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSourc
 // then covers all of them.  (By the row alone tiles of 64 and 128 features met 2 and 4 lanes per bank: one build of 393 k x 1017 in 64-bit words 365 -> 143 us,
 // by row list 139 -> 67, a tree 1480 -> 723 us; 2 M x 97 136 -> 91, 56 -> 46, 819 -> 690; 32-bit words by row list 60 -> 51 us.)
 template <int W, int IDX, bool RAG, int BB>
-__global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(RowSource src, IdxSet idxs,
+__global__ __launch_bounds__(IDX == 3 ? COUNT_THREADS : HIST_THREADS, HIST_WAVES) void hist_piece_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
                                                     const int32_t* __restrict__ table_counts, int64_t* hist_base,
-                                                    unsigned char* partials, int F, int nb, HistPlan plan,
-                                                    StepState* step) {
+                                                    unsigned char* partials, int F, int nb, HistPlan plan, CountSource cs) {
     using word = typename Acc<W>::word;
     constexpr int NPD = 4 / BB;  // bins per dword
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
-    const int n_entries = table_counts[0], n_items = table_counts[1];
+    int n_entries = 0, n_items = 0, segs = 1, records = 0;
+    if (IDX != 3) { n_entries = table_counts[0]; n_items = table_counts[1]; }
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     int tile, glane;
     tile_and_lane(plan.n_tiles, tile, glane);
-    const int n_lanes = (int)gridDim.x / plan.n_tiles;
-    if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
+    const int n_lanes = ((int)gridDim.x - (IDX == 3 ? 1 : 0)) / plan.n_tiles;
+    if (IDX != 3 && glane >= n_items) return;
+    if (IDX == 3 && blockIdx.x == gridDim.x - 1) tile = plan.n_tiles;  // makes the tables
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);  // at least 16 bytes
     const int ftp = plan.ftp;
     const int lds_words = nb * ftp;
     for (int w = threadIdx.x; w < lds_words; w += blockDim.x) lds[w] = 0;
-    __shared__ int s_start[TABLE_MAX];
-    load_item_starts(entries, n_entries, s_start);
+    __shared__ int s_start[TABLE_MAX + 1];
+    __shared__ __attribute__((aligned(16))) uint32_t s_row[IDX == 3 ? SELECT_ROWS : 1];
+    __shared__ int16_t s_gh[IDX == 3 ? SELECT_ROWS : 1];
+    __shared__ int s_n[2], s_seg[COUNT_THREADS / 64];
+    if constexpr (IDX == 3) {
+        if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+        n_items = count_starts(cs, plan, s_start, s_row, s_seg, n_entries, segs);
+        records = min(cs.batch_max, COUNT_RECORDS) * (int)sizeof(BatchEntry) / 16 * 16 / (int)sizeof(BatchEntry);
+        if (tile >= plan.n_tiles || glane >= n_items) {
+            if (tile >= plan.n_tiles && n_items > 0) count_tables(cs, plan, s_start, n_entries, n_items);
+            return;
+        }
+    } else {
+        load_item_starts(entries, n_entries, s_start);
+    }
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -393,16 +540,79 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
     const uint32_t pitch = (uint32_t)ftp * (uint32_t)sizeof(word);  // LDS bytes per bin row
     const int64_t row_bytes = (int64_t)F * BB;
 
-    for (int item = glane; item < n_items; item += n_lanes) {
-        const HistEntry en = entries[find_entry(s_start, n_entries, item)];
+    // rows of the list or slice that row_at and load_gh read; three stages in flight as in hist_kernel; rows past the end read the
+    // last one again and add zero
+    auto accumulate = [&](const uint8_t* colbase, int crow, auto row_at, auto load_gh) {
+        if (wave * rpi >= crow) return;
+        auto load_row = [&](int64_t row) {
+            uint4 v;
+            __builtin_memcpy(&v, colbase + (IDX == 2 ? row & src.code.id_mask : row) * row_bytes, 16);
+            return v;
+        };
+        const int step_rows = n_waves * rpi;
+        int p = wave * rpi + r;
+        int64_t row = row_at(p), rown = row_at(p + step_rows);
+        uint4 d = load_row(row);
+        int gv = load_gh(p, row);
+        for (int ro = wave * rpi; ro < crow; ro += step_rows, p += step_rows) {
+            const uint4 dn = load_row(rown);
+            const int gn = load_gh(p + step_rows, rown);
+            rown = row_at(p + 2 * step_rows);
+            if (lane_on) {
+                const word v = Acc<W>::expand(p < crow ? gv : 0, hmul);
+                const uint32_t a0 = rot8 ? d.z : d.x, a1 = rot8 ? d.w : d.y, a2 = rot8 ? d.x : d.z, a3 = rot8 ? d.y : d.w;
+                const uint32_t dw[4] = {rot4 ? a1 : a0, rot4 ? a2 : a1, rot4 ? a3 : a2, rot4 ? a0 : a3};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int k = 0; k < NPD; ++k) {
+                        const uint32_t b = __builtin_amdgcn_ubfe(dw[i], sh[k], 8u * BB);
+                        if (!RAG || okk[i][k])
+                            Acc<W>::add(reinterpret_cast<word*>(lds_raw + (__umul24(b, pitch) + fl[i][k])), v);
+                    }
+            }
+            d = dn; gv = gn;
+        }
+    };
+
+    for (int item = glane, turn = 0; item < n_items; item += n_lanes) {
+        if constexpr (IDX == 3) {
+            const int e = find_start(s_start, n_entries, item);
+            BatchEntry nd;
+            if (item == glane && e < records) read_record(reinterpret_cast<const BatchEntry*>(s_row) + e, nd); else read_record(cs.batch + e, nd);
+            const int local = item - s_start[e];
+            unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
+            const uint8_t* colbase = src.bins[BUF_ORIGINAL] + f0 * BB + at;
+            const int ibegin = local * segs * cs.seg_rows, iend = min(nd.count, ibegin + segs * cs.seg_rows);
+            RowSelect rs;
+            rs.load_list(idxs, nd, ibegin, min(iend - ibegin, SELECT_ROWS), wave, lane);
+            clear_large(local, (e + 1 < n_entries ? s_start[e + 1] : n_items) - s_start[e], plan, tile, hist_base + (int64_t)nd.new_slot * F * nb, (int64_t)F * nb);
+            rs.load_bins(src, cs, nd, min(iend - ibegin, SELECT_ROWS), wave, F, BB);
+            for (int r0 = ibegin; r0 < iend; r0 += SELECT_ROWS, turn ^= 1) {
+                const int n = min(iend - r0, SELECT_ROWS), ahead = min(iend - r0 - SELECT_ROWS, SELECT_ROWS);
+                __syncthreads();  // (the rows of the last list are done)
+                if (threadIdx.x == 0) s_n[turn ^ 1] = 0;
+                rs.emit(src, cs, nd, r0, n, wave, lane, tile == 0, s_row, s_gh, &s_n[turn], s_seg);
+                if (ahead > 0) rs.load_list(idxs, nd, r0 + SELECT_ROWS, ahead, wave, lane);
+                __syncthreads();
+                const int crow = s_n[turn];
+                if (tile == 0) rs.write_counts(cs, nd, r0, n, s_seg);
+                if (ahead > 0) rs.load_bins(src, cs, nd, ahead, wave, F, BB);
+                accumulate(colbase, crow, [&](int p) { return (int64_t)s_row[min(p, crow - 1)]; }, [&](int p, int64_t) { return (int)s_gh[min(p, crow - 1)]; });
+            }
+            __syncthreads();
+            store_partial<W>(lds, plan.lds_bytes, slot);
+            continue;
+        }
+        const HistEntry en = entries[find_start(s_start, n_entries, item)];
+        int64_t* hist = hist_base + (int64_t)en.slot * F * nb;
+        unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
+        const int sb = IDX ? BUF_ORIGINAL : en.buf;
+        const uint8_t* colbase = src.bins[sb] + f0 * BB + at;
         const int64_t rows_per_group = (en.count + en.groups - 1) / en.groups;
         const int64_t gbegin = min(en.count, (int64_t)(item - en.item_start) * rows_per_group);
         const int64_t gend = min(en.count, gbegin + rows_per_group);
-        int64_t* hist = hist_base + (int64_t)en.slot * F * nb;
-        unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
         const int32_t* idx = IDX ? (idxs.p[en.buf] + en.begin) : nullptr;
-        const int sb = IDX ? BUF_ORIGINAL : en.buf;
-        const uint8_t* colbase = src.bins[sb] + f0 * BB + at;
         const bool gpos = IDX && src.gh_pos != 0;  // packed gradients in list order
         const int16_t* gh = gpos ? src.gh[en.buf] + en.begin : src.gh[sb];
 
@@ -413,42 +623,8 @@ __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_piece_kernel(Ro
             __syncthreads();
             const int32_t* ib = IDX ? idx + cbegin : nullptr;
             const int64_t row_base = IDX ? 0 : en.begin + cbegin;
-            if (wave * rpi < crow) {
-                // three stages in flight as in hist_kernel; rows past the end read the last one again and add zero
-                auto row_at = [&](int p) { return IDX ? (int64_t)(uint32_t)ib[min(p, crow - 1)] : row_base + min(p, crow - 1); };
-                auto load_row = [&](int64_t row) {
-                    uint4 v;
-                    __builtin_memcpy(&v, colbase + (IDX == 2 ? row & src.code.id_mask : row) * row_bytes, 16);
-                    return v;
-                };
-                auto load_gh = [&](int p, int64_t row) {
-                    return IDX == 2 ? src.code.gh((uint32_t)row) : (int)gh[gpos ? cbegin + min(p, crow - 1) : row];
-                };
-                const int step_rows = n_waves * rpi;
-                int p = wave * rpi + r;
-                int64_t row = row_at(p), rown = row_at(p + step_rows);
-                uint4 d = load_row(row);
-                int gv = load_gh(p, row);
-                for (int ro = wave * rpi; ro < crow; ro += step_rows, p += step_rows) {
-                    const uint4 dn = load_row(rown);
-                    const int gn = load_gh(p + step_rows, rown);
-                    rown = row_at(p + 2 * step_rows);
-                    if (lane_on) {
-                        const word v = Acc<W>::expand(p < crow ? gv : 0, hmul);
-                        const uint32_t a0 = rot8 ? d.z : d.x, a1 = rot8 ? d.w : d.y, a2 = rot8 ? d.x : d.z, a3 = rot8 ? d.y : d.w;
-                        const uint32_t dw[4] = {rot4 ? a1 : a0, rot4 ? a2 : a1, rot4 ? a3 : a2, rot4 ? a0 : a3};
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-#pragma unroll
-                            for (int k = 0; k < NPD; ++k) {
-                                const uint32_t b = __builtin_amdgcn_ubfe(dw[i], sh[k], 8u * BB);
-                                if (!RAG || okk[i][k])
-                                    Acc<W>::add(reinterpret_cast<word*>(lds_raw + (__umul24(b, pitch) + fl[i][k])), v);
-                            }
-                    }
-                    d = dn; gv = gn;
-                }
-            }
+            accumulate(colbase, crow, [&](int p) { return IDX ? (int64_t)(uint32_t)ib[min(p, crow - 1)] : row_base + min(p, crow - 1); },
+                       [&](int p, int64_t row) { return IDX == 2 ? src.code.gh((uint32_t)row) : (int)gh[gpos ? cbegin + min(p, crow - 1) : row]; });
             __syncthreads();
             if (cend >= gend) store_partial<W>(lds, plan.lds_bytes, slot);
             else merge_local<W>(lds, lds_words, ftp, ft, f0, F, hist, plan.hshift, false);
@@ -474,29 +650,42 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
                                                                     const HistEntry* __restrict__ entries,
                                                                     const int32_t* __restrict__ table_counts,
                                                                     int64_t* hist_base, unsigned char* partials, int F,
-                                                                    int nb, HistPlan plan, StepState* step,
-                                                                    const uint16_t* __restrict__ mfb) {
+                                                                    int nb, HistPlan plan, CountSource cs, const uint16_t* __restrict__ mfb) {
     using word = typename Acc<W>::word;
     using vec = typename std::conditional<V == 16, uint4, uint2>::type;
     constexpr int NV = V / 4;  // dwords per lane
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
-    const int n_entries = table_counts[0], n_items = table_counts[1];
+    int n_entries = 0, n_items = 0, segs = 1, records = 0;
+    if (IDX != 3) { n_entries = table_counts[0]; n_items = table_counts[1]; }
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     int tile, glane;
     tile_and_lane(plan.n_tiles, tile, glane);
-    const int n_lanes = (int)gridDim.x / plan.n_tiles;
-    if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
+    const int n_lanes = ((int)gridDim.x - (IDX == 3 ? 1 : 0)) / plan.n_tiles;
+    if (IDX != 3 && glane >= n_items) return;
+    if (IDX == 3 && blockIdx.x == gridDim.x - 1) tile = plan.n_tiles;  // makes the tables
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);  // a multiple of V
     const int ftp = plan.ftp;
     const int lds_words = nb * ftp;
     for (int w = threadIdx.x; w < lds_words; w += blockDim.x) lds[w] = 0;
-    __shared__ int s_start[TABLE_MAX];
-    load_item_starts(entries, n_entries, s_start);
+    __shared__ int s_start[TABLE_MAX + 1];
+    __shared__ __attribute__((aligned(16))) uint32_t s_row[IDX == 3 ? SELECT_ROWS : 1];
+    __shared__ int16_t s_gh[IDX == 3 ? SELECT_ROWS : 1];
+    __shared__ int s_n[2], s_seg[COUNT_THREADS / 64];
+    if constexpr (IDX == 3) {
+        if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+        n_items = count_starts(cs, plan, s_start, s_row, s_seg, n_entries, segs);
+        records = min(cs.batch_max, COUNT_RECORDS) * (int)sizeof(BatchEntry) / 16 * 16 / (int)sizeof(BatchEntry);
+        if (tile >= plan.n_tiles || glane >= n_items) {
+            if (tile >= plan.n_tiles && n_items > 0) count_tables(cs, plan, s_start, n_entries, n_items);
+            return;
+        }
+    } else {
+        load_item_starts(entries, n_entries, s_start);
+    }
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -537,16 +726,100 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
     const uint32_t pitch = (uint32_t)ftp * (uint32_t)sizeof(word);
     const int S = U * rpi;
 
-    for (int item = glane; item < n_items; item += n_lanes) {
-        const HistEntry en = entries[find_entry(s_start, n_entries, item)];
+    // rows of the list or slice that row_at and load_gh read.  Three stages in flight: row ids of block n+2, bin pieces and packed
+    // gradients of block n+1, LDS atomics of block n; rows past the end re-read the last row and add zero
+    auto accumulate = [&](const uint8_t* colbase, int crow, auto row_at, auto load_gh) {
+        auto row_id = [&](int64_t e) { return IDX == 2 ? e & src.code.id_mask : e; };
+        if (wave * S >= crow) return;
+        int64_t rown[U];
+        vec d[U], dn[U];
+        int gv[U], gn[U];
+        {
+            int64_t rows[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) rows[u] = row_at(min(wave * S + u * rpi + r, crow - 1));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                d[u] = *reinterpret_cast<const vec*>(colbase + row_id(rows[u]) * F);
+                gv[u] = load_gh(min(wave * S + u * rpi + r, crow - 1), rows[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) rown[u] = row_at(min((wave + n_waves) * S + u * rpi + r, crow - 1));
+        }
+        for (int ro = wave * S; ro < crow; ro += n_waves * S) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                dn[u] = *reinterpret_cast<const vec*>(colbase + row_id(rown[u]) * F);
+                gn[u] = load_gh(min(ro + n_waves * S + u * rpi + r, crow - 1), rown[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) rown[u] = row_at(min(ro + 2 * n_waves * S + u * rpi + r, crow - 1));
+            if (lane_on) {  // lanes beyond the tile's width sit out (their loads alias piece 0)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool ok = ro + u * rpi + r < crow;
+                    const word v = Acc<W>::expand(ok ? gv[u] : 0, hmul);
+                    uint32_t dw[4];
+                    if constexpr (V == 16) {
+                        dw[0] = d[u].x; dw[1] = d[u].y; dw[2] = d[u].z; dw[3] = d[u].w;
+                    } else {
+                        dw[0] = swap ? d[u].y : d[u].x; dw[1] = swap ? d[u].x : d[u].y; dw[2] = 0; dw[3] = 0;
+                    }
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) {
+                        const uint32_t ioff = (V == 16) ? (uint32_t)(4 * i) * (uint32_t)sizeof(word) : (i ? step2 : 0u);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const uint32_t b = __builtin_amdgcn_ubfe(dw[i], sh[k], 8u);
+                            if (!SKIP || b != skipb[SKIP ? i : 0][k])
+                                Acc<W>::add(reinterpret_cast<word*>(lds_raw + (__umul24(b, pitch) + flk[k] + ioff)), v);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) { d[u] = dn[u]; gv[u] = gn[u]; }
+        }
+    };
+
+    for (int item = glane, turn = 0; item < n_items; item += n_lanes) {
+        if constexpr (IDX == 3) {
+            const int e = find_start(s_start, n_entries, item);
+            BatchEntry nd;
+            if (item == glane && e < records) read_record(reinterpret_cast<const BatchEntry*>(s_row) + e, nd); else read_record(cs.batch + e, nd);
+            const int local = item - s_start[e];
+            unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
+            const uint8_t* colbase = src.bins[BUF_ORIGINAL] + f0 + V * c;
+            const int ibegin = local * segs * cs.seg_rows, iend = min(nd.count, ibegin + segs * cs.seg_rows);
+            RowSelect rs;
+            rs.load_list(idxs, nd, ibegin, min(iend - ibegin, SELECT_ROWS), wave, lane);
+            clear_large(local, (e + 1 < n_entries ? s_start[e + 1] : n_items) - s_start[e], plan, tile, hist_base + (int64_t)nd.new_slot * F * nb, (int64_t)F * nb);
+            rs.load_bins(src, cs, nd, min(iend - ibegin, SELECT_ROWS), wave, F, 1);
+            for (int r0 = ibegin; r0 < iend; r0 += SELECT_ROWS, turn ^= 1) {
+                const int n = min(iend - r0, SELECT_ROWS), ahead = min(iend - r0 - SELECT_ROWS, SELECT_ROWS);
+                __syncthreads();  // (the rows of the last list are done)
+                if (threadIdx.x == 0) s_n[turn ^ 1] = 0;
+                rs.emit(src, cs, nd, r0, n, wave, lane, tile == 0, s_row, s_gh, &s_n[turn], s_seg);
+                if (ahead > 0) rs.load_list(idxs, nd, r0 + SELECT_ROWS, ahead, wave, lane);
+                __syncthreads();
+                const int crow = s_n[turn];
+                if (tile == 0) rs.write_counts(cs, nd, r0, n, s_seg);
+                if (ahead > 0) rs.load_bins(src, cs, nd, ahead, wave, F, 1);
+                accumulate(colbase, crow, [&](int p) { return (int64_t)s_row[p]; }, [&](int p, int64_t) { return (int)s_gh[p]; });
+            }
+            __syncthreads();
+            store_partial<W>(lds, plan.lds_bytes, slot);
+            continue;
+        }
+        const HistEntry en = entries[find_start(s_start, n_entries, item)];
+        int64_t* hist = hist_base + (int64_t)en.slot * F * nb;
+        unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
+        const int sb = IDX ? BUF_ORIGINAL : en.buf;
+        const uint8_t* colbase = src.bins[sb] + f0 + V * c;
         const int64_t rows_per_group = (en.count + en.groups - 1) / en.groups;
         const int64_t gbegin = min(en.count, (int64_t)(item - en.item_start) * rows_per_group);
         const int64_t gend = min(en.count, gbegin + rows_per_group);
-        int64_t* hist = hist_base + (int64_t)en.slot * F * nb;
-        unsigned char* slot = partials + ((size_t)item * plan.n_tiles + tile) * (size_t)plan.slot_bytes;
         const int32_t* idx = IDX ? (idxs.p[en.buf] + en.begin) : nullptr;
-        const int sb = IDX ? BUF_ORIGINAL : en.buf;
-        const uint8_t* colbase = src.bins[sb] + f0 + V * c;
         const bool gpos = IDX && src.gh_pos != 0;  // packed gradients in list order
         const int16_t* gh = gpos ? src.gh[en.buf] + en.begin : src.gh[sb];
 
@@ -556,69 +829,8 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
             __syncthreads();
             const int32_t* ib = IDX ? idx + cbegin : nullptr;
             const int64_t row_base = IDX ? 0 : en.begin + cbegin;
-            auto row_id = [&](int64_t e) { return IDX == 2 ? e & src.code.id_mask : e; };
-            if (wave * S < crow) {
-                // three stages in flight: row ids of block n+2, bin pieces and packed gradients of
-                // block n+1, LDS atomics of block n; rows past the end re-read the last row and add zero
-                int64_t rown[U];
-                vec d[U], dn[U];
-                int gv[U], gn[U];
-                {
-                    int64_t rows[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int p = min(wave * S + u * rpi + r, crow - 1);
-                        rows[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        d[u] = *reinterpret_cast<const vec*>(colbase + row_id(rows[u]) * F);
-                        gv[u] = IDX == 2 ? src.code.gh((uint32_t)rows[u]) : (int)gh[gpos ? cbegin + min(wave * S + u * rpi + r, crow - 1) : rows[u]];
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int p = min((wave + n_waves) * S + u * rpi + r, crow - 1);
-                        rown[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
-                    }
-                }
-                for (int ro = wave * S; ro < crow; ro += n_waves * S) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        dn[u] = *reinterpret_cast<const vec*>(colbase + row_id(rown[u]) * F);
-                        gn[u] = IDX == 2 ? src.code.gh((uint32_t)rown[u]) : (int)gh[gpos ? cbegin + min(ro + n_waves * S + u * rpi + r, crow - 1) : rown[u]];
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int p = min(ro + 2 * n_waves * S + u * rpi + r, crow - 1);
-                        rown[u] = IDX ? (int64_t)(uint32_t)ib[p] : row_base + p;
-                    }
-                    if (lane_on) {  // lanes beyond the tile's width sit out (their loads alias piece 0)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const bool ok = ro + u * rpi + r < crow;
-                        const word v = Acc<W>::expand(ok ? gv[u] : 0, hmul);
-                        uint32_t dw[4];
-                        if constexpr (V == 16) {
-                            dw[0] = d[u].x; dw[1] = d[u].y; dw[2] = d[u].z; dw[3] = d[u].w;
-                        } else {
-                            dw[0] = swap ? d[u].y : d[u].x; dw[1] = swap ? d[u].x : d[u].y; dw[2] = 0; dw[3] = 0;
-                        }
-#pragma unroll
-                        for (int i = 0; i < NV; ++i) {
-                            const uint32_t ioff = (V == 16) ? (uint32_t)(4 * i) * (uint32_t)sizeof(word) : (i ? step2 : 0u);
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                const uint32_t b = __builtin_amdgcn_ubfe(dw[i], sh[k], 8u);
-                                if (!SKIP || b != skipb[SKIP ? i : 0][k])
-                                    Acc<W>::add(reinterpret_cast<word*>(lds_raw + (__umul24(b, pitch) + flk[k] + ioff)), v);
-                            }
-                        }
-                    }
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) { d[u] = dn[u]; gv[u] = gn[u]; }
-                }
-            }
+            accumulate(colbase, crow, [&](int p) { return IDX ? (int64_t)(uint32_t)ib[p] : row_base + p; },
+                       [&](int p, int64_t row) { return IDX == 2 ? src.code.gh((uint32_t)row) : (int)gh[gpos ? cbegin + p : row]; });
             __syncthreads();
             if (cend >= gend) store_partial<W>(lds, plan.lds_bytes, slot);
             else merge_local<W>(lds, lds_words, ftp, ft, f0, F, hist, plan.hshift, plan.pad16 != 0);
@@ -643,15 +855,14 @@ __global__ __launch_bounds__(TWO ? 1024 : HIST_THREADS, TWO ? 1 : HIST_WAVES) vo
                                                          const HistEntry* __restrict__ entries,
                                                          const int32_t* __restrict__ table_counts,
                                                          int64_t* hist_base, unsigned char* partials, int F, int nb,
-                                                         HistPlan plan, StepState* step) {
+                                                         HistPlan plan) {
     using word = typename Acc<W>::word;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
     const int n_entries = table_counts[0], n_items = table_counts[1];
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     if ((int)blockIdx.x >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, 0, step);
 
     const int RPI = plan.flat_rows, L = plan.flat_lanes;
     const int BR = U * RPI;  // rows of one block of U iterations
@@ -696,7 +907,7 @@ __global__ __launch_bounds__(TWO ? 1024 : HIST_THREADS, TWO ? 1 : HIST_WAVES) vo
     const int chunk = (plan.chunk_rows - (align_rows - 1)) / BR * BR > 0 ? (plan.chunk_rows - (align_rows - 1)) / BR * BR : BR;
 
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const HistEntry en = entries[find_entry(s_start, n_entries, item)];
+        const HistEntry en = entries[find_start(s_start, n_entries, item)];
         const uint8_t* bins = src.bins[en.buf];
         const int16_t* gh = src.gh[en.buf];
         // the first rows up to a 16-byte aligned row start are taken by group 0, one dword at a time
@@ -878,9 +1089,9 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
                                                             const HistEntry* __restrict__ entries,
                                                             const int32_t* __restrict__ table_counts,
                                                             int64_t* hist_base, unsigned char* partials, int F,
-                                                            int nb, HistPlan plan, StepState* step) {
+                                                            int nb, HistPlan plan) {
     using word = typename Acc<W>::word;
-    extern __shared__ unsigned char lds_raw[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
     const int n_entries = table_counts[0], n_items = table_counts[1];
     const int hmul = (1 << (plan.hshift - 8)) - 1;
@@ -888,7 +1099,6 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) count_profile(entries, n_entries, IDX, step);
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
     const int lds_words = ft * nb;
@@ -901,7 +1111,7 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
     const int rpi = 64 / C;                  // rows per wavefront iteration
     const int r = lane / C, fl = lane % C;   // the lane's row of the iteration and first feature
     for (int item = glane; item < n_items; item += n_lanes) {
-        const HistEntry en = entries[find_entry(s_start, n_entries, item)];
+        const HistEntry en = entries[find_start(s_start, n_entries, item)];
         const int64_t rows_per_group = (en.count + en.groups - 1) / en.groups;
         const int64_t gbegin = min(en.count, (int64_t)(item - en.item_start) * rows_per_group);
         const int64_t gend = min(en.count, gbegin + rows_per_group);
@@ -951,6 +1161,7 @@ __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* _
     if (i0 >= i1) return;  // uniform over the workgroup
     __shared__ int s_start[TABLE_MAX];
     load_item_starts(entries, n_entries, s_start);
+    int e = find_start(s_start, n_entries, i0);  // (while all lanes are there)
     const int f0 = blockIdx.y * plan.ft;
     const int ft = min(plan.ft, F - f0);
     const int pitch = generic ? ft : plan.ftp;
@@ -962,7 +1173,6 @@ __global__ __launch_bounds__(256) void hist_reduce_kernel(const unsigned char* _
     const size_t stride = (size_t)gridDim.y * (size_t)plan.slot_bytes;  // bytes from one item's slot to the next
     const unsigned char* base = partials + (size_t)blockIdx.y * (size_t)plan.slot_bytes + (size_t)w * sizeof(word);
     const int64_t hoff = (int64_t)b * F + f0 + f;
-    int e = find_entry(s_start, n_entries, i0);
     int i = i0;
     while (i < i1) {
         const int iend = min(i1, entries[e].item_start + entries[e].groups);
@@ -1210,25 +1420,26 @@ HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int ac
     return p;
 }
 
-// The table of a stand-alone build, and its histogram cleared.
-__global__ void begin_build_kernel(HistEntry* entries, int32_t* counts, HistEntry e, int64_t* hist, int64_t n_words) {
+// The table of a stand-alone build, and its histogram cleared; its rows are counted in `prof`.
+__global__ void begin_build_kernel(HistEntry* entries, int32_t* counts, HistEntry e, int64_t* hist, int64_t n_words, HistProfile* prof, int gathered) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = t; i < n_words; i += (int64_t)gridDim.x * blockDim.x) hist[i] = 0;
     if (t == 0) {
         entries[0] = e;
         counts[0] = 1;
         counts[1] = e.groups;
+        prof->add(gathered ? HistProfile::IDS : HistProfile::CONTIGUOUS, e.count, 1);
     }
 }
 
 // (The row groups are counted on the host: on the device their chain of 64-bit divisions took 0.3 us of every build.)
-int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, int64_t* hist, int64_t n_words) {
+int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, bool gathered, int64_t* hist, int64_t n_words) {
     const int64_t t = hist_target_rows(plan, count, 1), g = (count + t - 1) / t;
     HistEntry e;
     e.begin = begin; e.count = count; e.buf = BUF_ORIGINAL; e.slot = 0; e.item_start = 0; e.groups = g < 1 ? 1 : (int32_t)g;
     const int64_t blocks = (n_words + 255) / 256;
     hipLaunchKernelGGL(begin_build_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks)), dim3(256), 0, ctx->stream, ctx->hist_entries,
-                       ctx->hist_counts, e, hist, n_words);
+                       ctx->hist_counts, e, hist, n_words, &ctx->step->prof, gathered ? 1 : 0);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
@@ -1267,11 +1478,26 @@ int prepare_hist_kernels(qgbdt_ctx* ctx) {
     return QGBDT_OK;
 }
 
+static bool rows_aligned16(const RowSource& rows) {
+    bool ok = true;
+    for (int b = 0; b <= ROW_BUFS; ++b) ok = ok && (((uintptr_t)rows.bins[b] & 15) == 0);
+    return ok;
+}
+
+bool counting_build_ok(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows) {
+    if (plan.bytewise || plan.lds_bytes > 64 * 1024 || rows.gh_pos || ctx->seg_supers) return false;
+    if (!(plan.wide_v > 0 ? rows_aligned16(rows) : plan.pieces > 0)) return false;
+    // no item of more than one chunk, and room in the table for as many items as count_item_segs makes
+    const int most = plan.single_rows / ctx->seg_rows, lanes = count_lanes(plan);
+    return most >= 1 && (int64_t)ctx->max_seg / most + ctx->batch_max + 1 <= plan.max_items && lanes / 2 + 1 + ctx->batch_max <= plan.max_items &&
+           lanes + 1 <= plan.max_items;
+}
+
 // Launches the kernel variant for (plan, row source).  `grid_items` is the host's upper bound on
 // the number of work items; workgroups beyond the table's item count return at once.
 int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, const IdxSet& idx, bool use_idx,
                 bool flat_ok, const HistEntry* entries, const int32_t* table_counts, int64_t* hist_base,
-                int64_t grid_items, StepState* step, const uint16_t* mfb, int reduce_above) {
+                int64_t grid_items, const uint16_t* mfb, int reduce_above, const CountSource* count) {
     const int F = ctx->shape.n_features, nb = ctx->shape.n_bins;
     unsigned char* partials = static_cast<unsigned char*>(ctx->hist_partials);
     // The kernels address slot (item, tile) for item < max_items of the plan they are given (the tables they read
@@ -1288,10 +1514,11 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     if (groups > plan.max_lanes) groups = plan.max_lanes;
     if (groups < 1) groups = 1;
     // row-group lanes in multiples of 8 (one per XCD), times the feature tiles, as one flat grid
-    const int64_t lanes = (groups + 7) / 8 * 8;
-    dim3 grid((unsigned)(lanes * plan.n_tiles)), block(plan.threads);
+    const int64_t lanes = count ? count_lanes(plan) : (groups + 7) / 8 * 8;
+    dim3 grid((unsigned)(lanes * plan.n_tiles) + (count ? 1 : 0)), block(count ? COUNT_THREADS : plan.threads);  // (one more: the tables)
     const bool fast = !plan.bytewise;
-    const int mode = !use_idx ? 0 : rows.code.on() ? 2 : 1;  // contiguous rows, row ids, row ids with their gradients
+    const int mode = count ? 3 : !use_idx ? 0 : rows.code.on() ? 2 : 1;  // contiguous rows, row ids, row ids with their gradients, rows that the launch selects
+    const CountSource cs = count ? *count : CountSource{};
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->profiling && ctx->ev_used + 2 <= ctx->ev_cap) {
         for (int k = 0; k < 2; ++k)
@@ -1304,12 +1531,12 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     const bool flat = fast && !use_idx && plan.flat_lanes > 0 && flat_ok;
     if (plan.two_level && !flat)
         return set_error(ctx, QGBDT_E_INVALID_ARG, "two-level plan for rows that the byte-stream kernel cannot read");
-    bool wide_ok = true;  // 16-byte loads need 16-byte aligned matrices (F is a multiple of 16 in that mode)
-    for (int b = 0; b <= ROW_BUFS; ++b) wide_ok = wide_ok && (((uintptr_t)rows.bins[b] & 15) == 0);
+    const bool wide_ok = rows_aligned16(rows);  // 16-byte loads need 16-byte aligned matrices (F is a multiple of 16 in that mode)
+    if (count && !counting_build_ok(ctx, plan, rows)) return set_error(ctx, QGBDT_E_INVALID_ARG, "no kernel of this plan counts rows on its own");
     if (flat) {
 #define QG_LAUNCH_FLAT(W_, TWO_)                                                                                  \
     hipLaunchKernelGGL((hist_flat_kernel<W_, 2, TWO_>), grid, block, plan.lds_bytes, ctx->stream, rows, entries,  \
-                       table_counts, hist_base, partials, F, nb, plan, step)
+                       table_counts, hist_base, partials, F, nb, plan)
         if (plan.two_level) QG_LAUNCH_FLAT(16, true);
         else if (plan.acc_width == 16) QG_LAUNCH_FLAT(16, false);
         else QG_LAUNCH_FLAT(32, false);
@@ -1318,7 +1545,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #define QG_LAUNCH_WIDE_S(W_, IDX_, V_, U_, S_)                                                                        \
     do {                                                                                                              \
         hipLaunchKernelGGL((hist_wide_kernel<W_, IDX_, V_, U_, S_>), grid, block, plan.lds_bytes, ctx->stream, rows,  \
-                           idx, entries, table_counts, hist_base, partials, F, nb, plan, step, mfb);                  \
+                           idx, entries, table_counts, hist_base, partials, F, nb, plan, cs, mfb);                  \
     } while (0)
 #define QG_LAUNCH_WIDE(W_, IDX_, V_, U_)                                                                              \
     do {                                                                                                              \
@@ -1327,9 +1554,9 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #define QG_LAUNCH_WIDE_V(W_, IDX_) \
     if (plan.wide_v == 16) QG_LAUNCH_WIDE(W_, IDX_, 16, 2); else QG_LAUNCH_WIDE(W_, IDX_, 8, 2)
         if (plan.acc_width == 16) {
-            if (mode == 2) { QG_LAUNCH_WIDE_V(16, 2); } else if (mode == 1) { QG_LAUNCH_WIDE_V(16, 1); } else { QG_LAUNCH_WIDE_V(16, 0); }
+            if (mode == 3) { QG_LAUNCH_WIDE_V(16, 3); } else if (mode == 2) { QG_LAUNCH_WIDE_V(16, 2); } else if (mode == 1) { QG_LAUNCH_WIDE_V(16, 1); } else { QG_LAUNCH_WIDE_V(16, 0); }
         } else {
-            if (mode == 2) { QG_LAUNCH_WIDE_V(32, 2); } else if (mode == 1) { QG_LAUNCH_WIDE_V(32, 1); } else { QG_LAUNCH_WIDE_V(32, 0); }
+            if (mode == 3) { QG_LAUNCH_WIDE_V(32, 3); } else if (mode == 2) { QG_LAUNCH_WIDE_V(32, 2); } else if (mode == 1) { QG_LAUNCH_WIDE_V(32, 1); } else { QG_LAUNCH_WIDE_V(32, 0); }
         }
 #undef QG_LAUNCH_WIDE_V
 #undef QG_LAUNCH_WIDE
@@ -1337,7 +1564,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     } else if (fast && plan.pieces > 0 && !(mode == 0 && plan.contig_dwords)) {
 #define QG_LAUNCH_PIECE_K(W_, IDX_, RAG_, BB_)                                                                      \
     hipLaunchKernelGGL((hist_piece_kernel<W_, IDX_, RAG_, BB_>), grid, block, plan.lds_bytes, ctx->stream, \
-                       rows, idx, entries, table_counts, hist_base, partials, F, nb, plan, step)
+                       rows, idx, entries, table_counts, hist_base, partials, F, nb, plan, cs)
 #define QG_LAUNCH_PIECE(W_, IDX_)                                                                                   \
     do {                                                                                                            \
         const bool whole = plan.ft * ctx->shape.bin_bytes % 16 == 0 && F % plan.ft * ctx->shape.bin_bytes % 16 == 0; \
@@ -1347,9 +1574,9 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         else QG_LAUNCH_PIECE_K(W_, IDX_, true, 1);                                                                  \
     } while (0)
         if (plan.acc_width == 16) {
-            if (mode == 2) QG_LAUNCH_PIECE(16, 2); else if (mode == 1) QG_LAUNCH_PIECE(16, 1); else QG_LAUNCH_PIECE(16, 0);
+            if (mode == 3) QG_LAUNCH_PIECE(16, 3); else if (mode == 2) QG_LAUNCH_PIECE(16, 2); else if (mode == 1) QG_LAUNCH_PIECE(16, 1); else QG_LAUNCH_PIECE(16, 0);
         } else {
-            if (mode == 2) QG_LAUNCH_PIECE(32, 2); else if (mode == 1) QG_LAUNCH_PIECE(32, 1); else QG_LAUNCH_PIECE(32, 0);
+            if (mode == 3) QG_LAUNCH_PIECE(32, 3); else if (mode == 2) QG_LAUNCH_PIECE(32, 2); else if (mode == 1) QG_LAUNCH_PIECE(32, 1); else QG_LAUNCH_PIECE(32, 0);
         }
 #undef QG_LAUNCH_PIECE
 #undef QG_LAUNCH_PIECE_K
@@ -1358,7 +1585,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         const int U = cap >= 8 ? 8 : cap >= 4 ? 4 : cap >= 2 ? 2 : 1;
 #define QG_LAUNCH_HIST_K(W_, IDX_, U_, RAG_, BB_)                                                                  \
     hipLaunchKernelGGL((hist_kernel<W_, IDX_, U_, RAG_, BB_>), grid, block, plan.lds_bytes, ctx->stream, rows, idx,   \
-                       entries, table_counts, hist_base, partials, F, nb, plan, step)
+                       entries, table_counts, hist_base, partials, F, nb, plan)
 #define QG_LAUNCH_HIST(W_, IDX_, U_)                                                                               \
     do {                                                                                                           \
         if (ctx->shape.bin_bytes == 2) {                                                                           \
@@ -1385,7 +1612,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     } else {
 #define QG_LAUNCH_GENERIC_K(W_, IDX_, BIN_)                                                                        \
     hipLaunchKernelGGL((hist_generic_kernel<W_, IDX_, BIN_>), grid, block, plan.lds_bytes, ctx->stream, rows, idx, \
-                       entries, table_counts, hist_base, partials, F, nb, plan, step)
+                       entries, table_counts, hist_base, partials, F, nb, plan)
 #define QG_LAUNCH_GENERIC(W_, BIN_) \
     if (mode == 2) QG_LAUNCH_GENERIC_K(W_, 2, BIN_); else if (mode == 1) QG_LAUNCH_GENERIC_K(W_, 1, BIN_); else QG_LAUNCH_GENERIC_K(W_, 0, BIN_)
         if (ctx->shape.bin_bytes == 2) {

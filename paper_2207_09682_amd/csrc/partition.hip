@@ -7,7 +7,7 @@
 // qgbdt_partition_rows (row ids only), then the batched form of grow_tree, which serves
 // all nodes of a round at once and, for narrow rows, also moves the bin rows and packed
 // gradients into leaf order.
-#include "split_device.h"
+#include "partition_device.h"
 
 namespace qgbdt {
 
@@ -160,21 +160,6 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
 // its segment; which of them go left is one 64-bit mask per 64 rows (128 bytes of masks for 1024 rows instead of a byte
 // per row), from which the scatter derives every destination without exchanging anything between wavefronts.
 
-// (The entries' first segments are copied into LDS once per workgroup and searched there: through global memory the
-// search is a chain of dependent loads per segment.)
-__device__ __forceinline__ void load_batch(const int32_t* __restrict__ batch_seg, int n_batch, int* s_start) {
-    for (int t = threadIdx.x; t < n_batch; t += blockDim.x) s_start[t] = batch_seg[t];
-    __syncthreads();
-}
-__device__ __forceinline__ int find_batch(const int* s_start, int n_batch, int item) {
-    int lo = 0, hi = n_batch - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s_start[mid] <= item) lo = mid; else hi = mid - 1;
-    }
-    return __builtin_amdgcn_readfirstlane(lo);
-}
-
 // Left-going rows per segment, as masks and counts; on the way the histogram slots
 // that this round's builds accumulate into are cleared.  In ordered mode the rows of a
 // node are physically contiguous in its buffer and the bin is read at the row's position;
@@ -209,7 +194,7 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
     load_batch(batch_seg, n_batch, s_start);
     int turn = 0;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x, turn ^= 1) {
-        const BatchEntry nd = batch[find_batch(s_start, n_batch, item)];
+        const BatchEntry nd = batch[find_start(s_start, n_batch, item)];
         const int seg = item - nd.seg_start;
         const int sbegin = seg * PART_SEG, n = min(nd.count - sbegin, PART_SEG);  // rows of the segment, inside the node's slice
         const int32_t* src = idxs.p[nd.buf] + nd.begin + sbegin;
@@ -260,7 +245,7 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
 // while the others move rows: it needs nothing of them but the left counts that the count kernel left behind.
 __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __restrict__ batch,
                              const int32_t* __restrict__ super_counts, HistEntry* hist_entries, int32_t* hist_counts,
-                             ScanPair* pairs, const HistPlan& plan, int super_len, int* s_start, int* s_left, int* s_tmp) {
+                             ScanPair* pairs, const HistPlan& plan, int super_len, int prof_kind, int* s_start, int* s_left, int* s_tmp) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_batch = step->n_batch;
     for (int t = tid; t < n_batch; t += 256) { s_start[t] = batch[t].super_start; s_left[t] = 0; }
@@ -312,31 +297,26 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
             P->n_left = nl;
             const bool left_small = nl <= nr;
             const int lslot = left_small ? be.new_slot : slot, rslot = left_small ? slot : be.new_slot;
-            const int cb = be.child_buf;
-            auto put = [&](int which, int64_t begin, int count, int64_t g, int64_t h, int sl) {
-                Node* c = &nodes[child + which];
-                c->begin = begin; c->count = count; c->sum_g = g; c->sum_h = h; c->n_left = 0; c->buf = cb; c->slot = sl;
-                c->state = 0; c->expanded = 0; c->child = -1; c->leaf_id = -1;
-                c->best.gain = 0.0; c->best.feature = -1; c->best.bin = -1;
-                c->best.left_g = c->best.left_h = c->best.right_g = c->best.right_h = c->best.left_count = 0;
-            };
-            put(0, be.begin, nl, lg, lh, lslot);
-            put(1, be.begin + nl, nr, rg, rh, rslot);
+            put_children(nodes, be, child, nl, lg, lh, rg, rh, lslot, rslot);
             HistEntry e;
-            e.begin = left_small ? be.begin : be.begin + nl; e.count = left_small ? nl : nr; e.buf = cb; e.slot = be.new_slot;
+            e.begin = left_small ? be.begin : be.begin + nl; e.count = left_small ? nl : nr; e.buf = be.child_buf; e.slot = be.new_slot;
             e.item_start = start; e.groups = groups;
             hist_entries[t] = e;
             ScanPair sp;
             sp.slot_a = be.new_slot; sp.slot_b = slot; sp.parent = slot; sp.a_item = left_small ? 0 : 1;
             sp.item_start = start; sp.groups = groups <= plan.search_sums ? groups : 0;
-            sp.merged = e.count > (int64_t)groups * plan.single_rows ? 1 : 0; sp.pad = 0;
-            const qgbdt_leafstat sl = {nl, lg, lh}, sr = {nr, rg, rh};
-            sp.stat[0] = left_small ? sl : sr; sp.stat[1] = left_small ? sr : sl;
+            sp.merged = e.count > (int64_t)groups * plan.single_rows ? 1 : 0; sp.seg_start = 0;
+            // (selected number by number: whole records go through scratch memory)
+            sp.stat[0].n_rows = left_small ? nl : nr; sp.stat[0].sum_g = left_small ? lg : rg; sp.stat[0].sum_h = left_small ? lh : rh;
+            sp.stat[1].n_rows = left_small ? nr : nl; sp.stat[1].sum_g = left_small ? rg : lg; sp.stat[1].sum_h = left_small ? rh : lh;
             pairs[t] = sp;
         }
     }
     big = __syncthreads_or(big);
-    if (tid == 0) { hist_counts[0] = n_batch; hist_counts[1] = base; hist_counts[2] = big; }
+    if (tid == 0) {
+        hist_counts[0] = n_batch; hist_counts[1] = base; hist_counts[2] = big;
+        step->prof.add(prof_kind, small_total, n_batch);
+    }
 }
 
 // Order-preserving scatter of every segment into the children's buffer.  The left rows in front of a segment are the sum
@@ -360,7 +340,8 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
     __shared__ int s_start[TABLE_MAX];
     __shared__ int s_dpos[MODE == 2 && PART_SEG > TABLE_MAX + 8 ? PART_SEG : TABLE_MAX + 8];  // (also child_tables' LDS)
     if (blockIdx.x == 0) {
-        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, pairs, plan, SUPER, s_start, s_dpos, s_dpos + TABLE_MAX);
+        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, pairs, plan, SUPER,
+                     MODE == 2 ? HistProfile::CONTIGUOUS : rows.code.on() ? HistProfile::CODED : HistProfile::IDS, s_start, s_dpos, s_dpos + TABLE_MAX);
         return;
     }
     const int n_items = step->n_part_items, n_batch = step->n_batch;
@@ -370,59 +351,12 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
     // Segments are taken from the last to the first: the count kernel has just streamed the same
     // rows front to back, so the tail of that stream is what the memory-side cache still holds.
     for (int item = n_items - (int)blockIdx.x; item >= 0; item -= (int)gridDim.x - 1) {
-        const BatchEntry nd = batch[find_batch(s_start, n_batch, item)];
-        const int seg = item - nd.seg_start, sup = seg / SUPER;
-        const int sbegin = seg * PART_SEG, n = min(nd.count - sbegin, PART_SEG);
-        const int n_sup = (nd.n_seg + SUPER - 1) / SUPER;
-        const int cbuf = nd.child_buf;
-        const bool identity = nd.buf == BUF_ORIGINAL;  // the root's list: row id = position, never stored
-        const int32_t* src = idxs.p[nd.buf] + nd.begin + sbegin;
-        int32_t* dst = idxs.p[cbuf] + nd.begin;
-        const int16_t* gsrc = MODE >= 1 ? rows.gh[nd.buf] + nd.begin + sbegin : nullptr;
-        int16_t* gdst = MODE >= 1 ? out.gh[cbuf] + nd.begin : nullptr;
-        // everything that is read, in flight together
-        int32_t v[R];
-        int g16[R];
-#pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int r = min((wave * R + u) * 64 + lane, n - 1);
-            v[u] = identity ? (int32_t)(nd.begin + sbegin + r) : src[r];
-            g16[u] = MODE >= 1 ? gsrc[r] : 0;
-        }
-        if (MODE == 0 && identity && rows.code.on()) {  // the root's children are the first lists: entries with their gradients
-#pragma unroll
-            for (int u = 0; u < R; ++u) v[u] = (int32_t)rows.code.entry((uint32_t)v[u], rows.gh[BUF_ORIGINAL][v[u]]);
-        }
-        const unsigned long long mk = lane < PART_SEG / 64 ? masks[(int64_t)item * (PART_SEG / 64) + lane] : 0ull;
-        int before = SUPER > 1 && lane < seg - sup * SUPER ? seg_counts[item - (seg - sup * SUPER) + lane] : 0;
-        int total = 0;
-        for (int k = lane; k < n_sup; k += 64) {
-            const int c = super_counts[nd.super_start + k];
-            total += c;
-            before += k < sup ? c : 0;
-        }
-        static_assert(SUPER <= 64 && PART_SEG / 64 <= 64, "one lane each");
-        before = wave_sum(before);  // left rows in earlier segments
-        total = wave_sum(total);    // left rows of the node
-        const int pc = __popcll(mk);
-        const int pre = wave_prefix(pc) - pc;  // left rows of the segment in front of a mask's 64 rows
-#pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int w = wave * R + u, r = w * 64 + lane;
-            const uint32_t mlo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mk, w);
-            const uint32_t mhi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mk >> 32), w);
-            const int left = __builtin_amdgcn_readlane(pre, w) + (int)__builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0u));
-            const bool fl = ((lane < 32 ? mlo : mhi) >> (lane & 31)) & 1u;
-            const int dp = fl ? before + left : total + (sbegin - before) + (r - left);
-            if (r < n) {
-                dst[dp] = v[u];
-                if (MODE >= 1) gdst[dp] = (int16_t)g16[u];
-                if (MODE == 2) s_dpos[r] = dp;
-            }
-        }
+        const BatchEntry nd = batch[find_start(s_start, n_batch, item)];
+        scatter_wave<MODE, R, SUPER>(rows, out.gh, idxs, nd, item, wave, lane, masks, seg_counts, super_counts, s_dpos);
         if (MODE == 2) {
+            const int sbegin = (item - nd.seg_start) * PART_SEG, n = min(nd.count - sbegin, PART_SEG);
             const uint8_t* bsrc = rows.bins[nd.buf] + (nd.begin + sbegin) * (int64_t)F;
-            uint8_t* bdst = out.bins[cbuf] + nd.begin * (int64_t)F;
+            uint8_t* bdst = out.bins[nd.child_buf] + nd.begin * (int64_t)F;
             __syncthreads();
             const uint32_t* s32 = reinterpret_cast<const uint32_t*>(bsrc);
             const int n_dw = n * dpr;

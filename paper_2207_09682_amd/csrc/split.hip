@@ -2,9 +2,10 @@
 // enumeration of Sec. 3 with the quantized gain of Sec. 4.1 eq. (gain)).
 // Integer prefix sums over the packed words, fp64 gain; compiled with FMA
 // contraction off so that the gain is evaluated operation by operation.
+#include <algorithm>
 #include <type_traits>
 
-#include "split_device.h"
+#include "partition_device.h"
 
 namespace qgbdt {
 
@@ -29,7 +30,7 @@ __global__ void scan_pairs_from_stats_kernel(const qgbdt_leafstat* stats, int n,
     if (2 * t < n) {
         ScanPair sp;
         sp.slot_a = 2 * t; sp.slot_b = 2 * t + 1 < n ? 2 * t + 1 : -1; sp.parent = -1; sp.a_item = 0;
-        sp.item_start = 0; sp.groups = 0; sp.merged = 0; sp.pad = 0;
+        sp.item_start = 0; sp.groups = 0; sp.merged = 0; sp.seg_start = 0;
         sp.stat[0] = stats[2 * t]; sp.stat[1] = stats[min(2 * t + 1, n - 1)];
         pairs[t] = sp;
     }
@@ -136,12 +137,17 @@ constexpr int SPREAD_PAIRS = 32;
 // Measured per launch with the reduce kernel's launch in front of it, against one workgroup per feature (or per 16 features and
 // 1024 threads) and histogram behind a full reduction: 1 M x 28, 255 bins 15.0 -> 12.6 us; 464 k x 90 28.1 -> 18.8 us;
 // 2 M x 40, 600 bins 38.1 -> 23.8 us; 400 k x 2000, 63 bins (and one launch less) 46.7 -> 28.6 us; 20 M x 200 34.1 -> 25.4 us.
-template <int T, int NB64, int KB, bool SPREAD>  // features per workgroup; bins, in units of 64; bins per thread; scan_spread
+template <int T, int NB64, int KB, bool SPREAD, int R>  // features per workgroup; bins, in units of 64; bins per thread; scan_spread; R > 0: moves rows too
 __global__ __launch_bounds__(64 * T * NB64 / KB) void scan_pair_kernel(int64_t* hist_base, const ScanPair* __restrict__ pairs,
                                                                   const int32_t* __restrict__ n_items_ptr, int max_pairs, SlotSource slots,
                                                                   int F, int nb, const float* __restrict__ delta, int min_data,
                                                                   double min_sum_hess, FeatCand* __restrict__ cand_base,
-                                                                  const uint16_t* __restrict__ mfb) {
+                                                                  const uint16_t* __restrict__ mfb, typename std::conditional<(R > 0), RowMover, int>::type mover) {
+    int n_blocks = (int)gridDim.x;
+    if constexpr (R > 0) {
+        n_blocks = mover.scan_blocks;
+        if ((int)blockIdx.x >= n_blocks) { move_rows<R>(mover, (int)blockIdx.x - n_blocks, (int)gridDim.x - n_blocks); return; }
+    }
     constexpr int NW = T * NB64 / KB;  // wavefronts
     const int n_items = *n_items_ptr;
     const double dg = (double)delta[0], dh = (double)delta[1];
@@ -159,12 +165,12 @@ __global__ __launch_bounds__(64 * T * NB64 / KB) void scan_pair_kernel(int64_t* 
     const int t0 = (sid / n_ft) * 8 + xcd;
     int tile = sid % n_ft, w = sid;
     ScanPair sp = pairs[min(t0, max_pairs - 1)];  // (in flight together with the number of items)
-    for (int t = t0;; t += (int)(gridDim.x / (8 * n_ft)) * 8) {
+    for (int t = t0;; t += n_blocks / (8 * n_ft) * 8) {
         if (spread) {
             const int i = xcd * share + w;
             if (w >= share || i >= n_work) break;
             t = i / n_ft; tile = i - t * n_ft;
-            w += (int)(gridDim.x >> 3);
+            w += n_blocks >> 3;
             sp = pairs[t];
         } else {
             if (t >= n_pairs) break;
@@ -172,6 +178,21 @@ __global__ __launch_bounds__(64 * T * NB64 / KB) void scan_pair_kernel(int64_t* 
         }
         const int f = tile * T + fl;
         const bool has_b = sp.slot_b >= 0;
+        if constexpr (R > 0) {  // the children's rows: left ones by segment
+            const int count = (int)sp.stat[0].n_rows, n_seg = (count + 256 * R - 1) / (256 * R);
+            const int32_t* c = mover.seg_counts + sp.seg_start;
+            int nl = 0;
+            for (int k = 0; k < n_seg; k += 4 * 64) {
+                int x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = c[min(k + 64 * u + lane, n_seg - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) nl += k + 64 * u + lane < n_seg ? x[u] : 0;
+            }
+            nl = wave_sum(nl);
+            sp.stat[0].n_rows = sp.a_item ? count - nl : nl;  // (the built child comes first)
+            sp.stat[1].n_rows = sp.a_item ? nl : count - nl;
+        }
         const int64_t at = (int64_t)b0 * F + f;  // histograms are [bin][feature]
         int64_t v[2][KB] = {};                    // words, then inclusive prefix sums
         if (f < F && b0 < nb) {
@@ -316,7 +337,7 @@ int scan_candidates(const qgbdt_shape& s) {
 
 int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs, const int32_t* n_items, int max_pairs,
                       const float* delta, int min_data, double min_sum_hess, FeatCand* cand, const uint16_t* mfb,
-                      const HistPlan* plan) {
+                      const HistPlan* plan, const RowMover* mover) {
     const int F = ctx->shape.n_features, nb = ctx->shape.n_bins;
     const int n_ft = scan_candidates(ctx->shape);
     SlotSource src{};
@@ -332,10 +353,19 @@ int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs,
     if (lanes > most) lanes = most;
     lanes = (lanes + 7) / 8 * 8;
     // (where every number of pairs up to max_pairs is spread, no more than there are tiles)
-#define QG_SCAN_S(T_, N_, K_, S_)                                                                                       \
-    hipLaunchKernelGGL((scan_pair_kernel<T_, N_, K_, S_>), dim3((unsigned)((lanes * n_ft + 7) / 8 * 8)),                \
+#define QG_SCAN_R(T_, N_, K_, S_, R_, M_, X_)                                                                           \
+    hipLaunchKernelGGL((scan_pair_kernel<T_, N_, K_, S_, R_>), dim3((unsigned)((lanes * n_ft + 7) / 8 * 8 + (X_))),     \
                        dim3(64 * T_ * N_ / K_), 0, ctx->stream, hist_base, pairs, n_items, max_pairs, src, F, nb,       \
-                       delta, min_data, min_sum_hess, cand, mfb)
+                       delta, min_data, min_sum_hess, cand, mfb, M_)
+#define QG_SCAN_S(T_, N_, K_, S_)                                                                                       \
+    do {                                                                                                                \
+        if (!mover) { QG_SCAN_R(T_, N_, K_, S_, 0, 0, 0); break; }                                                      \
+        RowMover mv = *mover;                                                                                           \
+        mv.scan_blocks = (int)((lanes * n_ft + 7) / 8 * 8);                                                             \
+        const int movers = (int)std::min<int64_t>(2048, ((int64_t)ctx->max_seg * 4 + T_ * N_ / K_ - 1) / (T_ * N_ / K_)) + 1; \
+        if (ctx->seg_rows == 256 * 8) QG_SCAN_R(T_, N_, K_, S_, 8, mv, movers);                                         \
+        else QG_SCAN_R(T_, N_, K_, S_, 2, mv, movers);                                                                  \
+    } while (0)
 #define QG_SCAN(T_, N_, K_)                                                                                             \
     do {                                                                                                                \
         if (scan_spread(n_ft, T_ * N_ / K_)) {                                                                          \
@@ -356,6 +386,7 @@ int launch_scan_pairs(qgbdt_ctx* ctx, int64_t* hist_base, const ScanPair* pairs,
     else if (F >= 64) QG_SCAN(4, 4, 4); else QG_SCAN(4, 4, 2);
 #undef QG_SCAN
 #undef QG_SCAN_S
+#undef QG_SCAN_R
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }

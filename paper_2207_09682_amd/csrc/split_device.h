@@ -15,7 +15,7 @@ struct ScanPair {
     int32_t item_start;      // first slot of a's row groups
     int32_t groups;          // > 0: a is the sum of that many slots, which the split search adds up; 0: it lies in hist[slot_a]
     int32_t merged;          // (groups > 0) hist[slot_a] holds what long row groups have merged already, to be added
-    int32_t pad;
+    int32_t seg_start;       // (counting build) first segment of the parent's rows; n_rows of both totals is then the parent's
     qgbdt_leafstat stat[2];  // totals of a, b
 };
 

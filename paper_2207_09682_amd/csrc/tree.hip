@@ -26,10 +26,23 @@
 #include <algorithm>
 #include <chrono>
 
+#include "partition_device.h"
 #include "refit_device.h"
-#include "split_device.h"
 
 namespace qgbdt {
+
+// Row lists: up to this many rows times tiles of features the histogram launch counts the left rows itself (CountSource) and the rows are moved
+// beside the split search, which leaves a round four dependent launches (three where no reduce kernel is launched) of six.  Every tile of a
+// row group goes through the parents' rows for itself, and a workgroup counts and accumulates one after the other: beyond the line
+// the count and scatter kernels, which fill the chip, are the faster way.  Trees with count and scatter kernels / without, bound: 28 features
+// 20 k rows 485 / 384 us, 200 k 585 / 509, 1 M 602 / 554, 2 M 733 / 688, 4 M 961 / 1010; three tiles (90 features) 200 k 513 / 455, 1 M 663 / 728; four (200) 500 k
+// 558 / 508, 1 M 677 / 704, (500, 63 bins) 200 k 509 / 420, 800 k 732 / 844; five (136, lambdarank) 200 k 598 / 574, 500 k 656 / 637, 1 M 800 / 831,
+// (40 of 16-bit bins) 100 k 407 / 380, 1 M 565 / 642; sixteen (2000, 63 bins) 20 k 394 / 324, 100 k 480 / 462, 400 k 916 / 986; not bound, where the
+// bins that are counted and those that are accumulated share their lines, 28 features 300 k 478 / 398, 1 M 550 / 510, 2.5 M 857 / 778, 5 M 1278 / 1293; 60
+// features 500 k 548 / 494.  A tree of many leaves and tiles has rounds of more nodes than there are row-group lanes: 57 k x 1323
+// (11 tiles, 16 lanes), 275 leaves 1426 / 1471; 43 k x 640 (5, 48), 277 leaves 983 / 859.
+constexpr int64_t COUNTING_ROWS = 2500000, COUNTING_ROWS_UNBOUND = 4000000;
+constexpr int COUNTING_NODES = 6;
 
 struct TreeOut {
     qgbdt_tree t;
@@ -69,6 +82,7 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
         step->done = 0; step->n_known = 0; step->n_list = 0; step->n_nodes = 1; step->n_leaves = 1; step->n_commits = 0; step->n_expanded = 0;
         step->n_slots = 1; step->n_batch = 0; step->rounds = 0; step->n_part_items = 0; step->n_scan_items = 1;
         step->hist_units = N * (int64_t)F;
+        step->prof.add(HistProfile::CONTIGUOUS, N, 1);
         Node r;
         r.begin = 0; r.count = N; r.sum_g = total[0]; r.sum_h = total[1]; r.n_left = 0; r.buf = root_buf; r.slot = 0;
         r.state = 1; r.expanded = 0; r.child = -1; r.leaf_id = 0;
@@ -81,7 +95,7 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
         ScanPair sp;
         sp.slot_a = 0; sp.slot_b = -1; sp.parent = -1; sp.a_item = 0; sp.item_start = 0;
         sp.groups = e.groups <= plan.search_sums ? e.groups : 0;
-        sp.merged = N > (int64_t)e.groups * plan.single_rows ? 1 : 0; sp.pad = 0;
+        sp.merged = N > (int64_t)e.groups * plan.single_rows ? 1 : 0; sp.seg_start = 0;
         sp.stat[0].n_rows = N; sp.stat[0].sum_g = r.sum_g; sp.stat[0].sum_h = r.sum_h;
         sp.stat[1] = sp.stat[0];
         pairs[0] = sp;
@@ -202,7 +216,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         if (tid == 0) report_to_host(report, report_seq, true, st1.w, st1.x, st0.w, st0.y);
         return;
     }
-    extern __shared__ unsigned char plan_lds[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char plan_lds[];
     const PlanLds lay = plan_lds_layout(max_nodes, batch_max, num_leaves);
     unsigned long long* const key = reinterpret_cast<unsigned long long*>(plan_lds + lay.key);
     unsigned long long* const okey = reinterpret_cast<unsigned long long*>(plan_lds + lay.okey);
@@ -535,7 +549,9 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         uint32_t taken = 1u << be.buf;
         for (int q = par[p]; q != (int)NO_NODE && corder[q] == NO_NODE; q = par[q]) taken |= 1u << ((ids[q] >> 12) & 15u);
         be.child_buf = __ffs((int)~taken) - 1;
-        be.pad[0] = be.pad[1] = 0;
+        // (counting build) the child that is built from its rows: the one of fewer rows as far as the hessians tell
+        be.built_left = nd->best.left_h <= nd->best.right_h ? 1 : 0;
+        be.pad = 0;
         nodes[i].expanded = 1;
         nodes[i].child = n_nodes + 2 * tid;
     }
@@ -737,16 +753,18 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     rc = launch_hist(ctx, root_plan, rows, idxs, false, ((uintptr_t)bins & 15) == 0,
                      ctx->hist_entries, ctx->hist_counts, ctx->hist_pool,
                      (N + hist_target_rows(root_plan, N, 1) - 1) / hist_target_rows(root_plan, N, 1),  // the build's row groups
-                     ctx->step, mfb, root_plan.search_sums);
+                     mfb, root_plan.search_sums);
     if (rc != QGBDT_OK) return rc;
-    auto search_splits = [&](const HistPlan& hp, int max_pairs) {
+    const bool counting = !ordered && !gh_lists && N * plan.n_tiles <= (bins_t ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND) &&
+                          p->num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, rows);
+    auto search_splits = [&](const HistPlan& hp, int max_pairs, const RowMover* mover) {
         int rc = launch_scan_pairs(ctx, ctx->hist_pool, ctx->scan_pairs, &ctx->step->n_scan_items, max_pairs, ctx->delta,
-                                   p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, &hp);
+                                   p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, &hp, mover);
         if (rc != QGBDT_OK || fused_cand) return rc;
         return launch_reduce_items(ctx, ctx->cand, ctx->scan_pairs, &ctx->step->n_scan_items, 2 * max_pairs,
                                    &ctx->nodes->best, sizeof(Node), ctx->step);
     };
-    rc = search_splits(root_plan, 1);
+    rc = search_splits(root_plan, 1, nullptr);
     if (rc != QGBDT_OK) return rc;
 
     const size_t plan_lds = plan_kernel_lds(ctx, p->num_leaves);  // at most what prepare_tree_kernels allowed
@@ -758,14 +776,23 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
                            report_seq, out, fused_cand, ctx->scan_pairs);
     };
     auto expand_batch = [&]() {  // partition, histograms and split search of the nodes the plan kernel has chosen
+        if (counting) {
+            const CountSource count = {bins_t, N, ctx->step, ctx->nodes, ctx->batch, ctx->batch_seg, ctx->part_masks, ctx->seg_counts,
+                                       ctx->hist_entries, ctx->hist_counts, ctx->scan_pairs, ctx->seg_rows, ctx->batch_max};
+            int rc = launch_hist(ctx, plan, rows, idxs, true, false, ctx->hist_entries, ctx->hist_counts, ctx->hist_pool,
+                                 plan.max_lanes, mfb, plan.search_sums, &count);
+            if (rc != QGBDT_OK) return rc;
+            const RowMover mover = {rows, idxs, ctx->step, ctx->nodes, ctx->batch, ctx->batch_seg, ctx->part_masks, ctx->seg_counts, 0};
+            return search_splits(plan, ctx->batch_max, &mover);
+        }
         int rc = launch_batch_partition_count(ctx, rows, bins_t, ordered);
         if (rc != QGBDT_OK) return rc;
         rc = launch_batch_partition_scatter(ctx, rows, ordered, plan);
         if (rc != QGBDT_OK) return rc;
         rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
-                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, ctx->step, mfb, plan.search_sums);
+                         ctx->hist_counts, ctx->hist_pool, plan.max_lanes, mfb, plan.search_sums);
         if (rc != QGBDT_OK) return rc;
-        return search_splits(plan, ctx->batch_max);
+        return search_splits(plan, ctx->batch_max, nullptr);
     };
     auto leaf_passes = [&]() {  // what is left to do when the tree is finished; returns at once while it is not
         ctx->tree_passes += 1;

@@ -109,6 +109,35 @@ def test_row_entries_with_gradients(N, bits_g, bits_h, F, nb, bb):
     assert np.allclose(t.leaf_value.cpu().numpy()[:L], e.leaf_value[:L], rtol=1e-9, atol=1e-13)
 
 
+# Trees whose histogram launches count the left rows themselves: row ids sorted by the split feature, so that whole stretches of a
+# parent's list go one way, and hessians by which the child of more rows is taken for the smaller one; rows on both sides of a segment
+# (512 rows, 2048 above 2^18) and of the 4096 that a workgroup reads at a time, work items of two such stretches (1.2 M rows), several tiles and
+# fewer lanes than nodes, 8- and 16-byte pieces, 16-bit bins, row ids without gradients, more than 64 nodes in a round.
+@pytest.mark.parametrize("N,F,nb,bb,L,bits,layout", [
+    (511, 16, 64, 1, 9, 3, 0), (4096, 28, 64, 1, 31, 3, 0), (4097, 17, 255, 1, 31, 3, 1), (8193, 33, 64, 1, 31, 5, 0),
+    (262_144, 16, 64, 1, 127, 3, 0), (262_145, 16, 64, 1, 127, 3, 1), (100_000, 16, 64, 1, 658, 3, 0), (1_200_001, 16, 32, 1, 63, 3, 0),
+    (30_000, 90, 255, 1, 127, 4, 0), (30_000, 72, 255, 1, 63, 8, 0), (20_000, 800, 63, 1, 63, 3, 0), (3000, 4096, 16, 1, 31, 3, 0),
+    (50_001, 40, 300, 2, 63, 3, 0), (40_000, 9, 300, 2, 63, 3, 1)])
+def test_histogram_launches_that_count(N, F, nb, bb, L, bits, layout):
+    rng = np.random.default_rng(N + F)
+    bins = rng.integers(0, nb, (N, F)).astype(np.uint16 if bb == 2 else np.uint8)
+    bins[:, 0] = np.arange(N, dtype=np.int64) * nb // N
+    x = bins[:, :4].astype(np.float64) / nb - 0.5
+    g = (3 * x[:, 0] + 2 * x[:, 1] * x[:, 2] + x[:, 0] * x[:, 3] + 0.2 * rng.normal(size=N)).astype(np.float32)
+    h = (np.where((x[:, 0] < 0.3) & (x[:, 1] < 0.3), 0.01, 0.25) * rng.uniform(0.9, 1.0, N)).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L, bin_bytes=bb)
+    dbins = torch.from_numpy(bins).cuda()
+    e = oracle.grow_tree(bins, nb, g, h, bits, bits, 5, 0, L, min_data=3)
+    n = e.n_leaves
+    assert n > L // 2
+    for bound in (True, False):
+        ctx.bind_bins(dbins if bound else None)
+        t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), bits, bits, 5, 0, L, min_data_in_leaf=3, row_layout=layout)
+        _check(t, e, N)
+        assert np.allclose(t.leaf_value.cpu().numpy()[:n], e.leaf_value[:n], rtol=1e-9, atol=1e-13)
+
+
 def test_rounds_beyond_those_enqueued_up_front():
     # a tree of more rounds than the one before it: whatever is missing, at most one round too many is enqueued and the passes over
     # the leaves at most four times
