@@ -67,24 +67,40 @@ __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const q
     }
 }
 
+// A histogram's totals, which the search has noted in its pair: both sides and which is which are read together.
+struct ScanTotals {
+    int64_t sum_g, sum_h;
+};
+__device__ __forceinline__ ScanTotals load_totals(const ScanPair* sp, int side) {
+    const int a = sp->a_item;
+    const int64_t g0 = sp->stat[0].sum_g, h0 = sp->stat[0].sum_h, g1 = sp->stat[1].sum_g, h1 = sp->stat[1].sum_h;
+    return {a == side ? g0 : g1, a == side ? h0 : h1};
+}
+
+// The first four candidates of lane `sl` of a group of `sub` lanes (past the last one: that one again).
+__device__ __forceinline__ void load_candidates(const FeatCand* cand, int F, int sl, int sub, FeatCand (&c)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[u] = cand[min(sl + u * sub, F - 1)];
+}
+
 // The same reduction by a group of `sub` consecutive lanes (a power of two, 64 at most; `sl` = lane inside
-// the group), so that one wavefront serves 64 / sub leaves at a time.  The winner's candidate travels with
-// the comparison: no load depends on another.  Every lane of the group returns the winner's gain and feature
+// the group), so that one wavefront serves 64 / sub leaves at a time.  c: the group's first candidates, loaded in advance.  The
+// winner's candidate travels with the comparison: no load depends on another.  Every lane of the group returns the winner's gain and feature
 // (feature < 0: no split).  (The count estimate is left out: growth counts rows, and a 64-bit division is a long chain.)
-__device__ inline void reduce_features_lanes(const FeatCand* cand, int F, const qgbdt_leafstat& st, qgbdt_split* out,
-                                             int sl, int sub, double& gain, int& feature) {
+__device__ __forceinline__ void reduce_candidates(FeatCand (&c)[4], const FeatCand* cand, int F, const ScanTotals& st, qgbdt_split* out,
+                                                  int sl, int sub, double& gain, int& feature) {
     double bg = 0.0;
     int bf = -1, bb = -1;  // (bf: the winner's feature)
     int64_t bl = 0;
-    for (int f0 = sl; f0 < F; f0 += 4 * sub) {  // four loads in flight
-        FeatCand c[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = cand[min(f0 + u * sub, F - 1)];
+    for (int f0 = sl;;) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {  // ascending features: strict > keeps the lowest
             const int f = f0 + u * sub;
             if (f < F && c[u].bin >= 0 && (c[u].gain > bg)) { bg = c[u].gain; bf = c[u].feature; bb = c[u].bin; bl = c[u].left; }
         }
+        f0 += 4 * sub;
+        if (f0 >= F) break;
+        load_candidates(cand, F, f0, sub, c);
     }
     for (int o = sub >> 1; o > 0; o >>= 1) {
         const double og = __shfl_xor(bg, o);

@@ -176,8 +176,8 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 //     are reduced to their nodes' best splits, by groups of lanes just wide enough that one pass serves all of them, which saves the launch that
 //     would do it.
 //  1. The known nodes that are not committed and have a gain are kept sorted by it in global memory; last round's
-//     children (node ids n_known ..) are merged in.  A node's place is a count of larger keys; every wavefront counts
-//     over a sixteenth of the keys for all nodes and the counts are added up in LDS.
+//     children (node ids n_known ..) are merged in: a new one's place is what a search among the old ones finds and a count of the
+//     larger new ones.
 //  2. Best-first selection (commit the open leaf with the largest gain, its children become open leaves; stop at the
 //     first that has not been expanded) without a replay: with distinct gains a node is selected when the *worst* rank
 //     on its path from an open leaf is reached, then the worst rank behind that one, and so on -- the order of
@@ -187,7 +187,8 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 //     expanded.  Equal gains are resolved by leaf ids, which depend on the order itself: if two known nodes tie, one
 //     wavefront replays the selection split by split (a bit per open leaf at its rank, the first set bit is next;
 //     0.25 us per split).
-//  3. All threads write the outputs of the committed splits.
+//  3. The outputs of the committed splits are written beside the batch's records, at the end: both wait for their nodes then at
+//     the same time.
 //  4. The batch is chosen with popcounts over the masks: the leaf the selection stopped at, the other open leaves that are
 //     not expanded (class 0), then nodes up to n_bufs - 2 levels below expanded open leaves (class 1; a node's rows outlive the
 //     expansions of that many levels below it), by rank, if the selection can reach them with the splits that remain: a node
@@ -198,7 +199,8 @@ __device__ __forceinline__ int leaf_id_at(const uint16_t* leaf, const uint16_t* 
 //     rounds per tree 51 -> 27 (lambdarank 20 M x 200), 27 -> 15 (200 k x 136), 13 -> 11 (10.5 M x 28), 12 -> 10 (464 k x 90).
 // Measured per launch against the version that kept all nodes in the order and replayed every split: 20.6 -> 10.1 us
 // (1 M x 28, 255 leaves, 20 splits and 44 new nodes per round), 25.6 -> 11.9 us (10.5 M x 28), 24.4 -> 15.6 us
-// (20 M x 200, 511 leaves).
+// (20 M x 200, 511 leaves).  With the first candidates requested together with the state, keys merged by search, order keys computed once and
+// the outputs last: 11.3 -> 10.5 us (1 M x 28), 11.8 -> 10.9 (464 k x 90), 16.2 -> 13.6 (20 M x 200).
 __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* nodes, BatchEntry* batch, int32_t* batch_seg,
                                                          int32_t* super_counts, PlanEntry* list, int32_t* hist_counts, int F, int n_cand, int num_leaves,
                                                          int batch_max, int max_expand, int seg_rows, int seg_supers, int n_bufs, TreeReport* report, uint64_t report_seq, TreeOut out,
@@ -212,6 +214,18 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     const int4* sp = reinterpret_cast<const int4*>(step);
     const int4 st0 = sp[0], st1 = sp[1], st2 = sp[2];
     PlanEntry mine = list[min(tid, max_nodes - 1)];
+    // Histogram j's candidates are reduced by a group of lanes that holds them all in four loads each; those of the first 32 are
+    // requested before it is known how many there are (all of them: more than a compute unit reads in the time that this saves).
+    int lg = 0;
+    while (lg < 6 && (4 << lg) < n_cand) ++lg;
+    const int sl = tid & ((1 << lg) - 1), first_item = tid >> lg;
+    const bool ahead = cand != nullptr && first_item < min(32, 2 * batch_max);
+    FeatCand fc[4];
+    ScanTotals totals;
+    if (ahead) {
+        load_candidates(cand + (int64_t)first_item * n_cand, n_cand, sl, 1 << lg, fc);
+        totals = load_totals(&scan_pairs[first_item >> 1], first_item & 1);
+    }
     if (st0.x) {  // done
         if (tid == 0) report_to_host(report, report_seq, true, st1.w, st1.x, st0.w, st0.y);
         return;
@@ -235,7 +249,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     __shared__ int s_reach[64];                        // open splits by bottleneck, per 64 ranks
     __shared__ int s_nc, s_nnew, s_tie, s_stop, s_nsup;
     __shared__ unsigned long long s_wsum[16];
-    __shared__ unsigned long long s_units[8], s_first[8];  // (eight partial results: an atomic on one address is expanded into a loop over the lanes)
+    __shared__ unsigned long long s_first[8];  // (eight partial results: an atomic on one address is expanded into a loop over the lanes)
     const int n_nodes = st0.y, leaves0 = st0.z, commits0 = st0.w;
     const int n_expanded0 = st1.x, n_slots = st1.y;
     const int n_known = st2.z, n_list = st2.w, n_scan = st2.y;
@@ -249,19 +263,18 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
     }
     if (tid < 64) { s_open[tid] = 0ull; s_exp[tid] = 0ull; s_comm[tid] = 0ull; s_reach[tid] = 0; }
     if (tid == 0) { s_nc = 0; s_nnew = 0; s_tie = 0; s_stop = -1; }
-    if (tid < 8) { s_units[tid] = 0ull; s_first[tid] = ~0ull; okey[n_list + tid] = 0ull; }
+    if (tid < 8) s_first[tid] = ~0ull;
     if (tid < 4) nkey[m_new + tid] = 0ull;
     // Scanned histogram j belongs to node n_known + j: the best splits of last round's children.
     if (cand != nullptr) {
-        int lg = 6;  // log2 of the lanes that share a histogram
-        while (lg > 0 && ((1 << (lg - 1)) >= n_cand || (1024 >> lg) < n_scan)) --lg;
-        const int sl = tid & ((1 << lg) - 1);
-        for (int item = tid >> lg; item < n_scan; item += 1024 >> lg) {
+        for (int item = first_item; item < n_scan; item += 1024 >> lg) {
+            if (item != first_item || !ahead) {
+                load_candidates(cand + (int64_t)item * n_cand, n_cand, sl, 1 << lg, fc);
+                totals = load_totals(&scan_pairs[item >> 1], item & 1);
+            }
             double gain = 0.0;
             int feature = -1;
-            const ScanPair* sp = &scan_pairs[item >> 1];
-            reduce_features_lanes(cand + (int64_t)item * n_cand, n_cand, sp->stat[sp->a_item == (item & 1) ? 0 : 1],
-                                  &nodes[n_known + item].best, sl, 1 << lg, gain, feature);
+            reduce_candidates(fc, cand + (int64_t)item * n_cand, n_cand, totals, &nodes[n_known + item].best, sl, 1 << lg, gain, feature);
             if (sl == 0)
                 nkey[item] = (feature >= 0 && gain > 0.0) ? (unsigned long long)__double_as_longlong(gain) : 0ull;
         }
@@ -273,20 +286,10 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         }
     }
     lds_barrier();
-    // merge: old entries keep their order and come first among equal keys; new ones follow by node id
-    // (a wavefront's share of the keys comes in runs of 4 new and 8 old ones, whose loads are in flight together; the
-    // entries behind the ends are 0 and larger than nothing)
-    for (int p0 = 0; p0 < n_list; p0 += 64) {
-        const int p = p0 + lane;
-        const unsigned long long kb = p < n_list ? okey[p] : ~0ull;
-        int c = 0;
-        for (int u0 = 4 * wave; u0 < m_new; u0 += 64) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) c += nkey[u0 + u] > kb ? 1 : 0;
-        }
-        if (c) atomicAdd(&shift[p], c);
-    }
-    for (int t0 = 0; t0 < m_new; t0 += 64) {
+    // merge: old entries keep their order and come first among equal keys; new ones follow by node id.  A new key's place among the
+    // old ones is searched for and counted there; the running sum of these counts is what the old ones move by.
+    // (Counting the larger keys for every entry instead is a matter of LDS bandwidth: 128 new and 200 old ones 2.1 us, 170 and 300 4.5 us.)
+    for (int t0 = 0; t0 < m_new; t0 += 64) {  // among the new keys: a wavefront's share comes in runs of 4, the entries behind the end are 0
         const int t = t0 + lane;
         const unsigned long long kb = t < m_new ? nkey[t] : 0ull;
         if (kb == 0ull) continue;  // (per lane: a child without a split has no rank)
@@ -295,17 +298,30 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
 #pragma unroll
             for (int u = 0; u < 4; ++u) c += (nkey[u0 + u] > kb || (nkey[u0 + u] == kb && u0 + u < t)) ? 1 : 0;
         }
-        for (int p0 = 8 * wave; p0 < n_list; p0 += 128) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) c += okey[p0 + u] >= kb ? 1 : 0;
-        }
         if (c) atomicAdd(&shift[n_list + t], c);
-        if (wave == 0) atomicAdd(&s_nnew, 1);
+    }
+    const int half = n_list > 0 ? 1 << (31 - __clz(n_list)) : 0;
+    for (int t0 = 1024 - 64 * (wave + 1); t0 < m_new; t0 += 1024) {  // among the old ones (by the last wavefronts)
+        const int t = t0 + lane;
+        const unsigned long long kb = t < m_new ? nkey[t] : 0ull;
+        const int found = __popcll(__ballot(kb != 0ull));
+        if (lane == 0 && found) atomicAdd(&s_nnew, found);
+        if (kb == 0ull) continue;
+        int at = 0;
+        for (int d = half; d > 0; d >>= 1)
+            if (at + d <= n_list && okey[at + d - 1] >= kb) at += d;
+        if (at < n_list) { atomicAdd(&shift[at], 1); atomicAdd(&s_reach[at >> 6], 1); }
+        if (at) atomicAdd(&shift[n_list + t], at);
     }
     lds_barrier();
-    for (int p = tid; p < n_list; p += 1024) {
+    const int moved = wave_prefix(s_reach[lane]) - s_reach[lane];  // new keys in front of every 64 old ones
+    const int P = n_list + s_nnew;  // ranks in use
+    for (int p0 = wave * 64; p0 < n_list; p0 += 1024) {
+        const int p = p0 + lane;
+        const int by = __builtin_amdgcn_readlane(moved, p0 >> 6) + wave_prefix(p < n_list ? shift[p] : 0);
+        if (p >= n_list) continue;
         const uint32_t id = oids[p];
-        const int q = p + shift[p];
+        const int q = p + by;
         key[q] = okey[p]; ids[q] = id; leaf[q] = oleaf[p];
         rank_of[id & NODE_ID] = (uint16_t)q;
     }
@@ -319,7 +335,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         rank_of[n_known + t] = (uint16_t)q;
     }
     lds_barrier();
-    const int P = n_list + s_nnew;  // ranks in use
+    if (tid < 64) s_reach[tid] = 0;
     // of every rank: the ranks of both children (info), expanded, tie with the next rank; of the children: their parent
     unsigned long long* const info = okey;
     uint16_t* const corder = oleaf;
@@ -351,9 +367,11 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
                 if (q > top) { k = (k >> 12) | ((unsigned long long)(q + 1) << 48); top = q; }
             return k;
         };
-        for (int p0 = wave * 64; p0 < P; p0 += 1024) {
-            const int p = p0 + lane;
-            if (p < P && !((info[p] >> 32) & 1ull)) atomicMin(&s_first[lane & 7], order_key(p));
+        unsigned long long mine_key = 0ull;  // of the thread's first rank
+        for (int p = tid; p < P; p += 1024) {
+            const unsigned long long k = order_key(p);
+            if (p < 1024) mine_key = k;
+            if (!((info[p] >> 32) & 1ull)) atomicMin(&s_first[lane & 7], k);
         }
         lds_barrier();
         unsigned long long first = s_first[0];
@@ -361,7 +379,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         for (int u = 1; u < 8; ++u) first = min(first, s_first[u]);
         for (int p = tid; p < P; p += 1024) {
             if (!((info[p] >> 32) & 1ull)) continue;
-            const unsigned long long k = order_key(p);
+            const unsigned long long k = p < 1024 ? mine_key : order_key(p);
             if (k < first) ckey[atomicAdd(&s_nc, 1)] = k;
         }
         lds_barrier();
@@ -440,33 +458,36 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         const unsigned long long mo = __ballot(open), me = __ballot(expanded), mc = __ballot(committed);
         if (lane == 0) { s_open[p0 >> 6] = mo; s_exp[p0 >> 6] = me; s_comm[p0 >> 6] = mc; }
     }
-    // outputs and node states of the splits committed above
-    for (int c = tid; c < n_commit; c += 1024) {
-        const int r = commit[c], lid = leaf_id_at(leaf, par, info, corder, leaves0, r), k = commits0 + c;
-        const int i = (int)(ids[r] & NODE_ID), ch = (int)(ids[r] >> 16);
-        const Node nd = nodes[i];
-        out.t.split_leaf[k] = lid; out.t.split_feature[k] = nd.best.feature; out.t.split_bin[k] = nd.best.bin;
-        out.t.split_gain[k] = nd.best.gain;
-        out.t.split_stats[4 * k + 0] = nd.best.left_g; out.t.split_stats[4 * k + 1] = nd.best.left_h;
-        out.t.split_stats[4 * k + 2] = nd.best.right_g; out.t.split_stats[4 * k + 3] = nd.best.right_h;
-        out.t.split_n_left[k] = nd.n_left;
-        const int64_t nl = nd.n_left, nr = nd.count - nd.n_left;
-        atomicAdd(&s_units[lane & 7], (unsigned long long)((nl <= nr ? nl : nr) * (int64_t)F));
-        // a child that has itself been committed in this call is internal; its own iteration says so
-        const int q0 = rank_of[ch], q1 = rank_of[ch + 1];
-        if (q0 == (int)NO_NODE || corder[q0] == NO_NODE) { nodes[ch].state = 1; nodes[ch].leaf_id = lid; }
-        if (q1 == (int)NO_NODE || corder[q1] == NO_NODE) { nodes[ch + 1].state = 1; nodes[ch + 1].leaf_id = leaves0 + c; }
-        nodes[i].state = 2;
-    }
+    // Outputs and node states of the splits committed above: behind the choice of the batch, which does not wait for the nodes then, and
+    // by the last threads, beside the batch's records.
+    auto put_commits = [&]() {
+        unsigned long long units = 0ull;
+        for (int c = 1023 - tid; c < n_commit; c += 1024) {
+            const int r = commit[c], lid = leaf_id_at(leaf, par, info, corder, leaves0, r), k = commits0 + c;
+            const int i = (int)(ids[r] & NODE_ID), ch = (int)(ids[r] >> 16);
+            const Node nd = nodes[i];
+            out.t.split_leaf[k] = lid; out.t.split_feature[k] = nd.best.feature; out.t.split_bin[k] = nd.best.bin;
+            out.t.split_gain[k] = nd.best.gain;
+            out.t.split_stats[4 * k + 0] = nd.best.left_g; out.t.split_stats[4 * k + 1] = nd.best.left_h;
+            out.t.split_stats[4 * k + 2] = nd.best.right_g; out.t.split_stats[4 * k + 3] = nd.best.right_h;
+            out.t.split_n_left[k] = nd.n_left;
+            const int64_t nl = nd.n_left, nr = nd.count - nd.n_left;
+            units += (unsigned long long)((nl <= nr ? nl : nr) * (int64_t)F);
+            // a child that has itself been committed in this call is internal; its own iteration says so
+            const int q0 = rank_of[ch], q1 = rank_of[ch + 1];
+            if (q0 == (int)NO_NODE || corder[q0] == NO_NODE) { nodes[ch].state = 1; nodes[ch].leaf_id = lid; }
+            if (q1 == (int)NO_NODE || corder[q1] == NO_NODE) { nodes[ch + 1].state = 1; nodes[ch + 1].leaf_id = leaves0 + c; }
+            nodes[i].state = 2;
+        }
+        if (1023 - 64 * wave - 63 < n_commit) {  // (the wavefront has splits)
+            for (int o = 32; o > 0; o >>= 1) units += __shfl_xor(units, o);
+        }
+        if (lane == 0 && units) atomicAdd(reinterpret_cast<unsigned long long*>(&step->hist_units), units);
+        if (tid == 0) { step->n_commits = commits0 + n_commit; step->n_leaves = leaves0 + n_commit; step->n_known = n_nodes; }
+    };
     lds_barrier();
-    if (tid == 0) {
-        unsigned long long units = s_units[0];
-#pragma unroll
-        for (int u = 1; u < 8; ++u) units += s_units[u];
-        step->hist_units += (int64_t)units;
-        step->n_commits = commits0 + n_commit; step->n_leaves = leaves0 + n_commit; step->n_known = n_nodes;
-    }
     if (done) {
+        put_commits();
         if (tid == 0) {
             step->done = 1; step->n_batch = 0; step->n_part_items = 0; step->n_scan_items = 0;
             hist_counts[0] = 0; hist_counts[1] = 0; hist_counts[2] = 0;
@@ -533,6 +554,7 @@ __global__ __launch_bounds__(1024) void tree_plan_kernel(StepState* step, Node* 
         }
     }
     lds_barrier();
+    put_commits();
     // the batch's records: segments of the batched partition, new histogram slots, child ids
     BatchEntry be;
     be.n_seg = 0;
