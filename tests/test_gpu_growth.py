@@ -138,6 +138,25 @@ def test_histogram_launches_that_count(N, F, nb, bb, L, bits, layout):
         assert np.allclose(t.leaf_value.cpu().numpy()[:n], e.leaf_value[:n], rtol=1e-9, atol=1e-13)
 
 
+# Trees beyond those whose histogram launches count: the counting pass in the order of the XCDs, in one step and in eight, with fewer and
+# more than 64 nodes in a round, sorted rows (a node's rows in one place of the matrix), and gathered builds of few and many row groups
+@pytest.mark.parametrize("N,F,nb,bb,L,bound", [(2_600_001, 16, 32, 1, 300, True), (1_100_003, 40, 600, 2, 63, False), (6_000_003, 5, 32, 1, 31, True)])
+def test_large_trees_of_row_lists(N, F, nb, bb, L, bound):
+    rng = np.random.default_rng(N + F)
+    bins = rng.integers(0, nb, (N, F), dtype=np.uint16 if bb == 2 else np.uint8)
+    bins[:, 0] = np.arange(N, dtype=np.int64) * nb // N
+    x = bins[:, :4].astype(np.float32) / nb - 0.5
+    g = (3 * x[:, 0] + 2 * x[:, 1] * x[:, 2] + x[:, 0] * x[:, 3] + 0.2 * rng.normal(size=N)).astype(np.float32)
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    ctx = Context(N, F, nb, max_leaves=L, bin_bytes=bb)
+    dbins = torch.from_numpy(bins).cuda()
+    e = oracle.grow_tree(bins, nb, g, h, 3, 3, 5, 0, L, min_data=20)
+    ctx.bind_bins(dbins if bound else None)
+    t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 3, 3, 5, 0, L, min_data_in_leaf=20, row_layout=0 if bound else 1)
+    _check(t, e, N)
+
+
 def test_rounds_beyond_those_enqueued_up_front():
     # a tree of more rounds than the one before it: whatever is missing, at most one round too many is enqueued and the passes over
     # the leaves at most four times

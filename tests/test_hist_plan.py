@@ -362,3 +362,90 @@ def test_small_trees_with_long_row_groups_need_no_reduction():
             p = describe_hist_plan(N, F, 255, 31, 1, bits, bits)
             small = N * p["n_tiles"] <= (2 ** 17 if p["n_tiles"] > 1 else 2 ** 14)
             assert p["search_sums"] == (2 ** 31 - 1 if small else 8), (N, F, bits)
+
+
+# Gathered builds: the row groups that an XCD holds of a build share one stretch of its list and take its blocks in turn.  Every row
+# once, no group more than a chunk, an XCD's stretches in the order of the XCDs.
+@pytest.mark.parametrize("count,groups,item_start,block,chunk", [
+    (100_000, 37, 5, 256, 10_000), (100_000, 8, 0, 256, 100_000), (5000, 3, 7, 320, 4681), (257, 2, 6, 256, 600), (1, 1, 3, 512, 1000),
+    (20_000, 64, 1, 144, 4000), (1_000_003, 97, 250, 256, 10_922), (9000, 40, 2, 512, 1000)])
+def test_row_groups_of_gathered_builds_cover_the_list(count, groups, item_start, block, chunk):
+    rows_per_group = -(-count // groups)
+    assert rows_per_group + block <= chunk
+    seen = np.zeros(count, np.int64)
+    begins = {}
+    for item in range(item_start, item_start + groups):
+        first = n = own = 0
+        x = item & 7
+        for y in range(x + 1):
+            g = (y - item_start) & 7
+            k = (groups - g + 7) >> 3 if groups > g else 0
+            if y < x:
+                first += k
+            else:
+                n, own = k, (item - item_start - g) >> 3
+        assert 0 <= own < n
+        begin = min(count, first * rows_per_group)
+        end = min(count, begin + n * rows_per_group)
+        begins.setdefault(x, begin)
+        assert begins[x] == begin
+        mine = 0
+        for b in range(begin + own * block, end, n * block):
+            seen[b:min(end, b + block)] += 1
+            mine += min(end, b + block) - b
+        assert mine <= chunk
+    assert (seen == 1).all()
+    assert [begins[x] for x in sorted(begins)] == sorted(begins.values())
+
+
+# Order of the counting pass: every XCD goes through its eighth of all nodes side by side.  Every segment once, whatever the nodes' sizes.
+@pytest.mark.parametrize("shift", [3, 5, 6])
+@pytest.mark.parametrize("n_nodes,grid", [(1, 520), (3, 1024), (64, 2048), (65, 2048), (200, 1032)])
+def test_counting_pass_takes_every_segment_once(n_nodes, grid, shift):
+    rng = np.random.default_rng(n_nodes + shift)
+    n = rng.integers(1, 3 * 1024 // n_nodes + 2, n_nodes)
+    n[rng.integers(0, n_nodes)] += 700
+    start = np.concatenate([[0], np.cumsum(n)[:-1]])
+    seen = np.zeros(int(n.sum()), np.int64)
+    for wg in range(grid):
+        part, end = (wg & 7) << (shift - 3), ((wg & 7) + 1) << (shift - 3)
+        in_front = lambda q: int(((n * q) >> shift).sum())  # noqa: E731
+        first, nxt = in_front(part), in_front(part + 1)
+        origin, at, done = first, wg, False
+        while not done:
+            want = origin + (at >> 3)
+            while want >= nxt and not done:
+                part += 1
+                done = part == end
+                if not done:
+                    first, nxt = nxt, in_front(part + 1)
+            if not done:
+                lo, hi = (n * part) >> shift, (n * (part + 1)) >> shift
+                incl = np.cumsum(hi - lo)
+                node = int((incl <= want - first).sum())
+                seen[start[node] + lo[node] + want - first - (incl[node] - (hi - lo)[node])] += 1
+                at += grid
+    assert (seen == 1).all()
+
+
+# Launches that count the left rows themselves: items of one chunk, as many as the table has room for.
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
+def test_items_of_launches_that_count(shape):
+    N, F, nb, L, bb = shape
+    seg_rows = 2048 if N > 1 << 18 else 512
+    for key, p in _plans(shape):
+        lanes = 256 // p["n_tiles"] // 8 * 8 if 256 // p["n_tiles"] >= 16 else 8
+        most = p["single_rows"] // seg_rows
+        if N * p["n_tiles"] > 4_000_000 or most < 1:
+            continue
+        max_seg = N // seg_rows + L + 2
+        if not (max_seg // most + L + 1 <= p["max_items"] and lanes // 2 + 1 + L <= p["max_items"] and lanes + 1 <= p["max_items"]):
+            continue
+        rng = np.random.default_rng(N)
+        for n_nodes in {1, 2, min(L, 17), L}:
+            for total in {n_nodes, max(n_nodes, N // seg_rows // 3), max(n_nodes, N // seg_rows + n_nodes - 1)}:
+                segs = rng.multinomial(total - n_nodes, np.ones(n_nodes) / n_nodes) + 1
+                places = max(lanes - (n_nodes - 1), (lanes + 1) // 2)
+                k = max(min(max(-(-total // places), -(-1024 // seg_rows)), most), 1)
+                assert k * seg_rows <= p["single_rows"], key
+                assert (-(-segs // k)).sum() <= p["max_items"], (key, n_nodes, total)
