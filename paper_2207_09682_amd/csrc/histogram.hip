@@ -98,6 +98,25 @@ __device__ __forceinline__ void tile_and_lane(int n_tiles, int& tile, int& glane
     glane = (s / n_tiles) * 8 + xcd;
 }
 
+// Where a gathered build's row groups lie in its list.  A list ascends, so position in the list is position in the matrix, and lines
+// that hold rows of several builds (or of a build's neighbouring rows) are fetched once if the builds pass them on one XCD at about
+// the same time: the groups that an XCD holds of a build (work items go round-robin to the XCDs) share one stretch of the list, the n-th of
+// the XCD number, and take its blocks of rows in turn.  Rows of one or two lines (hist_piece_kernel): per launch against groups of consecutive
+// rows 10.5 M x 28 63.7 -> 58.5 us, 2 M x 40 of 16-bit bins 26.9 -> 26.6; rows of many lines share none (20 M x 200 157.6 / 158.8, 400 k x 2000 66.7 / 67.8:
+// hist_wide_kernel keeps consecutive rows).
+struct GroupPlace {
+    int first, n, own;  // groups of the XCDs in front, groups of this XCD, which of them this one is
+};
+__device__ __forceinline__ GroupPlace group_place(int item_start, int groups, int item) {
+    GroupPlace p = {0, 0, 0};
+    const int x = item & 7;
+    for (int y = 0; y <= x; ++y) {
+        const int g = (y - item_start) & 7, n = groups > g ? (groups - g + 7) >> 3 : 0;
+        if (y < x) p.first += n; else { p.n = n; p.own = (item - item_start - g) >> 3; }
+    }
+    return p;
+}
+
 // Merge of the local bins into the total histogram and reset of the local bins.
 // Both are [bin][feature], so LDS is walked linearly (no bank conflicts) and the
 // atomics of a wavefront fall into consecutive words.
@@ -542,19 +561,19 @@ __global__ __launch_bounds__(IDX == 3 ? COUNT_THREADS : HIST_THREADS, HIST_WAVES
 
     // rows of the list or slice that row_at and load_gh read; three stages in flight as in hist_kernel; rows past the end read the
     // last one again and add zero
-    auto accumulate = [&](const uint8_t* colbase, int crow, auto row_at, auto load_gh) {
-        if (wave * rpi >= crow) return;
+    // (of them a block of n_waves * rpi rows out of every `step_rows`, the first one at `first`)
+    auto accumulate = [&](const uint8_t* colbase, int crow, int first, int step_rows, auto row_at, auto load_gh) {
+        if (first + wave * rpi >= crow) return;
         auto load_row = [&](int64_t row) {
             uint4 v;
             __builtin_memcpy(&v, colbase + (IDX == 2 ? row & src.code.id_mask : row) * row_bytes, 16);
             return v;
         };
-        const int step_rows = n_waves * rpi;
-        int p = wave * rpi + r;
+        int p = first + wave * rpi + r;
         int64_t row = row_at(p), rown = row_at(p + step_rows);
         uint4 d = load_row(row);
         int gv = load_gh(p, row);
-        for (int ro = wave * rpi; ro < crow; ro += step_rows, p += step_rows) {
+        for (int ro = first + wave * rpi; ro < crow; ro += step_rows, p += step_rows) {
             const uint4 dn = load_row(rown);
             const int gn = load_gh(p + step_rows, rown);
             rown = row_at(p + 2 * step_rows);
@@ -598,7 +617,7 @@ __global__ __launch_bounds__(IDX == 3 ? COUNT_THREADS : HIST_THREADS, HIST_WAVES
                 const int crow = s_n[turn];
                 if (tile == 0) rs.write_counts(cs, nd, r0, n, s_seg);
                 if (ahead > 0) rs.load_bins(src, cs, nd, ahead, wave, F, BB);
-                accumulate(colbase, crow, [&](int p) { return (int64_t)s_row[min(p, crow - 1)]; }, [&](int p, int64_t) { return (int)s_gh[min(p, crow - 1)]; });
+                accumulate(colbase, crow, 0, n_waves * rpi, [&](int p) { return (int64_t)s_row[min(p, crow - 1)]; }, [&](int p, int64_t) { return (int)s_gh[min(p, crow - 1)]; });
             }
             __syncthreads();
             store_partial<W>(lds, plan.lds_bytes, slot);
@@ -616,6 +635,18 @@ __global__ __launch_bounds__(IDX == 3 ? COUNT_THREADS : HIST_THREADS, HIST_WAVES
         const bool gpos = IDX && src.gh_pos != 0;  // packed gradients in list order
         const int16_t* gh = gpos ? src.gh[en.buf] + en.begin : src.gh[sb];
 
+        if (IDX != 0 && rows_per_group + n_waves * rpi <= plan.chunk_rows) {  // (a group takes a block more than its share at most: one chunk)
+            const GroupPlace at_ = group_place(en.item_start, en.groups, item);
+            const int64_t pbegin = min(en.count, at_.first * rows_per_group), pend = min(en.count, pbegin + at_.n * rows_per_group);
+            const int crow = (int)(pend - pbegin);
+            const int32_t* ib = idx + pbegin;
+            __syncthreads();
+            accumulate(colbase, crow, at_.own * n_waves * rpi, at_.n * n_waves * rpi, [&](int p) { return (int64_t)(uint32_t)ib[min(p, crow - 1)]; },
+                       [&](int p, int64_t row) { return IDX == 2 ? src.code.gh((uint32_t)row) : (int)gh[gpos ? pbegin + min(p, crow - 1) : row]; });
+            __syncthreads();
+            store_partial<W>(lds, plan.lds_bytes, slot);
+            continue;
+        }
         // a group without rows still hands over its (empty) bins
         for (int64_t cbegin = gbegin; cbegin < gend || cbegin == gbegin; cbegin += plan.chunk_rows) {
             const int64_t cend = min(gend, cbegin + (int64_t)plan.chunk_rows);
@@ -623,7 +654,7 @@ __global__ __launch_bounds__(IDX == 3 ? COUNT_THREADS : HIST_THREADS, HIST_WAVES
             __syncthreads();
             const int32_t* ib = IDX ? idx + cbegin : nullptr;
             const int64_t row_base = IDX ? 0 : en.begin + cbegin;
-            accumulate(colbase, crow, [&](int p) { return IDX ? (int64_t)(uint32_t)ib[min(p, crow - 1)] : row_base + min(p, crow - 1); },
+            accumulate(colbase, crow, 0, n_waves * rpi, [&](int p) { return IDX ? (int64_t)(uint32_t)ib[min(p, crow - 1)] : row_base + min(p, crow - 1); },
                        [&](int p, int64_t row) { return IDX == 2 ? src.code.gh((uint32_t)row) : (int)gh[gpos ? cbegin + min(p, crow - 1) : row]; });
             __syncthreads();
             if (cend >= gend) store_partial<W>(lds, plan.lds_bytes, slot);
@@ -729,31 +760,32 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
     // rows of the list or slice that row_at and load_gh read.  Three stages in flight: row ids of block n+2, bin pieces and packed
     // gradients of block n+1, LDS atomics of block n; rows past the end re-read the last row and add zero
     auto accumulate = [&](const uint8_t* colbase, int crow, auto row_at, auto load_gh) {
+        const int first = wave * S, step_rows = n_waves * S;
         auto row_id = [&](int64_t e) { return IDX == 2 ? e & src.code.id_mask : e; };
-        if (wave * S >= crow) return;
+        if (first >= crow) return;
         int64_t rown[U];
         vec d[U], dn[U];
         int gv[U], gn[U];
         {
             int64_t rows[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) rows[u] = row_at(min(wave * S + u * rpi + r, crow - 1));
+            for (int u = 0; u < U; ++u) rows[u] = row_at(min(first + u * rpi + r, crow - 1));
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 d[u] = *reinterpret_cast<const vec*>(colbase + row_id(rows[u]) * F);
-                gv[u] = load_gh(min(wave * S + u * rpi + r, crow - 1), rows[u]);
+                gv[u] = load_gh(min(first + u * rpi + r, crow - 1), rows[u]);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) rown[u] = row_at(min((wave + n_waves) * S + u * rpi + r, crow - 1));
+            for (int u = 0; u < U; ++u) rown[u] = row_at(min(first + step_rows + u * rpi + r, crow - 1));
         }
-        for (int ro = wave * S; ro < crow; ro += n_waves * S) {
+        for (int ro = first; ro < crow; ro += step_rows) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 dn[u] = *reinterpret_cast<const vec*>(colbase + row_id(rown[u]) * F);
-                gn[u] = load_gh(min(ro + n_waves * S + u * rpi + r, crow - 1), rown[u]);
+                gn[u] = load_gh(min(ro + step_rows + u * rpi + r, crow - 1), rown[u]);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) rown[u] = row_at(min(ro + 2 * n_waves * S + u * rpi + r, crow - 1));
+            for (int u = 0; u < U; ++u) rown[u] = row_at(min(ro + 2 * step_rows + u * rpi + r, crow - 1));
             if (lane_on) {  // lanes beyond the tile's width sit out (their loads alias piece 0)
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
