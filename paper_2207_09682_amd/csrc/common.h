@@ -376,12 +376,20 @@ __device__ __forceinline__ int find_start(const int* starts, int n, int at) {
     return c - 1;
 }
 
+constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
 // Totals of the quantizer's workgroups (sum g~, sum h~, sum |g~|), by a workgroup of 256 threads; every thread gets them.
 __device__ __forceinline__ void sum_totals(const int64_t* __restrict__ part, int n_part, int64_t (&s)[3]) {
     __shared__ int64_t t[3][4];
     s[0] = s[1] = s[2] = 0;
-    for (int i = threadIdx.x; i < n_part; i += 256)
-        for (int k = 0; k < 3; ++k) s[k] += part[3 * i + k];
+    for (int i0 = 0; i0 < n_part; i0 += 4 * 256) {  // (four in flight)
+        int64_t v[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (int k = 0; k < 3; ++k) v[u][k] = part[3 * min(i0 + 256 * u + (int)threadIdx.x, n_part - 1) + k];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (int k = 0; k < 3; ++k) s[k] += i0 + 256 * u + (int)threadIdx.x < n_part ? v[u][k] : 0;
+    }
     for (int k = 0; k < 3; ++k) {
         for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_xor(s[k], o);
         if ((threadIdx.x & 63) == 0) t[k][threadIdx.x >> 6] = s[k];
@@ -408,7 +416,6 @@ inline int refit_extra(int64_t n_rows) {  // about 512 rows per unit where a lea
     const int64_t x = n_rows / ((int64_t)refit_parts(n_rows) * 512);
     return x > REFIT_EXTRA ? REFIT_EXTRA : (int)x;
 }
-constexpr int QUANT_PARTS = 2048;  // most workgroups of the quantizer kernels
 // Rows per thread of a segment of the batched partition (256 threads; the loads of a thread's rows are in flight
 // together), and whether the left rows of PART_SUPER segments are summed up in one counter on the way.
 //  - Up to 2^18 rows 2 rows per thread: segments of 2048 rows would leave most compute units without one (count + scatter

@@ -7,12 +7,13 @@ namespace qgbdt {
 
 // Philox-4x32-10 (Salmon et al., SC'11): 10 rounds of two 32x32->64 multiplies
 // with the Weyl key schedule.  key = seed, counter = (row lo, row hi, iteration, 0).
+// (One multiplication of 64 bits each, not one for either half: with the maxima read at once 10.5 M rows 47.0 -> 42.5 us, 2.5 M 21.7 -> 18.4.)
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t& o0, uint32_t& o1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0, hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
         const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
         c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
@@ -74,10 +75,13 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ g
 // Maxima over the partial maxima of absmax_kernel, by every thread of a 256-thread workgroup.
 __device__ __forceinline__ void reduce_absmax(const float* __restrict__ part, int n_part, float& mg, float& mh) {
     mg = 0.0f; mh = 0.0f;
-    for (int i = threadIdx.x; i < n_part; i += blockDim.x) {
-        mg = fmaxf(mg, part[2 * i]);
-        mh = fmaxf(mh, part[2 * i + 1]);
-    }
+    const float2* const pairs = reinterpret_cast<const float2*>(part);
+    float2 v[QUANT_PARTS / 256];  // all of them in flight together (past the end: the last one again, or nothing)
+#pragma unroll
+    for (int u = 0; u < QUANT_PARTS / 256; ++u)
+        v[u] = 256 * u < n_part ? pairs[min((int)threadIdx.x + 256 * u, n_part - 1)] : make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int u = 0; u < QUANT_PARTS / 256; ++u) { mg = fmaxf(mg, v[u].x); mh = fmaxf(mh, v[u].y); }
     for (int o = 32; o > 0; o >>= 1) {
         mg = fmaxf(mg, __shfl_xor(mg, o));
         mh = fmaxf(mh, __shfl_xor(mh, o));
