@@ -48,7 +48,10 @@ extern "C" {
 #define QGBDT_E_WORKSPACE (-6) /* no workspace set, the block is too small, or it lacks the section a call needs */
 
 /* Optional sections of the workspace (qgbdt_workspace_bytes / qgbdt_set_workspace). */
-#define QGBDT_WS_BIND 1u       /* feature-major copy of a bound matrix: qgbdt_bind_bins (n_rows * n_features * bin_bytes) */
+#define QGBDT_WS_BIND 1u       /* feature-major copy of a bound matrix: qgbdt_bind_bins (n_rows * n_features * bin_bytes); for large matrices
+                                  (256 MB and more) of 72 to 248 uint8 features, 8 more than a multiple of 16, also a copy whose rows
+                                  begin on cache lines, where that takes at most 30 % more (n_rows * n_features rounded up to 128; a
+                                  block without room for it is accepted and does without) */
 #define QGBDT_WS_ROW_COPIES 2u /* three leaf-ordered copies of the bin rows: row_layout QGBDT_ROWS_ORDERED, and what
                                   QGBDT_ROWS_AUTO takes for a large unbound matrix of up to 32 uint8 features (16..64
                                   uint8 features, a multiple of 4; ignored for other shapes; 3 * n_rows * n_features) */
@@ -167,7 +170,8 @@ QGBDT_API const char* qgbdt_last_error(const qgbdt_ctx* ctx);
  * (in the QGBDT_WS_BIND section of the workspace; QGBDT_E_WORKSPACE without it).  The counting pass of
  * the row partition then reads the split feature's column -- the ascending row ids of a node fall into
  * few memory sectors -- instead of one sector of the row-major matrix per row, and narrow matrices, whose
- * rows are otherwise moved into leaf order level by level, are left in place.  The call also samples the
+ * rows are otherwise moved into leaf order level by level, are left in place.  Where the workspace holds a copy
+ * whose rows begin on cache lines, the histogram builds of trees read that one.  The call also samples the
  * columns for each feature's most frequent bin; when most features have a bin that holds most of their rows,
  * the wide-row histogram kernels leave that bin out and the entry is rebuilt from the totals.  Results do not
  * change.

@@ -128,7 +128,7 @@ static bool shape_allows_ordered(const qgbdt_shape& s) {
     return s.bin_bytes == 1 && s.n_features % 4 == 0 && s.n_features >= 16 && s.n_features <= 64;
 }
 
-static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
+static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags, bool padded) {
     Carver k{static_cast<unsigned char*>(base), 0};
     const qgbdt_shape& sh = c->shape;
     const size_t N = (size_t)sh.n_rows, F = (size_t)sh.n_features;
@@ -172,6 +172,8 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags) {
         k.take(&c->bins_t, N * F * (size_t)sh.bin_bytes);
         k.take(&c->mfb, F);
     } else if (base) { c->bins_t = nullptr; c->mfb = nullptr; }
+    if ((flags & QGBDT_WS_BIND) && padded && padded_pitch(sh) > 0) k.take(&c->bins_p, N * (size_t)padded_pitch(sh));
+    else if (base) c->bins_p = nullptr;
     if ((flags & QGBDT_WS_ROW_COPIES) && shape_allows_ordered(sh)) {
         for (int b = 0; b < COPY_BUFS; ++b) k.take(&c->obins[b], N * F);
     } else if (base) { for (int b = 0; b < COPY_BUFS; ++b) c->obins[b] = nullptr; }
@@ -333,7 +335,7 @@ int qgbdt_workspace_bytes(const qgbdt_shape* shape, uint32_t flags, size_t* byte
     memset(&tmp, 0, sizeof(tmp));
     tmp.shape = *shape;
     derive_sizes(&tmp);
-    *bytes = carve_workspace(&tmp, nullptr, flags);
+    *bytes = carve_workspace(&tmp, nullptr, flags, true);
     return QGBDT_OK;
 }
 
@@ -351,14 +353,19 @@ int qgbdt_set_workspace(qgbdt_ctx* ctx, void* dev, size_t bytes, uint32_t flags)
     if (!dev) return QGBDT_OK;  // detached: every step refuses until a block is set again
     if (((uintptr_t)dev & 255) != 0) return set_error(ctx, QGBDT_E_INVALID_ARG, "the workspace must be 256-byte aligned");
     size_t need = 0;
+    bool padded = true;  // (a block that has no room for the padded copy of wide rows will do without it)
     {
         qgbdt_ctx tmp = *ctx;
-        need = carve_workspace(&tmp, nullptr, flags);
+        need = carve_workspace(&tmp, nullptr, flags, true);
+        if (bytes < need) {
+            padded = false;
+            need = carve_workspace(&tmp, nullptr, flags, false);
+        }
     }
     if (bytes < need)
         return set_error(ctx, QGBDT_E_WORKSPACE, "workspace of %zu bytes is too small: this shape with flags 0x%x needs %zu",
                          bytes, flags, need);
-    carve_workspace(ctx, dev, flags);
+    carve_workspace(ctx, dev, flags, padded);
     ctx->ws_base = dev;
     ctx->ws_bytes = need;
     ctx->ws_flags = flags;
@@ -418,6 +425,7 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
     if (rc != QGBDT_OK) return rc;
     RowSource rows;
     rows.gh_pos = 0;  // the caller's packed gradients are in original row order
+    rows.pitch = ctx->shape.n_features * ctx->shape.bin_bytes;
     IdxSet idx;
     for (int b = 0; b <= ROW_BUFS; ++b) { rows.bins[b] = (const uint8_t*)bins; rows.gh[b] = gh; idx.p[b] = const_cast<int32_t*>(row_idx); }
     rows.code = PLAIN_ROWS;
@@ -441,6 +449,7 @@ int qgbdt_bind_bins(qgbdt_ctx* ctx, const void* bins) {
     if (!ctx->bins_t)
         return set_error(ctx, QGBDT_E_WORKSPACE, "the workspace has no room for the copy of a bound matrix (set it with QGBDT_WS_BIND)");
     int rc = launch_transpose_bins(ctx, bins, ctx->bins_t);
+    if (rc == QGBDT_OK && ctx->bins_p) rc = launch_pad_bins(ctx, bins, ctx->bins_p, padded_pitch(ctx->shape));
     if (rc != QGBDT_OK) return rc;
     // Most frequent bins (left out by the wide-row histogram kernels); the host learns how many features have one.
     // Only those kernels can use them, so narrow matrices skip the sampling.

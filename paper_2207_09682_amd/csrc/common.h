@@ -107,6 +107,17 @@ struct HistEntry {
     int32_t groups;
 };
 
+// Pitch of the copy of a bound matrix that the gathered builds of a tree read 8 bytes at a time (hist_wide_kernel; 0: none): whole cache
+// lines.  These builds are bound by the requests of 64 bytes, and the lines behind them, that a CU can have outstanding: a 32-byte piece
+// of a row of 200 bytes takes 1.375 requests, the row 2.5 lines instead of 2.  Where that costs at most 30 % more bytes per row, and the matrix is
+// larger than what the caches hold.  Trees without / with: 20 M x 200 9864 / 9367 us, 8 M x 232 3999 / 3714, 4 M x 200 2280 / 2154, 3 M x 120 1277 / 1158, 2 M x 200
+// 1470 / 1414, 1.5 M x 104 (156 MB) 742 / 747.  (Contiguous rows, and 16-byte pieces, whose rows are longer, gain nothing: one build of 20 M x 200 1425 / 1390 us, 400 k x
+// 2000 at a pitch of 2048 185 / 212 us, gathered 67 / 68.)
+inline int padded_pitch(const qgbdt_shape& s) {
+    const int F = s.n_features, pitch = (F + 127) / 128 * 128;
+    return s.bin_bytes == 1 && F > 64 && F < 256 && F % 16 == 8 && 10 * pitch <= 13 * F && s.n_rows * F >= (int64_t)256 << 20 ? pitch : 0;
+}
+
 // Work descriptor of one stand-alone row partition.
 struct PartWork {
     int64_t begin, count;
@@ -236,6 +247,7 @@ struct RowSource {
     const uint8_t* bins[ROW_BUFS + 1];
     const int16_t* gh[ROW_BUFS + 1];
     int32_t gh_pos;
+    int32_t pitch;  // bytes from a row to the next; more than a row's own: the padded copy of a bound matrix (padded_pitch)
     RowCode code;
 };
 // A histogram launch over the rows of a round's nodes that finds out itself which of them go to the child that it builds, and leaves
@@ -290,6 +302,7 @@ struct qgbdt_ctx {
     int16_t* ogh[qgbdt::ROW_BUFS];     // [N] each: packed gradients in the order of idx[b]
     int32_t* idx[qgbdt::ROW_BUFS];     // [N] each
     uint8_t* bins_t;       // [F][N] feature-major copy of the bound bin matrix (QGBDT_WS_BIND, filled by qgbdt_bind_bins), else null
+    uint8_t* bins_p;       // [N][padded_pitch] copy of the bound matrix (wide rows; QGBDT_WS_BIND), else null
     uint16_t* mfb;         // [F] most frequent bin of each feature of the bound matrix when it holds most rows, else 0xffff
     int mfb_features;      // features with such a bin (0: no skipping)
     const void* bound_bins; // the matrix that copy was made from
@@ -493,6 +506,7 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
                        int feature, int bin, int64_t* n_left_out);
 int launch_batch_partition_count(qgbdt_ctx* ctx, const RowSource& rows, const uint8_t* bins_t, bool ordered);
 int launch_transpose_bins(qgbdt_ctx* ctx, const void* bins, void* out);
+int launch_pad_bins(qgbdt_ctx* ctx, const void* bins, uint8_t* out, int pitch);
 int launch_frequent_bins(qgbdt_ctx* ctx, const void* bins_t, uint16_t* mfb);
 int launch_fix_frequent_bins(qgbdt_ctx* ctx, int64_t* hist, const int64_t* totals, const uint16_t* mfb);
 int require_workspace(qgbdt_ctx* ctx);   // QGBDT_E_WORKSPACE unless a workspace block is set

@@ -774,7 +774,7 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
             for (int u = 0; u < U; ++u) rows[u] = row_at(min(first + u * rpi + r, crow - 1));
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                d[u] = *reinterpret_cast<const vec*>(colbase + row_id(rows[u]) * F);
+                d[u] = *reinterpret_cast<const vec*>(colbase + row_id(rows[u]) * src.pitch);
                 gv[u] = load_gh(min(first + u * rpi + r, crow - 1), rows[u]);
             }
 #pragma unroll
@@ -783,7 +783,7 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
         for (int ro = first; ro < crow; ro += step_rows) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                dn[u] = *reinterpret_cast<const vec*>(colbase + row_id(rown[u]) * F);
+                dn[u] = *reinterpret_cast<const vec*>(colbase + row_id(rown[u]) * src.pitch);
                 gn[u] = load_gh(min(ro + step_rows + u * rpi + r, crow - 1), rown[u]);
             }
 #pragma unroll
@@ -1567,6 +1567,8 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         QG_HIP(ctx, hipEventRecord(e0, ctx->stream));
     }
     ctx->next_hist_is_root = 0;
+    if (rows.pitch != F * ctx->shape.bin_bytes && plan.wide_v == 0)
+        return set_error(ctx, QGBDT_E_INVALID_ARG, "only the wide-row kernels read padded rows");
     const bool flat = fast && !use_idx && plan.flat_lanes > 0 && flat_ok;
     if (plan.two_level && !flat)
         return set_error(ctx, QGBDT_E_INVALID_ARG, "two-level plan for rows that the byte-stream kernel cannot read");

@@ -554,6 +554,32 @@ __global__ __launch_bounds__(256) void transpose_bins4_kernel(const uint8_t* __r
     }
 }
 
+// Copy of a matrix of 8-byte units at a larger pitch; a workgroup takes consecutive units.
+__global__ __launch_bounds__(256) void pad_bins_kernel(const uint8_t* __restrict__ in, uint2* __restrict__ out, int64_t n_units, int row_units, int pitch_units,
+                                                       int64_t per_block) {
+    const int64_t first = (int64_t)blockIdx.x * per_block, last = min(n_units, first + per_block);
+    int64_t i = first + threadIdx.x;
+    if (i >= last) return;
+    int64_t row = i / row_units;
+    int c = (int)(i - row * row_units);
+    const int drow = 256 / row_units, dc = 256 - drow * row_units;
+    for (; i < last; i += 256) {
+        uint2 v;
+        __builtin_memcpy(&v, in + 8 * i, 8);  // (the caller's matrix may begin anywhere)
+        out[row * pitch_units + c] = v;
+        row += drow; c += dc;
+        if (c >= row_units) { c -= row_units; ++row; }
+    }
+}
+
+int launch_pad_bins(qgbdt_ctx* ctx, const void* bins, uint8_t* out, int pitch) {
+    const int64_t n = ctx->shape.n_rows * (ctx->shape.n_features / 8), per = (n + 8191) / 8192;
+    hipLaunchKernelGGL(pad_bins_kernel, dim3((unsigned)((n + per - 1) / per)), dim3(256), 0, ctx->stream, static_cast<const uint8_t*>(bins),
+                       reinterpret_cast<uint2*>(out), n, ctx->shape.n_features / 8, pitch / 8, per);
+    QG_HIP(ctx, hipGetLastError());
+    return QGBDT_OK;
+}
+
 // Most frequent bin of every feature, from a strided sample of at most 65536 rows of the feature-major copy (the
 // choice only steers which bin the histogram kernels leave out; any bin would be correct).  mfb[f] = that bin when
 // it holds at least half of the sampled rows, else 0xffff.  One workgroup per feature.

@@ -759,9 +759,17 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         idxs.p[b] = ctx->idx[b];
     }
     rows.gh_pos = (gh_lists && !ordered) ? 1 : 0;
+    rows.pitch = F * ctx->shape.bin_bytes;
     rows.bins[BUF_ORIGINAL] = bins; rows.gh[BUF_ORIGINAL] = ctx->gh; idxs.p[BUF_ORIGINAL] = ctx->idx[0];
     // the root's rows are the original arrays under the identity list
     const int root_buf = BUF_ORIGINAL;
+
+    // the copy at a pitch of whole cache lines serves the matrix it was made from, like the feature-major one
+    RowSource hist_rows = rows;
+    if (bins_t && ctx->bins_p && plan.wide_v == 8 && !ordered) {
+        for (int b = 0; b <= ROW_BUFS; ++b) hist_rows.bins[b] = ctx->bins_p;
+        hist_rows.pitch = padded_pitch(ctx->shape);
+    }
 
     // up to 256 candidates per histogram the plan kernel reduces them itself (one launch less per round)
     const int n_cand = scan_candidates(ctx->shape);
@@ -778,7 +786,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
                      mfb, root_plan.search_sums);
     if (rc != QGBDT_OK) return rc;
     const bool counting = !ordered && !gh_lists && N * plan.n_tiles <= (bins_t ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND) &&
-                          p->num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, rows);
+                          p->num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, hist_rows);
     auto search_splits = [&](const HistPlan& hp, int max_pairs, const RowMover* mover) {
         int rc = launch_scan_pairs(ctx, ctx->hist_pool, ctx->scan_pairs, &ctx->step->n_scan_items, max_pairs, ctx->delta,
                                    p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, &hp, mover);
@@ -801,7 +809,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         if (counting) {
             const CountSource count = {bins_t, N, ctx->step, ctx->nodes, ctx->batch, ctx->batch_seg, ctx->part_masks, ctx->seg_counts,
                                        ctx->hist_entries, ctx->hist_counts, ctx->scan_pairs, ctx->seg_rows, ctx->batch_max};
-            int rc = launch_hist(ctx, plan, rows, idxs, true, false, ctx->hist_entries, ctx->hist_counts, ctx->hist_pool,
+            int rc = launch_hist(ctx, plan, hist_rows, idxs, true, false, ctx->hist_entries, ctx->hist_counts, ctx->hist_pool,
                                  plan.max_lanes, mfb, plan.search_sums, &count);
             if (rc != QGBDT_OK) return rc;
             const RowMover mover = {rows, idxs, ctx->step, ctx->nodes, ctx->batch, ctx->batch_seg, ctx->part_masks, ctx->seg_counts, 0};
@@ -811,7 +819,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
         if (rc != QGBDT_OK) return rc;
         rc = launch_batch_partition_scatter(ctx, rows, ordered, plan);
         if (rc != QGBDT_OK) return rc;
-        rc = launch_hist(ctx, plan, rows, idxs, !ordered, ordered, ctx->hist_entries,
+        rc = launch_hist(ctx, plan, hist_rows, idxs, !ordered, ordered, ctx->hist_entries,
                          ctx->hist_counts, ctx->hist_pool, plan.max_lanes, mfb, plan.search_sums);
         if (rc != QGBDT_OK) return rc;
         return search_splits(plan, ctx->batch_max, nullptr);

@@ -157,6 +157,32 @@ def test_large_trees_of_row_lists(N, F, nb, bb, L, bound):
     _check(t, e, N)
 
 
+# A bound matrix large enough for the copy whose rows begin on cache lines, in a workspace with and without room for it, and from an
+# address that no wide load could use
+@pytest.mark.parametrize("N,F,bits_h", [(2_300_003, 120, 3), (1_400_000, 200, 8)])
+def test_trees_from_padded_rows(N, F, bits_h):
+    nb, L = 32, 15
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    store = torch.randint(0, nb, (N * F + 4,), generator=gen, device="cuda", dtype=torch.uint8)
+    dbins = store[4:].view(N, F)
+    bins = dbins.cpu().numpy()
+    rng = np.random.default_rng(N)
+    x = bins[:, :4].astype(np.float32) / nb - 0.5
+    g = (3 * x[:, 0] + 2 * x[:, 1] * x[:, 2] + x[:, 0] * x[:, 3] + 0.2 * rng.normal(size=N)).astype(np.float32)
+    h = rng.uniform(0.2, 0.25, N).astype(np.float32)
+    from paper_2207_09682_amd import Context
+    from paper_2207_09682_amd import binding as qb
+    ctx = Context(N, F, nb, max_leaves=L, workspace_flags=qb.WS_BIND)
+    e = oracle.grow_tree(bins, nb, g, h, 3, bits_h, 5, 0, L, min_data=20)
+    dg, dh = torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda()
+    ctx.bind_bins(dbins)
+    _check(ctx.grow_tree(dbins, dg, dh, 3, bits_h, 5, 0, L, min_data_in_leaf=20), e, N)
+    small = torch.empty(ctx.workspace_bytes - N * 128, dtype=torch.uint8, device="cuda")
+    ctx.set_workspace(small, flags=qb.WS_BIND)
+    ctx.bind_bins(dbins)
+    _check(ctx.grow_tree(dbins, dg, dh, 3, bits_h, 5, 0, L, min_data_in_leaf=20), e, N)
+
+
 def test_rounds_beyond_those_enqueued_up_front():
     # a tree of more rounds than the one before it: whatever is missing, at most one round too many is enqueued and the passes over
     # the leaves at most four times

@@ -52,6 +52,16 @@ def test_product_does_not_import_oracle():
     assert "paper_2207_09682_amd" not in otext and "libqgbdt.so" not in otext
 
 
+def test_workspace_of_a_padded_copy():
+    # rows of 8 more than a multiple of 16 features, a line's end at most 30 % away, 256 MB and more
+    from paper_2207_09682_amd import Context
+    from paper_2207_09682_amd import binding as b
+    for N, F, bb, pitch in ((2_300_000, 120, 1, 128), (1_400_000, 200, 1, 256), (1_300_000, 200, 1, 0), (3_000_000, 192, 1, 0), (3_000_000, 208, 1, 0),
+                            (3_000_000, 136, 1, 0), (5_000_000, 72, 1, 0), (1_200_000, 264, 1, 0), (3_000_000, 120, 2, 0), (3_000_000, 104, 1, 128)):
+        more = Context.workspace_bytes_for(N, F, 63, 15, bb, flags=b.WS_BIND) - Context.workspace_bytes_for(N, F, 63, 15, bb, flags=0)
+        assert 0 <= more - N * (F * bb + pitch) <= 2048, (N, F, bb)
+
+
 def test_workspace_bytes_follows_from_the_shape_alone():
     # host-only call: no context, no GPU.  Sections are 256-byte aligned, optional ones add what they hold.
     from paper_2207_09682_amd import Context
