@@ -37,11 +37,11 @@ namespace qgbdt {
 // the count and scatter kernels, which fill the chip, are the faster way.  Trees with count and scatter kernels / without, bound: 28 features
 // 20 k rows 485 / 384 us, 200 k 585 / 509, 1 M 602 / 554, 2 M 733 / 688, 4 M 961 / 1010; three tiles (90 features) 200 k 513 / 455, 1 M 663 / 728; four (200) 500 k
 // 558 / 508, 1 M 677 / 704, (500, 63 bins) 200 k 509 / 420, 800 k 732 / 844; five (136, lambdarank) 200 k 598 / 574, 500 k 656 / 637, 1 M 800 / 831,
-// (40 of 16-bit bins) 100 k 407 / 380, 1 M 565 / 642; sixteen (2000, 63 bins) 20 k 394 / 324, 100 k 480 / 462, 400 k 916 / 986; not bound, where the
+// (40 of 16-bit bins) 100 k 407 / 380, 1 M 565 / 642; nine (552, 31 bins) 260 k 580 / 663; sixteen (2000, 63 bins) 20 k 394 / 324, 100 k 480 / 462, 400 k 916 / 986; not bound, where the
 // bins that are counted and those that are accumulated share their lines, 28 features 300 k 478 / 398, 1 M 550 / 510, 2.5 M 857 / 778, 5 M 1278 / 1293; 60
 // features 500 k 548 / 494.  A tree of many leaves and tiles has rounds of more nodes than there are row-group lanes: 57 k x 1323
 // (11 tiles, 16 lanes), 275 leaves 1426 / 1471; 43 k x 640 (5, 48), 277 leaves 983 / 859.
-constexpr int64_t COUNTING_ROWS = 2500000, COUNTING_ROWS_UNBOUND = 4000000;
+constexpr int64_t COUNTING_ROWS = 2500000, COUNTING_ROWS_UNBOUND = 4000000, COUNTING_ROWS_TILED = 1600000;
 constexpr int COUNTING_NODES = 6;
 
 struct TreeOut {
@@ -785,7 +785,7 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
                      (N + hist_target_rows(root_plan, N, 1) - 1) / hist_target_rows(root_plan, N, 1),  // the build's row groups
                      mfb, root_plan.search_sums);
     if (rc != QGBDT_OK) return rc;
-    const bool counting = !ordered && !gh_lists && N * plan.n_tiles <= (bins_t ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND) &&
+    const bool counting = !ordered && !gh_lists && N * plan.n_tiles <= (plan.n_tiles > 5 ? COUNTING_ROWS_TILED : bins_t ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND) &&
                           p->num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, hist_rows);
     auto search_splits = [&](const HistPlan& hp, int max_pairs, const RowMover* mover) {
         int rc = launch_scan_pairs(ctx, ctx->hist_pool, ctx->scan_pairs, &ctx->step->n_scan_items, max_pairs, ctx->delta,
