@@ -1,12 +1,14 @@
 // Stable row partition of a leaf's index slice (the set I_s of Algorithm 1) by
-// bins[row][feature] <= bin.  Two passes: counts of left-going rows per segment
-// (flags kept as bytes), a prefix over the segments, then an order-preserving scatter
-// into another buffer.  No inter-workgroup waits: signalling between workgroups goes
-// through the memory side on this chip (~1-2 us per hop), which a single-pass
-// partition with look-back could not hide.  First the stand-alone form behind
-// qgbdt_partition_rows (row ids only), then the batched form of grow_tree, which serves
-// all nodes of a round at once and, for narrow rows, also moves the bin rows and packed
-// gradients into leaf order.
+// bins[row][feature] <= bin.  Two passes: counts of left-going rows per segment (which rows
+// they are is kept, as flag bytes here and as bit masks in the batched form), a prefix over
+// the segments, then an order-preserving scatter into another buffer.  No inter-workgroup
+// waits: signalling between workgroups goes through the memory side on this chip (~1-2 us
+// per hop), which a single-pass partition with look-back could not hide.  First the
+// stand-alone form behind qgbdt_partition_rows (row ids only), then the batched form of
+// grow_tree, which serves all nodes of a round at once and, for narrow rows, also moves the
+// bin rows and packed gradients into leaf order.  Trees of up to a few million rows on row
+// lists take neither batched pass: their histogram launch counts (CountSource) and
+// the split-search launch moves the rows (RowMover).
 #include "partition_device.h"
 
 namespace qgbdt {
@@ -229,9 +231,9 @@ struct PartOrder {
 // node are physically contiguous in its buffer and the bin is read at the row's position;
 // otherwise it is gathered from the original matrix through the row id.
 // Bound by the gather (a line of the split feature's column, or of the matrix, for one to a few rows at the deep
-// levels): all R row ids of a thread, then all its bins are in flight together.
-// Measured per round with one row in flight at a time and a flag byte per row, then so: 43.1 -> 41.2 us on 10.5 M x 28
-// (bound; 6 TB/s of lines), 7.2 -> 6.1 us on 1 M x 28, 12.1 -> 10.7 us on 2 M x 40 of 16-bit bins.
+// levels): all R row ids of a thread, then all its bins are in flight together, and PartOrder lets nodes share the
+// lines (both sides there; 10.5 M x 28, bound, 38.9 -> 27.5 us per launch).  Trees whose histogram launch counts the left rows
+// (CountSource) do without this pass.
 template <int R>
 __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, const uint8_t* __restrict__ bins_t, int64_t n_rows, int ordered,
                                                                int bb, int F, IdxSet idxs,
@@ -393,7 +395,8 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
 // another.  In ordered mode (MODE 2) the bin rows then move as dwords, eight independent loads per thread in flight,
 // coalesced on the reading side and in two compacted streams on the writing side; the packed gradients move with the row ids.
 // The first workgroup builds the next kernels' tables meanwhile (child_tables), which was a launch of its own between the
-// two passes: 12.2 us per round on 10.5 M x 28, 5.4 us on 1 M x 28.  The scatter itself: 29.1 -> 26.6 us and 5.0 -> 4.7 us.
+// two passes: 12.2 us per round on 10.5 M x 28.  Bound by the copy: 15.3 us per launch on 10.5 M x 28 (entries of 4 bytes),
+// 27 us on 20 M x 200 (row ids and packed gradients).
 template <int MODE, int R, int SUPER>  // 0: row ids, 1: row ids and packed gradients, 2: those and the bin rows (ordered mode)
 __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows, RowDest out, int F, IdxSet idxs,
                                                                  StepState* step, const BatchEntry* __restrict__ batch,

@@ -12,8 +12,9 @@
 //   2. expands that leaf and, speculatively, other nodes with large gains -- open leaves
 //      and, up to three levels ahead, descendants of open leaves that are already expanded -- as
 //      far as the leaf budget can still reach them: one batched partition, one batched
-//      histogram build for the smaller children, one batched subtraction and split
-//      search for all children.
+//      histogram build for one child of each, one batched subtraction and split
+//      search for all children.  Up to a few million rows the build counts the left rows
+//      on its way and the search's launch moves the rows (COUNTING_ROWS).
 // A speculative expansion that the replay never reaches is simply not part of the
 // tree: its node stays a leaf and its row slice is untouched, because children are
 // always written to another buffer (buffers rotate with the depth, so a node's rows
