@@ -158,7 +158,7 @@ static size_t carve_workspace(qgbdt_ctx* c, void* base, uint32_t flags, bool pad
     k.take(&c->plan_list, (size_t)c->max_nodes);
     k.take(&c->step, 1);
     k.take(&c->batch, (size_t)c->batch_max);
-    k.take(&c->batch_seg, (size_t)TABLE_MAX);
+    k.take(&c->batch_seg, (size_t)c->batch_max);
     k.take(&c->cand, (size_t)2 * c->batch_max * F);
     k.take(&c->hist_entries, (size_t)c->batch_max);
     k.take(&c->hist_counts, 4);

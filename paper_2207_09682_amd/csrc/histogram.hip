@@ -167,7 +167,7 @@ __device__ __forceinline__ void store_partial(typename Acc<W>::word* lds, int ld
 // Bound by a chain: tables 2.5 us, list entries and bins 2 us (a line per one or two of them below the first levels), rows and atomics 1 to
 // 6 us for 500 to 4000 rows, local bins handed over 0.6 us.  One workgroup of 1024 threads per CU; two of 512 took 18.7 us per launch
 // on 1 M x 28 where one takes 18.2.  Per round against the count, scatter and histogram launches it replaces (the scatter goes beside
-// the split search): 10 k x 28 13.0 -> 8.6 us, 100 k x 50 17.2 -> 13.2, 1 M x 28 24.3 -> 18.2, 2.5 M x 28 not bound 58.5 -> 46.1, 464 k x 90 25.2 -> 22.9,
+// the split search): 10 k x 28 13.0 -> 8.6 us, 100 k x 50 17.2 -> 13.2, 1 M x 28 24.3 -> 18.2, 2.5 M x 28 not bound 58.5 -> 42.2, 464 k x 90 25.2 -> 22.9,
 // 200 k x 136 (64-bit words) 19.8 -> 14.4.  Which child is built follows from the hessians, not from the rows, which are not known yet: the
 // histograms are the same, only their cost is not.
 
@@ -179,8 +179,8 @@ __device__ __forceinline__ int count_starts(const CountSource& cs, const HistPla
     static_assert(sizeof(BatchEntry) % 8 == 0 && COUNT_RECORDS * (int)sizeof(BatchEntry) / 16 <= COUNT_THREADS, "one load per thread");
     const bool mine = t < min(cs.batch_max, COUNT_RECORDS) * (int)sizeof(BatchEntry) / 16;
     const uint4 record = mine ? reinterpret_cast<const uint4*>(cs.batch)[t] : make_uint4(0u, 0u, 0u, 0u);
-    const int first = t < TABLE_MAX ? cs.batch_seg[t] : 0;  // (in flight together with the number of nodes; the section has TABLE_MAX places)
-    int next = t + 1 < TABLE_MAX ? cs.batch_seg[t + 1] : 0;
+    const int first = t < cs.batch_max ? cs.batch_seg[t] : 0;  // (in flight together with the number of nodes)
+    int next = t + 1 < cs.batch_max ? cs.batch_seg[t + 1] : 0;
     n_batch = cs.step->n_batch;
     const int n_segs = cs.step->n_part_items;
     if (n_batch <= 0) return 0;  // (uniform)
