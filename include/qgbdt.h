@@ -339,6 +339,24 @@ QGBDT_API int qgbdt_read_profile_roots(qgbdt_ctx* ctx, double* root_ms, int64_t*
 QGBDT_API int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g, int32_t bits_h, int32_t acc_width,
                              int32_t skewed, int64_t rows, int32_t n_builds, int64_t* out, int32_t n_out);
 
+/* How the rounds of a tree divide their rows, from the functions that the kernels use themselves (host-only: no context, no GPU
+ * call).  For tests and callers that check the division.
+ * _counting: a tree whose row lists hold row ids, with or without the gradients in the same 32 bits (QGBDT_ROWS_IDS, _IDS_CODED),
+ * of a 16-byte aligned matrix, bound or not.  out (host int64 [n_out], n_out >= 7): 1 where its histogram launches count the rows
+ * that go left, rows per segment of a node, row-group lanes of such a launch, segments per work item where a round's `n_builds`
+ * builds have `segments` segments together (0 where the launches do not count), most segments of a round, most builds of a round,
+ * most row groups of a build that the split search adds up itself.
+ * _row_group: the place in its build's list of work item `item` of a gathered build with the items item_start .. item_start + groups - 1;
+ * out3 (host): row groups in front of the stretch that it shares, row groups that share it, which of them it is.
+ * _segment_order: what workgroup `block` of `grid` (a multiple of 8) of the counting pass of a round of n_nodes nodes, with
+ * first segments starts[0] = 0 < starts[1] < ... and n_segs segments in all, goes through: n_out pairs of node and segment, of
+ * which at most `room` are written to out (host int32 [2 * room]). */
+QGBDT_API int qgbdt_describe_counting(const qgbdt_shape* shape, int32_t bits_g, int32_t bits_h, int32_t acc_width, int32_t bound,
+                            int32_t num_leaves, int32_t segments, int32_t n_builds, int64_t* out, int32_t n_out);
+QGBDT_API int qgbdt_describe_row_group(int32_t item_start, int32_t groups, int32_t item, int32_t* out3);
+QGBDT_API int qgbdt_describe_segment_order(const qgbdt_shape* shape, int32_t bound, const int32_t* starts, int32_t n_nodes, int32_t n_segs,
+                                 int32_t block, int32_t grid, int32_t* out, int64_t room, int64_t* n_out);
+
 /* Figures of the last grow_tree call on this context (host out int32[4]): rounds of
  * batched expansion, nodes expanded (committed splits plus speculative ones), committed
  * splits, nodes created.  For callers that time or tune; no paper quantity. */
@@ -353,6 +371,10 @@ QGBDT_API int qgbdt_tree_launches(const qgbdt_ctx* ctx, int32_t* out2);
  * _ORDERED or _IDS_CODED; QGBDT_ROWS_AUTO before the first tree.  A histogram build then reads per row, beside the bin row:
  * a row id and the packed gradients (6 bytes; 2 for _ORDERED, whose rows are contiguous) or one entry (4 bytes). */
 QGBDT_API int qgbdt_tree_layout(const qgbdt_ctx* ctx, int32_t* layout);
+
+/* Whether the histogram launches of the last grow_tree call on this context counted the rows that go left themselves (host out: 1), or a
+ * counting pass went before them (0).  For callers that time or tune. */
+QGBDT_API int qgbdt_tree_counting(const qgbdt_ctx* ctx, int32_t* counting);
 
 /* Streaming-read rate of this device as a plain kernel reaches it: `buf` (dev, 16-byte aligned, `bytes` a
  * multiple of 16, at least 16) is read `reps` times with 16-byte loads by one grid-stride kernel per repetition,

@@ -32,7 +32,8 @@ EXPORTS = [
     "qgbdt_boost_iteration_lambdarank",
     "qgbdt_set_profiling", "qgbdt_read_profile", "qgbdt_read_profile_roots", "qgbdt_tree_stats", "qgbdt_bind_bins",
     "qgbdt_measure_stream_read", "qgbdt_describe_hist_plan", "qgbdt_tree_layout",
-    "qgbdt_tree_launches",
+    "qgbdt_tree_launches", "qgbdt_tree_counting",
+    "qgbdt_describe_counting", "qgbdt_describe_row_group", "qgbdt_describe_segment_order",
 ]
 
 
@@ -107,6 +108,12 @@ def load_library() -> C.CDLL:
                                                   C.POINTER(C.c_int32)]
         lib.qgbdt_describe_hist_plan.argtypes = [C.POINTER(Shape), C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int64,
                                                  C.c_int32, C.POINTER(C.c_int64), C.c_int32]
+        lib.qgbdt_tree_counting.argtypes = [C.c_void_p, C.POINTER(C.c_int32)]
+        lib.qgbdt_describe_counting.argtypes = [C.POINTER(Shape), C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
+                                                C.POINTER(C.c_int64), C.c_int32]
+        lib.qgbdt_describe_row_group.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+        lib.qgbdt_describe_segment_order.argtypes = [C.POINTER(Shape), C.c_int32, C.POINTER(C.c_int32), C.c_int32, C.c_int32, C.c_int32, C.c_int32,
+                                                     C.POINTER(C.c_int32), C.c_int64, C.POINTER(C.c_int64)]
         _lib = lib
     return _lib
 
@@ -128,6 +135,45 @@ def describe_hist_plan(n_rows, n_features, n_bins, max_leaves=255, bin_bytes=1, 
     if rc != 0:
         raise QgbdtError(rc, lib.qgbdt_last_error(None).decode())
     return dict(zip(PLAN_FIELDS, (int(x) for x in out)))
+
+
+COUNTING_FIELDS = ("counts", "seg_rows", "lanes", "item_segs", "max_seg", "batch_max", "search_sums")
+
+
+def describe_counting(n_rows, n_features, n_bins, max_leaves=255, bin_bytes=1, bits_g=3, bits_h=3, acc_width=0, bound=True, num_leaves=None,
+                      segments=0, n_builds=1) -> dict:
+    """qgbdt_describe_counting: whether a tree's histogram launches count the left rows, and how they divide a round (host-only)."""
+    lib = load_library()
+    shape = Shape(n_rows, n_features, n_bins, bin_bytes, max_leaves)
+    out = (C.c_int64 * len(COUNTING_FIELDS))()
+    rc = lib.qgbdt_describe_counting(C.byref(shape), bits_g, bits_h, acc_width, 1 if bound else 0, max_leaves if num_leaves is None else num_leaves,
+                                     segments, n_builds, out, len(COUNTING_FIELDS))
+    if rc != 0:
+        raise QgbdtError(rc, lib.qgbdt_last_error(None).decode())
+    return dict(zip(COUNTING_FIELDS, (int(x) for x in out)))
+
+
+def describe_row_group(item_start, groups, item) -> tuple:
+    """qgbdt_describe_row_group: (groups in front, groups of the stretch, which of them) of a gathered build's work item (host-only)."""
+    lib = load_library()
+    out = (C.c_int32 * 3)()
+    rc = lib.qgbdt_describe_row_group(item_start, groups, item, out)
+    if rc != 0:
+        raise QgbdtError(rc, lib.qgbdt_last_error(None).decode())
+    return tuple(out)
+
+
+def describe_segment_order(n_rows, n_features, starts, n_segs, block, grid, bound=True) -> list:
+    """qgbdt_describe_segment_order: the (node, segment) pairs of one workgroup of a round's counting pass (host-only)."""
+    lib = load_library()
+    shape = Shape(n_rows, n_features, 255, 1, 255)
+    first = (C.c_int32 * len(starts))(*[int(x) for x in starts])
+    out, n = (C.c_int32 * (2 * n_segs))(), C.c_int64(0)
+    rc = lib.qgbdt_describe_segment_order(C.byref(shape), 1 if bound else 0, first, len(starts), n_segs, block, grid, out, n_segs, C.byref(n))
+    if rc != 0:
+        raise QgbdtError(rc, lib.qgbdt_last_error(None).decode())
+    assert n.value <= n_segs
+    return [(out[2 * k], out[2 * k + 1]) for k in range(n.value)]
 
 
 class QgbdtError(RuntimeError):
@@ -470,6 +516,16 @@ def _tree_launches(self):
 
 
 Context.tree_launches = _tree_launches
+
+
+def _tree_counting(self):
+    """Whether the histogram launches of the last grow_tree call counted the left rows themselves."""
+    out = C.c_int32(0)
+    self._chk(self.lib.qgbdt_tree_counting(self._h, C.byref(out)))
+    return bool(out.value)
+
+
+Context.tree_counting = _tree_counting
 
 
 def unpack_splits(raw: torch.Tensor):

@@ -757,6 +757,56 @@ int qgbdt_describe_hist_plan(const qgbdt_shape* shape, int32_t bits_g, int32_t b
     return QGBDT_OK;
 }
 
+int qgbdt_describe_counting(const qgbdt_shape* shape, int32_t bits_g, int32_t bits_h, int32_t acc_width, int32_t bound, int32_t num_leaves,
+                            int32_t segments, int32_t n_builds, int64_t* out, int32_t n_out) {
+    constexpr int VALUES = 7;
+    if (!out || n_out < VALUES) return set_error(nullptr, QGBDT_E_INVALID_ARG, "out must hold %d values", VALUES);
+    int rc = check_shape(shape);
+    if (rc != QGBDT_OK) return rc;
+    if (bits_g < 2 || bits_g > 8 || !(bits_h == 0 || (bits_h >= 2 && bits_h <= 8)) || (acc_width != 0 && acc_width != 16 && acc_width != 32) ||
+        num_leaves < 1 || num_leaves > shape->max_leaves || segments < 0 || n_builds < 1)
+        return set_error(nullptr, QGBDT_E_INVALID_ARG, "bits, acc_width, num_leaves, segments or n_builds out of range");
+    qgbdt_ctx tmp;
+    memset(&tmp, 0, sizeof(tmp));
+    tmp.shape = *shape;
+    derive_sizes(&tmp);
+    tmp.seg_supers = part_supers(shape->n_rows, bound != 0) ? 1 : 0;
+    const HistPlan p = make_hist_plan(*shape, bits_g, bits_h, acc_width, false);
+    const RowSource aligned{};
+    const bool counts = counts_rows(&tmp, p, aligned, bound != 0, num_leaves);
+    const int64_t v[VALUES] = {counts ? 1 : 0, tmp.seg_rows, count_lanes(p), counts ? count_item_segs(p, segments, n_builds, tmp.seg_rows) : 0,
+                               tmp.max_seg, tmp.batch_max, p.search_sums};
+    for (int i = 0; i < VALUES; ++i) out[i] = v[i];
+    return QGBDT_OK;
+}
+
+int qgbdt_describe_row_group(int32_t item_start, int32_t groups, int32_t item, int32_t* out3) {
+    if (!out3 || item_start < 0 || groups < 1 || item < item_start || item >= item_start + groups)
+        return set_error(nullptr, QGBDT_E_INVALID_ARG, "no such item of the build");
+    const GroupPlace p = group_place(item_start, groups, item);
+    out3[0] = p.first; out3[1] = p.n; out3[2] = p.own;
+    return QGBDT_OK;
+}
+
+int qgbdt_describe_segment_order(const qgbdt_shape* shape, int32_t bound, const int32_t* starts, int32_t n_nodes, int32_t n_segs, int32_t block,
+                                 int32_t grid, int32_t* out, int64_t room, int64_t* n_out) {
+    int rc = check_shape(shape);
+    if (rc != QGBDT_OK) return rc;
+    if (!starts || n_nodes < 1 || n_nodes > TABLE_MAX || starts[0] != 0 || n_segs < n_nodes || grid < 8 || grid % 8 != 0 || block < 0 || block >= grid ||
+        room < 0 || (room > 0 && !out) || !n_out)
+        return set_error(nullptr, QGBDT_E_INVALID_ARG, "starts, grid, block or out out of range");
+    for (int i = 1; i <= n_nodes; ++i)
+        if ((i < n_nodes ? starts[i] : n_segs) <= starts[i - 1]) return set_error(nullptr, QGBDT_E_INVALID_ARG, "every node has at least one segment");
+    *n_out = order_of_segments(*shape, bound != 0, starts, n_nodes, n_segs, block, grid, out, room);
+    return QGBDT_OK;
+}
+
+int qgbdt_tree_counting(const qgbdt_ctx* ctx, int32_t* counting) {
+    if (!ctx || !counting) return QGBDT_E_INVALID_ARG;
+    *counting = ctx->tree_counting;
+    return QGBDT_OK;
+}
+
 int qgbdt_tree_stats(const qgbdt_ctx* ctx, int32_t* out4) {
     if (!ctx || !out4 || !ctx->report) return QGBDT_E_INVALID_ARG;
     out4[0] = ctx->report->rounds; out4[1] = ctx->report->n_expanded;

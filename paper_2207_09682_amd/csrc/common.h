@@ -198,6 +198,22 @@ __host__ __device__ inline int count_item_segs(const HistPlan& p, int total, int
     return max(min(k, p.single_rows / seg_rows), 1);
 }
 
+// Where a gathered build's row groups lie in its list.  A list ascends, so position in the list is position in the matrix, and lines
+// that hold rows of several builds (or of a build's neighbouring rows) are fetched once if the builds pass them on one XCD at about
+// the same time: the groups that an XCD holds of a build (work items go round-robin to the XCDs) share one stretch of the list, the n-th of
+// the XCD number, and take its blocks of rows in turn.  Rows of one or two lines (hist_piece_kernel): per launch against groups of consecutive
+// rows 10.5 M x 28 63.7 -> 58.5 us, 2 M x 40 of 16-bit bins 26.9 -> 26.6; rows of many lines share none (20 M x 200 157.6 / 158.8, 400 k x 2000 66.7 / 67.8:
+// hist_wide_kernel keeps consecutive rows).
+struct GroupPlace {
+    int first, n, own;  // groups of the XCDs in front, groups of this XCD, which of them this one is
+};
+__host__ __device__ __forceinline__ GroupPlace group_place(int item_start, int groups, int item) {
+    // every XCD has groups / 8 of them, and those that the last, incomplete turn of eight meets, which starts at the first one's XCD, one more
+    const int x = item & 7, s = item_start & 7;
+    const uint32_t turn = (1u << (groups & 7)) - 1u, more = ((turn << s) | (turn >> (8 - s))) & 0xffu;
+    return {x * (groups >> 3) + (int)__builtin_popcount(more & ((1u << x) - 1u)), (groups >> 3) + (int)((more >> x) & 1u), (item - item_start) >> 3};
+}
+
 // One unit of the passes over finished leaves (refit, score update): in every part of the row order, piece
 // (part * n + unit - first) of the leaf's rows, piece_rows long.
 struct RefitUnit {
@@ -295,6 +311,7 @@ struct qgbdt_ctx {
     int max_super;
     int rounds_hint;
     int tree_layout;  // QGBDT_ROWS_* that the last tree was grown with
+    int tree_counting;  // 1: its histogram launches counted the left rows
     int tree_rounds, tree_passes;  // rounds and passes over its leaves that were enqueued for it
     // workspace
     int ordered;           // the workspace holds leaf-ordered copies of the rows (narrow rows, QGBDT_WS_ROW_COPIES)
@@ -478,6 +495,11 @@ int launch_quantize(qgbdt_ctx* ctx, const float* g, const float* h, int64_t n, i
                     int64_t* totals_out, float2* pairs_out);  // totals_out null: only the workgroups' totals (quantize_parts of them)
 int quantize_parts(const float* g, const float* h, const int16_t* gh, int64_t n);
 bool counting_build_ok(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows);  // a launch of `plan` can count the round's rows itself
+// Whether the histogram launches of a tree on row lists without gradient lists count the left rows (bound: there is a feature-major copy)
+bool counts_rows(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, bool bound, int num_leaves);
+// Segments that workgroup `block` of `grid` counts in a round of n_nodes nodes with first segments `starts` (n_segs in all):
+// pairs of node and segment; returns their number, of which at most `room` are written
+int64_t order_of_segments(const qgbdt_shape& s, bool bound, const int32_t* starts, int n_nodes, int n_segs, int block, int grid, int32_t* out, int64_t room);
 HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, bool skew = false);
 HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, int64_t rows, bool skew = false,
                             bool stream_ok = false);  // stream_ok: contiguous rows of a 16-byte aligned matrix

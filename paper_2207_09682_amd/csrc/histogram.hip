@@ -98,22 +98,6 @@ __device__ __forceinline__ void tile_and_lane(int n_tiles, int& tile, int& glane
     glane = (s / n_tiles) * 8 + xcd;
 }
 
-// Where a gathered build's row groups lie in its list.  A list ascends, so position in the list is position in the matrix, and lines
-// that hold rows of several builds (or of a build's neighbouring rows) are fetched once if the builds pass them on one XCD at about
-// the same time: the groups that an XCD holds of a build (work items go round-robin to the XCDs) share one stretch of the list, the n-th of
-// the XCD number, and take its blocks of rows in turn.  Rows of one or two lines (hist_piece_kernel): per launch against groups of consecutive
-// rows 10.5 M x 28 63.7 -> 58.5 us, 2 M x 40 of 16-bit bins 26.9 -> 26.6; rows of many lines share none (20 M x 200 157.6 / 158.8, 400 k x 2000 66.7 / 67.8:
-// hist_wide_kernel keeps consecutive rows).
-struct GroupPlace {
-    int first, n, own;  // groups of the XCDs in front, groups of this XCD, which of them this one is
-};
-__device__ __forceinline__ GroupPlace group_place(int item_start, int groups, int item) {
-    // every XCD has groups / 8 of them, and those that the last, incomplete turn of eight meets, which starts at the first one's XCD, one more
-    const int x = item & 7, s = item_start & 7;
-    const uint32_t turn = (1u << (groups & 7)) - 1u, more = ((turn << s) | (turn >> (8 - s))) & 0xffu;
-    return {x * (groups >> 3) + (int)__popc(more & ((1u << x) - 1u)), (groups >> 3) + (int)((more >> x) & 1u), (item - item_start) >> 3};
-}
-
 // Merge of the local bins into the total histogram and reset of the local bins.
 // Both are [bin][feature], so LDS is walked linearly (no bank conflicts) and the
 // atomics of a wavefront fall into consecutive words.

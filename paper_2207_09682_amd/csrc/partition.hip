@@ -162,70 +162,6 @@ int run_partition_rows(qgbdt_ctx* ctx, const uint8_t* bins, int32_t* row_idx, in
 // its segment; which of them go left is one 64-bit mask per 64 rows (128 bytes of masks for 1024 rows instead of a byte
 // per row), from which the scatter derives every destination without exchanging anything between wavefronts.
 
-// The order in which a round's segments are counted.  A node's rows are spread over all the matrix, in ascending order, so the s-th of its
-// n segments lies about s / n of the way through it, and nodes that split by the same feature read the same lines of its column (without
-// the feature-major copy: all nodes the same lines of the matrix).  Every XCD therefore takes an eighth of each node, the same one,
-// and goes through the eighths of all nodes side by side, in 2^shift / 8 steps: a line is then fetched by the first node and
-// found in the XCD's L2 by the others.  (Workgroup ids go round-robin to the XCDs.)
-// Per launch against segments in the order of the nodes, with 1 / 2 / 4 / 8 steps: 2 M x 40 of 16-bit bins 11.8 -> 9.8 / 10.0 / 10.3 / 10.4 us, 4 M x 28 15.0 -> 11.6 /
-// 11.7 / 12.5 / 13.0, 8 M x 28 31.0 -> 24.6 / 23.6 / 22.6 / 22.9, 10.5 M x 28 38.9 -> 30.0 / 28.5 / 27.5 / 27.5, 5 M x 100 18.2 -> 15.3 / 15.3 / 15.7 / 16.4, 20 M x
-// 200 42.2 -> 39.1 / 38.3 / 38.5 / 38.8; not bound, 8 M x 40 87 -> 85 / 84 / 79 / 72, 3 M x 100 47.7 -> 47.6 / 46.4 / 45.6 / 45.1.  Below about 1 M rows there is
-// nothing to gain (400 k x 2000 7.6 -> 8.3 with four steps).
-constexpr int ORDER_ITEMS = 512;
-inline int order_shift(int64_t n_rows, bool bound) { return !bound ? 6 : n_rows > 6000000 ? 5 : 3; }
-struct PartOrder {
-    const int* s_start;
-    int n_batch, n_items, lane, shift;
-    bool spread;
-    int origin, part, first, next;  // first segment of the XCD; the part that holds the last segment asked for: its first one, the next part's
-
-    __device__ __forceinline__ int segments(int j) const { return j < n_batch ? (j + 1 < n_batch ? s_start[j + 1] : n_items) - s_start[j] : 0; }
-    // segments of all nodes in front of part q
-    __device__ __forceinline__ int in_front(int q) const {
-        int c = 0;
-        for (int j = 0; j < n_batch; j += 64) c += (segments(j + lane) * q) >> shift;
-        return wave_sum(c);
-    }
-    __device__ __forceinline__ void start(const int* starts, int nodes, int items, int l, int sh) {
-        s_start = starts; n_batch = nodes; n_items = items; lane = l; shift = sh;
-        spread = shift > 0 && n_items >= ORDER_ITEMS;
-        if (!spread) return;
-        part = ((int)blockIdx.x & 7) << (shift - 3);
-        first = in_front(part); next = in_front(part + 1);
-        origin = first;
-    }
-    // Segment number `at` of the launch (ascending from call to call): its node and its number among all segments; false: no more
-    __device__ __forceinline__ bool at(int at, int& node, int& item) {
-        if (!spread) {
-            if (at >= n_items) return false;
-            item = at;
-            node = find_start(s_start, n_batch, at);
-            return true;
-        }
-        const int end = ((at & 7) + 1) << (shift - 3);
-        const int want = origin + (at >> 3);
-        while (want >= next) {
-            if (++part == end) return false;
-            first = next; next = in_front(part + 1);
-        }
-        int before = want - first;  // segments of this part in front of it
-        for (int j0 = 0; j0 < n_batch; j0 += 64) {
-            const int n = segments(j0 + lane);
-            const int from = (n * part) >> shift, share = ((n * (part + 1)) >> shift) - from;
-            const int incl = wave_prefix(share);
-            const int all = __builtin_amdgcn_readlane(incl, 63);
-            if (before < all) {
-                const int l = __popcll(__ballot(incl <= before));
-                node = j0 + l;
-                item = s_start[node] + __builtin_amdgcn_readlane(from, l) + before - (__builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(share, l));
-                return true;
-            }
-            before -= all;
-        }
-        return false;
-    }
-};
-
 // Left-going rows per segment, as masks and counts; on the way the histogram slots
 // that this round's builds accumulate into are cleared.  In ordered mode the rows of a
 // node are physically contiguous in its buffer and the bin is read at the row's position;
@@ -259,8 +195,8 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
     __shared__ int s_start[TABLE_MAX];
     load_batch(batch_seg, n_batch, s_start);
     int turn = 0;
-    PartOrder order;
-    order.start(s_start, n_batch, n_items, lane, shift);
+    PartOrder<WaveNodes> order;
+    order.start(WaveNodes{lane}, s_start, n_batch, n_items, (int)blockIdx.x, shift);
     for (int at = blockIdx.x; ; at += gridDim.x, turn ^= 1) {
         int node, item;
         if (!order.at(at, node, item)) break;
@@ -464,6 +400,40 @@ static IdxSet idx_set(const qgbdt_ctx* ctx) {
     for (int b = 0; b < ROW_BUFS; ++b) s.p[b] = ctx->idx[b];
     s.p[BUF_ORIGINAL] = ctx->idx[0];
     return s;
+}
+
+namespace {
+struct HostNodes {  // WaveNodes, one node after the other
+    template <class F>
+    int sum(int n, F f) const {
+        int c = 0;
+        for (int j = 0; j < n; ++j) c += f(j);
+        return c;
+    }
+    int last_start(const int* starts, int n, int at) const {
+        int c = 0;
+        while (c < n && starts[c] <= at) ++c;
+        return c - 1;
+    }
+    template <class F>
+    bool find(int n, F share, int& at, int& node, int& from) const {
+        for (node = 0; node < n; ++node) {
+            const int k = share(node, from);
+            if (at < k) return true;
+            at -= k;
+        }
+        return false;
+    }
+};
+}  // namespace
+
+int64_t order_of_segments(const qgbdt_shape& s, bool bound, const int32_t* starts, int n_nodes, int n_segs, int block, int grid, int32_t* out, int64_t room) {
+    PartOrder<HostNodes> order;
+    order.start(HostNodes{}, starts, n_nodes, n_segs, block, order_shift(s.n_rows, bound));
+    int64_t n = 0;
+    for (int at = block, node, item; order.at(at, node, item); at += grid, ++n)
+        if (n < room) { out[2 * n] = node; out[2 * n + 1] = item; }
+    return n;
 }
 
 int launch_batch_partition_count(qgbdt_ctx* ctx, const RowSource& rows, const uint8_t* bins_t, bool ordered) {

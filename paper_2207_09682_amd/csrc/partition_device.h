@@ -12,6 +12,90 @@ __device__ __forceinline__ void load_batch(const int32_t* __restrict__ batch_seg
     __syncthreads();
 }
 
+// The order in which a round's segments are counted.  A node's rows are spread over all the matrix, in ascending order, so the s-th of its
+// n segments lies about s / n of the way through it, and nodes that split by the same feature read the same lines of its column (without
+// the feature-major copy: all nodes the same lines of the matrix).  Every XCD therefore takes an eighth of each node, the same one,
+// and goes through the eighths of all nodes side by side, in 2^shift / 8 steps: a line is then fetched by the first node and
+// found in the XCD's L2 by the others.  (Workgroup ids go round-robin to the XCDs.)
+// Per launch against segments in the order of the nodes, with 1 / 2 / 4 / 8 steps: 2 M x 40 of 16-bit bins 11.8 -> 9.8 / 10.0 / 10.3 / 10.4 us, 4 M x 28 15.0 -> 11.6 /
+// 11.7 / 12.5 / 13.0, 8 M x 28 31.0 -> 24.6 / 23.6 / 22.6 / 22.9, 10.5 M x 28 38.9 -> 30.0 / 28.5 / 27.5 / 27.5, 5 M x 100 18.2 -> 15.3 / 15.3 / 15.7 / 16.4, 20 M x
+// 200 42.2 -> 39.1 / 38.3 / 38.5 / 38.8; not bound, 8 M x 40 87 -> 85 / 84 / 79 / 72, 3 M x 100 47.7 -> 47.6 / 46.4 / 45.6 / 45.1.  Below about 1 M rows there is
+// nothing to gain (400 k x 2000 7.6 -> 8.3 with four steps).
+constexpr int ORDER_ITEMS = 512;
+inline int order_shift(int64_t n_rows, bool bound) { return !bound ? 6 : n_rows > 6000000 ? 5 : 3; }
+
+// Nodes of a round looked at by a wavefront, 64 at a time (what is asked about a node behind the last one is 0).
+struct WaveNodes {
+    int lane;
+    template <class F>
+    __device__ __forceinline__ int sum(int n, F f) const {
+        int c = 0;
+        for (int j = 0; j < n; j += 64) c += f(j + lane);
+        return wave_sum(c);
+    }
+    __device__ __forceinline__ int last_start(const int* starts, int n, int at) const { return find_start(starts, n, at); }
+    // The node that holds number `at` of the nodes' shares in a row: its share's start, and the number inside the share; false: there are not as many.
+    template <class F>
+    __device__ __forceinline__ bool find(int n, F share, int& at, int& node, int& from) const {
+        for (int j0 = 0; j0 < n; j0 += 64) {
+            int f;
+            const int k = share(j0 + lane, f), incl = wave_prefix(k), all = __builtin_amdgcn_readlane(incl, 63);
+            if (at < all) {
+                const int l = __popcll(__ballot(incl <= at));
+                at -= __builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(k, l);
+                node = j0 + l;
+                from = __builtin_amdgcn_readlane(f, l);
+                return true;
+            }
+            at -= all;
+        }
+        return false;
+    }
+};
+
+template <class Nodes>
+struct PartOrder {
+    Nodes nodes;
+    const int* s_start;
+    int n_batch, n_items, shift;
+    bool spread;
+    int origin, part, first, next;  // first segment of the XCD; the part that holds the last segment asked for: its first one, the next part's
+
+    __host__ __device__ __forceinline__ int segments(int j) const { return j < n_batch ? (j + 1 < n_batch ? s_start[j + 1] : n_items) - s_start[j] : 0; }
+    // segments of all nodes in front of part q
+    __host__ __device__ __forceinline__ int in_front(int q) const {
+        return nodes.sum(n_batch, [&](int j) { return (segments(j) * q) >> shift; });
+    }
+    __host__ __device__ __forceinline__ void start(const Nodes& w, const int* starts, int count, int items, int block, int sh) {
+        nodes = w; s_start = starts; n_batch = count; n_items = items; shift = sh;
+        spread = shift > 0 && n_items >= ORDER_ITEMS;
+        if (!spread) return;
+        part = (block & 7) << (shift - 3);
+        first = in_front(part); next = in_front(part + 1);
+        origin = first;
+    }
+    // Segment number `at` of the launch (ascending from call to call): its node and its number among all segments; false: no more
+    __host__ __device__ __forceinline__ bool at(int at, int& node, int& item) {
+        if (!spread) {
+            if (at >= n_items) return false;
+            item = at;
+            node = nodes.last_start(s_start, n_batch, at);
+            return true;
+        }
+        const int end = ((at & 7) + 1) << (shift - 3);
+        const int want = origin + (at >> 3);
+        while (want >= next) {
+            if (++part == end) return false;
+            first = next; next = in_front(part + 1);
+        }
+        int rest = want - first, from = 0;  // segments of this part in front of it
+        if (!nodes.find(n_batch, [&](int j, int& f) { const int n = segments(j); f = (n * part) >> shift; return ((n * (part + 1)) >> shift) - f; }, rest, node, from))
+            return false;
+        item = s_start[node] + from + rest;
+        return true;
+    }
+};
+
 // The children of an expanded node: `nl` of its rows go left.
 __device__ __forceinline__ void put_children(Node* nodes, const BatchEntry& be, int child, int nl, int64_t lg, int64_t lh, int64_t rg, int64_t rh,
                                              int lslot, int rslot) {

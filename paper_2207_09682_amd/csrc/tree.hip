@@ -45,6 +45,11 @@ namespace qgbdt {
 constexpr int64_t COUNTING_ROWS = 2500000, COUNTING_ROWS_UNBOUND = 4000000, COUNTING_ROWS_TILED = 1600000;
 constexpr int COUNTING_NODES = 6;
 
+bool counts_rows(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, bool bound, int num_leaves) {
+    const int64_t most = plan.n_tiles > 5 ? COUNTING_ROWS_TILED : bound ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND;
+    return ctx->shape.n_rows * plan.n_tiles <= most && num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, rows);
+}
+
 struct TreeOut {
     qgbdt_tree t;
     int32_t max_leaves;
@@ -786,8 +791,8 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
                      (N + hist_target_rows(root_plan, N, 1) - 1) / hist_target_rows(root_plan, N, 1),  // the build's row groups
                      mfb, root_plan.search_sums);
     if (rc != QGBDT_OK) return rc;
-    const bool counting = !ordered && !gh_lists && N * plan.n_tiles <= (plan.n_tiles > 5 ? COUNTING_ROWS_TILED : bins_t ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND) &&
-                          p->num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, hist_rows);
+    const bool counting = !ordered && !gh_lists && counts_rows(ctx, plan, hist_rows, bins_t != nullptr, p->num_leaves);
+    ctx->tree_counting = counting ? 1 : 0;
     auto search_splits = [&](const HistPlan& hp, int max_pairs, const RowMover* mover) {
         int rc = launch_scan_pairs(ctx, ctx->hist_pool, ctx->scan_pairs, &ctx->step->n_scan_items, max_pairs, ctx->delta,
                                    p->min_data_in_leaf, p->min_sum_hessian, ctx->cand, mfb, &hp, mover);

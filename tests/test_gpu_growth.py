@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2207_09682_amd.binding import describe_counting, describe_hist_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -131,9 +132,15 @@ def test_histogram_launches_that_count(N, F, nb, bb, L, bits, layout):
     e = oracle.grow_tree(bins, nb, g, h, bits, bits, 5, 0, L, min_data=3)
     n = e.n_leaves
     assert n > L // 2
+    seg_rows = 512 if N <= 2 ** 18 else 2048
+    c, p = describe_counting(N, F, nb, L, bb, bits, bits, segments=-(-N // seg_rows)), describe_hist_plan(N, F, nb, L, bb, bits, bits)
+    assert c["seg_rows"] == seg_rows and (c["item_segs"] * seg_rows > 4096) == (N > 1_200_000)   # an item of two stretches
+    assert (c["search_sums"] == 8) == (N * p["n_tiles"] > (2 ** 17 if p["n_tiles"] > 1 else 2 ** 14))   # the reduce kernel adds up
+    assert (c["lanes"] < L) == ((F, L) in ((16, 658), (90, 127), (800, 63), (4096, 31)))   # a round may have more nodes than lanes
     for bound in (True, False):
         ctx.bind_bins(dbins if bound else None)
         t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), bits, bits, 5, 0, L, min_data_in_leaf=3, row_layout=layout)
+        assert ctx.tree_counting()
         _check(t, e, N)
         assert np.allclose(t.leaf_value.cpu().numpy()[:n], e.leaf_value[:n], rtol=1e-9, atol=1e-13)
 
@@ -154,6 +161,7 @@ def test_large_trees_of_row_lists(N, F, nb, bb, L, bound):
     e = oracle.grow_tree(bins, nb, g, h, 3, 3, 5, 0, L, min_data=20)
     ctx.bind_bins(dbins if bound else None)
     t = ctx.grow_tree(dbins, torch.from_numpy(g).cuda(), torch.from_numpy(h).cuda(), 3, 3, 5, 0, L, min_data_in_leaf=20, row_layout=0 if bound else 1)
+    assert not ctx.tree_counting()
     _check(t, e, N)
 
 

@@ -7,7 +7,7 @@ import itertools
 import numpy as np
 import pytest
 
-from paper_2207_09682_amd.binding import describe_hist_plan
+from paper_2207_09682_amd.binding import describe_counting, describe_hist_plan, describe_row_group, describe_segment_order
 
 SHAPES = [  # n_rows, n_features, n_bins, max_leaves, bin_bytes
     (10_500_000, 28, 255, 255, 1), (1_000_000, 28, 255, 255, 1), (10_000, 28, 63, 15, 1),
@@ -364,88 +364,90 @@ def test_small_trees_with_long_row_groups_need_no_reduction():
             assert p["search_sums"] == (2 ** 31 - 1 if small else 8), (N, F, bits)
 
 
-# Gathered builds: the row groups that an XCD holds of a build share one stretch of its list and take its blocks in turn.  Every row
-# once, no group more than a chunk, an XCD's stretches in the order of the XCDs.
+# Gathered builds: the row groups that an XCD holds of a build share one stretch of its list and take its blocks in turn (places as
+# the library gives them).  Every row once, no group more than a chunk, an XCD's stretches in the order of the XCDs.
 @pytest.mark.parametrize("count,groups,item_start,block,chunk", [
     (100_000, 37, 5, 256, 10_000), (100_000, 8, 0, 256, 100_000), (5000, 3, 7, 320, 4681), (257, 2, 6, 256, 600), (1, 1, 3, 512, 1000),
-    (20_000, 64, 1, 144, 4000), (1_000_003, 97, 250, 256, 10_922), (9000, 40, 2, 512, 1000)])
+    (20_000, 64, 1, 144, 4000), (1_000_003, 97, 250, 256, 10_922), (9000, 40, 2, 512, 1000), (777, 7, 4, 64, 500), (50_000, 1023, 9, 16, 200)])
 def test_row_groups_of_gathered_builds_cover_the_list(count, groups, item_start, block, chunk):
     rows_per_group = -(-count // groups)
     assert rows_per_group + block <= chunk
     seen = np.zeros(count, np.int64)
-    begins = {}
+    begins, members = {}, {}
     for item in range(item_start, item_start + groups):
-        first = n = own = 0
-        x = item & 7
-        for y in range(x + 1):
-            g = (y - item_start) & 7
-            k = (groups - g + 7) >> 3 if groups > g else 0
-            if y < x:
-                first += k
-            else:
-                n, own = k, (item - item_start - g) >> 3
-        assert 0 <= own < n
+        first, n, own = describe_row_group(item_start, groups, item)
+        assert 0 <= first and 0 <= own < n and first + n <= groups
+        x = item % 8
         begin = min(count, first * rows_per_group)
         end = min(count, begin + n * rows_per_group)
-        begins.setdefault(x, begin)
-        assert begins[x] == begin
+        assert begins.setdefault(x, begin) == begin
+        members.setdefault(x, []).append(own)
         mine = 0
         for b in range(begin + own * block, end, n * block):
             seen[b:min(end, b + block)] += 1
             mine += min(end, b + block) - b
         assert mine <= chunk
     assert (seen == 1).all()
+    assert all(sorted(m) == list(range(len(m))) for m in members.values())
     assert [begins[x] for x in sorted(begins)] == sorted(begins.values())
 
 
-# Order of the counting pass: every XCD goes through its eighth of all nodes side by side.  Every segment once, whatever the nodes' sizes.
-@pytest.mark.parametrize("shift", [3, 5, 6])
-@pytest.mark.parametrize("n_nodes,grid", [(1, 520), (3, 1024), (64, 2048), (65, 2048), (200, 1032)])
-def test_counting_pass_takes_every_segment_once(n_nodes, grid, shift):
-    rng = np.random.default_rng(n_nodes + shift)
+# Order of the counting pass as the library goes through it: every segment once and with its own node, whatever the nodes' sizes; every
+# XCD stays inside its eighth of each node and goes through it in ascending order.  (Steps per eighth: 1, 4 and 8.)
+@pytest.mark.parametrize("n_rows,bound", [(3_000_000, True), (7_000_000, True), (3_000_000, False)])
+@pytest.mark.parametrize("n_nodes,grid", [(1, 520), (3, 1024), (64, 2048), (65, 2048), (200, 1032), (658, 8)])
+def test_counting_pass_takes_every_segment_once(n_nodes, grid, n_rows, bound):
+    rng = np.random.default_rng(n_nodes + n_rows)
     n = rng.integers(1, 3 * 1024 // n_nodes + 2, n_nodes)
     n[rng.integers(0, n_nodes)] += 700
-    start = np.concatenate([[0], np.cumsum(n)[:-1]])
+    starts = np.concatenate([[0], np.cumsum(n)[:-1]])
     seen = np.zeros(int(n.sum()), np.int64)
     for wg in range(grid):
-        part, end = (wg & 7) << (shift - 3), ((wg & 7) + 1) << (shift - 3)
-        in_front = lambda q: int(((n * q) >> shift).sum())  # noqa: E731
-        first, nxt = in_front(part), in_front(part + 1)
-        origin, at, done = first, wg, False
-        while not done:
-            want = origin + (at >> 3)
-            while want >= nxt and not done:
-                part += 1
-                done = part == end
-                if not done:
-                    first, nxt = nxt, in_front(part + 1)
-            if not done:
-                lo, hi = (n * part) >> shift, (n * (part + 1)) >> shift
-                incl = np.cumsum(hi - lo)
-                node = int((incl <= want - first).sum())
-                seen[start[node] + lo[node] + want - first - (incl[node] - (hi - lo)[node])] += 1
-                at += grid
+        last = {}
+        for node, seg in describe_segment_order(n_rows, 28, starts, int(n.sum()), wg, grid, bound):
+            local = seg - starts[node]
+            assert 0 <= local < n[node]
+            assert (n[node] * (wg % 8)) // 8 <= local < (n[node] * (wg % 8 + 1)) // 8
+            assert last.get(node, -1) < local
+            last[node] = local
+            seen[seg] += 1
     assert (seen == 1).all()
 
 
+def test_counting_pass_of_few_segments_goes_from_node_to_node():
+    starts = [0, 1, 40, 41]
+    got = [p for wg in range(16) for p in describe_segment_order(3_000_000, 28, starts, 511, wg, 16)]
+    assert sorted(s for _, s in got) == list(range(511))
+    assert all(node == max(i for i in range(4) if starts[i] <= seg) for node, seg in got)
+
+
 # Launches that count the left rows themselves: items of one chunk, as many as the table has room for.
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
+COUNTING_SHAPES = [(10_000, 28, 63, 15, 1), (100_003, 50, 255, 31, 1), (65_536, 120, 255, 31, 1), (43_690, 90, 255, 63, 1), (1_000_000, 28, 255, 255, 1),
+                   (463_715, 90, 255, 255, 1), (200_000, 136, 255, 63, 1), (100_000, 16, 64, 658, 1), (1_900_000, 48, 255, 127, 1), (20_000, 800, 63, 63, 1),
+                   # short chunks and few row-group lanes: more items than the table holds, or nearly as many
+                   (262_144, 200, 255, 63, 1), (262_144, 150, 255, 255, 1), (150_000, 200, 255, 63, 1),
+                   (50_001, 40, 300, 63, 2), (60_000, 56, 255, 15, 1), (3000, 4096, 16, 31, 1), (500_000, 200, 255, 255, 1)]
+
+
+@pytest.mark.parametrize("shape", SHAPES + COUNTING_SHAPES, ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
 def test_items_of_launches_that_count(shape):
     N, F, nb, L, bb = shape
-    seg_rows = 2048 if N > 1 << 18 else 512
-    for key, p in _plans(shape):
-        lanes = 256 // p["n_tiles"] // 8 * 8 if 256 // p["n_tiles"] >= 16 else 8
-        most = p["single_rows"] // seg_rows
-        if N * p["n_tiles"] > 4_000_000 or most < 1:
+    checked = 0
+    for (bg, bh), acc, bound in itertools.product(BITS + [(6, 6), (7, 2)], (0, 16, 32), (True, False)):
+        key = (bg, bh, acc)
+        p = describe_hist_plan(N, F, nb, L, bb, *key)
+        c = describe_counting(N, F, nb, L, bb, *key, bound)
+        if not c["counts"]:
             continue
-        max_seg = N // seg_rows + L + 2
-        if not (max_seg // most + L + 1 <= p["max_items"] and lanes // 2 + 1 + L <= p["max_items"] and lanes + 1 <= p["max_items"]):
-            continue
+        assert p["lds_bytes"] <= 64 * 1024 and not p["bytewise"] and c["seg_rows"] == (2048 if N > 1 << 18 else 512)
+        whole = -(-N // c["seg_rows"])
         rng = np.random.default_rng(N)
         for n_nodes in {1, 2, min(L, 17), L}:
-            for total in {n_nodes, max(n_nodes, N // seg_rows // 3), max(n_nodes, N // seg_rows + n_nodes - 1)}:
+            for total in {n_nodes, max(n_nodes, whole // 3), whole + n_nodes - 1}:
                 segs = rng.multinomial(total - n_nodes, np.ones(n_nodes) / n_nodes) + 1
-                places = max(lanes - (n_nodes - 1), (lanes + 1) // 2)
-                k = max(min(max(-(-total // places), -(-1024 // seg_rows)), most), 1)
-                assert k * seg_rows <= p["single_rows"], key
+                k = describe_counting(N, F, nb, L, bb, *key, bound, None, total, n_nodes)["item_segs"]
+                assert k >= 1 and k * c["seg_rows"] <= p["single_rows"], key
+                assert total <= c["max_seg"] and n_nodes <= c["batch_max"]
                 assert (-(-segs // k)).sum() <= p["max_items"], (key, n_nodes, total)
+        checked += 1
+    assert checked > 0 or shape in SHAPES   # (COUNTING_SHAPES are there because they do)
