@@ -35,19 +35,54 @@ namespace qgbdt {
 // Row lists: up to this many rows times tiles of features the histogram launch counts the left rows itself (CountSource) and the rows are moved
 // beside the split search, which leaves a round four dependent launches (three where no reduce kernel is launched) of six.  Every tile of a
 // row group goes through the parents' rows for itself, and a workgroup counts and accumulates one after the other: beyond the line
-// the count and scatter kernels, which fill the chip, are the faster way.  Trees with count and scatter kernels / without, bound: 28 features
-// 20 k rows 485 / 384 us, 200 k 585 / 509, 1 M 602 / 554, 2 M 733 / 688, 4 M 961 / 1010; three tiles (90 features) 200 k 513 / 455, 1 M 663 / 728; four (200) 500 k
-// 558 / 508, 1 M 677 / 704, (500, 63 bins) 200 k 509 / 420, 800 k 732 / 844; five (136, lambdarank) 200 k 598 / 574, 500 k 656 / 637, 1 M 800 / 831,
-// (40 of 16-bit bins) 100 k 407 / 380, 1 M 565 / 642; nine (552, 31 bins) 260 k 580 / 663; sixteen (2000, 63 bins) 20 k 394 / 324, 100 k 480 / 462, 400 k 916 / 986; not bound, where the
-// bins that are counted and those that are accumulated share their lines, 28 features 300 k 478 / 398, 1 M 550 / 510, 2.5 M 857 / 778, 5 M 1278 / 1293; 60
-// features 500 k 548 / 494.  A tree of many leaves and tiles has rounds of more nodes than there are row-group lanes: 57 k x 1323
-// (11 tiles, 16 lanes), 275 leaves 1426 / 1471; 43 k x 640 (5, 48), 277 leaves 983 / 859.
-constexpr int64_t COUNTING_ROWS = 2500000, COUNTING_ROWS_UNBOUND = 4000000, COUNTING_ROWS_TILED = 1600000;
+// the count and scatter kernels, which fill the chip, are the faster way.  Not bound, every tile gathers lines of the matrix for its count, so
+// that the line lies lower the more tiles there are; pieces at any address (hist_piece_kernel) take several tiles longer than the wide rows' aligned ones.
+// Trees of 31 / 127 leaves, time without over time with, at millions of rows x tiles (3 bits, 255 bins where nothing else is said):
+//   one tile    28 features bound 1.25: 1.03 / 1.04, 1.9: 1.04 / 1.05, 2.35: 1.00 / 1.01; 21 (5 bits) 1.9: 1.02 / 1.03, 2.35: 0.97 / 0.97; 40 (2 bits) 2.35: 1.01 / 1.03;
+//               not bound 28 1.25: 1.08 / 1.06, 2.2: 1.02 / 1.00, 2.65: 0.86 / 0.79, 5: 0.88 / 0.86 (255 leaves); 40 2.35: 1.00 / 0.99
+//   two         100 bound 1.25: 1.10 / 1.11, 2.35: 1.02 / 0.99, not bound 2.35: 1.05 / 0.98; 60 (5 bits) 2.35: 1.01 / 1.02, not bound 1.02 / 1.02
+//   three       90 bound 1.6: 1.05 / 1.05, 2.05: 1.00 / 1.01, 2.35: 1.02 / 0.96, not bound 2.05: 1.03 / 1.01, 2.35: 1.00 / 0.92
+//   four, wide  200 bound 1.9: 1.08 / 1.06, 2.35: 1.08 / 1.03, 3: 0.91 / 0.98 (255 leaves); not bound 1.9: 1.06 / 1.02, 2.35: 1.08 / 0.98
+//   four, pieces  500 (63 bins) bound 1.4: 1.08 / 1.05, 1.9: 1.01 / 1.01, 2.05: 1.00 / 0.97, not bound 1.4: 1.08 / 1.04, 1.6: 1.04 / 1.00, 2.05: 1.01 / 0.96
+//   five, wide  136 (8-bit hessians) bound 1.9: 1.06 / 1.02, 2.35: 1.02 / 1.00, not bound 1.6: 1.06 / 1.02, 1.75: 1.04 / 0.97
+//   five, pieces  300 (127 bins) bound 1.6: 1.04 / 1.00, 1.9: 1.03 / 0.97, not bound 1.25: 1.07 / 1.04, 1.6: 1.03 / 0.98
+//   nine        552 (31 bins) bound 1.6: 1.04 / 1.01, 1.9: 0.99 / 0.98, not bound 1: 1.06 / 1.04, 1.25: 1.04 / 0.98, 1.6: 0.98 / 0.95
+//   sixteen     2000 (63 bins), 31 leaves bound 1.6: 1.03, 2.2: 0.96, not bound 1: 1.00, 1.6: 0.98
+// 64-bit words accumulate at half the rate, and a workgroup's share of a parent may hold anything between none and all of its built child's rows: in several
+// tiles their line lies lower (one tile stays: 24 features bound 2.25: 1.04, not bound 56 features, 31 bins 2.35: 0.93).  So does that of trees whose rounds have more
+// nodes than there are row-group lanes, which then have two items each: 255 leaves, 64-bit words 232 features, 127 bins (64 lanes) bound 1: 1.00, 2.05: 0.89, 166 features (80)
+// 0.87: 0.97, 168 features 1.9: 0.91; 32-bit words 200 features (64) 2: 1.05, 400 features, 31 bins (128), 511 leaves not bound 2.4: 0.95; 1213 features (8 lanes), 31
+// leaves 1.46: 0.92.  Over 900 shapes drawn from 12 to 1500 features, 15 to 400 bins, 2 to 8 bits, 250 k to 2.8 M rows x tiles, 15 to 511 leaves
+// trees take 7.9 % less time by this rule than without counting; the better of both ways everywhere would be 8.2 %.  (Figures of single shapes vary by 2 %.)
+// Beyond six times the lanes not at all: 57 k x 1323 (11 tiles, 16 lanes), 275 leaves 1426 / 1471 us; 43 k x 640 (5, 48), 277 leaves 983 / 859.
 constexpr int COUNTING_NODES = 6;
+static int64_t counting_rows(const HistPlan& plan, bool bound, int num_leaves) {
+    const int T = plan.n_tiles, lanes = count_lanes(plan);
+    const bool wide = plan.wide_v > 0, words64 = plan.acc_width == 32;
+    if (num_leaves > COUNTING_NODES * lanes) return 0;
+    int64_t most = words64 && T > 1 ? 2000000 : 2400000;
+    if (T > 5) most = bound ? 1600000 : 1100000;
+    else if (T > 2 && !(bound && wide)) most = std::min<int64_t>(most, T == 3 || (T == 4 && wide) ? 2000000 : bound || wide ? 1600000 : 1400000);
+    if (num_leaves > 2 * lanes) most = std::min<int64_t>(most, words64 || T > 5 ? 1100000 : 2000000);
+    return most;
+}
+
+// An item of such a launch is one chunk at most (count_item_segs), which for short chunks makes more items than row-group lanes in the rounds of the
+// whole matrix: the lanes' second items take as long as the first ones.  Two turns pay up to 2 M rows x tiles, where the second is not nearly
+// empty or the items are short and later rounds, whose nodes are fewer rows, outweigh; three never do.  Trees of 31 / 127 leaves, time without over time with, 4
+// bits (4096 rows per item), by the turns that all rows fill: 28 features bound 1.2: 0.97 / 0.99, 1.5: 0.99 / 0.99, 2.1: 0.91 / 0.93, not bound 1.2: 1.02 / 1.01, 1.5: 1.06 / 1.03, 2.1: 0.93 /
+// 0.94; 90 features 1.0: 0.96 / 0.99 (not bound 0.97 / 0.99), 1.3: 0.98 / 1.01 (1.02 / 1.03), 1.6: 1.00 / 1.02 (1.06 / 1.07), 2.1: 0.90 / 0.94 (0.95 / 0.97); 400 features, 63 bins 1.2: 1.00 / 1.03, 1.3: 1.06 /
+// 1.07, 2.0: 1.02 / 1.00, 2.1: 0.94 / 0.95; 32 features, 63 leaves, not bound 1.2: 1.06, 72 features (two tiles), 255 leaves, not bound 1.2: 1.09.  6144 rows per item: 22 features, 31 bins,
+// 31 leaves 1.2: 0.89, 141 features, 15 bins, 255 leaves 1.2: 0.91.
+static bool counting_turns_pay(const HistPlan& plan, int64_t n_rows, int seg_rows, int num_leaves) {
+    const int64_t segs = (n_rows + seg_rows - 1) / seg_rows, turn = (int64_t)count_lanes(plan) * (plan.single_rows / seg_rows);
+    if (segs <= turn) return true;
+    return segs <= 2 * turn && n_rows * plan.n_tiles <= 2000000 && (10 * segs >= 13 * turn || (num_leaves > 32 && plan.single_rows < 6144));
+}
 
 bool counts_rows(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, bool bound, int num_leaves) {
-    const int64_t most = plan.n_tiles > 5 ? COUNTING_ROWS_TILED : bound ? COUNTING_ROWS : COUNTING_ROWS_UNBOUND;
-    return ctx->shape.n_rows * plan.n_tiles <= most && num_leaves <= COUNTING_NODES * count_lanes(plan) && counting_build_ok(ctx, plan, rows);
+    const int64_t N = ctx->shape.n_rows;
+    return N * plan.n_tiles <= counting_rows(plan, bound, num_leaves) && counting_build_ok(ctx, plan, rows) && counting_turns_pay(plan, N, ctx->seg_rows, num_leaves);
 }
 
 struct TreeOut {

@@ -451,3 +451,29 @@ def test_items_of_launches_that_count(shape):
                 assert (-(-segs // k)).sum() <= p["max_items"], (key, n_nodes, total)
         checked += 1
     assert checked > 0 or shape in SHAPES   # (COUNTING_SHAPES are there because they do)
+
+
+# Up to how many rows times tiles the histogram launches count, bound and not bound, for whole and wide pieces of rows; and that they do
+# not where the items' one chunk makes a second turn of the lanes that is nearly empty, or a third one (4 bits: 4096 rows per item)
+# (64-bit words in several tiles, and more than twice as many leaves as row-group lanes: lower lines)
+@pytest.mark.parametrize("F,nb,bh,leaves,tiles,wide,bound,unbound", [
+    (28, 255, 3, 31, 1, False, 2_400_000, 2_400_000), (28, 255, 8, 255, 1, False, 2_400_000, 2_400_000), (60, 255, 8, 31, 2, False, 2_000_000, 2_000_000), (100, 255, 3, 31, 2, False, 2_400_000, 2_400_000),
+    (90, 255, 3, 31, 3, False, 2_000_000, 2_000_000), (400, 31, 3, 511, 2, True, 2_000_000, 2_000_000), (166, 127, 8, 255, 3, False, 1_100_000, 1_100_000),
+    (200, 255, 3, 31, 4, True, 2_400_000, 2_000_000), (500, 63, 3, 31, 4, False, 1_600_000, 1_400_000), (136, 255, 8, 31, 5, True, 2_000_000, 1_600_000),
+    (300, 127, 3, 31, 5, False, 1_600_000, 1_400_000), (552, 31, 3, 31, 9, True, 1_600_000, 1_100_000), (2000, 63, 3, 31, 16, True, 1_600_000, 1_100_000),
+    (2000, 63, 3, 96, 16, True, 1_100_000, 1_100_000), (2000, 63, 3, 97, 16, True, 0, 0)])
+def test_trees_up_to_the_lines_count(F, nb, bh, leaves, tiles, wide, bound, unbound):
+    p = describe_hist_plan(100_000, F, nb, leaves, 1, 3, bh)
+    assert p["n_tiles"] == tiles and (p["wide_v"] > 0) == wide and (p["acc_width"] == 32) == (bh == 8)
+    for b, line in ((True, bound), (False, unbound)):
+        for N in (max(line // tiles, 1000), line // tiles + 1001):
+            assert describe_counting(N, F, nb, leaves, 1, 3, bh, 0, b)["counts"] == (N * tiles <= line), (b, N)
+
+
+@pytest.mark.parametrize("F,nb,tiles", [(28, 255, 1), (90, 255, 3), (400, 63, 4)])
+def test_launches_that_count_take_two_turns_at_most(F, nb, tiles):
+    turn = (256 // tiles // 8 * 8) * 4096
+    most = min(2 * turn, 2_000_000 // tiles)
+    for leaves in (32, 33):
+        for rows, counts in ((turn, 1), (turn + 1, leaves > 32), (int(1.28 * turn), leaves > 32), (int(1.32 * turn), 1), (int(1.5 * turn), 1), (most, 1), (most + 1, 0)):
+            assert describe_counting(rows, F, nb, leaves, 1, 4, 4, 0, True)["counts"] == counts, (rows, leaves)
