@@ -186,15 +186,32 @@ __host__ __device__ inline int64_t hist_target_rows(const HistPlan& p, int64_t t
     return t;
 }
 
+// In tree growth the split search sums a build's slots itself when there are at most this many (a thread's loads of them are
+// all in flight at once); builds of more row groups are summed up by the reduce kernel, which spreads them over the
+// whole chip and otherwise returns at once.  Trees with 8 / 64: 400 k x 2000 1283 / 1396 us, 2 M x 40 of 16-bit bins
+// 924 / 980 us, 1 M x 28 the same.
+// Where no build has more than 33 groups (hist_target_rows, count_item_segs) the search adds them all up and the reduce kernel, 3 us of every round with the gap in
+// front of it, is not launched: up to 2^14 rows in one tile, 2^17 rows times tiles in several, unless the bits
+// of a forced word width allow short groups only.  Trees of 15 / 63 leaves with the launch, without it: 16 k x 28 194 / 312, 189 / 300 us, 8 k x 500 of 63 bins 205 / 370, 193 /
+// 347, 33 k x 500 239 / 404, 229 / 387, 44 k x 90 229 / 341, 222 / 328, 65 k x 100 253 / 398, 254 / 392, 65 k x 56 (8 bits) 228 / 340, 237 / 333, 33 k x 200 249 / 410, 266 /
+// 421; beyond the lines 32 k x 50 215 / 347, 220 / 345, 131 k x 100 263 / 393, 278 / 397, 66 k x 200 260 / 395, 276 / 412 (65 k x 500 254 / 369, 241 / 351).  With 8 bits in 32-bit
+// words (groups of 129 rows) 16 k x 28 280 / 308 us, 30 k x 100 410 / 518 us, 65 k x 68 339 / 540 us.
+constexpr int REDUCE_ABOVE = 8;
+constexpr int SEARCH_SUMS_MOST = 33;  // (32 and one that rounding may add)
+constexpr int ALL_GROUPS = 0x7fffffff;
+
 // Counting build (CountSource): workgroups of 1024 threads, one per CU, and row-group lanes in multiples of 8.
 constexpr int COUNT_THREADS = 1024;
 __host__ __device__ inline int count_lanes(const HistPlan& p) { return 256 / p.n_tiles >= 16 ? 256 / p.n_tiles / 8 * 8 : 8; }
 // Segments per work item, `total` of them in the round's `n_entries` builds: no more items than workgroups, with a place left for the item
 // of every build that is not full (a CU with two of them takes twice as long: 1 M x 28 19 -> 25 us), of at least 1024 rows (512 or 2048
-// rows: within 3 % on 10 k to 1 M rows) and of one chunk, so that nothing is merged.
+// rows: within 3 % on 10 k to 1 M rows) and of one chunk, so that nothing is merged.  Where the search adds up every build, no build has more than
+// SEARCH_SUMS_MOST items (the plan sees to it where the chunk is the limit).  Trees of 15 / 63 leaves without / with that limit: 65 k x 56, 8 bits
+// 258 / 235, 354 / 331 us, x 120 256 / 237, 386 / 368; 44 k x 90 230 / 222, 336 / 329; 34 k x 50, 5 bits 235 / 225, 356 / 347.
 __host__ __device__ inline int count_item_segs(const HistPlan& p, int total, int n_entries, int seg_rows) {
     const int lanes = count_lanes(p), places = max(lanes - (n_entries - 1), (lanes + 1) / 2);
-    const int k = max((total + places - 1) / places, (1024 + seg_rows - 1) / seg_rows);
+    int k = max((total + places - 1) / places, (1024 + seg_rows - 1) / seg_rows);
+    if (p.search_sums == ALL_GROUPS) k = max(k, (total + SEARCH_SUMS_MOST - 1) / SEARCH_SUMS_MOST);
     return max(min(k, p.single_rows / seg_rows), 1);
 }
 
@@ -458,18 +475,6 @@ inline int refit_extra(int64_t n_rows) {  // about 512 rows per unit where a lea
 //    5.5 M x 20 1145 / 1154 us.  The lines lie where the two are level: between 4.7 and 5.5 M rows bound, below 3.5 M not bound.
 inline int part_rows(int64_t n_rows) { return n_rows > ((int64_t)1 << 18) ? 8 : 2; }
 inline bool part_supers(int64_t n_rows, bool bound) { return n_rows > ((int64_t)(bound ? 5 : 3) << 20); }
-// In tree growth the split search sums a build's slots itself when there are at most this many (a thread's loads of them are
-// all in flight at once); builds of more row groups are summed up by the reduce kernel, which spreads them over the
-// whole chip and otherwise returns at once.  Trees with 8 / 64: 400 k x 2000 1283 / 1396 us, 2 M x 40 of 16-bit bins
-// 924 / 980 us, 1 M x 28 the same.
-// Where no build can have more than 32 groups the search adds them all up and the reduce kernel, 3 us of every round with the gap in
-// front of it, is not launched: up to 2^14 rows in one tile, 2^17 rows times tiles in several (hist_target_rows), unless the bits
-// of a forced word width allow short groups only.  Trees with / without the launch: 10 k x 28 196 / 187 us, 16 k x 28 281 / 272 us,
-// 60 k x 100 284 / 270 us, 8 k x 500 452 / 436 us; beyond the lines 30 k x 28 267 / 269 us, 100 k x 50 311 / 332 us, and with 8 bits in 32-bit
-// words (groups of 129 rows) 16 k x 28 280 / 308 us, 30 k x 100 410 / 518 us, 65 k x 68 339 / 540 us.
-constexpr int REDUCE_ABOVE = 8;
-constexpr int SEARCH_SUMS_MOST = 33;  // (32 and one that rounding may add)
-constexpr int ALL_GROUPS = 0x7fffffff;
 constexpr int PART_SUPER = 32;  // segments whose left rows are summed up in one counter
 // Most nodes expanded in one round = most builds of a histogram launch (the leaf budget; the growth bookkeeping
 // limits it to 658).  Kernels keep the first work item of every build / node in LDS and search there: a binary

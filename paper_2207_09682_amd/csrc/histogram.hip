@@ -25,6 +25,7 @@
 // the four features of a dword is rotated per row so that lanes of one instruction
 // spread over the features.  Lanes that have no place in a tile are masked for the
 // atomics (they would otherwise hit one word together and serialize).
+#include <algorithm>
 #include <type_traits>
 
 #include "split_device.h"
@@ -1402,7 +1403,9 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
     p.single_rows = p.chunk_rows >= 1024 ? p.chunk_rows - 320 : p.chunk_rows / 2;
     if (p.single_rows < 1) p.single_rows = 1;
     const int64_t t = hist_target_rows(p, s.n_rows, 1);
-    const bool few = s.n_rows * p.n_tiles <= (p.n_tiles > 1 ? 1 << 17 : 1 << 14) && (s.n_rows + t - 1) / t <= SEARCH_SUMS_MOST;
+    const int64_t seg = 256 * part_rows(s.n_rows), item = std::max<int64_t>(p.single_rows / seg * seg, 1);  // (longest item of a launch that counts)
+    const bool few = s.n_rows * p.n_tiles <= (p.n_tiles > 1 ? 1 << 17 : 1 << 14) && (s.n_rows + t - 1) / t <= SEARCH_SUMS_MOST &&
+                     (item < seg || (s.n_rows + item - 1) / item <= SEARCH_SUMS_MOST);
     p.search_sums = few ? ALL_GROUPS : REDUCE_ABOVE;
     return p;
 }
