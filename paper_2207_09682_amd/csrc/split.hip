@@ -312,7 +312,7 @@ __global__ __launch_bounds__(256) void reduce_items_kernel(const FeatCand* __res
     for (int item = blockIdx.x * 4 + wave; item < n_items; item += gridDim.x * 4) {
         const ScanPair* sp = &pairs[item >> 1];
         reduce_features_wave(cand_base + (int64_t)item * n_cand, n_cand, sp->stat[sp->a_item == (item & 1) ? 0 : 1],
-                             reinterpret_cast<qgbdt_split*>(out + (int64_t)(first + item) * stride), lane);
+                             reinterpret_cast<qgbdt_split*>(out + (int64_t)(first + item) * stride), lane, step == nullptr);
     }
 }
 

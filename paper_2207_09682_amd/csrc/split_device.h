@@ -38,9 +38,10 @@ __device__ __forceinline__ int64_t count_estimate(int64_t HL, int64_t Hs, int64_
 
 // Reduces the candidates of one leaf (F of them, one per tile of ascending features) to its best split: largest gain,
 // ties to the lowest feature.  Called by all 64 lanes of one wavefront; lane 0
-// writes the result.
+// writes the result.  estimate: with the left row count by the hessians; not in growth, which counts rows and whose
+// pairs may hold the parent's number of rows (ScanPair::seg_start).
 __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const qgbdt_leafstat& st, qgbdt_split* out,
-                                            int lane) {
+                                            int lane, bool estimate) {
     double bg = 0.0;
     int bf = -1;
     for (int f = lane; f < F; f += 64) {
@@ -61,7 +62,7 @@ __device__ inline void reduce_features_wave(const FeatCand* cand, int F, const q
             s.gain = c.gain; s.feature = c.feature; s.bin = c.bin;
             s.left_g = packed_g(c.left); s.left_h = packed_h(c.left);
             s.right_g = st.sum_g - s.left_g; s.right_h = st.sum_h - s.left_h;
-            s.left_count = count_estimate(s.left_h, st.sum_h, st.n_rows);
+            if (estimate) s.left_count = count_estimate(s.left_h, st.sum_h, st.n_rows);
         }
         *out = s;
     }
