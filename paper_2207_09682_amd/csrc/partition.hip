@@ -333,8 +333,10 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
 // The first workgroup builds the next kernels' tables meanwhile (child_tables), which was a launch of its own between the
 // two passes: 12.2 us per round on 10.5 M x 28.  Bound by the copy: 15.3 us per launch on 10.5 M x 28 (entries of 4 bytes),
 // 27 us on 20 M x 200 (row ids and packed gradients).
+// Bin rows that come from beyond the caches (MODE 2 with the counters): five wavefronts per SIMD, not the six that the registers allow, copy 14 M x 32 in 155
+// instead of 161 us per launch (trees of 14 M x 32 3738 / 3660 us, 12 M x 16 2148 / 2133, 7 M x 28 1570 / 1567; smaller ones, without the counters, 3 M x 20 1060 / 1078).
 template <int MODE, int R, int SUPER>  // 0: row ids, 1: row ids and packed gradients, 2: those and the bin rows (ordered mode)
-__global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows, RowDest out, int F, IdxSet idxs,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MODE == 2 && SUPER > 1 ? 5 : 8))) void batch_part_scatter_kernel(RowSource rows, RowDest out, int F, IdxSet idxs,
                                                                  StepState* step, const BatchEntry* __restrict__ batch,
                                                                  const int32_t* __restrict__ batch_seg, Node* nodes,
                                                                  const unsigned long long* __restrict__ masks,
@@ -355,8 +357,9 @@ __global__ __launch_bounds__(256) void batch_part_scatter_kernel(RowSource rows,
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int dpr = F / 4;
     load_batch(batch_seg, n_batch, s_start);
-    // Segments are taken from the last to the first: the count kernel has just streamed the same
-    // rows front to back, so the tail of that stream is what the memory-side cache still holds.
+    // Segments are taken from the last to the first: in ordered mode the count kernel has just streamed the same rows front to back, so the
+    // tail of that stream is what the memory-side cache still holds.  (Row lists, counted by PartOrder, take the same time either
+    // way: 10.5 M x 28 16.1 / 16.2 us per launch, 5 M x 200 17.5 / 17.5, 8 M x 28 not bound 14.5 / 14.8.)
     for (int item = n_items - (int)blockIdx.x; item >= 0; item -= (int)gridDim.x - 1) {
         const BatchEntry nd = batch[find_start(s_start, n_batch, item)];
         scatter_wave<MODE, R, SUPER>(rows, out.gh, idxs, nd, item, wave, lane, masks, seg_counts, super_counts, s_dpos);
