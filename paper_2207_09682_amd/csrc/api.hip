@@ -421,7 +421,7 @@ int qgbdt_build_histograms(qgbdt_ctx* ctx, const void* bins, const int16_t* gh, 
     const HistPlan plan = make_hist_plan_for(ctx->shape, bits_g, bits_h, acc_width, count, mfb != nullptr,
                                              row_idx == nullptr && ((uintptr_t)bins & 15) == 0);
     if (mfb && plan.wide_v == 0) mfb = nullptr;  // only those kernels skip
-    rc = launch_begin_build(ctx, plan, begin, count, row_idx != nullptr, hist_out, W);
+    rc = launch_begin_build(ctx, plan, begin, count, hist_out, W);
     if (rc != QGBDT_OK) return rc;
     RowSource rows;
     rows.gh_pos = 0;  // the caller's packed gradients are in original row order

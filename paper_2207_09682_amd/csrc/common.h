@@ -28,8 +28,10 @@ struct Node {
     qgbdt_split best;      // best split of this node (feature < 0: none)
 };
 
-// What the histogram launches have had to do, counted where their tables are made.  (By a thread of the histogram kernels, which
-// walked the table, one load after the other, in front of its workgroup's first barrier, it held up every launch of many builds.)
+// What the histogram launches have had to do.  Counted by the first thread of each from a total that the tables hold.  (Their makers, which
+// counted before, end at once and waited for the three atomics: stand-alone builds 3 M x 28 by row list 26.3 / 25.9 us, 500 k x 13 15.8 / 15.4, a
+// tree's first launch 0.3 us.  Walking the table instead held up every launch of many builds.)  Launches that select their rows
+// (CountSource) learn the total last: there the kernel behind them counts.
 struct HistProfile {
     enum { CONTIGUOUS = 0, IDS = 1, CODED = 2 };  // rows: contiguous, gathered by row id, gathered by entries that hold their gradients (RowCode)
     unsigned long long rows[3];
@@ -363,7 +365,7 @@ struct qgbdt_ctx {
     int32_t* batch_seg;          // [batch_max] their first segments, for the search segment -> node
     qgbdt::FeatCand* cand;       // [2*batch_max][F]
     qgbdt::HistEntry* hist_entries;  // [batch_max]
-    int32_t* hist_counts;        // [3] entries, items, 1: an entry has more groups than the split search adds up (HistPlan::search_sums)
+    int32_t* hist_counts;        // [4] entries, items, 1: an entry has more groups than the split search adds up (HistPlan::search_sums), rows of all entries
     qgbdt::ScanPair* scan_pairs; // [batch_max]
     qgbdt::RefitUnit* refit_units;  // [max_leaves + REFIT_EXTRA] of the leaves last laid out
     int2* refit_leaves;          // [max_leaves + 1] first unit and units of a leaf; behind the leaves: number of units
@@ -509,7 +511,7 @@ HistPlan make_hist_plan(const qgbdt_shape& s, int bits_g, int bits_h, int acc_wi
 HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int acc_width, int64_t rows, bool skew = false,
                             bool stream_ok = false);  // stream_ok: contiguous rows of a 16-byte aligned matrix
 int64_t max_rows_for_width(int bits_g, int bits_h, int w);
-int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, bool gathered, int64_t* hist, int64_t n_words);
+int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, int64_t* hist, int64_t n_words);
 int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, const IdxSet& idx, bool use_idx,
                 bool flat_ok, const HistEntry* entries, const int32_t* table_counts, int64_t* hist_base,
                 int64_t grid_items, const uint16_t* mfb = nullptr,

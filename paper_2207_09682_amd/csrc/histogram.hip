@@ -332,18 +332,19 @@ template <int W, int IDX, int U, bool RAG, int BB>
 __global__ __launch_bounds__(HIST_THREADS, HIST_WAVES) void hist_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
                                                     const int32_t* __restrict__ table_counts, int64_t* hist_base,
-                                                    unsigned char* partials, int F, int nb, HistPlan plan) {
+                                                    unsigned char* partials, int F, int nb, HistPlan plan, HistProfile* prof) {
     using word = typename Acc<W>::word;
     constexpr int NPD = 4 / BB;  // bins per dword
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
-    const int n_entries = table_counts[0], n_items = table_counts[1];
+    const int n_entries = table_counts[0], n_items = table_counts[1], all_rows = table_counts[3];
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     int tile, glane;
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;  // row-group lanes (a multiple of 8)
     if (glane >= n_items) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) prof->add(IDX, all_rows, n_entries);
 
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
@@ -477,19 +478,20 @@ template <int W, int IDX, bool RAG, int BB>
 __global__ __launch_bounds__(IDX == 3 ? COUNT_THREADS : HIST_THREADS, HIST_WAVES) void hist_piece_kernel(RowSource src, IdxSet idxs,
                                                     const HistEntry* __restrict__ entries,
                                                     const int32_t* __restrict__ table_counts, int64_t* hist_base,
-                                                    unsigned char* partials, int F, int nb, HistPlan plan, CountSource cs) {
+                                                    unsigned char* partials, int F, int nb, HistPlan plan, CountSource cs, HistProfile* prof) {
     using word = typename Acc<W>::word;
     constexpr int NPD = 4 / BB;  // bins per dword
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
-    int n_entries = 0, n_items = 0, segs = 1, records = 0;
-    if (IDX != 3) { n_entries = table_counts[0]; n_items = table_counts[1]; }
+    int n_entries = 0, n_items = 0, all_rows = 0, segs = 1, records = 0;
+    if (IDX != 3) { n_entries = table_counts[0]; n_items = table_counts[1]; all_rows = table_counts[3]; }
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     int tile, glane;
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = ((int)gridDim.x - (IDX == 3 ? 1 : 0)) / plan.n_tiles;
     if (IDX != 3 && glane >= n_items) return;
+    if (IDX != 3 && blockIdx.x == 0 && threadIdx.x == 0) prof->add(IDX, all_rows, n_entries);
     if (IDX == 3 && blockIdx.x == gridDim.x - 1) tile = plan.n_tiles;  // makes the tables
 
     const int f0 = tile * plan.ft;
@@ -668,20 +670,21 @@ __global__ __launch_bounds__(1024) void hist_wide_kernel(RowSource src, IdxSet i
                                                                     const HistEntry* __restrict__ entries,
                                                                     const int32_t* __restrict__ table_counts,
                                                                     int64_t* hist_base, unsigned char* partials, int F,
-                                                                    int nb, HistPlan plan, CountSource cs, const uint16_t* __restrict__ mfb) {
+                                                                    int nb, HistPlan plan, CountSource cs, HistProfile* prof, const uint16_t* __restrict__ mfb) {
     using word = typename Acc<W>::word;
     using vec = typename std::conditional<V == 16, uint4, uint2>::type;
     constexpr int NV = V / 4;  // dwords per lane
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
-    int n_entries = 0, n_items = 0, segs = 1, records = 0;
-    if (IDX != 3) { n_entries = table_counts[0]; n_items = table_counts[1]; }
+    int n_entries = 0, n_items = 0, all_rows = 0, segs = 1, records = 0;
+    if (IDX != 3) { n_entries = table_counts[0]; n_items = table_counts[1]; all_rows = table_counts[3]; }
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     int tile, glane;
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = ((int)gridDim.x - (IDX == 3 ? 1 : 0)) / plan.n_tiles;
     if (IDX != 3 && glane >= n_items) return;
+    if (IDX != 3 && blockIdx.x == 0 && threadIdx.x == 0) prof->add(IDX, all_rows, n_entries);
     if (IDX == 3 && blockIdx.x == gridDim.x - 1) tile = plan.n_tiles;  // makes the tables
 
     const int f0 = tile * plan.ft;
@@ -879,14 +882,15 @@ __global__ __launch_bounds__(TWO ? 1024 : HIST_THREADS, TWO ? 1 : HIST_WAVES) vo
                                                          const HistEntry* __restrict__ entries,
                                                          const int32_t* __restrict__ table_counts,
                                                          int64_t* hist_base, unsigned char* partials, int F, int nb,
-                                                         HistPlan plan) {
+                                                         HistPlan plan, HistProfile* prof) {
     using word = typename Acc<W>::word;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
 
-    const int n_entries = table_counts[0], n_items = table_counts[1];
+    const int n_entries = table_counts[0], n_items = table_counts[1], all_rows = table_counts[3];
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     if ((int)blockIdx.x >= n_items) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) prof->add(HistProfile::CONTIGUOUS, all_rows, n_entries);
 
     const int RPI = plan.flat_rows, L = plan.flat_lanes;
     const int BR = U * RPI;  // rows of one block of U iterations
@@ -1113,16 +1117,17 @@ __global__ __launch_bounds__(HIST_THREADS) void hist_generic_kernel(RowSource sr
                                                             const HistEntry* __restrict__ entries,
                                                             const int32_t* __restrict__ table_counts,
                                                             int64_t* hist_base, unsigned char* partials, int F,
-                                                            int nb, HistPlan plan) {
+                                                            int nb, HistPlan plan, HistProfile* prof) {
     using word = typename Acc<W>::word;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     word* lds = reinterpret_cast<word*>(lds_raw);
-    const int n_entries = table_counts[0], n_items = table_counts[1];
+    const int n_entries = table_counts[0], n_items = table_counts[1], all_rows = table_counts[3];
     const int hmul = (1 << (plan.hshift - 8)) - 1;
     int tile, glane;
     tile_and_lane(plan.n_tiles, tile, glane);
     const int n_lanes = (int)gridDim.x / plan.n_tiles;
     if (glane >= n_items) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) prof->add(IDX, all_rows, n_entries);
     const int f0 = tile * plan.ft;
     const int ft = min(plan.ft, F - f0);
     const int lds_words = ft * nb;
@@ -1446,26 +1451,26 @@ HistPlan make_hist_plan_for(const qgbdt_shape& s, int bits_g, int bits_h, int ac
     return p;
 }
 
-// The table of a stand-alone build, and its histogram cleared; its rows are counted in `prof`.
-__global__ void begin_build_kernel(HistEntry* entries, int32_t* counts, HistEntry e, int64_t* hist, int64_t n_words, HistProfile* prof, int gathered) {
+// The table of a stand-alone build, and its histogram cleared.
+__global__ void begin_build_kernel(HistEntry* entries, int32_t* counts, HistEntry e, int64_t* hist, int64_t n_words) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = t; i < n_words; i += (int64_t)gridDim.x * blockDim.x) hist[i] = 0;
     if (t == 0) {
         entries[0] = e;
         counts[0] = 1;
         counts[1] = e.groups;
-        prof->add(gathered ? HistProfile::IDS : HistProfile::CONTIGUOUS, e.count, 1);
+        counts[3] = (int32_t)e.count;
     }
 }
 
 // (The row groups are counted on the host: on the device their chain of 64-bit divisions took 0.3 us of every build.)
-int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, bool gathered, int64_t* hist, int64_t n_words) {
+int launch_begin_build(qgbdt_ctx* ctx, const HistPlan& plan, int64_t begin, int64_t count, int64_t* hist, int64_t n_words) {
     const int64_t t = hist_target_rows(plan, count, 1), g = (count + t - 1) / t;
     HistEntry e;
     e.begin = begin; e.count = count; e.buf = BUF_ORIGINAL; e.slot = 0; e.item_start = 0; e.groups = g < 1 ? 1 : (int32_t)g;
     const int64_t blocks = (n_words + 255) / 256;
     hipLaunchKernelGGL(begin_build_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks)), dim3(256), 0, ctx->stream, ctx->hist_entries,
-                       ctx->hist_counts, e, hist, n_words, &ctx->step->prof, gathered ? 1 : 0);
+                       ctx->hist_counts, e, hist, n_words);
     QG_HIP(ctx, hipGetLastError());
     return QGBDT_OK;
 }
@@ -1545,6 +1550,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     const bool fast = !plan.bytewise;
     const int mode = count ? 3 : !use_idx ? 0 : rows.code.on() ? 2 : 1;  // contiguous rows, row ids, row ids with their gradients, rows that the launch selects
     const CountSource cs = count ? *count : CountSource{};
+    HistProfile* const prof = &ctx->step->prof;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->profiling && ctx->ev_used + 2 <= ctx->ev_cap) {
         for (int k = 0; k < 2; ++k)
@@ -1564,7 +1570,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     if (flat) {
 #define QG_LAUNCH_FLAT(W_, TWO_)                                                                                  \
     hipLaunchKernelGGL((hist_flat_kernel<W_, 2, TWO_>), grid, block, plan.lds_bytes, ctx->stream, rows, entries,  \
-                       table_counts, hist_base, partials, F, nb, plan)
+                       table_counts, hist_base, partials, F, nb, plan, prof)
         if (plan.two_level) QG_LAUNCH_FLAT(16, true);
         else if (plan.acc_width == 16) QG_LAUNCH_FLAT(16, false);
         else QG_LAUNCH_FLAT(32, false);
@@ -1573,7 +1579,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
 #define QG_LAUNCH_WIDE_S(W_, IDX_, V_, U_, S_)                                                                        \
     do {                                                                                                              \
         hipLaunchKernelGGL((hist_wide_kernel<W_, IDX_, V_, U_, S_>), grid, block, plan.lds_bytes, ctx->stream, rows,  \
-                           idx, entries, table_counts, hist_base, partials, F, nb, plan, cs, mfb);                  \
+                           idx, entries, table_counts, hist_base, partials, F, nb, plan, cs, prof, mfb);            \
     } while (0)
 #define QG_LAUNCH_WIDE(W_, IDX_, V_, U_)                                                                              \
     do {                                                                                                              \
@@ -1592,7 +1598,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     } else if (fast && plan.pieces > 0 && !(mode == 0 && plan.contig_dwords)) {
 #define QG_LAUNCH_PIECE_K(W_, IDX_, RAG_, BB_)                                                                      \
     hipLaunchKernelGGL((hist_piece_kernel<W_, IDX_, RAG_, BB_>), grid, block, plan.lds_bytes, ctx->stream, \
-                       rows, idx, entries, table_counts, hist_base, partials, F, nb, plan, cs)
+                       rows, idx, entries, table_counts, hist_base, partials, F, nb, plan, cs, prof)
 #define QG_LAUNCH_PIECE(W_, IDX_)                                                                                   \
     do {                                                                                                            \
         const bool whole = plan.ft * ctx->shape.bin_bytes % 16 == 0 && F % plan.ft * ctx->shape.bin_bytes % 16 == 0; \
@@ -1613,7 +1619,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
         const int U = cap >= 8 ? 8 : cap >= 4 ? 4 : cap >= 2 ? 2 : 1;
 #define QG_LAUNCH_HIST_K(W_, IDX_, U_, RAG_, BB_)                                                                  \
     hipLaunchKernelGGL((hist_kernel<W_, IDX_, U_, RAG_, BB_>), grid, block, plan.lds_bytes, ctx->stream, rows, idx,   \
-                       entries, table_counts, hist_base, partials, F, nb, plan)
+                       entries, table_counts, hist_base, partials, F, nb, plan, prof)
 #define QG_LAUNCH_HIST(W_, IDX_, U_)                                                                               \
     do {                                                                                                           \
         if (ctx->shape.bin_bytes == 2) {                                                                           \
@@ -1640,7 +1646,7 @@ int launch_hist(qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, con
     } else {
 #define QG_LAUNCH_GENERIC_K(W_, IDX_, BIN_)                                                                        \
     hipLaunchKernelGGL((hist_generic_kernel<W_, IDX_, BIN_>), grid, block, plan.lds_bytes, ctx->stream, rows, idx, \
-                       entries, table_counts, hist_base, partials, F, nb, plan)
+                       entries, table_counts, hist_base, partials, F, nb, plan, prof)
 #define QG_LAUNCH_GENERIC(W_, BIN_) \
     if (mode == 2) QG_LAUNCH_GENERIC_K(W_, 2, BIN_); else if (mode == 1) QG_LAUNCH_GENERIC_K(W_, 1, BIN_); else QG_LAUNCH_GENERIC_K(W_, 0, BIN_)
         if (ctx->shape.bin_bytes == 2) {

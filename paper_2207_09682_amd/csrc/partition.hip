@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256) void batch_part_count_kernel(RowSource rows, c
 // while the others move rows: it needs nothing of them but the left counts that the count kernel left behind.
 __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __restrict__ batch,
                              const int32_t* __restrict__ super_counts, HistEntry* hist_entries, int32_t* hist_counts,
-                             ScanPair* pairs, const HistPlan& plan, int super_len, int prof_kind, int* s_start, int* s_left, int* s_tmp) {
+                             ScanPair* pairs, const HistPlan& plan, int super_len, int* s_start, int* s_left, int* s_tmp) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_batch = step->n_batch;
     for (int t = tid; t < n_batch; t += 256) { s_start[t] = batch[t].super_start; s_left[t] = 0; }
@@ -319,10 +319,7 @@ __device__ void child_tables(StepState* step, Node* nodes, const BatchEntry* __r
         }
     }
     big = __syncthreads_or(big);
-    if (tid == 0) {
-        hist_counts[0] = n_batch; hist_counts[1] = base; hist_counts[2] = big;
-        step->prof.add(prof_kind, small_total, n_batch);
-    }
+    if (tid == 0) { hist_counts[0] = n_batch; hist_counts[1] = base; hist_counts[2] = big; hist_counts[3] = (int32_t)small_total; }
 }
 
 // Order-preserving scatter of every segment into the children's buffer.  The left rows in front of a segment are the sum
@@ -349,8 +346,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MODE == 
     __shared__ int s_start[TABLE_MAX];
     __shared__ int s_dpos[MODE == 2 && PART_SEG > TABLE_MAX + 8 ? PART_SEG : TABLE_MAX + 8];  // (also child_tables' LDS)
     if (blockIdx.x == 0) {
-        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, pairs, plan, SUPER,
-                     MODE == 2 ? HistProfile::CONTIGUOUS : rows.code.on() ? HistProfile::CODED : HistProfile::IDS, s_start, s_dpos, s_dpos + TABLE_MAX);
+        child_tables(step, nodes, batch, super_counts, hist_entries, hist_counts, pairs, plan, SUPER, s_start, s_dpos, s_dpos + TABLE_MAX);
         return;
     }
     const int n_items = step->n_part_items, n_batch = step->n_batch;

@@ -123,7 +123,6 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
         step->done = 0; step->n_known = 0; step->n_list = 0; step->n_nodes = 1; step->n_leaves = 1; step->n_commits = 0; step->n_expanded = 0;
         step->n_slots = 1; step->n_batch = 0; step->rounds = 0; step->n_part_items = 0; step->n_scan_items = 1;
         step->hist_units = N * (int64_t)F;
-        step->prof.add(HistProfile::CONTIGUOUS, N, 1);
         Node r;
         r.begin = 0; r.count = N; r.sum_g = total[0]; r.sum_h = total[1]; r.n_left = 0; r.buf = root_buf; r.slot = 0;
         r.state = 1; r.expanded = 0; r.child = -1; r.leaf_id = 0;
@@ -132,7 +131,7 @@ __global__ __launch_bounds__(256) void tree_init_kernel(int64_t N, int F, StepSt
         HistEntry e;
         e.begin = 0; e.count = N; e.buf = root_buf; e.slot = 0; e.item_start = 0; e.groups = hist_groups(N, plan);
         hist_entries[0] = e;
-        hist_counts[0] = 1; hist_counts[1] = e.groups; hist_counts[2] = e.groups > plan.search_sums ? 1 : 0;
+        hist_counts[0] = 1; hist_counts[1] = e.groups; hist_counts[2] = e.groups > plan.search_sums ? 1 : 0; hist_counts[3] = (int32_t)N;
         ScanPair sp;
         sp.slot_a = 0; sp.slot_b = -1; sp.parent = -1; sp.a_item = 0; sp.item_start = 0;
         sp.groups = e.groups <= plan.search_sums ? e.groups : 0;
