@@ -48,10 +48,10 @@ extern "C" {
 #define QGBDT_E_WORKSPACE (-6) /* no workspace set, the block is too small, or it lacks the section a call needs */
 
 /* Optional sections of the workspace (qgbdt_workspace_bytes / qgbdt_set_workspace). */
-#define QGBDT_WS_BIND 1u       /* feature-major copy of a bound matrix: qgbdt_bind_bins (n_rows * n_features * bin_bytes); for large matrices
-                                  (256 MB and more) of 72 to 248 uint8 features, 8 more than a multiple of 16, also a copy whose rows
-                                  begin on cache lines, where that takes at most 30 % more (n_rows * n_features rounded up to 128; a
-                                  block without room for it is accepted and does without) */
+#define QGBDT_WS_BIND 1u       /* feature-major copy of a bound matrix: qgbdt_bind_bins (n_rows * n_features * bin_bytes); for matrices of
+                                  256 MB and more with 104, 120, 200, 216, 232 or 248 uint8 features also a copy whose rows begin on
+                                  cache lines (n_rows * n_features rounded up to 128; a block without room for it is accepted and does
+                                  without) */
 #define QGBDT_WS_ROW_COPIES 2u /* three leaf-ordered copies of the bin rows: row_layout QGBDT_ROWS_ORDERED, and what
                                   QGBDT_ROWS_AUTO takes for a large unbound matrix of up to 32 uint8 features (16..64
                                   uint8 features, a multiple of 4; ignored for other shapes; 3 * n_rows * n_features) */

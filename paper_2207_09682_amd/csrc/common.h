@@ -111,10 +111,11 @@ struct HistEntry {
 
 // Pitch of the copy of a bound matrix that the gathered builds of a tree read 8 bytes at a time (hist_wide_kernel; 0: none): whole cache
 // lines.  These builds are bound by the requests of 64 bytes, and the lines behind them, that a CU can have outstanding: a 32-byte piece
-// of a row of 200 bytes takes 1.375 requests, the row 2.5 lines instead of 2.  Where that costs at most 30 % more bytes per row, and the matrix is
-// larger than what the caches hold.  Trees without / with: 20 M x 200 9864 / 9367 us, 8 M x 232 3999 / 3714, 4 M x 200 2280 / 2154, 3 M x 120 1277 / 1158, 2 M x 200
-// 1470 / 1414, 1.5 M x 104 (156 MB) 742 / 747.  (Contiguous rows, and 16-byte pieces, whose rows are longer, gain nothing: one build of 20 M x 200 1425 / 1390 us, 400 k x
-// 2000 at a pitch of 2048 185 / 212 us, gathered 67 / 68.)
+// of a row of 200 bytes takes 1.375 requests, the row 2.5 lines instead of 2.  Where that costs at most 30 % more bytes per row (104, 120, 200, 216, 232 and
+// 248 features), and the matrix is larger than what the caches hold.  Trees without / with: 20 M x 200 9864 / 9367 us, 8 M x 232 3999 / 3714, 4 M x 200 2280 / 2154,
+// 3 M x 120 1277 / 1158, 2 M x 200 1470 / 1414, 1.5 M x 104 (156 MB) 742 / 747.  Contiguous rows gain little: one build of 20 M x 200 1425 / 1390 us.  Matrices read 16 bytes at a
+// time have no such copy: 400 k x 2000 loses (at a pitch of 2048 185 / 212 us, gathered 67 / 68), 112 to 240 features would gain in 32-bit words (8 M x 112 2774 / 2414 us, 6 M x 208
+// 3297 / 3072, 5 M x 224 2876 / 2742, 5 M x 240 3109 / 2831, 1.5 M x 208 1104 / 1076) and not in 64-bit ones (3 M x 240 2307 / 2306).
 inline int padded_pitch(const qgbdt_shape& s) {
     const int F = s.n_features, pitch = (F + 127) / 128 * 128;
     return s.bin_bytes == 1 && F > 64 && F < 256 && F % 16 == 8 && 10 * pitch <= 13 * F && s.n_rows * F >= (int64_t)256 << 20 ? pitch : 0;

@@ -760,15 +760,13 @@ int run_grow_tree(qgbdt_ctx* ctx, const uint8_t* bins, const float* g, const flo
     ctx->seg_supers = part_supers(N, bins_t != nullptr) ? 1 : 0;
     // Without the feature-major copy the partition's count gathers a line of the row-major matrix per row, once per level; keeping
     // the rows in leaf order reads and writes the whole row at every level instead.  Rows of 36 bytes and more are cheaper to
-    // gather, shorter ones too while the matrix is in the caches, those of up to 20 bytes less long the more levels a tree has.  Index /
-    // ordered, ms per tree: 20 M x 48 5.99 / 7.45, 20 M x 36
-    // 5.21 / 5.54, 60 M x 32 16.6 / 15.7, 8 M x 32 1.87 / 1.94, 20 M x 28 4.76 / 4.57, 6 M x 28 1.73 / 1.68, 5 M x 28 1.45 / 1.47, 2.5 M x 28
-    // 0.84 / 0.84, 1 M x 28 0.70 / 0.75, 7 M x 20 1.48 / 1.34, 5 M x 16 1.11 / 1.03, 1 M x 16 0.51 / 0.53, 10 k x 28 0.205 / 0.219.
-    // Time ordered / index with 31, 127 and 511 leaves: 1 M x 16 1.06 1.04 1.07, 1.5 M 1.04 1.00 1.01, 2 M 1.02 0.97 0.98, 3 M 0.99 0.93 0.91;
-    // 1 M x 20 1.00 0.99 0.98, 1.5 M 0.97 0.94 0.93, 2 M 0.97 0.92 0.94; 2 M x 24 1.00 0.96 0.95 (5 bits 1.06 1.03 0.99), 4 M 1.05 0.98 0.95
-    // (1.14 1.07 1.03), 6 M 1.04 0.97 0.96 (1.04 0.97 0.97); with 15, 63 and 255 leaves 2 M x 16 1.04 1.04 0.95, 3 M x 16 1.05 0.99 0.91,
-    // 2 M x 20 1.00 0.94 0.92, 3 M x 20 1.01 0.94 0.89.  (With the
-    // feature-major copy moving row ids wins throughout: 10.5 M x 28 1.85 against 2.54 ms.)
+    // gather (20 M x 48 5.99 / 7.45 ms per tree, index / ordered), shorter ones too while the matrix is in the caches, those of up to 20 bytes less long the more
+    // levels a tree has.  The line lies where both were level before the counting pass took the order of the XCDs and histogram launches counted; since then
+    // index trees are the faster ones on both sides of it, up to 10 to 30 M rows.  Time ordered / index now with 31, 127 and 511 leaves: 1 M x 16 1.44 1.33 1.31, 1.5 M 1.31
+    // 1.23 1.27, 2 M 1.29 1.19 1.17, 3 M 1.17 1.14 1.16, 7 M 1.28 1.20 1.12; 1 M x 20 1.23 1.24 1.28, 2 M 1.18 1.09 1.04, 3 M 1.17 1.12 1.10, 7 M 1.26 1.16 1.07; 2 M x 24 1.21 1.12 1.09, 4.5 M 1.32 1.25
+    // 1.17 (4 M, 5 bits 1.35 1.30 1.28), 7 M 1.24 1.17 1.07; 1 M x 28 1.28 1.22 1.20, 4.5 M 1.33 1.26 1.16, 7 M 1.28 1.19 1.12; 7 M x 32 1.29 1.24 1.20; with 31 and 255 leaves 10 M x 16 1.21 1.06,
+    // 16 M 1.04 0.97, 30 M 0.98 0.86; 10 M x 20 1.15 1.02, 30 M 0.93 0.84; 10 M x 28 1.20 1.09, 30 M 1.01 0.94; 10 M x 32 1.23 1.18, 30 M 1.08 1.02.  (With the
+    // feature-major copy moving row ids wins throughout: 10.5 M x 28 1.64 against 2.54 ms.)
     // Without ordered rows the packed gradients still move with the row ids (2 bytes per moved row): a gathered
     // build then reads them in sequence, which takes one of the ~2.2 cache lines per sparse narrow row away.
     // A matrix that the caches hold gathers cheaply anyway and gains nothing from the move (1 M x 28: 1.15 to
