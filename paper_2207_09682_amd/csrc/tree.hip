@@ -35,45 +35,39 @@ namespace qgbdt {
 // Row lists: up to this many rows times tiles of features the histogram launch counts the left rows itself (CountSource) and the rows are moved
 // beside the split search, which leaves a round four dependent launches (three where no reduce kernel is launched) of six.  Every tile of a
 // row group goes through the parents' rows for itself, and a workgroup counts and accumulates one after the other: beyond the line
-// the count and scatter kernels, which fill the chip, are the faster way.  Not bound, every tile gathers lines of the matrix for its count, so
-// that the line lies lower the more tiles there are; pieces at any address (hist_piece_kernel) take several tiles longer than the wide rows' aligned ones.
-// Trees of 31 / 127 leaves, time without over time with, at millions of rows x tiles (3 bits, 255 bins where nothing else is said):
-//   one tile    28 features bound 1.25: 1.03 / 1.04, 1.9: 1.04 / 1.05, 2.35: 1.00 / 1.01; 21 (5 bits) 1.9: 1.02 / 1.03, 2.35: 0.97 / 0.97; 40 (2 bits) 2.35: 1.01 / 1.03;
-//               not bound 28 1.25: 1.08 / 1.06, 2.2: 1.02 / 1.00, 2.65: 0.86 / 0.79, 5: 0.88 / 0.86 (255 leaves); 40 2.35: 1.00 / 0.99
-//   two         100 bound 1.25: 1.10 / 1.11, 2.35: 1.02 / 0.99, not bound 2.35: 1.05 / 0.98; 60 (5 bits) 2.35: 1.01 / 1.02, not bound 1.02 / 1.02
-//   three       90 bound 1.6: 1.05 / 1.05, 2.05: 1.00 / 1.01, 2.35: 1.02 / 0.96, not bound 2.05: 1.03 / 1.01, 2.35: 1.00 / 0.92
-//   four, wide  200 bound 1.9: 1.08 / 1.06, 2.35: 1.08 / 1.03, 3: 0.91 / 0.98 (255 leaves); not bound 1.9: 1.06 / 1.02, 2.35: 1.08 / 0.98
-//   four, pieces  500 (63 bins) bound 1.4: 1.08 / 1.05, 1.9: 1.01 / 1.01, 2.05: 1.00 / 0.97, not bound 1.4: 1.08 / 1.04, 1.6: 1.04 / 1.00, 2.05: 1.01 / 0.96
-//   five, wide  136 (8-bit hessians) bound 1.9: 1.06 / 1.02, 2.35: 1.02 / 1.00, not bound 1.6: 1.06 / 1.02, 1.75: 1.04 / 0.97
-//   five, pieces  300 (127 bins) bound 1.6: 1.04 / 1.00, 1.9: 1.03 / 0.97, not bound 1.25: 1.07 / 1.04, 1.6: 1.03 / 0.98
-//   nine        552 (31 bins) bound 1.6: 1.04 / 1.01, 1.9: 0.99 / 0.98, not bound 1: 1.06 / 1.04, 1.25: 1.04 / 0.98, 1.6: 0.98 / 0.95
-//   sixteen     2000 (63 bins), 31 leaves bound 1.6: 1.03, 2.2: 0.96, not bound 1: 1.00, 1.6: 0.98
-// 64-bit words accumulate at half the rate, and a workgroup's share of a parent may hold anything between none and all of its built child's rows: in several
-// tiles their line lies lower (one tile stays: 24 features bound 2.25: 1.04, not bound 56 features, 31 bins 2.35: 0.93).  So does that of trees whose rounds have more
-// nodes than there are row-group lanes, which then have two items each: 255 leaves, 64-bit words 232 features, 127 bins (64 lanes) bound 1: 1.00, 2.05: 0.89, 166 features (80)
-// 0.87: 0.97, 168 features 1.9: 0.91; 32-bit words 200 features (64) 2: 1.05, 400 features, 31 bins (128), 511 leaves not bound 2.4: 0.95; 1213 features (8 lanes), 31
-// leaves 1.46: 0.92.  Over 900 shapes drawn from 12 to 1500 features, 15 to 400 bins, 2 to 8 bits, 250 k to 2.8 M rows x tiles, 15 to 511 leaves
-// trees take 7.9 % less time by this rule than without counting; the better of both ways everywhere would be 8.2 %.  (Figures of single shapes vary by 2 %.)
+// the count and scatter kernels, which fill the chip, are the faster way.  A tree of few leaves has few rounds of little work per launch, so its line lies
+// higher; one whose rounds have more nodes than there are row-group lanes has lanes with two items, which 64-bit words, accumulated at half the rate, make worse; with more
+// than six tiles there are few lanes, and not bound every tile gathers lines of the matrix for its count.  Trees, time without counting over time with it, mean (and
+// least) of 1722 shapes drawn from 12 to 1500 features, 15 to 400 bins, 2 to 8 bits, 15 to 511 leaves, by millions of rows x tiles (single shapes vary by 2 %):
+//                                                          up to 0.5   0.9         1.4         1.8         2.4         3.0         4.5
+//   up to six tiles, leaves <= lanes / 4                   1.15 (1.04) 1.12 (1.06) 1.09 (1.00) 1.08 (1.01) 1.04 (0.98) 1.02 (0.94) 0.99 (0.90)
+//                    more leaves                           1.16 (1.06) 1.13 (1.02) 1.08 (0.94) 1.05 (0.92) 1.00 (0.88) 0.98 (0.90) 0.96 (0.85)
+//                    64-bit words, leaves > 2 lanes        1.12 (1.09)             1.03 (0.98) 0.99 (0.94) 0.94 (0.86) 0.93 (0.88) 0.91 (0.79)
+//   more tiles, bound                                      1.10 (1.04) 1.07 (0.99) 1.04 (0.96) 1.01 (0.91) 0.94 (0.86) 0.94 (0.84) 0.90 (0.78)
+//               not bound                                  1.10 (1.05) 1.04 (0.99) 1.00 (0.88) 0.95 (0.80) 0.91 (0.74) 0.85 (0.65)
 // Beyond six times the lanes not at all: 57 k x 1323 (11 tiles, 16 lanes), 275 leaves 1426 / 1471 us; 43 k x 640 (5, 48), 277 leaves 983 / 859.
+// Single ones, us without / with: 28 features (255 leaves) 1 M 549 / 521, 2 M 690 / 668, not bound 1 M 615 / 541, 2 M 769 / 761, 3 M 863 / 1039; 200 features 500 k 854 /
+// 812, 750 k 940 / 965; 136 features, 8-bit hessians 200 k 752 / 690, not bound 600 k 858 / 931; 552 features, 31 bins (31 leaves) 111 k 368 / 327, 333 k 397 / 449.
+// 64-bit words of many features per tile have a line at 0.9 besides, where N x F is above 100 M and the leaves are not few: 0.98 on average beyond it (0.90 to 1.13; 467 k x 240
+// in one tile 1.21).  All 1722 shapes take 5.5 % less time by this rule than without counting (the better of both ways everywhere: 5.8 %); 20 of them more than 2 % more.
 constexpr int COUNTING_NODES = 6;
-static int64_t counting_rows(const HistPlan& plan, bool bound, int num_leaves) {
-    const int T = plan.n_tiles, lanes = count_lanes(plan);
-    const bool wide = plan.wide_v > 0, words64 = plan.acc_width == 32;
+static int64_t counting_rows(const HistPlan& plan, bool bound, int num_leaves, int64_t n_bins) {
+    const int lanes = count_lanes(plan);
+    const bool words64 = plan.acc_width == 32;
     if (num_leaves > COUNTING_NODES * lanes) return 0;
-    int64_t most = words64 && T > 1 ? 2000000 : 2400000;
-    if (T > 5) most = bound ? 1600000 : 1100000;
-    else if (T > 2 && !(bound && wide)) most = std::min<int64_t>(most, T == 3 || (T == 4 && wide) ? 2000000 : bound || wide ? 1600000 : 1400000);
-    if (num_leaves > 2 * lanes) most = std::min<int64_t>(most, words64 || T > 5 ? 1100000 : 2000000);
-    return most;
+    if (words64 && n_bins > 100000000 && 4 * num_leaves > lanes) return 900000;
+    if (plan.n_tiles > 6) return bound ? 1600000 : 1100000;
+    if (4 * num_leaves <= lanes) return 3000000;
+    return words64 && num_leaves > 2 * lanes ? 1400000 : 2000000;
 }
 
 // An item of such a launch is one chunk at most (count_item_segs), which for short chunks makes more items than row-group lanes in the rounds of the
 // whole matrix: the lanes' second items take as long as the first ones.  Two turns pay up to 2 M rows x tiles, where the second is not nearly
-// empty or the items are short and later rounds, whose nodes are fewer rows, outweigh; three never do.  Trees of 31 / 127 leaves, time without over time with, 4
-// bits (4096 rows per item), by the turns that all rows fill: 28 features bound 1.2: 0.97 / 0.99, 1.5: 0.99 / 0.99, 2.1: 0.91 / 0.93, not bound 1.2: 1.02 / 1.01, 1.5: 1.06 / 1.03, 2.1: 0.93 /
-// 0.94; 90 features 1.0: 0.96 / 0.99 (not bound 0.97 / 0.99), 1.3: 0.98 / 1.01 (1.02 / 1.03), 1.6: 1.00 / 1.02 (1.06 / 1.07), 2.1: 0.90 / 0.94 (0.95 / 0.97); 400 features, 63 bins 1.2: 1.00 / 1.03, 1.3: 1.06 /
-// 1.07, 2.0: 1.02 / 1.00, 2.1: 0.94 / 0.95; 32 features, 63 leaves, not bound 1.2: 1.06, 72 features (two tiles), 255 leaves, not bound 1.2: 1.09.  6144 rows per item: 22 features, 31 bins,
-// 31 leaves 1.2: 0.89, 141 features, 15 bins, 255 leaves 1.2: 0.91.
+// empty or the items are short and later rounds, whose nodes have fewer rows, outweigh; three never do.  The shapes above of up to six tiles, columns up to 1.4, 1.8, 2.4, 3.0:
+//   two turns, the second at least three tenths full, or       1.02 (0.98) 1.04 (0.97) 1.01 (0.91) 0.95 (0.91)
+//     more than 32 leaves and items of less than 6144 rows
+//   two turns otherwise                                        1.04 (0.98) 0.95 (0.90) 0.93 (0.87) 0.87 (0.78)
+//   three and more                                                                     0.95 (0.88) 0.97 (0.91)
 static bool counting_turns_pay(const HistPlan& plan, int64_t n_rows, int seg_rows, int num_leaves) {
     const int64_t segs = (n_rows + seg_rows - 1) / seg_rows, turn = (int64_t)count_lanes(plan) * (plan.single_rows / seg_rows);
     if (segs <= turn) return true;
@@ -82,7 +76,7 @@ static bool counting_turns_pay(const HistPlan& plan, int64_t n_rows, int seg_row
 
 bool counts_rows(const qgbdt_ctx* ctx, const HistPlan& plan, const RowSource& rows, bool bound, int num_leaves) {
     const int64_t N = ctx->shape.n_rows;
-    return N * plan.n_tiles <= counting_rows(plan, bound, num_leaves) && counting_build_ok(ctx, plan, rows) && counting_turns_pay(plan, N, ctx->seg_rows, num_leaves);
+    return N * plan.n_tiles <= counting_rows(plan, bound, num_leaves, N * ctx->shape.n_features) && counting_build_ok(ctx, plan, rows) && counting_turns_pay(plan, N, ctx->seg_rows, num_leaves);
 }
 
 struct TreeOut {

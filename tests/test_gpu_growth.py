@@ -149,7 +149,7 @@ def test_histogram_launches_that_count(N, F, nb, bb, L, bits, layout):
 # Trees beyond those whose histogram launches count: the counting pass in the order of the XCDs, in one step and in eight, with fewer and
 # more than 64 nodes in a round, sorted rows (a node's rows in one place of the matrix), and gathered builds of few and many row groups
 @pytest.mark.parametrize("N,F,nb,bb,L,bound", [(2_600_001, 16, 32, 1, 300, True), (1_100_003, 40, 600, 2, 63, False), (6_000_003, 5, 32, 1, 31, True),
-                                                (2_500_003, 16, 32, 1, 31, False)])
+                                                (2_500_003, 16, 32, 1, 127, False)])
 def test_large_trees_of_row_lists(N, F, nb, bb, L, bound):
     rng = np.random.default_rng(N + F)
     bins = rng.integers(0, nb, (N, F), dtype=np.uint16 if bb == 2 else np.uint8)

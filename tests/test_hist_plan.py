@@ -423,10 +423,10 @@ def test_counting_pass_of_few_segments_goes_from_node_to_node():
 
 # Launches that count the left rows themselves: items of one chunk, as many as the table has room for.
 COUNTING_SHAPES = [(10_000, 28, 63, 15, 1), (100_003, 50, 255, 31, 1), (65_536, 120, 255, 31, 1), (43_690, 90, 255, 63, 1), (1_000_000, 28, 255, 255, 1),
-                   (463_715, 90, 255, 255, 1), (200_000, 136, 255, 63, 1), (100_000, 16, 64, 658, 1), (1_900_000, 48, 255, 127, 1), (20_000, 800, 63, 63, 1),
+                   (463_715, 90, 255, 255, 1), (200_000, 136, 255, 63, 1), (100_000, 16, 64, 658, 1), (1_700_000, 48, 255, 127, 1), (20_000, 800, 63, 63, 1),
                    # short chunks and few row-group lanes: more items than the table holds, or nearly as many
                    (262_144, 200, 255, 63, 1), (262_144, 150, 255, 255, 1), (150_000, 200, 255, 63, 1),
-                   (50_001, 40, 300, 63, 2), (60_000, 56, 255, 15, 1), (65_536, 50, 255, 63, 1), (3000, 4096, 16, 31, 1), (500_000, 200, 255, 255, 1)]
+                   (50_001, 40, 300, 63, 2), (60_000, 56, 255, 15, 1), (65_536, 50, 255, 63, 1), (3000, 4096, 16, 31, 1), (440_000, 200, 255, 255, 1)]
 
 
 @pytest.mark.parametrize("shape", SHAPES + COUNTING_SHAPES, ids=lambda s: f"{s[0]}x{s[1]}_nb{s[2]}_L{s[3]}_b{s[4]}")
@@ -455,19 +455,21 @@ def test_items_of_launches_that_count(shape):
     assert checked > 0 or shape in SHAPES   # (COUNTING_SHAPES are there because they do)
 
 
-# Up to how many rows times tiles the histogram launches count, bound and not bound, for whole and wide pieces of rows; and that they do
+# Up to how many rows times tiles the histogram launches count, bound and not bound, by leaves, tiles and word width; and that they do
 # not where the items' one chunk makes a second turn of the lanes that is nearly empty, or a third one (4 bits: 4096 rows per item)
-# (64-bit words in several tiles, and more than twice as many leaves as row-group lanes: lower lines)
-@pytest.mark.parametrize("F,nb,bh,leaves,tiles,wide,bound,unbound", [
-    (28, 255, 3, 31, 1, False, 2_400_000, 2_400_000), (28, 255, 8, 255, 1, False, 2_400_000, 2_400_000), (60, 255, 8, 31, 2, False, 2_000_000, 2_000_000), (100, 255, 3, 31, 2, False, 2_400_000, 2_400_000),
-    (90, 255, 3, 31, 3, False, 2_000_000, 2_000_000), (400, 31, 3, 511, 2, True, 2_000_000, 2_000_000), (166, 127, 8, 255, 3, False, 1_100_000, 1_100_000),
-    (200, 255, 3, 31, 4, True, 2_400_000, 2_000_000), (500, 63, 3, 31, 4, False, 1_600_000, 1_400_000), (136, 255, 8, 31, 5, True, 2_000_000, 1_600_000),
-    (300, 127, 3, 31, 5, False, 1_600_000, 1_400_000), (552, 31, 3, 31, 9, True, 1_600_000, 1_100_000), (2000, 63, 3, 31, 16, True, 1_600_000, 1_100_000),
-    (2000, 63, 3, 96, 16, True, 1_100_000, 1_100_000), (2000, 63, 3, 97, 16, True, 0, 0)])
-def test_trees_up_to_the_lines_count(F, nb, bh, leaves, tiles, wide, bound, unbound):
+@pytest.mark.parametrize("F,nb,bh,leaves,tiles,bound,unbound", [
+    (28, 255, 3, 64, 1, 3_000_000, 3_000_000), (28, 255, 3, 65, 1, 2_000_000, 2_000_000), (28, 255, 8, 513, 1, 1_400_000, 1_400_000),
+    (100, 255, 3, 32, 2, 3_000_000, 3_000_000), (100, 255, 3, 255, 2, 2_000_000, 2_000_000), (90, 255, 3, 20, 3, 3_000_000, 3_000_000),
+    (90, 255, 3, 255, 3, 2_000_000, 2_000_000), (140, 127, 8, 160, 3, 2_000_000, 2_000_000), (140, 127, 8, 161, 3, 1_400_000, 1_400_000), (512, 15, 8, 63, 2, 900_000, 900_000), (512, 15, 8, 32, 2, 3_000_000, 3_000_000),
+    (200, 255, 3, 31, 4, 2_000_000, 2_000_000), (136, 255, 8, 12, 5, 3_000_000, 3_000_000), (552, 31, 3, 31, 9, 1_600_000, 1_100_000),
+    (2000, 63, 3, 96, 16, 1_600_000, 1_100_000), (2000, 63, 3, 97, 16, 0, 0)])
+def test_trees_up_to_the_lines_count(F, nb, bh, leaves, tiles, bound, unbound):
     p = describe_hist_plan(100_000, F, nb, leaves, 1, 3, bh)
-    assert p["n_tiles"] == tiles and (p["wide_v"] > 0) == wide and (p["acc_width"] == 32) == (bh == 8)
+    assert p["n_tiles"] == tiles and (p["acc_width"] == 32) == (bh == 8)
+    lanes = 256 // tiles // 8 * 8
     for b, line in ((True, bound), (False, unbound)):
+        if bh != 8:
+            line = min(line, lanes * 10240 * tiles)   # (one turn of the lanes: 10 602 rows are five segments)
         for N in (max(line // tiles, 1000), line // tiles + 1001):
             assert describe_counting(N, F, nb, leaves, 1, 3, bh, 0, b)["counts"] == (N * tiles <= line), (b, N)
 
@@ -475,7 +477,7 @@ def test_trees_up_to_the_lines_count(F, nb, bh, leaves, tiles, wide, bound, unbo
 @pytest.mark.parametrize("F,nb,tiles", [(28, 255, 1), (90, 255, 3), (400, 63, 4)])
 def test_launches_that_count_take_two_turns_at_most(F, nb, tiles):
     turn = (256 // tiles // 8 * 8) * 4096
-    most = min(2 * turn, 2_000_000 // tiles)
-    for leaves in (32, 33):
+    for leaves in (15, 32, 33):
+        most = min(2 * turn, 2_000_000 // tiles)
         for rows, counts in ((turn, 1), (turn + 1, leaves > 32), (int(1.28 * turn), leaves > 32), (int(1.32 * turn), 1), (int(1.5 * turn), 1), (most, 1), (most + 1, 0)):
             assert describe_counting(rows, F, nb, leaves, 1, 4, 4, 0, True)["counts"] == counts, (rows, leaves)
