@@ -48,14 +48,15 @@ namespace qgbdt {
 // Beyond six times the lanes not at all: 57 k x 1323 (11 tiles, 16 lanes), 275 leaves 1426 / 1471 us; 43 k x 640 (5, 48), 277 leaves 983 / 859.
 // Single ones, us without / with: 28 features (255 leaves) 1 M 549 / 521, 2 M 690 / 668, not bound 1 M 615 / 541, 2 M 769 / 761, 3 M 863 / 1039; 200 features 500 k 854 /
 // 812, 750 k 940 / 965; 136 features, 8-bit hessians 200 k 752 / 690, not bound 600 k 858 / 931; 552 features, 31 bins (31 leaves) 111 k 368 / 327, 333 k 397 / 449.
-// 64-bit words of many features per tile have a line at 0.9 besides, where N x F is above 100 M and the leaves are not few: 0.98 on average beyond it (0.90 to 1.13; 467 k x 240
-// in one tile 1.21).  All 1722 shapes take 5.5 % less time by this rule than without counting (the better of both ways everywhere: 5.8 %); 20 of them more than 2 % more.
+// 64-bit words of many features in one or two tiles have a line at 0.9 besides, where N x F is above 100 M and the leaves are not few: 0.97 on average beyond it (0.93 to 1.03;
+// below it 467 k x 240 1.21, in six tiles 206 k x 1440 1.07).  All 1722 shapes take 5.5 % less time by this rule than without counting (the better of both ways everywhere:
+// 5.8 %); 22 of them more than 2 % more.
 constexpr int COUNTING_NODES = 6;
 static int64_t counting_rows(const HistPlan& plan, bool bound, int num_leaves, int64_t n_bins) {
     const int lanes = count_lanes(plan);
     const bool words64 = plan.acc_width == 32;
     if (num_leaves > COUNTING_NODES * lanes) return 0;
-    if (words64 && n_bins > 100000000 && 4 * num_leaves > lanes) return 900000;
+    if (words64 && plan.n_tiles <= 2 && n_bins > 100000000 && 4 * num_leaves > lanes) return 900000;
     if (plan.n_tiles > 6) return bound ? 1600000 : 1100000;
     if (4 * num_leaves <= lanes) return 3000000;
     return words64 && num_leaves > 2 * lanes ? 1400000 : 2000000;

@@ -460,7 +460,7 @@ def test_items_of_launches_that_count(shape):
 @pytest.mark.parametrize("F,nb,bh,leaves,tiles,bound,unbound", [
     (28, 255, 3, 64, 1, 3_000_000, 3_000_000), (28, 255, 3, 65, 1, 2_000_000, 2_000_000), (28, 255, 8, 513, 1, 1_400_000, 1_400_000),
     (100, 255, 3, 32, 2, 3_000_000, 3_000_000), (100, 255, 3, 255, 2, 2_000_000, 2_000_000), (90, 255, 3, 20, 3, 3_000_000, 3_000_000),
-    (90, 255, 3, 255, 3, 2_000_000, 2_000_000), (140, 127, 8, 160, 3, 2_000_000, 2_000_000), (140, 127, 8, 161, 3, 1_400_000, 1_400_000), (512, 15, 8, 63, 2, 900_000, 900_000), (512, 15, 8, 32, 2, 3_000_000, 3_000_000),
+    (90, 255, 3, 255, 3, 2_000_000, 2_000_000), (140, 127, 8, 160, 3, 2_000_000, 2_000_000), (140, 127, 8, 161, 3, 1_400_000, 1_400_000), (512, 15, 8, 63, 2, 900_000, 900_000), (512, 15, 8, 32, 2, 3_000_000, 3_000_000), (768, 15, 8, 63, 3, 2_000_000, 2_000_000),
     (200, 255, 3, 31, 4, 2_000_000, 2_000_000), (136, 255, 8, 12, 5, 3_000_000, 3_000_000), (552, 31, 3, 31, 9, 1_600_000, 1_100_000),
     (2000, 63, 3, 96, 16, 1_600_000, 1_100_000), (2000, 63, 3, 97, 16, 0, 0)])
 def test_trees_up_to_the_lines_count(F, nb, bh, leaves, tiles, bound, unbound):
