@@ -161,8 +161,8 @@ static_assert(6 * MAX_TREE_LEAVES + 1 < 4096 && BUF_ORIGINAL < 16, "a node's id 
 // p_max: all nodes that can be known.  Arrays by gain rank unless noted.
 struct PlanLds {
     int key;      // u64 [p_max] gain bits in the new order
-    int okey;     // u64 [p_max + 8] gain bits in the kept order; once merged: `info`, what the selection needs of a rank (the last eight places only shift the arrays
-                  // behind them by a quarter of the LDS banks: 464 k x 90 11.06 -> 10.97 us per launch, 1 M x 28 10.41 -> 10.35)
+    int okey;     // u64 [p_max + 8] gain bits in the kept order; once merged: `info`, what the selection needs of a rank (the last eight places only move the arrays
+                  // behind them on by 64 bytes of LDS banks: 464 k x 90 11.06 -> 10.97 us per launch, 1 M x 28 10.41 -> 10.35)
     int ids;      // u32 [p_max] node | row buffer << 12 | left child << 16
     int oids;     // u32 [p_max] the same in the kept order; once merged: `ckey`, u64 [p_max / 2], order of the splits committed now
     int leaf;     // u16 [p_max] leaf id of an open leaf, else NO_NODE
